@@ -1,12 +1,17 @@
 // Draft-model body in front of the LM head (Sec. 5.1 "Ensemble learning via Batched Inference", Sec. 4.1 "Target and
 // Draft Models"): one decode step of a LLaMA-style decoder for the n*B rows of the batch of drafting methods, each
 // with its own key / value cache.  At 64 rows every projection streams a few megabytes of weights and is bound by
-// launch and latency, not bandwidth: the contraction is split into ranges so that a few hundred workgroups have
-// their loads in flight at once, the partial sums go to slabs that the consumer of the projection (rotary
-// embedding + cache append + attention, residual + RMSNorm, SwiGLU) adds in a fixed order.  Storage points: bf16 for
-// weights, caches and everything that feeds a projection; fp32 for the residual stream and the projections'
-// results.  Shapes the split kernels do not take go through the LM head's kernels (any [rows,K] x [N,K]^T -> fp32).
+// launch and latency, not bandwidth, so a layer is five launches and nothing in between: every projection normalises
+// (or merges the attention's partial results) while its weights are on their way and finishes what its result feeds --
+// rotation and cache append, residual addition, SwiGLU -- before it stores.  Storage points: bf16 for weights, caches
+// and everything that feeds a projection; fp32 for the residual stream, the rotated queries and the attention's
+// partial sums.
 #include <hip/hip_bf16.h>
+
+#include <algorithm>
+#include <cmath>
+#include <mutex>
+#include <utility>
 
 #include "device_utils.h"
 #include "internal.h"
@@ -15,12 +20,15 @@ namespace tabed {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4b;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4b;
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {            // round to nearest even
-    const uint32_t u = __builtin_bit_cast(uint32_t, f);
-    return (uint16_t)((u + (((u >> 16) & 1u) + 0x7FFFu)) >> 16);
+    return __builtin_bit_cast(uint16_t, (__bf16)f);
+}
+
+__device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d) {
+    return make_uint2(f32_to_bf16_bits(a) | ((uint32_t)f32_to_bf16_bits(b) << 16), f32_to_bf16_bits(c) | ((uint32_t)f32_to_bf16_bits(d) << 16));
 }
 
 __device__ __forceinline__ float block_sum_f32(float v, float* lds4) {
@@ -32,322 +40,543 @@ __device__ __forceinline__ float block_sum_f32(float v, float* lds4) {
     return r;
 }
 
-// A projection's result arrives as `ks` partial sums over disjoint ranges of the contraction index (slabs, `slab`
-// floats apart), summed here in slab order: the split keeps every compute unit busy on matrices this small, and
-// a fixed order keeps the result reproducible bit for bit.
-__device__ __forceinline__ float slab_sum(const float* __restrict__ p, int ks, size_t slab) {
-    float v = p[0];
-    for (int j = 1; j < ks; ++j) v += p[(size_t)j * slab];
-    return v;
-}
-
-// ---------------------------------------------------------------- embedding + first RMSNorm
-__global__ __launch_bounds__(kBlock) void k_body_embed_norm(int d, int V, float eps, const int32_t* __restrict__ token_src,
-                                                            int token_stride, int rows_per_token,
-                                                            const uint16_t* __restrict__ embed, const float* __restrict__ g,
-                                                            float* __restrict__ x, uint16_t* __restrict__ hb) {
-    __shared__ float s_red[kWavesPerBlock];
+// ---------------------------------------------------------------- embedding
+// The second half of the workgroup's work: cos and sin of the row's position times every rotation frequency, which all
+// layers share, in fp64 (a position times a tiny frequency loses digits in fp32).
+__global__ __launch_bounds__(kBlock) void k_body_embed(int d, int V, const int32_t* __restrict__ token_src, int token_stride,
+                                                       int rows_per_token, const uint16_t* __restrict__ embed,
+                                                       float* __restrict__ x, const int32_t* __restrict__ ctx_len, int max_ctx,
+                                                       int hd, double log2_theta, double2* __restrict__ trig /* [rows][hd/2] */) {
     const int r = blockIdx.x;
+    const int pos = min(max(ctx_len[r], 0), max_ctx - 1);
     int tok = token_src[(size_t)(r / rows_per_token) * token_stride];
     tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
     const uint16_t* e = embed + (size_t)tok * d;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < d; i += kBlock) {
-        const float v = bf16_bits_to_f32(e[i]);
-        x[(size_t)r * d + i] = v;
-        ss += v * v;
+    for (int i = threadIdx.x; i < d / 8; i += kBlock) {
+        const u32x4b w = *reinterpret_cast<const u32x4b*>(e + 8 * i);
+        float4* xp = reinterpret_cast<float4*>(x + (size_t)r * d + 8 * i);
+        auto lo = [&](int q) { return __builtin_bit_cast(float, w[q] << 16); };
+        auto hi = [&](int q) { return __builtin_bit_cast(float, w[q] & 0xffff0000u); };
+        xp[0] = make_float4(lo(0), hi(0), lo(1), hi(1));
+        xp[1] = make_float4(lo(2), hi(2), lo(3), hi(3));
     }
-    const float inv = 1.f / sqrtf(block_sum_f32(ss, s_red) / (float)d + eps);
-    for (int i = threadIdx.x; i < d; i += kBlock)
-        hb[(size_t)r * d + i] = f32_to_bf16_bits(bf16_bits_to_f32(e[i]) * inv * g[i]);
+    const int i = kBlock - 1 - threadIdx.x;                                // hd / 2 <= 64 angles: the last wave's lanes
+    if (i < hd / 2) {
+        double sn, cs;
+        sincos((double)pos * exp2(-2.0 * (double)i / (double)hd * log2_theta), &sn, &cs);
+        trig[(size_t)r * (hd / 2) + i] = make_double2(cs, sn);
+    }
 }
 
-// ---------------------------------------------------------------- residual + RMSNorm (+ position advance at the end of a step)
-// One workgroup per row, a thread per four consecutive elements; the slabs are requested eight at a time so that
-// a row costs two or three trips to memory, not one per slab.
-constexpr int kSlabBatch = 8;
-__global__ __launch_bounds__(kBlock) void k_body_add_norm(int d, float eps, int ks, size_t slab, float* __restrict__ x,
-                                                          const float* __restrict__ y /* [ks][rows,d] */,
-                                                          const float* __restrict__ g, uint16_t* __restrict__ out,
-                                                          int32_t* ctx_len_advance) {
+// ---------------------------------------------------------------- RMSNorm of the residual stream (+ position advance at the end of a step)
+__global__ __launch_bounds__(kBlock) void k_body_norm(int d, float eps, const float* __restrict__ x, const float* __restrict__ g,
+                                                      uint16_t* __restrict__ out, int32_t* __restrict__ ctx_len_advance) {
     __shared__ float s_red[kWavesPerBlock];
-    extern __shared__ __attribute__((aligned(16))) float4 s_row[];        // [d / 4] the row after the addition
     const int r = blockIdx.x;
+    const float4* xr = reinterpret_cast<const float4*>(x + (size_t)r * d);
     float ss = 0.f;
     for (int i = threadIdx.x; i < d / 4; i += kBlock) {
-        float4 v = *reinterpret_cast<const float4*>(x + (size_t)r * d + 4 * i);
-        const float* yp = y + (size_t)r * d + 4 * i;
-        for (int j0 = 0; j0 < ks; j0 += kSlabBatch) {
-            float4 part[kSlabBatch];
-#pragma unroll
-            for (int u = 0; u < kSlabBatch; ++u)                             // past the last slab: re-read it, add nothing
-                part[u] = *reinterpret_cast<const float4*>(yp + (size_t)min(j0 + u, ks - 1) * slab);
-#pragma unroll
-            for (int u = 0; u < kSlabBatch; ++u)
-                if (j0 + u < ks) { v.x += part[u].x; v.y += part[u].y; v.z += part[u].z; v.w += part[u].w; }
-        }
-        *reinterpret_cast<float4*>(x + (size_t)r * d + 4 * i) = v;
-        s_row[i] = v;
+        const float4 v = xr[i];
         ss += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     }
     const float inv = 1.f / sqrtf(block_sum_f32(ss, s_red) / (float)d + eps);
     for (int i = threadIdx.x; i < d / 4; i += kBlock) {
-        const float4 v = s_row[i], gg = *reinterpret_cast<const float4*>(g + 4 * i);
-        const uint32_t lo = f32_to_bf16_bits(v.x * inv * gg.x) | ((uint32_t)f32_to_bf16_bits(v.y * inv * gg.y) << 16);
-        const uint32_t hi = f32_to_bf16_bits(v.z * inv * gg.z) | ((uint32_t)f32_to_bf16_bits(v.w * inv * gg.w) << 16);
-        *reinterpret_cast<uint2*>(out + (size_t)r * d + 4 * i) = make_uint2(lo, hi);
+        const float4 v = xr[i];
+        const float4 gg = *reinterpret_cast<const float4*>(g + 4 * i);
+        *reinterpret_cast<uint2*>(out + (size_t)r * d + 4 * i) = pack_bf16x4(v.x * inv * gg.x, v.y * inv * gg.y, v.z * inv * gg.z, v.w * inv * gg.w);
     }
     if (ctx_len_advance != nullptr && threadIdx.x == 0) ctx_len_advance[r] += 1;
 }
 
-// ---------------------------------------------------------------- SwiGLU: silu(gate) * up
-__global__ __launch_bounds__(kBlock) void k_body_silu_mul(int rows, int d_ff, int ks, size_t slab,
-                                                          const float* __restrict__ gu /* [ks][rows, 2 d_ff] */,
+// ---------------------------------------------------------------- projections
+// One workgroup = 16 * MB rows and one 16-column tile of the result (two tiles that belong together for the rotation and
+// for SwiGLU), over the whole contraction: its waves take k-blocks of 64 in turn, read W straight into the operand layout
+// of v_mfma_f32_16x16x32_bf16 and meet through LDS, where the results are added in wave order.  A lane's two 16-byte
+// pieces of a k-block are adjacent (the contraction index is permuted alike in both operands), so that four lanes read
+// one whole 128-byte line of a row.  Everything a wave needs is requested before anything is used (G = k-blocks a wave
+// requests together), what is needed first first.
+//   IN  kInNorm:    X = bf16(x * inv_rms * g): a wave reads whole rows of the residual stream (CI pieces of 256 columns),
+//                   so that it has their sums of squares, and leaves the rows in LDS
+//       kInBf16:    X as it is, straight into operand layout
+//       kInMerge:   X = the attention's partial results of `splits` key ranges, merged into LDS
+//   EPI kEpiRope:   q/k/v columns: rotation in fp64, queries to `q`, the new key and value to the caches
+//       kEpiSilu:   gate and up columns of the same 16 units: silu(gate) * up
+//       kEpiAdd:    residual addition in place
+// At 64 rows of d = 768, d_ff = 3072 a launch moves 1 to 9 MB: latency, the rate at which a compute unit takes in W and X
+// (64 bytes a cycle: every workgroup reads its rows of X whole) and the instructions fetched once bound it.  Measured
+// there: q/k/v 7.5, o 4.7, gate/up 9.7, down 8.0 us; with the contraction split over workgroups, partial sums in memory and
+// rotation, residual + norm and SwiGLU kernels of their own a layer took 62 us instead of 50.
+enum { kInNorm = 0, kInBf16 = 1, kInMerge = 2 };
+enum { kEpiRope = 0, kEpiSilu = 1, kEpiAdd = 2 };
+
+struct ProjArgs {
+    int M, N, K;                 // rows, columns of the result (kEpiSilu: units), contraction
+    const uint16_t* W;
+    const uint16_t* X;           // kInBf16: [M,K]
+    float* x;                    // residual stream [M,d]: read by kInNorm, updated by kEpiAdd
+    const float* g;              // kInNorm
+    float eps;
+    const float* po;             // kInMerge: [splits][M,K] sums of p * v, not normalised
+    const float* pml;            // kInMerge: [M][heads][splits][2] maximum (base 2) and sum of p
+    int splits, hd;
+    float* q;                    // kEpiRope: [M,d]
+    uint16_t* kc;
+    uint16_t* vc;
+    const int32_t* ctx_len;
+    int max_ctx;
+    const double2* trig;         // kEpiRope: [M][hd/2] cos, sin of the rows' positions
+    uint16_t* act;               // kEpiSilu: [M,N]
+};
+
+__host__ __device__ constexpr int staged_row(int K) { return (K + 63) / 64 * 64 + 8; }   // bf16 of one staged row of X, padded
+
+// kInMerge: the rows' attention output, merged over SP key ranges, U pieces of four columns per thread in flight.
+template <int SP, int U>
+__device__ __forceinline__ void merge_splits(const ProjArgs& a, int m0, int threads, uint16_t* s_x) {
+    const int xrow = staged_row(a.K), per_row = (a.K + 63) / 64 * 16, heads = a.K / a.hd, total = min(16, a.M - m0) * per_row;
+    for (int u0 = threadIdx.x; u0 < total; u0 += threads * U) {
+        float4 o[U][SP];
+        float2 ml[U][SP];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int idx = min(u0 + u * threads, total - 1), m = m0 + idx / per_row, k = min((idx % per_row) * 4, a.K - 4);
+#pragma unroll
+            for (int s = 0; s < SP; ++s) {
+                ml[u][s] = *reinterpret_cast<const float2*>(a.pml + (((size_t)m * heads + k / a.hd) * SP + s) * 2);
+                o[u][s] = *reinterpret_cast<const float4*>(a.po + ((size_t)s * a.M + m) * a.K + k);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int idx = u0 + u * threads;
+            float M = ml[u][0].x;
+#pragma unroll
+            for (int s = 1; s < SP; ++s) M = fmaxf(M, ml[u][s].x);
+            float L = 0.f;
+            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int s = 0; s < SP; ++s) {
+                const float w = __builtin_amdgcn_exp2f(ml[u][s].x - M);
+                L += ml[u][s].y * w;
+                t.x += o[u][s].x * w; t.y += o[u][s].y * w; t.z += o[u][s].z * w; t.w += o[u][s].w * w;
+            }
+            if (idx < total) {
+                const int row = idx / per_row, k = (idx % per_row) * 4;
+                const float inv = 1.f / L;
+                *reinterpret_cast<uint2*>(s_x + row * xrow + k) = k < a.K ? pack_bf16x4(t.x * inv, t.y * inv, t.z * inv, t.w * inv) : make_uint2(0u, 0u);
+            }
+        }
+    }
+}
+
+template <int NW, int MB, int G, int CI, int IN, int EPI>
+__global__ __launch_bounds__(NW * 64) void k_body_proj(ProjArgs a) {
+    constexpr int NB = (EPI == kEpiAdd) ? 1 : 2;
+    constexpr int kThreads = NW * 64;
+    constexpr int kElems = (MB * 256 + kThreads - 1) / kThreads;          // result positions (or pairs) per thread
+    constexpr int RW = MB * 16 / NW;                                      // kInNorm: rows a wave stages
+    static_assert(IN != kInMerge || MB == 1, "the merge stages 16 rows");
+    // staged rows of X, then (after a barrier) the waves' results [NW][NB][MB][16][20]
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
+    uint16_t* const s_x = reinterpret_cast<uint16_t*>(s_dyn);
+    float* const s_acc = reinterpret_cast<float*>(s_dyn);
+    const int tile = blockIdx.x, m0 = blockIdx.y * (MB * 16), tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, c = lane >> 4, K = a.K, KB = (K + 63) / 64, xrow = staged_row(K);
+
+    // which columns: [part][d] for q/k/v; the second tile is the rotation's other half, the up column, or the next 16
+    int col0 = tile * 16, col1 = 0, lim0 = a.N, part = 0, j0 = 0;
+    if (EPI == kEpiRope) {
+        const int d = a.N / 3, per_part = (d + 31) / 32;
+        part = tile / per_part;
+        const int t = tile % per_part;
+        if (a.hd >= 32) {
+            const int per_head = a.hd / 32, head = t / per_head;
+            j0 = (t % per_head) * 16;
+            col0 = part * d + head * a.hd + j0;
+            col1 = col0 + a.hd / 2;
+        } else {
+            j0 = t * 32;                                                  // first of 32 adjacent columns: whole heads
+            col0 = part * d + j0;
+            col1 = col0 + 16;
+        }
+        lim0 = part * d + d;
+    } else if (EPI == kEpiSilu) {
+        col1 = a.N + col0;
+    }
+    // uniform bases and 32-bit lane offsets (in bytes): a load is one instruction with no 64-bit address arithmetic
+    const char* wb[NB];
+    uint32_t wo[NB], xo[MB];
+    wb[0] = reinterpret_cast<const char*>(a.W) + (size_t)col0 * K * 2;
+    wo[0] = (uint32_t)min(r16, lim0 - 1 - col0) * (uint32_t)K * 2u;
+    if (NB == 2) {                                                        // (hd < 32: the second 16 columns may start past the part)
+        const int lim1 = (EPI == kEpiSilu) ? 2 * a.N : lim0, first = min(col1, lim1 - 1);
+        wb[NB - 1] = reinterpret_cast<const char*>(a.W) + (size_t)first * K * 2;
+        wo[NB - 1] = (uint32_t)min(r16, lim1 - 1 - first) * (uint32_t)K * 2u;
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) xo[mb] = (uint32_t)min(mb * 16 + r16, a.M - 1 - m0) * (uint32_t)K * 2u;
+
+    // ---- requests, in the order of use
+    int pos[kElems];
+    if (EPI == kEpiRope) {
+#pragma unroll
+        for (int e = 0; e < kElems; ++e) pos[e] = a.ctx_len[min(m0 + ((tid + e * kThreads) >> 4), a.M - 1)];
+    }
+    f32x4b xr[(IN == kInNorm) ? RW : 1][(IN == kInNorm) ? CI : 1], gr[(IN == kInNorm) ? CI : 1];
+    if (IN == kInNorm) {
+        const char* xbase = reinterpret_cast<const char*>(a.x) + (size_t)m0 * K * 4;
+#pragma unroll
+        for (int i = 0; i < CI; ++i) {
+            const uint32_t k = (uint32_t)min((i * 64 + lane) * 4, K - 4) * 4u;
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+                if (m0 + wave + r * NW < a.M)                             // uniform: rows that are not there are not read
+                    xr[r][i] = *reinterpret_cast<const f32x4b*>(xbase + (size_t)((wave + r * NW) * K) * 4 + k);
+        }
+#pragma unroll
+        for (int i = 0; i < CI; ++i)
+            gr[i] = *reinterpret_cast<const f32x4b*>(reinterpret_cast<const char*>(a.g) + (uint32_t)min((i * 64 + lane) * 4, K - 4) * 4u);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    bf16x8 wv[G][NB][2], xb[(IN == kInBf16) ? G : 1][MB][2];
+    auto request = [&](int b0) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int kb = min(b0 + q * NW, KB - 1);                      // past the last block: re-read, not used
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const uint32_t k = min((uint32_t)(kb * 128 + c * 32 + p * 16), (uint32_t)K * 2u - 16u);   // past the last column: masked below
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) wv[q][nb][p] = *reinterpret_cast<const bf16x8*>(wb[nb] + (wo[nb] + k));
+                if (IN == kInBf16) {
+                    const char* xbase = reinterpret_cast<const char*>(a.X) + (size_t)m0 * K * 2;
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+                        if (m0 + mb * 16 + r16 < a.M) xb[q][mb][p] = *reinterpret_cast<const bf16x8*>(xbase + (xo[mb] + k));
+                }
+            }
+        }
+    };
+    request(wave);
+    float xold[kElems];                                                   // kEpiAdd: the residual stream's entries of this thread
+    if (EPI == kEpiAdd) {
+#pragma unroll
+        for (int e = 0; e < kElems; ++e) {
+            const int idx = tid + e * kThreads;
+            xold[e] = a.x[(size_t)min(m0 + (idx >> 4), a.M - 1) * a.N + min(col0 + (idx & 15), a.N - 1)];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- while W is on its way: the staged rows
+    if (IN == kInNorm) {
+        float mine = 0.f;                                                 // lane r: row r's sum of squares, then 1 / rms
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            float ss = 0.f;
+#pragma unroll
+            for (int i = 0; i < CI; ++i) {
+                const f32x4b v = xr[r][i];
+                const float t = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+                ss += ((i * 64 + lane) * 4 < K) ? t : 0.f;
+            }
+            ss = wave_sum(ss);
+            mine = (lane == r) ? ss : mine;
+        }
+        mine = 1.f / sqrtf(mine / (float)K + a.eps);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const float inv = lane_f32(mine, r);
+#pragma unroll
+            for (int i = 0; i < CI; ++i) {
+                const int k = (i * 64 + lane) * 4;
+                const f32x4b v = xr[r][i];
+                if (k < KB * 64)
+                    *reinterpret_cast<uint2*>(s_x + (wave + r * NW) * xrow + k) =
+                        k < K ? pack_bf16x4(v[0] * inv * gr[i][0], v[1] * inv * gr[i][1], v[2] * inv * gr[i][2], v[3] * inv * gr[i][3])
+                              : make_uint2(0u, 0u);
+            }
+        }
+    }
+    if (IN == kInMerge) {
+        if (a.splits == 2) merge_splits<2, 6>(a, m0, kThreads, s_x);
+        else if (a.splits == 4) merge_splits<4, 3>(a, m0, kThreads, s_x);
+        else merge_splits<8, 2>(a, m0, kThreads, s_x);
+    }
+    double2 cs[kElems];
+    int ia[kElems], ib[kElems];                                           // columns (0..31 of the two tiles) of a pair
+    if (EPI == kEpiRope) {
+        const int half = a.hd / 2;
+#pragma unroll
+        for (int e = 0; e < kElems; ++e) {
+            const int n = (tid + e * kThreads) & 15;
+            pos[e] = pos[e] < 0 ? 0 : (pos[e] >= a.max_ctx ? a.max_ctx - 1 : pos[e]);   // never write outside the row's cache
+            ia[e] = (a.hd >= 32) ? n : (n / half) * a.hd + n % half;
+            ib[e] = (a.hd >= 32) ? n + 16 : ia[e] + half;
+            cs[e] = a.trig[(size_t)min(m0 + ((tid + e * kThreads) >> 4), a.M - 1) * half + ((a.hd >= 32) ? j0 + n : n % half)];
+        }
+    }
+    if (IN != kInBf16) lds_barrier();
+
+    f32x4b acc[NB][MB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4b{0.f, 0.f, 0.f, 0.f};
+    const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    const bool ragged = (K & 63) != 0;
+    for (int b0 = wave; b0 < KB; b0 += NW * G) {
+        if (b0 != wave) request(b0);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int kb = b0 + q * NW;
+            if (kb < KB) {
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const int k = kb * 64 + c * 16 + p * 8;
+                    if (ragged && k >= K) {                               // K is a multiple of 8: a piece is in or out
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) wv[q][nb][p] = zero;
+                        if (IN == kInBf16) {
+#pragma unroll
+                            for (int mb = 0; mb < MB; ++mb) xb[q][mb][p] = zero;
+                        }
+                    }
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb) {
+                        const bf16x8 xv = (IN == kInBf16) ? xb[q][mb][p]
+                                        : *reinterpret_cast<const bf16x8*>(s_x + (IN == kInMerge ? min(r16, a.M - 1 - m0) : mb * 16 + r16) * xrow + k);
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[q][nb][p], xv, acc[nb][mb], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+    if (IN != kInBf16) __syncthreads();                                   // every wave is done with the staged rows
+    // accumulator: lane holds row r16 of the block, columns 4 c .. 4 c + 3 of the tile
+    auto slot_of = [&](int w, int nb, int mb, int row, int col) { return (((w * NB + nb) * MB + mb) * 16 + row) * 20 + col; };
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) *reinterpret_cast<f32x4b*>(s_acc + slot_of(wave, nb, mb, r16, 4 * c)) = acc[nb][mb];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kElems; ++e) {
+        const int idx = tid + e * kThreads;
+        if (idx >= MB * 256) break;
+        const int mb = idx >> 8, ml = (idx >> 4) & 15, n = idx & 15, m = m0 + mb * 16 + ml;
+        auto total = [&](int col) {
+            float t = s_acc[slot_of(0, col >> 4, mb, ml, col & 15)];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) t += s_acc[slot_of(w, col >> 4, mb, ml, col & 15)];
+            return t;
+        };
+        if (m >= a.M) continue;
+        if (EPI == kEpiAdd) {
+            const int col = col0 + n;
+            if (col < a.N) a.x[(size_t)m * a.N + col] = xold[e] + total(n);
+        } else if (EPI == kEpiSilu) {
+            const int col = col0 + n;
+            if (col < a.N) {
+                const float gte = total(n), up = total(16 + n);
+                a.act[(size_t)m * a.N + col] = f32_to_bf16_bits(gte / (1.f + __expf(-gte)) * up);
+            }
+        } else {
+            const int d = a.N / 3;
+            const int ca = (a.hd >= 32) ? col0 - part * d + n : j0 + ia[e], cb = (a.hd >= 32) ? ca + a.hd / 2 : j0 + ib[e];
+            if (cb < d) {
+                const float v0 = total(ia[e]), v1 = total(ib[e]);
+                const size_t slot = ((size_t)m * a.max_ctx + pos[e]) * d;
+                if (part == 2) {
+                    a.vc[slot + ca] = f32_to_bf16_bits(v0);
+                    a.vc[slot + cb] = f32_to_bf16_bits(v1);
+                } else {
+                    const float y0 = (float)((double)v0 * cs[e].x - (double)v1 * cs[e].y), y1 = (float)((double)v1 * cs[e].x + (double)v0 * cs[e].y);
+                    if (part == 0) {
+                        a.q[(size_t)m * d + ca] = y0;
+                        a.q[(size_t)m * d + cb] = y1;
+                    } else {
+                        a.kc[slot + ca] = f32_to_bf16_bits(y0);
+                        a.kc[slot + cb] = f32_to_bf16_bits(y1);
+                    }
+                }
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------- many rows: what the projections above do in their epilogues
+// Beyond fused_rows() the projections are GEMMs of their own (the LM head's kernels) with fp32 results `y`.
+__global__ __launch_bounds__(kBlock) void k_body_add(size_t count4, float4* __restrict__ x, const float4* __restrict__ y) {
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= count4) return;
+    const float4 a = x[i], b = y[i];
+    x[i] = make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+
+__global__ __launch_bounds__(kBlock) void k_body_silu_mul(int rows, int d_ff, const float* __restrict__ gu /* [rows, 2 d_ff] */,
                                                           uint16_t* __restrict__ act) {
     const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= (size_t)rows * d_ff) return;
     const size_t r = i / d_ff, f = i % d_ff;
-    const float gte = slab_sum(gu + r * 2 * d_ff + f, ks, slab), up = slab_sum(gu + r * 2 * d_ff + d_ff + f, ks, slab);
+    const float gte = gu[r * 2 * d_ff + f], up = gu[r * 2 * d_ff + d_ff + f];
     act[i] = f32_to_bf16_bits(gte / (1.f + __expf(-gte)) * up);
 }
 
-// ---------------------------------------------------------------- projection for <= 64 rows, split over the contraction
-// Y[ks][m][n] = sum over the ks-th K range of X[m][k] W[n][k].  One workgroup = one 32-column tile of the result
-// and one K range; its four waves take a quarter of the range each, reading W and X straight into the MFMA operand
-// layout (lane = row, 8 consecutive k: 32 bytes per row and instruction, whole lines over four instructions),
-// and meet through LDS: wave w sums, in wave order, the quarter of the accumulator it then stores.  The matrices
-// are a few megabytes: what matters is that a few hundred workgroups each have their loads in flight at once.
-constexpr int kProjGroup = 4;                         // k-steps (of 16) requested together
-template <int MT>
-__global__ __launch_bounds__(kBlock) void k_body_proj(int M, int N, int K, int steps_per_wave,
-                                                      const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
-                                                      float* __restrict__ Y, size_t slab) {
-    __shared__ __attribute__((aligned(16))) float4 s_acc[kWavesPerBlock][MT][4][kWave];
-    const int tile = blockIdx.x, ks = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nn = lane & 31, half = lane >> 5;
-    const int k0 = ((ks * kWavesPerBlock + wave) * steps_per_wave) * 16 + half * 8;
-    const uint16_t* wp = W + (size_t)min(tile * 32 + nn, N - 1) * K + k0;
-    const uint16_t* xp[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) xp[mt] = X + (size_t)min(mt * 32 + nn, M - 1) * K + k0;
-    f32x16 acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
-    for (int s0 = 0; s0 < steps_per_wave; s0 += kProjGroup) {
-        bf16x8 wv[kProjGroup], xv[kProjGroup][MT];
-#pragma unroll
-        for (int q = 0; q < kProjGroup; ++q) {
-            const int s = min(s0 + q, steps_per_wave - 1);          // a short last group re-reads its last step
-            wv[q] = *reinterpret_cast<const bf16x8*>(wp + s * 16);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) xv[q][mt] = *reinterpret_cast<const bf16x8*>(xp[mt] + s * 16);
-        }
-#pragma unroll
-        for (int q = 0; q < kProjGroup; ++q) {
-            if (s0 + q < steps_per_wave) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv[q], xv[q][mt], acc[mt], 0, 0, 0);
-            }
-        }
-    }
-    // accumulator: lane holds result row m = nn (+ 32 mt), columns n = 8 g + 4 half + 0..3 in registers 4 g .. 4 g + 3
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            s_acc[wave][mt][g][lane] = make_float4(acc[mt][4 * g], acc[mt][4 * g + 1], acc[mt][4 * g + 2], acc[mt][4 * g + 3]);
-    __syncthreads();
-    const int g = wave;                                              // this wave finishes column group g
-    const int n = tile * 32 + 8 * g + 4 * half;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        float4 t = s_acc[0][mt][g][lane];
-#pragma unroll
-        for (int w = 1; w < kWavesPerBlock; ++w) {
-            const float4 o = s_acc[w][mt][g][lane];
-            t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
-        }
-        const int m = mt * 32 + nn;
-        if (m < M && n < N) *reinterpret_cast<float4*>(Y + (size_t)ks * slab + (size_t)m * N + n) = t;   // N % 4 == 0
-    }
-}
-
-// ---------------------------------------------------------------- projection for <= 64 rows, wide results
-// The same contraction for results wide enough to fill the chip with fewer K ranges: one workgroup = four
-// 32-column tiles (one per wave) and one K range of KG * 64.  The X chunk of the range is staged once into LDS
-// and shared by the four waves (all workgroups read the same few X lines, so fetching them once per workgroup
-// instead of once per wave matters); every wave requests all of its W before anything else.
-template <int MT, int KG>
-__global__ __launch_bounds__(kBlock) void k_body_proj_wide(int M, int N, int K, const uint16_t* __restrict__ X,
-                                                           const uint16_t* __restrict__ W, float* __restrict__ Y, size_t slab) {
-    constexpr int KC = KG * 64, CH = KC / 8, XROW = KC * 2 + 16;          // chunk width, its 16-byte pieces, padded LDS row
-    __shared__ __attribute__((aligned(16))) unsigned char s_x[MT * 32 * XROW];
-    const int ks = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nn = lane & 31, half = lane >> 5;
-    const int tile = blockIdx.x * kWavesPerBlock + wave;
-    const int kbase = ks * KC;
-    const uint16_t* wp = W + (size_t)min(tile * 32 + nn, N - 1) * K + kbase + half * 8;
-    bf16x8 wv[KG * 4];
-#pragma unroll
-    for (int q = 0; q < KG * 4; ++q) wv[q] = *reinterpret_cast<const bf16x8*>(wp + q * 16);
-    constexpr int kPieces = MT * 32 * CH, kPer = (kPieces + kBlock - 1) / kBlock;
-    u32x4b xr[kPer];
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int p = min(tid + q * kBlock, kPieces - 1), row = min(p / CH, M - 1), c = p % CH;
-        xr[q] = *reinterpret_cast<const u32x4b*>(X + (size_t)row * K + kbase + c * 8);
-    }
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int p = tid + q * kBlock;
-        if (p < kPieces) *reinterpret_cast<u32x4b*>(s_x + (p / CH) * XROW + (p % CH) * 16) = xr[q];
-    }
-    __syncthreads();
-    f32x16 acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
-#pragma unroll
-    for (int q = 0; q < KG * 4; ++q)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const bf16x8 xv = *reinterpret_cast<const bf16x8*>(s_x + (mt * 32 + nn) * XROW + (2 * q + half) * 16);
-            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv[q], xv, acc[mt], 0, 0, 0);
-        }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int m = mt * 32 + nn;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int n = tile * 32 + 8 * g + 4 * half;
-            if (m < M && n < N)
-                *reinterpret_cast<float4*>(Y + (size_t)ks * slab + (size_t)m * N + n) =
-                    make_float4(acc[mt][4 * g], acc[mt][4 * g + 1], acc[mt][4 * g + 2], acc[mt][4 * g + 3]);
-        }
-    }
-}
-
-// ---------------------------------------------------------------- rotary embedding + cache append + attention
-// Grid (head, row), four waves.  The rotation is done in fp64 (a position times a tiny frequency loses digits in
-// fp32).  A key's (value's) head slice is hd contiguous bf16: LPK = hd / 8 lanes read it as 16-byte pieces, so one
-// wave instruction fetches 64 / LPK whole slices, and every lane keeps four such loads in flight.  Scores: dot
-// product over the LPK lanes, softmax over the workgroup through LDS.  Values: every lane accumulates its 8
-// dimensions over the keys it sees; lanes, then waves, are summed in a fixed order.
-constexpr int kAttnUnroll = 4;
-template <int LPK>
-__global__ __launch_bounds__(kBlock) void k_body_rope_attn(int d, int max_ctx, double theta, int ks, size_t slab,
-                                                           const float* __restrict__ qkv /* [ks][rows,3d] */,
-                                                           const int32_t* __restrict__ ctx_len,
-                                                           uint16_t* __restrict__ kc /* [rows,max_ctx,d] of this layer */,
-                                                           uint16_t* __restrict__ vc, uint16_t* __restrict__ att /* [rows,d] */) {
-    constexpr int hd = LPK * 8, G = kWave / LPK;                          // G keys per wave instruction
-    extern __shared__ __attribute__((aligned(16))) float s_sc[];          // [max_ctx] scores, then probabilities
-    __shared__ float s_q[hd], s_part[kWavesPerBlock][hd];
-    __shared__ float s_redf[kWavesPerBlock];
-    const int hh = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int pos = ctx_len[r];
-    pos = pos < 0 ? 0 : (pos >= max_ctx ? max_ctx - 1 : pos);            // never write outside the row's cache
-    const float* q = qkv + (size_t)r * 3 * d + hh * hd;
-    const float* k = q + d;
-    const float* v = q + 2 * d;
-    uint16_t* Kr = kc + (size_t)r * max_ctx * d + hh * hd;                // key t of this head: Kr + t * d
-    uint16_t* Vr = vc + (size_t)r * max_ctx * d + hh * hd;
-    if (tid < hd / 2) {
-        const int i = tid;
-        const double ang = (double)pos * pow(theta, -2.0 * (double)i / (double)hd);
-        double sn, cs;
-        sincos(ang, &sn, &cs);
-        const double q0 = (double)slab_sum(q + i, ks, slab), q1 = (double)slab_sum(q + i + hd / 2, ks, slab);
-        const double k0 = (double)slab_sum(k + i, ks, slab), k1 = (double)slab_sum(k + i + hd / 2, ks, slab);
-        s_q[i] = (float)(q0 * cs - q1 * sn);
-        s_q[i + hd / 2] = (float)(q1 * cs + q0 * sn);
-        Kr[(size_t)pos * d + i] = f32_to_bf16_bits((float)(k0 * cs - k1 * sn));
-        Kr[(size_t)pos * d + i + hd / 2] = f32_to_bf16_bits((float)(k1 * cs + k0 * sn));
-    }
-    if (tid >= 128 && tid < 128 + hd) {
-        const int i = tid - 128;
-        Vr[(size_t)pos * d + i] = f32_to_bf16_bits(slab_sum(v + i, ks, slab));
-    }
-    __syncthreads();                    // the new key and value are read back below by other waves of this workgroup
-    const int g = lane / LPK, c = lane % LPK;
-    float qr[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) qr[e] = s_q[c * 8 + e];
-    const float scale = 1.f / sqrtf((float)hd);
-    constexpr int kStride = kWavesPerBlock * G;                           // keys per workgroup instruction
-    float mx = -INFINITY;
-    for (int base = wave * G + g; base - g - wave * G <= pos; base += kStride * kAttnUnroll) {
-        u32x4b w4[kAttnUnroll];
-#pragma unroll
-        for (int u = 0; u < kAttnUnroll; ++u)                            // keys past the end re-read key pos
-            w4[u] = *reinterpret_cast<const u32x4b*>(Kr + (size_t)min(base + u * kStride, pos) * d + c * 8);
-#pragma unroll
-        for (int u = 0; u < kAttnUnroll; ++u) {
-            float acc = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc += qr[2 * e] * __builtin_bit_cast(float, w4[u][e] << 16);
-                acc += qr[2 * e + 1] * __builtin_bit_cast(float, w4[u][e] & 0xffff0000u);
-            }
-#pragma unroll
-            for (int off = 1; off < LPK; off <<= 1) acc += __shfl_xor(acc, off);
-            const int t = base + u * kStride;
-            if (t <= pos) {
-                acc *= scale;
-                if (c == 0) s_sc[t] = acc;
-                mx = fmaxf(mx, acc);
-            }
-        }
-    }
-    mx = block_max(mx, s_redf);                                          // its barriers also publish s_sc
-    float zs = 0.f;
-    for (int t = tid; t <= pos; t += kBlock) {
-        const float p = __expf(s_sc[t] - mx);
-        s_sc[t] = p;
-        zs += p;
-    }
-    const float Z = block_sum_f32(zs, s_redf);
-    float o[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = 0.f;
-    for (int base = wave * G + g; base - g - wave * G <= pos; base += kStride * kAttnUnroll) {
-        u32x4b w4[kAttnUnroll];
-        float p[kAttnUnroll];
-#pragma unroll
-        for (int u = 0; u < kAttnUnroll; ++u) {
-            const int t = base + u * kStride;
-            w4[u] = *reinterpret_cast<const u32x4b*>(Vr + (size_t)min(t, pos) * d + c * 8);
-            p[u] = (t <= pos) ? s_sc[t] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < kAttnUnroll; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                o[2 * e] += p[u] * __builtin_bit_cast(float, w4[u][e] << 16);
-                o[2 * e + 1] += p[u] * __builtin_bit_cast(float, w4[u][e] & 0xffff0000u);
-            }
-    }
-#pragma unroll
-    for (int off = LPK; off < kWave; off <<= 1)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], off);
-    if (lane < LPK) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s_part[wave][lane * 8 + e] = o[e];
-    }
-    __syncthreads();
-    if (tid < hd) {
-        const float sum = ((s_part[0][tid] + s_part[1][tid]) + (s_part[2][tid] + s_part[3][tid])) / Z;
-        att[(size_t)r * d + hh * hd + tid] = f32_to_bf16_bits(sum);
+__global__ __launch_bounds__(kBlock) void k_body_rope(int d, int hd, int max_ctx, const float* __restrict__ qkv /* [rows,3d] */,
+                                                      const double2* __restrict__ trig, const int32_t* __restrict__ ctx_len,
+                                                      float* __restrict__ q, uint16_t* __restrict__ kc, uint16_t* __restrict__ vc) {
+    const int r = blockIdx.x, half = hd / 2;
+    const int pos = min(max(ctx_len[r], 0), max_ctx - 1);
+    const size_t slot = ((size_t)r * max_ctx + pos) * d;
+    for (int t = threadIdx.x; t < d / 2; t += kBlock) {
+        const int i = t % half, ca = t / half * hd + i, cb = ca + half;
+        const double2 cs = trig[(size_t)r * half + i];
+        const float* y = qkv + (size_t)r * 3 * d;
+        auto first = [&](const float* p) { return (float)((double)p[ca] * cs.x - (double)p[cb] * cs.y); };
+        auto second = [&](const float* p) { return (float)((double)p[cb] * cs.x + (double)p[ca] * cs.y); };
+        q[(size_t)r * d + ca] = first(y);
+        q[(size_t)r * d + cb] = second(y);
+        kc[slot + ca] = f32_to_bf16_bits(first(y + d));
+        kc[slot + cb] = f32_to_bf16_bits(second(y + d));
+        vc[slot + ca] = f32_to_bf16_bits(y[2 * d + ca]);
+        vc[slot + cb] = f32_to_bf16_bits(y[2 * d + cb]);
     }
 }
 
 __global__ void k_body_fill_ones(float* p, int count) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) p[i] = 1.f;
+}
+
+// ---------------------------------------------------------------- attention over the row's cache
+// Grid (head, row, key range), four waves.  A key's (value's) head slice is hd contiguous bf16: LPK = hd / 8 lanes read it
+// as 16-byte pieces, so one wave instruction fetches 64 / LPK whole slices.  Keys and values of a batch are requested
+// together and one batch ahead of the one being used; every group of LPK lanes keeps a running maximum, sum and its 8
+// dimensions of sum p v, and groups, then waves, are merged in a fixed order.  A row's keys are cut into gridDim.z ranges
+// of equal length, whose sums the output projection merges.  HBM-bound at 64 rows (100 MB of keys and values in 20.3 us, 24.5 us
+// with a pass over the keys, the softmax through LDS and a pass over the values); at few rows bound by how many compute
+// units read (4 rows of 12 heads, 1250 positions: 33.5 us in one range, 6.5 us in eight).
+constexpr int kAttnUnroll = 4;
+template <int LPK>
+__global__ __launch_bounds__(kBlock) void k_body_attn(int d, int max_ctx, const float* __restrict__ q, const int32_t* __restrict__ ctx_len,
+                                                      const uint16_t* __restrict__ kc /* [rows,max_ctx,d] of this layer */,
+                                                      const uint16_t* __restrict__ vc, uint16_t* __restrict__ att /* [rows,d]: one range */,
+                                                      float* __restrict__ po, float* __restrict__ pml /* several ranges */) {
+    constexpr int hd = LPK * 8, G = kWave / LPK;                          // G keys per wave instruction
+    constexpr int kStride = kWavesPerBlock * G;                           // keys per workgroup instruction
+    __shared__ float s_o[kWavesPerBlock][hd], s_m[kWavesPerBlock], s_l[kWavesPerBlock];
+    const int hh = blockIdx.x, r = blockIdx.y, sp = blockIdx.z, S = gridDim.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int pos = ctx_len[r];
+    pos = pos < 0 ? 0 : (pos >= max_ctx ? max_ctx - 1 : pos);
+    const int T = pos + 1, chunk = ((T + S - 1) / S + kStride - 1) / kStride * kStride;
+    const int t0 = sp * chunk, t1 = min(T, t0 + chunk);
+    const int g = lane / LPK, c = lane % LPK;
+    const uint16_t* Kr = kc + (size_t)r * max_ctx * d + hh * hd + c * 8;  // key t of this lane: Kr + t * d
+    const uint16_t* Vr = vc + (size_t)r * max_ctx * d + hh * hd + c * 8;
+    float qr[8];
+    {
+        const float scale = 1.44269504f / sqrtf((float)hd);               // scores in base 2
+        const float4* qp = reinterpret_cast<const float4*>(q + (size_t)r * d + hh * hd + c * 8);
+        const float4 a = qp[0], b = qp[1];
+        qr[0] = a.x * scale; qr[1] = a.y * scale; qr[2] = a.z * scale; qr[3] = a.w * scale;
+        qr[4] = b.x * scale; qr[5] = b.y * scale; qr[6] = b.z * scale; qr[7] = b.w * scale;
+    }
+    float m = -1e30f, l = 0.f, o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = 0.f;
+    if (t0 < t1) {
+        const int mine = wave * G + g;
+        u32x4b kw[kAttnUnroll], vw[kAttnUnroll], kn[kAttnUnroll], vn[kAttnUnroll];
+        auto request = [&](u32x4b (&k4)[kAttnUnroll], u32x4b (&v4)[kAttnUnroll], int tb) {
+#pragma unroll
+            for (int u = 0; u < kAttnUnroll; ++u)                        // keys past the end re-read the last one
+                k4[u] = *reinterpret_cast<const u32x4b*>(Kr + (size_t)min(tb + mine + u * kStride, t1 - 1) * d);
+#pragma unroll
+            for (int u = 0; u < kAttnUnroll; ++u)
+                v4[u] = *reinterpret_cast<const u32x4b*>(Vr + (size_t)min(tb + mine + u * kStride, t1 - 1) * d);
+        };
+        request(kw, vw, t0);
+        for (int tb = t0; tb < t1; tb += kStride * kAttnUnroll) {
+            const bool more = tb + kStride * kAttnUnroll < t1;
+            if (more) request(kn, vn, tb + kStride * kAttnUnroll);
+            float sc[kAttnUnroll];
+            float mn = m;
+#pragma unroll
+            for (int u = 0; u < kAttnUnroll; ++u) {
+                float acc = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc += qr[2 * e] * __builtin_bit_cast(float, kw[u][e] << 16);
+                    acc += qr[2 * e + 1] * __builtin_bit_cast(float, kw[u][e] & 0xffff0000u);
+                }
+                if (LPK > 1) acc += dpp_f32<kDppXor1>(acc);
+                if (LPK > 2) acc += dpp_f32<kDppXor2>(acc);
+                if (LPK > 4) acc += dpp_f32<kDppHalfMirror>(acc);
+                if (LPK > 8) acc += dpp_f32<kDppMirror>(acc);
+                sc[u] = (tb + mine + u * kStride < t1) ? acc : -INFINITY;
+                mn = fmaxf(mn, sc[u]);
+            }
+            const float keep = __builtin_amdgcn_exp2f(m - mn);
+            m = mn;
+            l *= keep;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] *= keep;
+#pragma unroll
+            for (int u = 0; u < kAttnUnroll; ++u) {
+                const float p = __builtin_amdgcn_exp2f(sc[u] - mn);
+                l += p;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    o[2 * e] += p * __builtin_bit_cast(float, vw[u][e] << 16);
+                    o[2 * e + 1] += p * __builtin_bit_cast(float, vw[u][e] & 0xffff0000u);
+                }
+            }
+            if (more) {
+#pragma unroll
+                for (int u = 0; u < kAttnUnroll; ++u) { kw[u] = kn[u]; vw[u] = vn[u]; }
+            }
+        }
+    }
+    float mw = m;
+#pragma unroll
+    for (int off = LPK; off < kWave; off <<= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
+    const float keep = __builtin_amdgcn_exp2f(m - mw);
+    l *= keep;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] *= keep;
+#pragma unroll
+    for (int off = LPK; off < kWave; off <<= 1) {
+        l += __shfl_xor(l, off);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], off);
+    }
+    if (lane < LPK) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s_o[wave][lane * 8 + e] = o[e];
+        if (lane == 0) { s_m[wave] = mw; s_l[wave] = l; }
+    }
+    __syncthreads();
+    if (tid < hd) {
+        const float M = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+        float sum = 0.f, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+            const float f = __builtin_amdgcn_exp2f(s_m[w] - M);
+            sum += s_o[w][tid] * f;
+            L += s_l[w] * f;
+        }
+        if (S == 1) {
+            att[(size_t)r * d + hh * hd + tid] = f32_to_bf16_bits(sum / L);
+        } else {
+            po[((size_t)sp * gridDim.y + r) * d + hh * hd + tid] = sum;
+            if (tid == 0)
+                *reinterpret_cast<float2*>(pml + (((size_t)r * gridDim.x + hh) * S + sp) * 2) = make_float2(M, L);
+        }
+    }
 }
 
 __global__ void k_body_rollback(int rows, int rows_per_seq, int gamma, const int32_t* __restrict__ ctx_base,
@@ -362,8 +591,12 @@ __global__ void k_body_rollback(int rows, int rows_per_seq, int gamma, const int
 // ---------------------------------------------------------------- host side
 static size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 
-// A projection [rows,K] x [N,K]^T can also run as an LM head with vocabulary N, hidden size K, one draft and `rows`
-// sequences: the route of shapes the split kernel does not take.
+// Whether the fused projections run.  They read W once per 16 or 32 rows, a GEMM once per 256: two layers take 512 us
+// against 937 us with GEMMs at 512 rows of d = 768 (702 against 881 at d = 1024), 843 against 982 at 1024 rows, 1555 against
+// 1149 at 2048 (1142 against 937 at 1024 rows of d = 1024; 454 against 523 at 2048 rows of d = 256).
+static bool fused_rows(int d, int rows) { return rows <= 512 || (long)rows * d <= 1024 * 768; }
+
+// A projection [rows,K] x [N,K]^T as an LM head with vocabulary N, hidden size K, one draft and `rows` sequences.
 static tabed_cfg gemm_cfg(int rows, int K, int N) {
     tabed_cfg c{};
     c.V = N; c.d = K; c.n = 1; c.B = rows; c.gamma = 1; c.h = 1; c.w_dtype = 1; c.distance = 0; c.policy = 0;
@@ -371,60 +604,39 @@ static tabed_cfg gemm_cfg(int rows, int K, int N) {
     return c;
 }
 
-// Number of K ranges of the split kernel (0: the shape goes through the LM-head kernels instead).  Every wave gets
-// the same whole number of 16-wide k-steps, at least two; the split stops growing once a launch has 256 workgroups.
-static int proj_splits(int rows, int K, int N) {
-    if (rows > 64 || K % 64 != 0 || N % 4 != 0) return 0;
-    const int tiles = (N + 31) / 32, units = K / 64;       // a unit = one k-step for each of the four waves
-    int best = 0;
-    for (int ks = 1; ks <= 16; ++ks) {
-        if (units % ks != 0 || units / ks < 2) continue;
-        best = ks;
-        if (tiles * ks >= 256) break;
-    }
-    return best;                                           // 0 when K == 64
-}
+constexpr int kMaxStagedD = 2048;   // hidden sizes whose normalised rows a projection stages in LDS itself
 
-// Chunk width (in 64s) of the wide kernel, 0 when the shape keeps to the kernel above: results of at least 2048
-// columns, the widest chunk that still gives about a hundred workgroups, at most 16 ranges.
-static int proj_wide_kg(int rows, int K, int N) {
-    if (proj_splits(rows, K, N) == 0 || N < 2048) return 0;
-    const int groups = (N + 127) / 128;
-    int pick = 0;
-    for (int kg = 1; kg <= 4; ++kg) {
-        if (K % (kg * 64) != 0 || K / (kg * 64) > 16) continue;
-        if (pick == 0 || groups * (K / (kg * 64)) >= 100) pick = kg;
-    }
-    return pick;
-}
-
-static int proj_slabs(int rows, int K, int N) {
-    const int kg = proj_wide_kg(rows, K, N);
-    if (kg != 0) return K / (kg * 64);
-    const int ks = proj_splits(rows, K, N);
-    return ks > 0 ? ks : 1;
+// Key ranges a row's attention is cut into: enough for 768 workgroups (three per compute unit), at most 8, none shorter
+// than 64 positions of a full cache; one where the output projection could not stage the merged rows in LDS.  Measured at
+// 64 rows of 12 heads, 256 to 768 positions: attention 20.3 / 19.0 / 18.5 us with 1 / 2 / 4 ranges, but the projection that
+// merges them 4.7 / 6.3 / 7.3 us.  4 rows of 12 heads, 600 to 1900 positions: 33 us with one range, 6.5 us with 8.
+static int attn_splits(const tabed_body_cfg& c, int rows) {
+    if (c.d > 1536 || !fused_rows(c.d, rows)) return 1;
+    int S = 1;
+    while (S < 8 && (long)rows * c.heads * S < 768 && c.max_ctx / (2 * S) >= 64) S *= 2;
+    return S;
 }
 
 BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     BodyLayout L;
     const int act = (c.d > c.d_ff) ? c.d : c.d_ff;
-    const int shapes[4][2] = {{c.d, 3 * c.d}, {c.d, c.d}, {c.d, 2 * c.d_ff}, {c.d_ff, c.d}};   // {K, N}
-    size_t ybytes = 0, g = 0;
-    for (const auto& kn : shapes) {
-        const int ks = proj_splits(rows, kn[0], kn[1]);
-        const size_t yb = sizeof(float) * (size_t)proj_slabs(rows, kn[0], kn[1]) * rows * kn[1];
-        ybytes = yb > ybytes ? yb : ybytes;
-        if (ks == 0) {
-            const size_t t = ws_layout(gemm_cfg(rows, kn[0], kn[1])).total;
-            g = t > g ? t : g;
-        }
-    }
+    const size_t S = (size_t)attn_splits(c, rows);
     size_t off = 0;
-    L.off_ones = off; off = al256(off + sizeof(float) * (size_t)rows);
     L.off_x = off;    off = al256(off + sizeof(float) * (size_t)rows * c.d);
-    L.off_y = off;    off = al256(off + ybytes);
+    L.off_q = off;    off = al256(off + sizeof(float) * (size_t)rows * c.d);
+    L.off_trig = off; off = al256(off + sizeof(double2) * (size_t)rows * ((c.d / c.heads) / 2));
     L.off_hb = off;   off = al256(off + sizeof(uint16_t) * (size_t)rows * act);
-    L.off_gemm = off; off = al256(off + g);
+    const bool many = !fused_rows(c.d, rows);
+    L.off_hn = off;   off = al256(off + (c.d > kMaxStagedD || many ? sizeof(uint16_t) * (size_t)rows * c.d : 0));
+    L.off_po = off;   off = al256(off + (S > 1 ? sizeof(float) * S * rows * c.d : 0));
+    L.off_pml = off;  off = al256(off + (S > 1 ? sizeof(float) * 2 * S * rows * c.heads : 0));
+    size_t gemm = 0;
+    if (many)
+        for (const auto& kn : {std::pair<int, int>{c.d, 3 * c.d}, {c.d, c.d}, {c.d, 2 * c.d_ff}, {c.d_ff, c.d}})
+            gemm = std::max(gemm, ws_layout(gemm_cfg(rows, kn.first, kn.second)).total);
+    L.off_y = off;    off = al256(off + (many ? sizeof(float) * (size_t)rows * std::max(3 * c.d, 2 * c.d_ff) : 0));
+    L.off_gemm = off; off = al256(off + gemm);
+    L.off_ones = off; off = al256(off + (many ? sizeof(float) * (size_t)rows : 0));
     L.total = off;
     return L;
 }
@@ -438,134 +650,163 @@ int validate_body_cfg(const tabed_body_cfg* c, int rows) {
     if (c->V < 1 || c->max_ctx < 1 || c->max_ctx > 8192) return TABED_ERANGE;
     if (!(c->rope_theta > 0.f) || !(c->rms_eps > 0.f)) return TABED_EINVAL;
     if (rows < 1 || rows > 65535) return TABED_ERANGE;
-    if (c->d > 8192 || 2 * c->d_ff > 262144) return TABED_ERANGE;      // a row of the residual stream sits in LDS
+    if (c->d > 8192 || 2 * c->d_ff > 262144) return TABED_ERANGE;
     return TABED_OK;
 }
 
+// Only the GEMM route has something to prepare: the temperatures (all one) that the LM head's kernels divide by.
 hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStream_t s) {
+    if (fused_rows(c.d, rows)) return hipSuccess;
     const BodyLayout L = body_layout(c, rows);
     launch(nullptr, k_body_fill_ones, dim3((rows + 255) / 256), dim3(256), 0, s, reinterpret_cast<float*>(ws + L.off_ones), rows);
     return hipGetLastError();
 }
 
-struct Slabs {
-    int ks;          // partial sums the consumer adds up
-    size_t stride;   // floats between them
-};
-
-// y[ks][rows,N] = in[rows,K] x W[N,K]^T, as `ks` partial sums
-static hipError_t projection(int rows, int K, int N, char* gemm_ws, const void* W, const uint16_t* in, const float* ones,
-                             float* y, Slabs* out, hipStream_t s) {
-    const int ks = proj_splits(rows, K, N);
-    out->stride = (size_t)rows * N;
-    if (ks == 0) {
-        out->ks = 1;
-        const tabed_cfg gc = gemm_cfg(rows, K, N);
-        return launch_lmhead(gc, ws_layout(gc), gemm_ws, W, in, ones, y, s, TABED_K_BODY);
-    }
+template <int NW, int MB, int G, int CI, int IN, int EPI>
+static hipError_t launch_proj_t(int tiles, hipStream_t s, const ProjArgs& a) {
+    constexpr int NB = (EPI == kEpiAdd) ? 1 : 2;
+    const size_t staged = (IN == kInBf16) ? 0 : sizeof(uint16_t) * MB * 16 * (size_t)staged_row(a.K);
+    const size_t results = sizeof(float) * NW * NB * MB * 16 * 20;
+    static std::once_flag once;
+    static hipError_t rc = hipSuccess;
+    const size_t most = std::max(results, (IN == kInBf16) ? (size_t)0 : sizeof(uint16_t) * MB * 16 * (size_t)staged_row(IN == kInNorm ? CI * 256 : 1536));
+    if (raise_lds_limit(&k_body_proj<NW, MB, G, CI, IN, EPI>, most, once, rc) != hipSuccess) return rc;
     ProfScope prof(TABED_K_BODY, s);
-    const uint16_t* Wb = static_cast<const uint16_t*>(W);
-    const int kg = proj_wide_kg(rows, K, N);
-    if (kg != 0) {
-        out->ks = K / (kg * 64);
-        const dim3 wgrid((N + 127) / 128, out->ks);
-        const bool one = rows <= 32;
-#define TABED_WIDE(KG_)                                                                                              \
-    if (kg == KG_) {                                                                                                 \
-        if (one) launch(&prof, k_body_proj_wide<1, KG_>, wgrid, dim3(kBlock), 0, s, rows, N, K, in, Wb, y, out->stride); \
-        else     launch(&prof, k_body_proj_wide<2, KG_>, wgrid, dim3(kBlock), 0, s, rows, N, K, in, Wb, y, out->stride); \
-    }
-        TABED_WIDE(1) TABED_WIDE(2) TABED_WIDE(3) TABED_WIDE(4)
-#undef TABED_WIDE
-        return hipGetLastError();
-    }
-    out->ks = ks;
-    const dim3 grid((N + 31) / 32, ks);
-    const int steps_per_wave = K / 64 / ks;
-    if (rows <= 32)
-        launch(&prof, k_body_proj<1>, grid, dim3(kBlock), 0, s, rows, N, K, steps_per_wave, in, static_cast<const uint16_t*>(W), y,
-               out->stride);
-    else
-        launch(&prof, k_body_proj<2>, grid, dim3(kBlock), 0, s, rows, N, K, steps_per_wave, in, static_cast<const uint16_t*>(W), y,
-               out->stride);
+    launch(&prof, k_body_proj<NW, MB, G, CI, IN, EPI>, dim3(tiles, (a.M + MB * 16 - 1) / (MB * 16)), dim3(NW * 64), std::max(staged, results), s, a);
     return hipGetLastError();
 }
 
+// Waves per workgroup and k-blocks a wave requests together: four waves up to 1024 of contraction, eight beyond, and as
+// many requests as cover a wave's share where that is at most eight.  Two row blocks per workgroup where the tiles of
+// one already fill the chip twice: W is then read half as often.
+template <int IN, int EPI>
+static hipError_t projection(const ProjArgs& a, int tiles, hipStream_t s) {
+    const int mblocks = (a.M + 15) / 16;
+    const bool two = mblocks > 1 && (long)tiles * mblocks >= (IN == kInNorm ? 256 : 512);
+    const int KB = (a.K + 63) / 64;
+    if constexpr (IN == kInMerge) {
+        return launch_proj_t<8, 1, 3, 1, IN, EPI>(tiles, s, a);
+    } else if constexpr (IN == kInNorm) {
+        if (a.K <= 768) return two ? launch_proj_t<8, 2, 2, 3, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 2, 3, IN, EPI>(tiles, s, a);
+        if (a.K <= 1024) return two ? launch_proj_t<8, 2, 2, 4, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 2, 4, IN, EPI>(tiles, s, a);
+        return launch_proj_t<8, 1, 4, 8, IN, EPI>(tiles, s, a);
+    } else {
+        if constexpr (EPI == kEpiAdd) {
+            if (KB <= 12) return two ? launch_proj_t<4, 2, 3, 1, IN, EPI>(tiles, s, a) : launch_proj_t<4, 1, 3, 1, IN, EPI>(tiles, s, a);
+            if (KB <= 16) return two ? launch_proj_t<4, 2, 4, 1, IN, EPI>(tiles, s, a) : launch_proj_t<4, 1, 4, 1, IN, EPI>(tiles, s, a);
+            if (KB > 48) return two ? launch_proj_t<8, 2, 8, 1, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 8, 1, IN, EPI>(tiles, s, a);
+        }
+        return two ? launch_proj_t<8, 2, 6, 1, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 6, 1, IN, EPI>(tiles, s, a);
+    }
+}
+
+static hipError_t launch_norm(const ProjArgs& a, uint16_t* out, int32_t* ctx_len_advance, hipStream_t s) {
+    ProfScope prof(TABED_K_BODY, s);
+    launch(&prof, k_body_norm, dim3(a.M), dim3(kBlock), 0, s, a.K, a.eps, static_cast<const float*>(a.x), a.g, out, ctx_len_advance);
+    return hipGetLastError();
+}
+
+// The GEMM route of a projection: GEMM, then the epilogue as a kernel of its own.
+template <int EPI>
+static hipError_t gemm_projection(const ProjArgs& a, const uint16_t* X, char* ws, const BodyLayout& L, hipStream_t s) {
+    const int N = (EPI == kEpiSilu) ? 2 * a.N : a.N;
+    const tabed_cfg gc = gemm_cfg(a.M, a.K, N);
+    float* y = reinterpret_cast<float*>(ws + L.off_y);
+    const hipError_t e = launch_lmhead(gc, ws_layout(gc), ws + L.off_gemm, a.W, X, reinterpret_cast<const float*>(ws + L.off_ones), y, s,
+                                       TABED_K_BODY);
+    if (e != hipSuccess) return e;
+    ProfScope prof(TABED_K_BODY, s);
+    if (EPI == kEpiRope) {
+        launch(&prof, k_body_rope, dim3(a.M), dim3(kBlock), 0, s, a.K, a.hd, a.max_ctx, static_cast<const float*>(y), a.trig, a.ctx_len, a.q,
+               a.kc, a.vc);
+    } else {
+        const size_t count = (EPI == kEpiSilu) ? (size_t)a.M * a.N : (size_t)a.M * a.N / 4;
+        const dim3 grid((unsigned)((count + kBlock - 1) / kBlock));
+        if (EPI == kEpiSilu) launch(&prof, k_body_silu_mul, grid, dim3(kBlock), 0, s, a.M, a.N, static_cast<const float*>(y), a.act);
+        else launch(&prof, k_body_add, grid, dim3(kBlock), 0, s, count, reinterpret_cast<float4*>(a.x), reinterpret_cast<const float4*>(y));
+    }
+    return hipGetLastError();
+}
+
+// RMSNorm + projection: in one launch where the rows fit LDS.
+template <int EPI>
+static hipError_t norm_projection(ProjArgs a, uint16_t* hn, int tiles, char* ws, const BodyLayout& L, hipStream_t s) {
+    const bool many = !fused_rows(a.K, a.M);
+    if (!many && a.K <= kMaxStagedD) return projection<kInNorm, EPI>(a, tiles, s);
+    const hipError_t e = launch_norm(a, hn, nullptr, s);
+    if (e != hipSuccess) return e;
+    if (many) return gemm_projection<EPI>(a, hn, ws, L, s);
+    a.X = hn;
+    return projection<kInBf16, EPI>(a, tiles, s);
+}
+
 template <int LPK>
-static void launch_attn(const ProfScope* prof, const tabed_body_cfg& c, int rows, Slabs sl, const float* y, const int32_t* ctx_len,
-                        uint16_t* kc, uint16_t* vc, uint16_t* att, hipStream_t s) {
-    launch(prof, k_body_rope_attn<LPK>, dim3(c.heads, rows), dim3(kBlock), sizeof(float) * (size_t)c.max_ctx, s, c.d, c.max_ctx,
-           (double)c.rope_theta, sl.ks, sl.stride, y, ctx_len, kc, vc, att);
+static void launch_attn(const ProfScope* prof, const tabed_body_cfg& c, int rows, int splits, const float* q, const int32_t* ctx_len,
+                        const uint16_t* kc, const uint16_t* vc, uint16_t* att, float* po, float* pml, hipStream_t s) {
+    launch(prof, k_body_attn<LPK>, dim3(c.heads, rows, splits), dim3(kBlock), 0, s, c.d, c.max_ctx, q, ctx_len, kc, vc, att, po, pml);
 }
 
 hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w, char* ws, int rows,
                             const int32_t* token_src, int token_stride, int rows_per_token, int32_t* ctx_len,
                             uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s) {
     const BodyLayout L = body_layout(c, rows);
-    const float* ones = reinterpret_cast<const float*>(ws + L.off_ones);
-    float* x = reinterpret_cast<float*>(ws + L.off_x);
-    float* y = reinterpret_cast<float*>(ws + L.off_y);
     uint16_t* hb = reinterpret_cast<uint16_t*>(ws + L.off_hb);
-    char* gws = ws + L.off_gemm;
-    const int d = c.d, hd = c.d / c.heads;
+    float* po = reinterpret_cast<float*>(ws + L.off_po);
+    float* pml = reinterpret_cast<float*>(ws + L.off_pml);
+    const int d = c.d, hd = c.d / c.heads, splits = attn_splits(c, rows);
+    const bool many = !fused_rows(c.d, rows);
+    uint16_t* hn = reinterpret_cast<uint16_t*>(ws + L.off_hn);
+    ProjArgs base{};
+    base.M = rows; base.eps = c.rms_eps; base.hd = hd; base.max_ctx = c.max_ctx;
+    base.ctx_len = ctx_len; base.splits = splits; base.po = po; base.pml = pml;
+    base.x = reinterpret_cast<float*>(ws + L.off_x);
+    base.q = reinterpret_cast<float*>(ws + L.off_q);
+    base.X = hb; base.act = hb;
+    double2* trig = reinterpret_cast<double2*>(ws + L.off_trig);
+    base.trig = trig;
     hipError_t e;
-    Slabs sl;
-#define TABED_BODY_CHECK()            \
-    e = hipGetLastError();            \
-    if (e != hipSuccess) return e
     {
         ProfScope prof(TABED_K_BODY, s);
-        launch(&prof, k_body_embed_norm, dim3(rows), dim3(kBlock), 0, s, d, c.V, c.rms_eps, token_src, token_stride,
-               rows_per_token, static_cast<const uint16_t*>(w.embed), w.g_attn[0], x, hb);
-        TABED_BODY_CHECK();
+        launch(&prof, k_body_embed, dim3(rows), dim3(kBlock), 0, s, d, c.V, token_src, token_stride, rows_per_token,
+               static_cast<const uint16_t*>(w.embed), base.x, static_cast<const int32_t*>(ctx_len), c.max_ctx, hd,
+               std::log2((double)c.rope_theta), trig);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (int l = 0; l < c.layers; ++l) {
-        e = projection(rows, d, 3 * d, gws, w.wqkv[l], hb, ones, y, &sl, s);
-        if (e != hipSuccess) return e;
+        const size_t layer_off = (size_t)l * rows * c.max_ctx * d;
+        ProjArgs a = base;
+        a.kc = kcache + layer_off; a.vc = vcache + layer_off;
+        a.W = static_cast<const uint16_t*>(w.wqkv[l]); a.N = 3 * d; a.K = d; a.g = w.g_attn[l];
+        if ((e = norm_projection<kEpiRope>(a, hn, 3 * ((d + 31) / 32), ws, L, s)) != hipSuccess) return e;
         {
             ProfScope prof(TABED_K_BODY, s);
-            const size_t layer_off = (size_t)l * rows * c.max_ctx * d;
-            uint16_t* kc = kcache + layer_off;
-            uint16_t* vc = vcache + layer_off;
             switch (hd) {
-                case 8: launch_attn<1>(&prof, c, rows, sl, y, ctx_len, kc, vc, hb, s); break;
-                case 16: launch_attn<2>(&prof, c, rows, sl, y, ctx_len, kc, vc, hb, s); break;
-                case 32: launch_attn<4>(&prof, c, rows, sl, y, ctx_len, kc, vc, hb, s); break;
-                case 64: launch_attn<8>(&prof, c, rows, sl, y, ctx_len, kc, vc, hb, s); break;
-                case 128: launch_attn<16>(&prof, c, rows, sl, y, ctx_len, kc, vc, hb, s); break;
+                case 8: launch_attn<1>(&prof, c, rows, splits, a.q, ctx_len, a.kc, a.vc, hb, po, pml, s); break;
+                case 16: launch_attn<2>(&prof, c, rows, splits, a.q, ctx_len, a.kc, a.vc, hb, po, pml, s); break;
+                case 32: launch_attn<4>(&prof, c, rows, splits, a.q, ctx_len, a.kc, a.vc, hb, po, pml, s); break;
+                case 64: launch_attn<8>(&prof, c, rows, splits, a.q, ctx_len, a.kc, a.vc, hb, po, pml, s); break;
+                case 128: launch_attn<16>(&prof, c, rows, splits, a.q, ctx_len, a.kc, a.vc, hb, po, pml, s); break;
                 default: return hipErrorInvalidValue;
             }
-            TABED_BODY_CHECK();
+            if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        e = projection(rows, d, d, gws, w.wo[l], hb, ones, y, &sl, s);
+        a = base;
+        a.W = static_cast<const uint16_t*>(w.wo[l]); a.N = d; a.K = d;
+        if (many) e = gemm_projection<kEpiAdd>(a, hb, ws, L, s);
+        else if (splits > 1) e = projection<kInMerge, kEpiAdd>(a, (d + 15) / 16, s);
+        else e = projection<kInBf16, kEpiAdd>(a, (d + 15) / 16, s);
         if (e != hipSuccess) return e;
-        {
-            ProfScope prof(TABED_K_BODY, s);
-            launch(&prof, k_body_add_norm, dim3(rows), dim3(kBlock), sizeof(float) * (size_t)d, s, d, c.rms_eps, sl.ks, sl.stride, x, y,
-                   w.g_mlp[l], hb, static_cast<int32_t*>(nullptr));
-            TABED_BODY_CHECK();
-        }
-        e = projection(rows, d, 2 * c.d_ff, gws, w.wgu[l], hb, ones, y, &sl, s);
+        a = base;
+        a.W = static_cast<const uint16_t*>(w.wgu[l]); a.N = c.d_ff; a.K = d; a.g = w.g_mlp[l];
+        if ((e = norm_projection<kEpiSilu>(a, hn, (c.d_ff + 15) / 16, ws, L, s)) != hipSuccess) return e;
+        a = base;
+        a.W = static_cast<const uint16_t*>(w.wdown[l]); a.N = d; a.K = c.d_ff;
+        e = many ? gemm_projection<kEpiAdd>(a, hb, ws, L, s) : projection<kInBf16, kEpiAdd>(a, (d + 15) / 16, s);
         if (e != hipSuccess) return e;
-        {
-            ProfScope prof(TABED_K_BODY, s);
-            const size_t count = (size_t)rows * c.d_ff;
-            launch(&prof, k_body_silu_mul, dim3((unsigned)((count + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, rows, c.d_ff, sl.ks,
-                   sl.stride, y, hb);
-            TABED_BODY_CHECK();
-        }
-        e = projection(rows, c.d_ff, d, gws, w.wdown[l], hb, ones, y, &sl, s);
-        if (e != hipSuccess) return e;
-        {
-            ProfScope prof(TABED_K_BODY, s);
-            const bool last = (l + 1 == c.layers);
-            launch(&prof, k_body_add_norm, dim3(rows), dim3(kBlock), sizeof(float) * (size_t)d, s, d, c.rms_eps, sl.ks, sl.stride, x, y,
-                   last ? w.g_final : w.g_attn[l + 1], last ? H : hb, last ? ctx_len : static_cast<int32_t*>(nullptr));
-            TABED_BODY_CHECK();
-        }
     }
-#undef TABED_BODY_CHECK
-    return hipSuccess;
+    ProjArgs a = base;
+    a.K = d; a.g = w.g_final;
+    return launch_norm(a, H, ctx_len, s);
 }
 
 hipError_t launch_body_rollback(int rows, int rows_per_seq, int gamma, const int32_t* ctx_base, const int32_t* accept_len,

@@ -65,6 +65,13 @@ __device__ __forceinline__ double wave_sum(double v) {
     return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
 }
 
+// Workgroup barrier that orders LDS traffic only: it waits for this wave's LDS operations and nothing else, so
+// a wave reaches it with its global loads still in flight.  (A barrier written so that it also waits for vector
+// memory would stall a workgroup until all of its outstanding requests have landed.)
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // Workgroup reductions over kBlock threads through a 4-entry LDS array.  Two barriers each, so the
 // scratch array can be reused by the next call.
 __device__ __forceinline__ float block_max(float v, float* lds4) {

@@ -93,11 +93,16 @@ hipError_t launch_philox(const tabed_cfg& c, uint64_t round, float* out, hipStre
 
 // ---------------------------------------------------------------- draft-model body
 struct BodyLayout {
-    size_t off_ones;   // float [rows]: the "temperature" the projection launches divide by
     size_t off_x;      // float [rows,d] residual stream
-    size_t off_y;      // float [rows, max(3d, 2 d_ff)] result of the current projection
-    size_t off_hb;     // bf16 [rows, max(d, d_ff)] input of the next projection
-    size_t off_gemm;   // scratch of the projection launches (softmax partials nobody reads)
+    size_t off_q;      // float [rows,d] rotated queries of the current layer
+    size_t off_trig;   // double2 [rows][head_dim/2] cos and sin of the rows' positions
+    size_t off_hb;     // bf16 [rows, max(d, d_ff)] input of the output / down projection
+    size_t off_hn;     // bf16 [rows,d] normalised rows (only where a projection does not stage them in LDS itself)
+    size_t off_po;     // float [splits][rows,d] attention sums of every key range (more than one range only)
+    size_t off_pml;    // float [rows][heads][splits][2] their maxima and sums of probabilities
+    size_t off_y;      // many rows (GEMM route) only: float [rows, max(3d, 2 d_ff)] result of the current projection,
+    size_t off_gemm;   //   scratch of the GEMM launches (softmax partials nobody reads),
+    size_t off_ones;   //   float [rows]: the "temperature" they divide by
     size_t total;
 };
 BodyLayout body_layout(const tabed_body_cfg& c, int rows);
@@ -131,7 +136,18 @@ struct ProfScope {
 
 #if defined(__HIPCC__)
 #include <hip/hip_ext.h>
+
+#include <mutex>
 namespace tabed {
+// Raises a kernel's dynamic-LDS limit once per process; a failure is remembered and returned by every later call.
+template <typename K>
+inline hipError_t raise_lds_limit(K kernel, size_t lds, std::once_flag& once, hipError_t& rc) {
+    std::call_once(once, [&] {
+        rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    });
+    return rc;
+}
+
 template <typename K, typename... Args>
 inline void launch(const ProfScope* prof, K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, Args... args) {
     if (prof != nullptr && prof->on)

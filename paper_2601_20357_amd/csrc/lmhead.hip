@@ -195,13 +195,6 @@ __global__ __launch_bounds__(kBlock) void k_lmhead_bf16(int M, int d, int V, int
     store_tile_32x32(acc, m0 + wm * 32, v0 + wn * 32, M, V, NT, s_invt, m0, L, pm, ps);
 }
 
-// Workgroup barrier that orders LDS traffic only: it waits for this wave's LDS operations and nothing else, so
-// a wave reaches it with its W requests still in flight.  (A barrier written so that it also waits for vector
-// memory would stall a workgroup until all of its outstanding W requests have landed.)
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // ---------------------------------------------------------------- bf16, skinny M (<= 64 rows): W-streaming kernel
 // With n*B <= 64 rows the GEMM moves 2*d bytes of W per n*B*2*d flops: it is bound by streaming W from HBM
 // once, not by the matrix cores.  Design:
@@ -677,15 +670,6 @@ static int skinny_kc_kh(const tabed_cfg& c, int M) {
     for (int KH : (M > 32 ? order_two : order_one))
         if (c.d % (KH * 128) == 0 && c.d / (KH * 128) >= 2) return KH;
     return 0;
-}
-
-// Raises a kernel's dynamic-LDS limit once per process; a failure is remembered and returned by every later call.
-template <typename K>
-static hipError_t raise_lds_limit(K kernel, size_t lds, std::once_flag& once, hipError_t& rc) {
-    std::call_once(once, [&] {
-        rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    });
-    return rc;
 }
 
 template <int KH, int MT>

@@ -250,3 +250,28 @@ def test_rounds_with_the_body_in_the_loop_are_reproducible_bit_for_bit():
         for x, y in zip(a, b):
             assert torch.equal(x, y)
     assert all(torch.isfinite(t[2]).all() for t in one[:3])
+
+
+# Where the step's kernels change: key ranges 2, 4, 8 merged by the output projection (few rows, long caches), one and two
+# row blocks per workgroup, 8 waves and 8 column pieces (d > 1024), rows normalised by a kernel of their own (d > 2048), a
+# contraction that is no multiple of 64 with more than 48 k-blocks, the GEMM route (many rows).
+ROUTES = [
+    ("ranges8_hd64", synth.BodyConfig(layers=2, d=256, heads=4, d_ff=1024, V=100, max_ctx=1100), 3),
+    ("ranges4_hd16", synth.BodyConfig(layers=1, d=48, heads=3, d_ff=80, V=40, max_ctx=520), 17),
+    ("ranges2_hd128", synth.BodyConfig(layers=1, d=512, heads=4, d_ff=264, V=40, max_ctx=140), 50),
+    ("two_row_blocks", synth.BodyConfig(layers=1, d=768, heads=24, d_ff=2056, V=64, max_ctx=33), 49),
+    ("d1152", synth.BodyConfig(layers=1, d=1152, heads=9, d_ff=3144, V=64, max_ctx=20), 18),
+    ("d2112", synth.BodyConfig(layers=1, d=2112, heads=33, d_ff=136, V=32, max_ctx=12), 17),
+    ("gemm_route", synth.BodyConfig(layers=1, d=1536, heads=12, d_ff=72, V=40, max_ctx=5), 513),
+]
+
+
+@pytest.mark.parametrize("name,bc,rows", ROUTES, ids=[c[0] for c in ROUTES])
+def test_body_step_on_every_route(oracle, name, bc, rows):
+    pair = BodyPair(oracle, bc, rows, seed=len(name), fill=lambda g: g.integers(0, bc.max_ctx - 2, size=rows))
+    pair.ctx[0] = 0                                   # one key: every range but the first is empty
+    pair.ctx[-1] = bc.max_ctx - 2
+    pair.d_ctx.copy_(pair.torch.from_numpy(pair.ctx))
+    g = np.random.default_rng(6)
+    for _ in range(2):
+        pair.step(g.integers(0, bc.V, size=rows))
