@@ -6,6 +6,7 @@
 // correctness configuration) use plain FMAs.
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -18,11 +19,13 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // four floats that are only 4-byte aligned
 
-__device__ __forceinline__ float row_inv_temperature(const float* temperature, int row, int n) {
-    const float T = temperature[row / n];
-    return (T > 0.f) ? 1.f / T : 1.f;
-}
+__device__ __forceinline__ float inv_temperature(float T) { return (T > 0.f) ? 1.f / T : 1.f; }
+__device__ __forceinline__ float row_inv_temperature(const float* temperature, int row, int n) { return inv_temperature(temperature[row / n]); }
+// row / n for row < 65536 without an integer division: (row + 1/2) / n is at least 1 / 32 away from an integer (n <= 16),
+// far more than the error of the reciprocal.
+__device__ __forceinline__ int sequence_of(int row, int n) { return (int)(((float)row + 0.5f) * __builtin_amdgcn_rcpf((float)n)); }
 
 // Reductions over the 32 lanes that share lane/32 (xor offsets < 32 never leave the half-wave).
 __device__ __forceinline__ float half_max(float v) {
@@ -34,38 +37,6 @@ __device__ __forceinline__ float half_sum(float v) {
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
-}
-
-// Epilogue of one 32x32 accumulator tile: lane holds column (lane % 32) and the 16 rows
-// 8*(r/4) + 4*(lane/32) + r%4 of the block that starts at row m_base.  Writes logits and the tile's softmax
-// partials.  inv_t[i] = 1/T of row m_table0 + i (an LDS table filled by the caller).
-__device__ __forceinline__ void store_tile_32x32(const f32x16& acc, int m_base, int v_base, int M, int V, int NT,
-                                                 const float* inv_t, int m_table0, float* __restrict__ L,
-                                                 float* __restrict__ pm, float* __restrict__ ps) {
-    if (v_base >= V) return;
-    const int lane = threadIdx.x & 63;
-    const int col = lane & 31, half = lane >> 5;
-    const int v = v_base + col;
-    const int tile = v_base / kTileV;
-    const bool vlive = (v < V);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int m = m_base + 8 * (r / 4) + 4 * half + (r % 4);
-        const bool live = (m < M);          // uniform over the half-wave
-        const float x = acc[r];
-        float s = -INFINITY;
-        if (live && vlive) {
-            L[(size_t)m * V + v] = x;
-            s = x * inv_t[m - m_table0];
-        }
-        const float mx = half_max(s);
-        const float e = (s > -INFINITY) ? __expf(s - mx) : 0.f;
-        const float sum = half_sum(e);
-        if (live && col == 0) {
-            pm[(size_t)m * NT + tile] = mx;
-            ps[(size_t)m * NT + tile] = sum;
-        }
-    }
 }
 
 // Epilogue of one 32x32 accumulator tile held TRANSPOSED: lane holds result row m_base + lane % 32 and the 16
@@ -83,18 +54,23 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
     const int m = m_base + col;
     const bool live = (m < M);
     const float it = live ? inv_t[m] : 1.f;
+    const bool full = v_base + 32 <= V;            // uniform: only the last tile of a row is ragged
     float sc[16];
     float mx = -INFINITY;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int v = v_base + 8 * (r / 4) + 4 * half + (r % 4);
-        sc[r] = (live && v < V) ? acc[r] * it : -INFINITY;
-        mx = fmaxf(mx, sc[r]);
+    for (int r = 0; r < 16; ++r) sc[r] = acc[r] * it;      // (rows past the end: computed, not stored)
+    if (!full) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (v_base + 8 * (r / 4) + 4 * half + (r % 4) >= V) sc[r] = -INFINITY;
     }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float base = (mx > -INFINITY) ? mx : 0.f;        // a tile of -inf sums to 0
     float sum = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sum += (sc[r] > -INFINITY) ? __expf(sc[r] - mx) : 0.f;
+    for (int r = 0; r < 16; ++r) sum += __expf(sc[r] - base);
     sum += __shfl_xor(sum, 32);
     if (live && half == 0) {
         if (pstage != nullptr) {                    // collected per workgroup: [array][row][tile of the group]
@@ -105,7 +81,7 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
             ps[(size_t)m * NT + v_base / kTileV] = sum;
         }
     }
-    if ((V & 3) == 0 && v_base + 32 <= V) {
+    if (full) {
         // Full tile: turn the block through the wave's LDS patch ([32 rows][32 v] floats, 144-byte rows) so
         // that 8 lanes store one whole 128-byte line of a row, and stream it past L2: the logits are next
         // read tens of megabytes later, and full-line streaming stores measured 1.9 us faster per launch
@@ -118,14 +94,14 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
         for (int i = 0; i < 4; ++i) {
             const int mr = 8 * i + (lane >> 3), q = lane & 7;
             const float4 val = *reinterpret_cast<const float4*>(tpatch + mr * 144 + q * 16);
-            if (m_base + mr < M)
-                __builtin_nontemporal_store(f32x4{val.x, val.y, val.z, val.w},
-                                            reinterpret_cast<f32x4*>(L + (size_t)(m_base + mr) * V + v_base + 4 * q));
+            if (m_base + mr < M)                   // (rows of an odd vocabulary are only 4-byte aligned)
+                __builtin_nontemporal_store(f32x4u{val.x, val.y, val.z, val.w},
+                                            reinterpret_cast<f32x4u*>(L + (size_t)(m_base + mr) * V + v_base + 4 * q));
         }
         return;
     }
     if (!live) return;
-    float* row = L + (size_t)m * V;                // ragged last tile or unaligned rows: element-wise
+    float* row = L + (size_t)m * V;                // ragged last tile: element-wise
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -135,67 +111,7 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
         }
 }
 
-// ---------------------------------------------------------------- bf16, any shape: LDS-tiled MFMA GEMM
-// Workgroup tile 64 (rows) x 64 (vocabulary) x 64 (k); wave w owns the 32x32 quadrant (w/2, w%2).
-// Both operands are K-contiguous in memory, which is exactly the per-lane 8-element run the MFMA wants,
-// so LDS only transposes "who holds which row".  Rows are padded by 16 bytes against bank conflicts.
-constexpr int kBM = 64, kBN = 64, kBK = 64, kPad = 8;
-
-__global__ __launch_bounds__(kBlock) void k_lmhead_bf16(int M, int d, int V, int n, int NT,
-                                                        const __hip_bfloat16* __restrict__ W,
-                                                        const __hip_bfloat16* __restrict__ H,
-                                                        const float* __restrict__ temperature,
-                                                        float* __restrict__ L, float* __restrict__ pm,
-                                                        float* __restrict__ ps) {
-    __shared__ __attribute__((aligned(16))) uint16_t sA[kBM][kBK + kPad];
-    __shared__ __attribute__((aligned(16))) uint16_t sB[kBN][kBK + kPad];
-    __shared__ float s_invt[kBM];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int v0 = blockIdx.x * kBN, m0 = blockIdx.y * kBM;
-    if (tid < kBM && m0 + tid < M) s_invt[tid] = row_inv_temperature(temperature, m0 + tid, n);
-    const int wm = wave >> 1, wn = wave & 1;
-    const uint16_t* Wg = reinterpret_cast<const uint16_t*>(W);
-    const uint16_t* Hg = reinterpret_cast<const uint16_t*>(H);
-
-    f32x16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-
-    // each thread moves two 16-byte pieces of each operand per k-block: piece q -> row q/8, k-offset (q%8)*8
-    u32x4 ra[2], rb[2];
-    auto fetch = [&](int kb) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int q = tid + t * kBlock, row = q >> 3, k = kb * kBK + (q & 7) * 8;
-            const u32x4 zero = {0u, 0u, 0u, 0u};
-            ra[t] = (m0 + row < M && k < d) ? *reinterpret_cast<const u32x4*>(Hg + (size_t)(m0 + row) * d + k) : zero;
-            rb[t] = (v0 + row < V && k < d) ? *reinterpret_cast<const u32x4*>(Wg + (size_t)(v0 + row) * d + k) : zero;
-        }
-    };
-    const int KB = (d + kBK - 1) / kBK;
-    fetch(0);
-    for (int kb = 0; kb < KB; ++kb) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int q = tid + t * kBlock, row = q >> 3, kk = (q & 7) * 8;
-            *reinterpret_cast<u32x4*>(&sA[row][kk]) = ra[t];
-            *reinterpret_cast<u32x4*>(&sB[row][kk]) = rb[t];
-        }
-        __syncthreads();
-        if (kb + 1 < KB) fetch(kb + 1);
-#pragma unroll
-        for (int ks = 0; ks < kBK / 16; ++ks) {
-            const int kk = ks * 16 + 8 * (lane >> 5);
-            const bf16x8 av = *reinterpret_cast<const bf16x8*>(&sA[wm * 32 + (lane & 31)][kk]);
-            const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&sB[wn * 32 + (lane & 31)][kk]);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    store_tile_32x32(acc, m0 + wm * 32, v0 + wn * 32, M, V, NT, s_invt, m0, L, pm, ps);
-}
-
-// ---------------------------------------------------------------- bf16, skinny M (<= 64 rows): W-streaming kernel
+// ---------------------------------------------------------------- bf16, 33 to 64 rows, d = 512, 768 or 896: W-streaming kernel
 // With n*B <= 64 rows the GEMM moves 2*d bytes of W per n*B*2*d flops: it is bound by streaming W from HBM
 // once, not by the matrix cores.  Design:
 //   * 8 waves per workgroup, one workgroup per compute unit.  All of H (<= 64 x d bf16) is staged once into
@@ -211,7 +127,7 @@ __global__ __launch_bounds__(kBlock) void k_lmhead_bf16(int M, int d, int V, int
 //   * The two K-halves meet through the same patches (LDS-only barriers), each wave finishing one 32-row
 //     block of the 64 x 32 result: logits (turned through the patch once more, stored as whole 128-byte lines
 //     past L2) + softmax partials of the tile.
-// KH = k-blocks (of 64) per wave = d / 128; MT = 32-row blocks of M (1 or 2).
+// KH = k-blocks (of 64) per wave = d / 128; MT = 32-row blocks of M (2).
 constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyThreads = kSkinnyWaves * 64;
 constexpr int kPatchBytes = 32 * 144;
@@ -235,7 +151,8 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny(int M, int V, 
     unsigned char* const patch = lds + MT * 32 * HROW + wave * kPatchBytes;
     unsigned char* const partner_patch = lds + MT * 32 * HROW + (wave ^ 4) * kPatchBytes;
     const int nn = lane & 31, half = lane >> 5;
-    if (tid < M) s_invt[tid] = row_inv_temperature(temperature, tid, n);
+    // requested here, used after the loads below
+    const float my_temp = temperature[sequence_of(min(tid, M - 1), n)];
 
     // ---- request H first (it must land before any MFMA)
     u32x4 hreg[MT * KH];
@@ -278,6 +195,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny(int M, int V, 
         const int p = tid + q * kSkinnyThreads, row = p / CH, c = p % CH;
         *reinterpret_cast<u32x4*>(ldsH + row * HROW + c * 16) = hreg[q];
     }
+    if (tid < M) s_invt[tid] = inv_temperature(my_temp);
     lds_barrier();                                 // also publishes s_invt
 
     for (int g = blockIdx.x;; g += gridDim.x) {    // tile group g = 4 tiles, one per wave pair; trip count is
@@ -376,7 +294,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny_kc(int M, int 
     unsigned char* const patch = lds + MT * 32 * HROW + wave * kPatchBytes;
     unsigned char* const partner_patch = lds + MT * 32 * HROW + (wave ^ 4) * kPatchBytes;
     const int nn = lane & 31, half = lane >> 5;
-    if (tid < M) s_invt[tid] = row_inv_temperature(temperature, tid, n);
+    const float my_temp = temperature[sequence_of(min(tid, M - 1), n)];   // used after the requests below
 
     u32x4 hreg[MT * KH];
     auto request_h = [&](int chunk) {               // rows >= M are clamped: their results are never stored
@@ -415,6 +333,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny_kc(int M, int 
     for (int kb = 0; kb < kPF; ++kb) request_kblock(src, 0, kb);
     __builtin_amdgcn_sched_barrier(0);
     write_h();
+    if (tid < M) s_invt[tid] = inv_temperature(my_temp);
     lds_barrier();                                  // also publishes s_invt
 
     for (int g = blockIdx.x;; g += gridDim.x) {
@@ -494,105 +413,329 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny_kc(int M, int 
     }
 }
 
-// ---------------------------------------------------------------- bf16, many rows (M > 64): MFMA-bound tiled GEMM
-// With hundreds of rows (stress shape: n*B = 512) the LM head is a real GEMM: 2*M*d*V flops against one
-// pass over W.  Workgroup tile 256 (rows) x 256 (vocabulary) x 64 (k), 8 waves, each wave a 128 (rows) x 64
-// (vocabulary) block (2 x 4 MFMA 32x32x16 tiles, W as the row operand so the accumulator is
-// [vocabulary][row] and the cheap transposed epilogue applies).  Both operands are staged through LDS in two
-// buffers; the operand fragments of k-step s+1 are read from LDS while the MFMAs of k-step s run, and the
-// global loads of k-block i+1 are in flight (one register set) while k-block i-1 and i are multiplied --
-// one barrier per k-block.  A k-block of 64 is one whole 128-byte line of every row (measured 4.5 % faster than
-// k-blocks of 32 with two register sets: 318 against 334 us at the stress shape).  Rows padded by 16 bytes
-// against bank conflicts.  Workgroups are numbered so that
-// the row blocks that share a vocabulary block run back to back on the same XCD (workgroup w goes to XCD
-// w % 8): W is then read from HBM once and from L2 afterwards.
-constexpr int kLBM = 256, kLBN = 256, kLBK = 64, kLRow = (kLBK + 8) * 2;   // LDS row stride in bytes (144)
+// ---------------------------------------------------------------- bf16, up to 64 rows, any hidden size: W-streaming kernel
+// The kernel for up to 32 rows, and for 33 to 64 where the two above do not apply.  Bound by streaming W from HBM once:
+// V = 152064, d = 896, 32 rows: 54.8 us for 292 MB, 5.3 TB/s (the kernels above took 56.4); V = 32000, d = 768, 4 rows 9.0 us
+// (10.4); V = 50261, d = 1160, 15 rows 28.6 us (39.2 with 64 x 64 tiles through LDS, which these sizes took before).
+//   * Eight waves per workgroup.  KS of them share a 32-entry vocabulary tile, each taking its share of the k-blocks of 64; a
+//     workgroup owns 8 / KS tiles and walks over the vocabulary.
+//   * A wave reads its k-block of W as whole 128-byte lines, 8 lanes a row, PF k-blocks ahead of the one being multiplied,
+//     and turns it through a wave-private LDS patch.  (Read straight into operand layout, where 16 consecutive lanes hold
+//     16 different rows, a load instruction looks up 64 lines instead of 8 and W comes in at a quarter of the rate.)
+//   * 16 * MT rows of H sit in LDS (rows padded by 16 bytes against bank conflicts), all of K at once where that fits, else
+//     in chunks of kc columns: the next chunk is requested into registers at the start of a chunk's k-blocks.
+//   * W is the row operand, so that an accumulator is [vocabulary][row].  The KS partial results meet in the patches, 32 rows
+//     at a time, from where eight lanes add them, reduce the tile's softmax partials and store one whole 128-byte line of a
+//     logits row past L2.
+// Loads are never predicated (their number in flight has to be known): rows, vocabulary entries and k-blocks past the end
+// re-read the last one.
+constexpr int kStreamThreads = 512;
+constexpr int kStreamHPieces(int MT) { return MT == 1 ? 8 : MT == 2 ? 8 : 12; }        // 16-byte pieces of an H chunk per thread
+constexpr int kStreamMaxKC(int MT) { return kStreamHPieces(MT) * kStreamThreads * 8 / (MT * 16); }
+
+template <int MT, int KS, int PF, bool CH>
+__global__ __launch_bounds__(kStreamThreads) void k_lmhead_stream(int M, int d, int V, int n, int NT, int groups, int kc,
+                                                                  int nchunks, int unit, int unit_inv, const uint16_t* __restrict__ W,
+                                                                  const uint16_t* __restrict__ H, const float* __restrict__ temperature,
+                                                                  float* __restrict__ L, float* __restrict__ pm, float* __restrict__ ps) {
+    constexpr int kTiles = 8 / KS, VW = kTiles * 32;                        // vocabulary entries of a workgroup
+    constexpr int SR = (MT == 1) ? 16 : 32;                                 // rows that meet in LDS at a time
+    constexpr int HP = kStreamHPieces(MT), RP = (MT == 1) ? 16 : 32, CPP = kStreamThreads / (RP * 16);
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    __shared__ float s_invt[MT * 16];
+    const int hrow = kc * 2 + 16;
+    unsigned char* const s_h = lds;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ks = wave % KS, tile = wave / KS, r16 = lane & 15, c = lane >> 4, lrow = lane >> 3, lchunk = lane & 7;
+    unsigned char* const patches = lds + MT * 16 * hrow;                    // one per wave: 32 rows of 144 bytes
+    unsigned char* const patch = patches + wave * kPatchBytes;
+    const float my_temp = temperature[sequence_of(min(tid, M - 1), n)];     // used after the requests below
+
+    // ---- H chunks: 16 lanes read 256 contiguous bytes of a row
+    u32x4 hreg[HP];
+    const char* const hbase = reinterpret_cast<const char*>(H);
+    const int hr = (tid >> 4) % RP, hcg = (tid >> 4) / RP, hc = tid & 15;
+    const int hcols = kc / (128 * CPP) + ((kc / 128) % CPP != 0);           // column passes of a chunk
+    auto request_h = [&](int chunk) {
+        int rp = RP;
+        asm volatile("" : "+s"(rp));
+#pragma unroll
+        for (int q = 0; q < HP; ++q) {
+            const int row = hr + (q % (MT * 16 / RP)) * rp, col = ((q / (MT * 16 / RP)) * CPP + hcg) * 128 + hc * 8;
+            if (q / (MT * 16 / RP) < hcols) {
+                const uint32_t k = min((uint32_t)(chunk * kc + col) * 2u, (uint32_t)d * 2u - 16u);
+                hreg[q] = *reinterpret_cast<const u32x4*>(hbase + ((uint32_t)min(row, M - 1) * (uint32_t)d * 2u + k));
+            }
+        }
+    };
+    auto write_h = [&](int chunk) {
+        int rp = RP;
+        asm volatile("" : "+s"(rp));
+#pragma unroll
+        for (int q = 0; q < HP; ++q) {
+            const int row = hr + (q % (MT * 16 / RP)) * rp, col = ((q / (MT * 16 / RP)) * CPP + hcg) * 128 + hc * 8;
+            if (col < kc) {
+                const u32x4 zero = {0u, 0u, 0u, 0u};
+                *reinterpret_cast<u32x4*>(s_h + row * hrow + col * 2) = (chunk * kc + col < d) ? hreg[q] : zero;
+            }
+        }
+    };
+
+    // ---- W: step j of a chunk is k-block (chunk * kc / 64) + j * KS + ks of this wave's tile
+    const int KB = (d + 63) / 64, kbc = kc / 64, steps = kbc / KS, psteps = (steps + PF - 1) / PF * PF;
+    u32x4 ring[PF][4];                                                      // [slot][rows 8 i .. 8 i + 7], 8 lanes a row
+    const char* wbase;
+    uint32_t woff[4];
+    auto aim = [&](int g) {
+        const int v0 = g * VW + tile * 32;
+        const int first = min(v0, V - 1);
+        wbase = reinterpret_cast<const char*>(W) + (size_t)first * d * 2;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) woff[i] = (uint32_t)min(8 * i + lrow, V - 1 - first) * (uint32_t)d * 2u;
+    };
+    // k-block (of a chunk) of this wave's step j: all of them, runs of `unit` in turn between two waves, or every fourth
+    auto step_kb = [&](int j) {
+        const int run = (KS == 2) ? (j * unit_inv) >> 16 : 0;
+        return KS == 1 ? j : KS == 2 ? run * unit + ks * unit + j : j * KS + ks;
+    };
+    auto request_w = [&](int slot, int chunk, int j) {
+        const int kb = min(chunk * kbc + step_kb(min(j, steps - 1)), KB - 1);
+        const uint32_t k = min((uint32_t)(kb * 128 + lchunk * 16), (uint32_t)d * 2u - 16u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ring[slot][i] = *reinterpret_cast<const u32x4*>(wbase + (woff[i] + k));
+    };
+    request_h(0);
+    __builtin_amdgcn_sched_barrier(0);
+    aim(blockIdx.x);
+#pragma unroll
+    for (int q = 0; q < PF; ++q) request_w(q, 0, q);
+    __builtin_amdgcn_sched_barrier(0);
+    write_h(0);
+    if (tid < M) s_invt[tid] = inv_temperature(my_temp);
+    lds_barrier();
+
+    const bool ragged = (d & 63) != 0;
+    for (int g = blockIdx.x;; g += gridDim.x) {
+        const bool more = g + (int)gridDim.x < groups;
+        f32x4 acc[2][MT];
+#pragma unroll
+        for (int vb = 0; vb < 2; ++vb)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[vb][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int chunk = 0; chunk < (CH ? nchunks : 1); ++chunk) {
+            const bool last = !CH || chunk + 1 == nchunks;
+            const bool restage = CH && (!last || more);
+            if (restage) request_h(last ? 0 : chunk + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            // PF steps; the slots they free are filled with the steps PF later (ahead = 0: of this chunk, 1: of the next
+            // chunk or vocabulary group, 2: nothing is left to request)
+            auto block = [&](int j0, auto ahead) {
+#pragma unroll
+                for (int q = 0; q < PF; ++q) {
+                    const int j = j0 + q, kbl = step_kb(j);
+                    const bool use = j < steps && chunk * kbc + kbl < KB;   // uniform
+                    if (use) {                                              // LDS operations of one wave execute in order: no barrier
+                        const bool out = ragged && (chunk * kbc + kbl) * 64 + lchunk * 8 >= d;
+                        const u32x4 zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            *reinterpret_cast<u32x4*>(patch + (8 * i + lrow) * 144 + lchunk * 16) = out ? zero : ring[q][i];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (ahead.value == 0) request_w(q, chunk, j + PF);
+                    if constexpr (ahead.value == 1) request_w(q, last ? 0 : chunk + 1, q);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (use) {
+                        // operands of the next GM rows of 16 are read while the present ones are multiplied
+                        constexpr int GM = MT < 4 ? MT : 4, NG = 2 * MT / GM;
+                        int hr16 = 16 * hrow;
+                        asm volatile("" : "+s"(hr16));                      // not worth a register per row block: recomputed
+                        const unsigned char* const hp = s_h + r16 * hrow + kbl * 128 + c * 16;
+                        bf16x8 w[2][2], hv[2][GM];
+#pragma unroll
+                        for (int p = 0; p < 2; ++p)
+#pragma unroll
+                            for (int vb = 0; vb < 2; ++vb) w[p][vb] = *reinterpret_cast<const bf16x8*>(patch + (vb * 16 + r16) * 144 + p * 64 + c * 16);
+                        auto read_h = [&](int gi) {
+                            const int p = gi / (MT / GM), t0 = gi % (MT / GM) * GM;
+#pragma unroll
+                            for (int i = 0; i < GM; ++i) hv[gi & 1][i] = *reinterpret_cast<const bf16x8*>(hp + (t0 + i) * hr16 + p * 64);
+                        };
+                        read_h(0);
+#pragma unroll
+                        for (int gi = 0; gi < NG; ++gi) {
+                            if (gi + 1 < NG) read_h(gi + 1);
+                            __builtin_amdgcn_sched_barrier(0);
+                            const int p = gi / (MT / GM), t0 = gi % (MT / GM) * GM;
+#pragma unroll
+                            for (int i = 0; i < GM; ++i)
+#pragma unroll
+                                for (int vb = 0; vb < 2; ++vb)
+                                    acc[vb][t0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[p][vb], hv[gi & 1][i], acc[vb][t0 + i], 0, 0, 0);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+            };
+            for (int j0 = 0; j0 + PF < psteps; j0 += PF) block(j0, std::integral_constant<int, 0>{});
+            if (last && !more) {
+                block(psteps - PF, std::integral_constant<int, 2>{});
+            } else {
+                if (last) aim(g + gridDim.x);
+                block(psteps - PF, std::integral_constant<int, 1>{});
+            }
+            if (restage) {
+                lds_barrier();                                              // every wave is done with this chunk of H
+                write_h(last ? 0 : chunk + 1);
+                lds_barrier();
+            }
+        }
+
+        // ---- the KS partial results meet, SR rows at a time
+        int Vrow = V, NTrow = NT;
+        asm volatile("" : "+s"(Vrow), "+s"(NTrow));                         // (addresses are not kept in registers across the loop above)
+#pragma unroll
+        for (int r0 = 0; r0 < MT * 16; r0 += SR) {
+            if (r0 < M) {                                                   // uniform
+#pragma unroll
+                for (int i = 0; i < SR / 16; ++i)
+#pragma unroll
+                    for (int vb = 0; vb < 2; ++vb)
+                        *reinterpret_cast<f32x4*>(patch + (i * 16 + r16) * 144 + vb * 64 + c * 16) = acc[vb][r0 / 16 + i];
+                lds_barrier();
+#pragma unroll
+                for (int e = 0; e < SR * VW / 4; e += kStreamThreads) {
+                    const int idx = e + tid, row = idx / (VW / 4), q4 = idx % (VW / 4);
+                    if (SR * VW / 4 >= kStreamThreads || idx < SR * VW / 4) {
+                        const unsigned char* part = patches + (q4 >> 3) * KS * kPatchBytes + row * 144 + (q4 & 7) * 16;
+                        f32x4 x = *reinterpret_cast<const f32x4*>(part);
+#pragma unroll
+                        for (int w = 1; w < KS; ++w) x += *reinterpret_cast<const f32x4*>(part + w * kPatchBytes);
+                        const int m = r0 + row, v = g * VW + 4 * q4;
+                        const bool live = m < M;
+                        const float it = live ? s_invt[m] : 1.f;
+                        float sc[4], mx = -INFINITY;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            sc[u] = (v + u < V) ? x[u] * it : -INFINITY;
+                            mx = fmaxf(mx, sc[u]);
+                        }
+                        mx = fmaxf(mx, dpp_f32<kDppXor1>(mx));
+                        mx = fmaxf(mx, dpp_f32<kDppXor2>(mx));
+                        mx = fmaxf(mx, dpp_f32<kDppHalfMirror>(mx));
+                        float sum = 0.f;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) sum += (sc[u] > -INFINITY) ? __expf(sc[u] - mx) : 0.f;
+                        sum += dpp_f32<kDppXor1>(sum);
+                        sum += dpp_f32<kDppXor2>(sum);
+                        sum += dpp_f32<kDppHalfMirror>(sum);
+                        if (live && v < V) {
+                            if ((q4 & 7) == 0) {
+                                pm[(size_t)m * NTrow + v / kTileV] = mx;
+                                ps[(size_t)m * NTrow + v / kTileV] = sum;
+                            }
+                            float* out = L + (size_t)m * Vrow + v;
+                            if (v + 4 <= V) {
+                                __builtin_nontemporal_store(f32x4u(x), reinterpret_cast<f32x4u*>(out));
+                            } else {
+#pragma unroll
+                                for (int u = 0; u < 4; ++u)
+                                    if (v + u < V) out[u] = x[u];
+                            }
+                        }
+                    }
+                }
+                lds_barrier();                                              // the patches may be written again
+            }
+        }
+        if (!more) break;
+    }
+}
+
+// ---------------------------------------------------------------- bf16, many rows (M > 64): tiled GEMM
+// Workgroup tile BM (rows) x BN (vocabulary) x 64 (k), 8 waves, each a BM/2 x BN/4 block of 32x32 MFMA tiles (W as the row
+// operand, so that the accumulator is [vocabulary][row] and the transposed epilogue applies).  Both operands are staged
+// through LDS in two buffers; the operand fragments of k-step s+1 are read from LDS while the MFMAs of k-step s run, and the
+// global loads of the next PF k-blocks are in flight in PF register sets -- one barrier per k-block.  A k-block of 64 is one
+// whole 128-byte line of every row.  Rows padded by 16 bytes against bank conflicts.  Workgroups are numbered so that the row
+// blocks that share a vocabulary block run back to back on the same XCD (workgroup w goes to XCD w % 8): W is then read from
+// HBM once and from L2 afterwards.  Bound by how fast a workgroup takes in its operands and, with few k-blocks, by the logits'
+// stores, which the larger tiles do not overlap with another tile's products: 512 rows of V = 128256, d = 2048 312 us = 0.86
+// PFLOP/s; 128 rows of V = 32000, d = 768 14.4 us (28.5 when every tile was 256 x 256).
+constexpr int kLBK = 64, kLRow = (kLBK + 8) * 2;                            // k-block; LDS row stride in bytes (144)
 constexpr int kLCh = kLBK / 8;                                              // 16-byte chunks per row of a k-block
-constexpr int kLargeStage = (kLBM + kLBN) * kLRow;                          // bytes per buffer (73728)
+constexpr int kLargeThreads = 512;
 
-// Eight waves per workgroup, each 128 rows x 64 vocabulary entries, two waves per SIMD.  (Four waves of 128 x 128 with
-// register staging spill ~300 registers; four waves fed by global_load_lds measured no faster: the loop is bound by
-// how fast a workgroup pulls its operand tiles, 1 byte per 128 flop at this tile size, through L1 from L2.)
-constexpr int kLargeWaves = 8;
-
-__global__ __launch_bounds__(kLargeWaves * 64) void k_lmhead_large(int M, int d, int V, int n, int NT, int mblocks,
-                                                                const uint16_t* __restrict__ W,
+// Off: type of a byte offset inside a tile (32 bits while a tile's rows span less than 4 GiB).
+template <int BM, int BN, int PF, typename Off>
+__global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128) ? 4 : 2) void k_lmhead_tile(int M, int d, int V, int n, int NT,
+                                                                int mblocks, const uint16_t* __restrict__ W,
                                                                 const uint16_t* __restrict__ H,
                                                                 const float* __restrict__ temperature,
                                                                 float* __restrict__ L, float* __restrict__ pm,
                                                                 float* __restrict__ ps) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    __shared__ float s_invt[kLBM];
-    constexpr int NW = kLargeWaves;
-    constexpr int kLargeThreads = NW * 64;
-    constexpr int kLWPieces = kLBN * kLCh / kLargeThreads, kLHPieces = kLBM * kLCh / kLargeThreads;
-    static_assert(kLBN * kLCh % kLargeThreads == 0 && kLBM * kLCh % kLargeThreads == 0, "staging split");
-    constexpr int WNT = (NW == 8) ? 2 : 4;                // 32-wide vocabulary tiles per wave
+    __shared__ float s_invt[BM];
+    constexpr int kStage = (BM + BN) * kLRow;
+    constexpr int WP = BN * kLCh / kLargeThreads, HP = BM * kLCh / kLargeThreads;   // 16-byte pieces per thread
+    constexpr int TV = BN / 128, TM = BM / 64;                                      // 32-wide tiles of a wave
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nn = lane & 31, half = lane >> 5;
     // XCD-aware numbering: workgroup w runs on XCD w % 8; consecutive slots of one XCD walk the row blocks
     // of one vocabulary block before moving to the next vocabulary block.
     const int w = blockIdx.x, xcd = w & 7, slot = w >> 3;
     const int mb = slot % mblocks, nb = (slot / mblocks) * 8 + xcd;
-    const int m0 = mb * kLBM, v0 = nb * kLBN;
+    const int m0 = mb * BM, v0 = nb * BN;
     if (v0 >= V) return;                                  // uniform: padding workgroups of the last XCD round
-    const int wm = (NW == 8) ? wave >> 2 : wave >> 1;     // wave block: rows m0 + 128*wm ..,
-    const int wn = (NW == 8) ? wave & 3 : wave & 1;       // vocabulary v0 + 32*WNT*wn ..
-    if (tid < kLBM && m0 + tid < M) s_invt[tid] = row_inv_temperature(temperature, m0 + tid, n);
+    const int wm = wave >> 2, wn = wave & 3;              // wave block: rows m0 + BM/2 * wm .., vocabulary v0 + BN/4 * wn ..
+    const float my_temp = temperature[min(m0 + (tid & (BM - 1)), M - 1) / n];       // used after the requests below
 
-    // ---- global -> register staging: kLWPieces of W and kLHPieces of H per thread (16 bytes each), one k-block
-    //      ahead of the one in LDS.
-    u32x4 rw[kLWPieces], rh[kLHPieces];
-    auto fetch = [&](int kb) {
-        const int k = kb * kLBK;
+    // ---- global -> register staging: piece q of a k-block is row q / 8, 16-byte chunk q % 8 (eight lanes a row).  Rows past
+    //      the end re-read the last one (masked in the epilogue); chunks past the end of a row are zeroed.
+    u32x4 rw[PF][WP], rh[PF][HP];
+    const char* const wbase = reinterpret_cast<const char*>(W) + (size_t)v0 * d * 2;
+    const char* const hbase = reinterpret_cast<const char*>(H) + (size_t)m0 * d * 2;
+    Off wo[WP], ho[HP];
 #pragma unroll
-        for (int t = 0; t < kLWPieces; ++t) {
-            const int q = tid + t * kLargeThreads, row = q / kLCh, c = q % kLCh;
-            const int v = min(v0 + row, V - 1);           // clamped rows are masked in the epilogue
-            rw[t] = *reinterpret_cast<const u32x4*>(W + (size_t)v * d + k + c * 8);
-        }
+    for (int t = 0; t < WP; ++t) wo[t] = (Off)min((tid + t * kLargeThreads) / kLCh, V - 1 - v0) * (Off)d * 2u;
 #pragma unroll
-        for (int t = 0; t < kLHPieces; ++t) {
-            const int q = tid + t * kLargeThreads, row = q / kLCh, c = q % kLCh;
-            const int m = min(m0 + row, M - 1);
-            rh[t] = *reinterpret_cast<const u32x4*>(H + (size_t)m * d + k + c * 8);
-        }
+    for (int t = 0; t < HP; ++t) ho[t] = (Off)min((tid + t * kLargeThreads) / kLCh, M - 1 - m0) * (Off)d * 2u;
+    const int KB = (d + kLBK - 1) / kLBK, ch = tid % kLCh;
+    auto fetch = [&](int set, int kb) {                   // unconditional: the number of loads in flight has to be known
+        const uint32_t k = min((uint32_t)min(kb, KB - 1) * 128u + (uint32_t)ch * 16u, (uint32_t)d * 2u - 16u);
+#pragma unroll
+        for (int t = 0; t < WP; ++t) rw[set][t] = *reinterpret_cast<const u32x4*>(wbase + (wo[t] + k));
+#pragma unroll
+        for (int t = 0; t < HP; ++t) rh[set][t] = *reinterpret_cast<const u32x4*>(hbase + (ho[t] + k));
     };
-    auto stash = [&](int buf) {
-        unsigned char* sW = lds + buf * kLargeStage;
-        unsigned char* sH = sW + kLBN * kLRow;
+    auto stash = [&](int set, int kb) {
+        unsigned char* sW = lds + (kb & 1) * kStage + tid / kLCh * kLRow + ch * 16;
+        const bool out = kb * kLBK + ch * 8 >= d;
+        const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int t = 0; t < kLWPieces; ++t) {
-            const int q = tid + t * kLargeThreads, row = q / kLCh, c = q % kLCh;
-            *reinterpret_cast<u32x4*>(sW + row * kLRow + c * 16) = rw[t];
-        }
+        for (int t = 0; t < WP; ++t) *reinterpret_cast<u32x4*>(sW + t * (kLargeThreads / kLCh) * kLRow) = out ? zero : rw[set][t];
 #pragma unroll
-        for (int t = 0; t < kLHPieces; ++t) {
-            const int q = tid + t * kLargeThreads, row = q / kLCh, c = q % kLCh;
-            *reinterpret_cast<u32x4*>(sH + row * kLRow + c * 16) = rh[t];
-        }
+        for (int t = 0; t < HP; ++t) *reinterpret_cast<u32x4*>(sW + (BN + t * (kLargeThreads / kLCh)) * kLRow) = out ? zero : rh[set][t];
     };
 
-    f32x16 acc[WNT][4];                                   // [vocabulary tile][row tile]
+    f32x16 acc[TV][TM];                                   // [vocabulary tile][row tile]
 #pragma unroll
-    for (int a = 0; a < WNT; ++a)
+    for (int a = 0; a < TV; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < TM; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
-    auto multiply = [&](int buf) {
-        const unsigned char* sW = lds + buf * kLargeStage;
-        const unsigned char* sH = sW + kLBN * kLRow;
+    auto multiply = [&](int kb) {
+        const unsigned char* sW = lds + (kb & 1) * kStage + (wn * 32 * TV + nn) * kLRow + half * 16;
+        const unsigned char* sH = lds + (kb & 1) * kStage + (BN + wm * (BM / 2) + nn) * kLRow + half * 16;
         // operand fragments of k-step ks+1 are read from LDS while the MFMAs of k-step ks run
-        bf16x8 wf[2][WNT], hf[2][4];
+        bf16x8 wf[2][TV], hf[2][TM];
         auto read_frags = [&](int ks, int set) {
 #pragma unroll
-            for (int a = 0; a < WNT; ++a)
-                wf[set][a] = *reinterpret_cast<const bf16x8*>(sW + (wn * 32 * WNT + a * 32 + nn) * kLRow + (2 * ks + half) * 16);
+            for (int a = 0; a < TV; ++a) wf[set][a] = *reinterpret_cast<const bf16x8*>(sW + a * 32 * kLRow + ks * 32);
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-                hf[set][b] = *reinterpret_cast<const bf16x8*>(sH + (wm * 128 + b * 32 + nn) * kLRow + (2 * ks + half) * 16);
+            for (int b = 0; b < TM; ++b) hf[set][b] = *reinterpret_cast<const bf16x8*>(sH + b * 32 * kLRow + ks * 32);
         };
         read_frags(0, 0);
 #pragma unroll
@@ -600,35 +743,45 @@ __global__ __launch_bounds__(kLargeWaves * 64) void k_lmhead_large(int M, int d,
             if (ks + 1 < kLBK / 16) read_frags(ks + 1, (ks + 1) & 1);
             __builtin_amdgcn_sched_barrier(0);            // keep the reads ahead of the MFMAs they overlap with
 #pragma unroll
-            for (int a = 0; a < WNT; ++a)
+            for (int a = 0; a < TV; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+                for (int b = 0; b < TM; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][a], hf[ks & 1][b], acc[a][b], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    // k-block kb+1 is requested while k-block kb-1 is multiplied and written to LDS after k-block kb: its loads have
-    // one multiply (about 2000 MFMA cycles per SIMD, more than an L2 round trip) to arrive.
-    const int KB = d / kLBK;
-    fetch(0);
-    stash(0);
-    if (1 < KB) fetch(1);
+#pragma unroll
+    for (int q = 0; q < PF; ++q) fetch(q, q);
+    __builtin_amdgcn_sched_barrier(0);
+    stash(0, 0);
+    if (tid < BM) s_invt[tid] = inv_temperature(my_temp);
+    fetch(0, PF);
     lds_barrier();
-    for (int kb = 0; kb < KB; ++kb) {
-        multiply(kb & 1);
-        if (kb + 1 < KB) stash((kb + 1) & 1);
-        if (kb + 2 < KB) fetch(kb + 2);
-        lds_barrier();
-    }
-    // ---- epilogue: every wave turns its four 32x32 blocks through a private patch carved from buffer 0
+    // register set q holds k-block kb + 1 with (kb + 1) % PF = q: it goes to LDS after k-block kb is multiplied and is
+    // refilled with the k-block PF later, except in the last PF k-blocks
+    auto block = [&](int kb0, auto refill) {
+#pragma unroll
+        for (int q = 0; q < PF; ++q) {
+            const int kb = kb0 + q;
+            if (kb < KB) {
+                multiply(kb);
+                if (kb + 1 < KB) stash((q + 1) % PF, kb + 1);
+                if constexpr (refill.value) fetch((q + 1) % PF, kb + 1 + PF);
+                lds_barrier();
+            }
+        }
+    };
+    int kb0 = 0;
+    for (; kb0 + PF < KB; kb0 += PF) block(kb0, std::true_type{});
+    block(kb0, std::false_type{});
+    // ---- epilogue: every wave turns its 32x32 blocks through a private patch carved from buffer 0
     unsigned char* tpatch = lds + wave * kPatchBytes;
 #pragma unroll
-    for (int a = 0; a < WNT; ++a)
+    for (int a = 0; a < TV; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-            store_tile_32x32_t(acc[a][b], m0 + wm * 128 + b * 32, v0 + wn * 32 * WNT + a * 32, M, V, NT, s_invt - m0, L, pm, ps,
-                               tpatch);
+        for (int b = 0; b < TM; ++b)
+            store_tile_32x32_t(acc[a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
 }
 
 // ---------------------------------------------------------------- fp32 operands: one output per thread
@@ -662,12 +815,11 @@ __global__ __launch_bounds__(kBlock) void k_lmhead_f32(int M, int d, int V, int 
     }
 }
 
-// Chunked variant: d a multiple of 768, 512 or 896 (k per chunk), at least two chunks.
+// Chunked variant: d a multiple of 512, 768 or 896 (k per chunk; the 512-wide chunk is the one that keeps the H prefetch in
+// registers without spills), at least two chunks.
 static int skinny_kc_kh(const tabed_cfg& c, int M) {
     if (c.w_dtype != 1 || M > 64) return 0;
-    // with two row blocks the 512-wide chunk is the one that keeps the H prefetch in registers without spills
-    const int order_two[3] = {4, 6, 7}, order_one[3] = {6, 4, 7};
-    for (int KH : (M > 32 ? order_two : order_one))
+    for (int KH : {4, 6, 7})
         if (c.d % (KH * 128) == 0 && c.d / (KH * 128) >= 2) return KH;
     return 0;
 }
@@ -690,23 +842,15 @@ static hipError_t launch_skinny_kc_t(const ProfScope* prof, const tabed_cfg& c, 
 static hipError_t launch_skinny_kc(const ProfScope* prof, int KH, const tabed_cfg& c, const WsLayout& Lay, int M,
                              const void* W, const void* H, const float* temperature, float* logits, float* pm,
                              float* ps, hipStream_t s) {
-    const int MT = (M + 31) / 32;
-#define TABED_SKINNY_KC(KH_)                                                                              \
-    if (KH == KH_) {                                                                                      \
-        if (MT == 1) return launch_skinny_kc_t<KH_, 1>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);   \
-        else         return launch_skinny_kc_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);   \
-    }
+#define TABED_SKINNY_KC(KH_) \
+    if (KH == KH_) return launch_skinny_kc_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     TABED_SKINNY_KC(4) TABED_SKINNY_KC(6) TABED_SKINNY_KC(7)
 #undef TABED_SKINNY_KC
     return hipErrorInvalidValue;
 }
 
 static bool skinny_applies(const tabed_cfg& c, int M) {
-    if (c.w_dtype != 1 || M > 64 || c.d % 128 != 0) return false;
-    const int KH = c.d / 128, MT = (M + 31) / 32;
-    if (KH != 4 && KH != 6 && KH != 7 && KH != 8) return false;
-    const size_t lds = (size_t)MT * 32 * (c.d * 2 + 16) + (size_t)kSkinnyWaves * kPatchBytes;
-    return lds <= 160 * 1024;
+    return c.w_dtype == 1 && M <= 64 && (c.d == 4 * 128 || c.d == 6 * 128 || c.d == 7 * 128);
 }
 
 template <int KH, int MT>
@@ -727,15 +871,75 @@ static hipError_t launch_skinny_t(const ProfScope* prof, const tabed_cfg& c, con
 
 static hipError_t launch_skinny(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
                           const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
-    const int KH = c.d / 128, MT = (M + 31) / 32;
-#define TABED_SKINNY(KH_)                                                                              \
-    if (KH == KH_) {                                                                                   \
-        if (MT == 1) return launch_skinny_t<KH_, 1>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);  \
-        else         return launch_skinny_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);  \
-    }
-    TABED_SKINNY(4) TABED_SKINNY(6) TABED_SKINNY(7) TABED_SKINNY(8)
+    const int KH = c.d / 128;
+#define TABED_SKINNY(KH_) \
+    if (KH == KH_) return launch_skinny_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+    TABED_SKINNY(4) TABED_SKINNY(6) TABED_SKINNY(7)
 #undef TABED_SKINNY
     return hipErrorInvalidValue;
+}
+
+template <int MT, int KS, int PF, bool CH>
+static hipError_t launch_stream_t(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int kc, int nchunks, int unit,
+                                  const void* W, const void* H, const float* temperature, float* logits, float* pm, float* ps,
+                                  hipStream_t s) {
+    constexpr int VW = 8 / KS * 32;
+    const size_t lds = (size_t)MT * 16 * (kc * 2 + 16) + 8 * (size_t)kPatchBytes;
+    static std::once_flag once;
+    static hipError_t rc = hipSuccess;
+    if (raise_lds_limit(&k_lmhead_stream<MT, KS, PF, CH>, (size_t)MT * 16 * (kStreamMaxKC(MT) * 2 + 16) + 8 * (size_t)kPatchBytes, once, rc) != hipSuccess) return rc;
+    const int groups = (c.V + VW - 1) / VW;
+    const int grid = std::min(groups, lds <= 80 * 1024 ? 512 : 256);       // persistent: two workgroups a compute unit where LDS allows
+    launch(prof, k_lmhead_stream<MT, KS, PF, CH>, dim3(grid), dim3(kStreamThreads), lds, s, Lay.M, c.d, c.V, c.n, Lay.NT, groups, kc,
+           nchunks, unit, 65536 / unit + 1, static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
+    return hipSuccess;
+}
+
+template <int MT, int KS>
+static hipError_t launch_stream_k(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int unit, const void* W, const void* H,
+                                  const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
+    const int granule = std::max(128, 64 * KS * unit), most = kStreamMaxKC(MT) / granule * granule;
+    const int nchunks = (c.d + most - 1) / most;
+    const int kc = (((c.d + nchunks - 1) / nchunks) + granule - 1) / granule * granule, steps = kc / 64 / KS;
+    // three or four k-blocks ahead: whichever divides a chunk's steps with less of a remainder
+    const bool four = KS <= 2 && (steps + 3) / 4 * 4 <= (steps + 2) / 3 * 3;
+#define TABED_STREAM(PF_, CH_) return launch_stream_t<MT, KS, PF_, CH_>(prof, c, Lay, kc, nchunks, unit, W, H, temperature, logits, pm, ps, s)
+    if constexpr (KS <= 2)
+        if (four) { if (nchunks > 1) TABED_STREAM(4, true); else TABED_STREAM(4, false); }
+    if (nchunks > 1) TABED_STREAM(3, true); else TABED_STREAM(3, false);
+#undef TABED_STREAM
+}
+
+// Waves per vocabulary tile, and which k-blocks each of them adds up.  A logit's value depends on this order in its last
+// bit, and with 1e5 bins a sampled token on the last bits of all of them; so the order stays what it was for every size:
+//   * d = 512, 768, 896 and multiples: two waves, runs of d / 128 (of a chunk's half) in turn;
+//   * other hidden sizes: one wave, all k-blocks in order, where groups of 128 entries would not be one round of a group per
+//     compute unit (V = 38000, d = 1280, 4 rows: 18.9 us, 22.1 with two waves).
+// Up to there two waves take turns (V = 32000, d = 1280, 20 rows: 15.0 us, 17.1 with one), and vocabularies of less than 128
+// groups are cut finer, four waves a tile (V = 10000, d = 1160, 20 rows: 9.0 us, 11.0 with two, 17.9 with one): fewer bins
+// have fewer edges for a uniform to land on.
+template <int MT>
+static hipError_t launch_stream(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, const void* W, const void* H,
+                                const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
+    int run = (c.d == 1024) ? 8 : 0;
+    for (int KH : {6, 4, 7}) if (run == 0 && c.d % (KH * 128) == 0) run = KH;
+    if (c.V <= 128 * 128) return launch_stream_k<MT, 4>(prof, c, Lay, 1, W, H, temperature, logits, pm, ps, s);
+    if (run == 0 && c.V > 256 * 128) return launch_stream_k<MT, 1>(prof, c, Lay, 1, W, H, temperature, logits, pm, ps, s);
+    return launch_stream_k<MT, 2>(prof, c, Lay, run ? run : 1, W, H, temperature, logits, pm, ps, s);
+}
+
+template <int BM, int BN, int PF, typename Off>
+static hipError_t launch_tile(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
+                              const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
+    const size_t lds = 2 * (size_t)(BM + BN) * kLRow;
+    static std::once_flag once;
+    static hipError_t rc = hipSuccess;
+    if (raise_lds_limit(&k_lmhead_tile<BM, BN, PF, Off>, lds, once, rc) != hipSuccess) return rc;
+    const int mblocks = (M + BM - 1) / BM, nblocks = (c.V + BN - 1) / BN;
+    const int nrounds = (nblocks + 7) / 8;             // vocabulary blocks are dealt to the 8 XCDs in rounds
+    launch(prof, k_lmhead_tile<BM, BN, PF, Off>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
+           static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
+    return hipSuccess;
 }
 
 hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, const void* W, const void* H,
@@ -744,32 +948,36 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
     float* pm = reinterpret_cast<float*>(ws + Lay.off_pm);
     float* ps = reinterpret_cast<float*>(ws + Lay.off_ps);
     const int M = Lay.M;
+    hipError_t e = hipSuccess;
     if (c.w_dtype == 0) {
         const dim3 grid(Lay.NT, (M + 7) / 8);
         launch(&prof, k_lmhead_f32, grid, dim3(kBlock), 0, s, M, c.d, c.V, c.n, Lay.NT,
                            static_cast<const float*>(W), static_cast<const float*>(H), temperature, logits, pm, ps);
+    } else if (c.d > (1 << 22)) {                       // rows of more than 8 MB: 64-bit offsets inside a tile
+        e = launch_tile<128, 128, 2, uint64_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+    } else if (M <= 16) {
+        e = launch_stream<1>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
+    } else if (M <= 32) {
+        e = launch_stream<2>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
     } else if (skinny_applies(c, M)) {
-        const hipError_t e = launch_skinny(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
-        if (e != hipSuccess) return e;
+        e = launch_skinny(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     } else if (skinny_kc_kh(c, M) != 0) {
-        const hipError_t e = launch_skinny_kc(&prof, skinny_kc_kh(c, M), c, Lay, M, W, H, temperature, logits, pm, ps, s);
-        if (e != hipSuccess) return e;
-    } else if (M > 64 && c.d % 64 == 0) {
-        static std::once_flag attr_once;                   // raise the dynamic-LDS limit once
-        static hipError_t attr_rc = hipSuccess;
-        const size_t lds = 2 * (size_t)kLargeStage;
-        if (raise_lds_limit(&k_lmhead_large, lds, attr_once, attr_rc) != hipSuccess) return attr_rc;
-        const int mblocks = (M + kLBM - 1) / kLBM, nblocks = (c.V + kLBN - 1) / kLBN;
-        const int nrounds = (nblocks + 7) / 8;             // vocabulary blocks are dealt to the 8 XCDs in rounds
-        const dim3 grid(nrounds * mblocks * 8);
-        launch(&prof, k_lmhead_large, grid, dim3(kLargeWaves * 64), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
-               static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
+        e = launch_skinny_kc(&prof, skinny_kc_kh(c, M), c, Lay, M, W, H, temperature, logits, pm, ps, s);
+    } else if (M <= 64 && (c.d <= kStreamMaxKC(4) || c.V <= 256 * 128)) {
+        // (H in several chunks and several groups per workgroup: the tiles below are faster, 67.5 against 79.5 us at 64 rows
+        // of V = 100000, d = 1280)
+        e = launch_stream<4>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
     } else {
-        const dim3 grid((c.V + kBN - 1) / kBN, (M + kBM - 1) / kBM);
-        launch(&prof, k_lmhead_bf16, grid, dim3(kBlock), 0, s, M, c.d, c.V, c.n, Lay.NT,
-                           static_cast<const __hip_bfloat16*>(W), static_cast<const __hip_bfloat16*>(H),
-                           temperature, logits, pm, ps);
+        // the largest tile that still gives the chip three workgroups for every four compute units (a tile reads
+        // (BM + BN) / (BM BN) operand elements per product): 312 / 340 / 371 us for 256 x 256, 128 x 256, 128 x 128 at 512 rows
+        // of V = 128256, d = 2048; 89 / 103 / 102 at 256 rows of V = 100000, d = 1024; but 30 / 18.1 / 14.4 at 128 rows of
+        // V = 32000, d = 768, where they are 125, 125 and 250 workgroups
+        auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((c.V + bn - 1) / bn); };
+        if (M > 128 && tiles(256, 256) >= 192) e = launch_tile<256, 256, 1, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else if (tiles(128, 256) >= 192) e = launch_tile<128, 256, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else e = launch_tile<128, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     }
+    if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 

@@ -1,0 +1,51 @@
+"""LM head on the GPU against a 64-bit product of the same stored values, at the sizes where its kernels and tiles change."""
+import pytest
+import torch
+
+from paper_2601_20357_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+SHAPES = [
+    # V,     d,    n,  B    rows = n * B
+    # W-streaming kernel, 16 rows: four waves a tile, two, K in chunks, one vocabulary tile, several groups per workgroup
+    (8003, 72, 1, 1), (33, 8, 16, 1), (32003, 1160, 3, 5), (5000, 2056, 1, 7), (31001, 2056, 1, 3), (140001, 256, 1, 5),
+    # 32 rows
+    (6000, 648, 1, 17), (32777, 1032, 4, 8), (31000, 1088, 1, 32), (70001, 1096, 2, 16),
+    # 64 rows (hidden sizes that the kernels with a compile-time size do not take), K whole and in chunks
+    (3001, 640, 1, 33), (32767, 640, 8, 8), (33001, 640, 1, 64), (33001, 1096, 1, 20), (9000, 1160, 1, 50), (32768, 776, 1, 64),
+    # tiles of 128 x 128, 128 x 256, 256 x 256 rows x vocabulary; one k-block, a ragged last one, a last row block of one row
+    (4099, 72, 1, 65), (33000, 1160, 1, 50), (8200, 2048, 1, 128), (2000, 8, 1, 129),
+    (49153, 264, 1, 66), (24600, 136, 1, 257), (49161, 264, 1, 129), (25000, 64, 1, 511),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"V{s[0]}d{s[1]}M{s[2] * s[3]}")
+def test_logits_and_log_sum_exp(shape):
+    V, d, n, B = shape
+    M = n * B
+    print(f"lm head {shape}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(V + d)
+    cfg = binding.make_cfg(V=V, d=d, n=n, B=B, gamma=2, h=1, w_dtype=1, seed=1)
+    buf = binding.RoundBuffers(cfg, DEV)
+    buf.weights.fill_(1.0 / n)
+    W = (torch.randn((V, d), generator=g, device=DEV) * 0.05).bfloat16()
+    H = torch.randn((B, n, d), generator=g, device=DEV).bfloat16()
+    temp = torch.ones(B, device=DEV)
+    temp[1::3], temp[2::3] = 0.7, 0.0
+    buf.draft_logits.fill_(7.0)
+    buf.draft_step(0, 1, W, H, temp)
+    torch.cuda.synchronize()
+    Hd, Wd = H.view(M, d).double(), W.double()
+    exact = Hd @ Wd.t()
+    # products of bf16 are exact in fp32; a sum of d of them in any order is off by at most d 2^-24 times the sum of their sizes
+    bound = d * 2.0 ** -24 * (Hd.abs() @ Wd.abs().t())
+    err = (buf.draft_logits[1].view(M, V).double() - exact).abs()
+    assert bool((err <= bound + 1e-30).all()), float((err - bound).max())
+    assert bool((buf.draft_logits[0] == 7.0).all())                # the other slot is untouched
+    inv = torch.where(temp > 0, 1 / temp, torch.ones_like(temp)).double().repeat_interleave(n)
+    lse = torch.logsumexp(exact * inv[:, None], -1)
+    # the log-sum-exp moves by at most the largest error of a scaled logit; 2e-6 for the fp32 exponentials and their sums
+    tol = (bound.max(-1).values * inv) + 2e-6
+    assert bool(((buf.draft_lse[1].view(M) - lse).abs() <= tol).all())
