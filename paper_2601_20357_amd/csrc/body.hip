@@ -90,22 +90,22 @@ __global__ __launch_bounds__(kBlock) void k_body_norm(int d, float eps, const fl
 
 // ---------------------------------------------------------------- projections
 // One workgroup = 16 * MB rows and one 16-column tile of the result (two tiles that belong together for the rotation and
-// for SwiGLU), over the whole contraction: its waves take k-blocks of 64 in turn, read W straight into the operand layout
-// of v_mfma_f32_16x16x32_bf16 and meet through LDS, where the results are added in wave order.  A lane's two 16-byte
-// pieces of a k-block are adjacent (the contraction index is permuted alike in both operands), so that four lanes read
-// one whole 128-byte line of a row.  Everything a wave needs is requested before anything is used (G = k-blocks a wave
-// requests together), what is needed first first.
+// for SwiGLU), over the whole contraction: its waves take k-blocks of 64 in turn and meet through LDS, where the results are
+// added in wave order.  A wave reads W as whole 128-byte lines, 8 lanes a row, and turns every k-block through a private LDS
+// patch into the operand layout of v_mfma_f32_16x16x32_bf16 (read straight into that layout, 16 consecutive lanes hold 16
+// different rows and a load instruction looks up 64 lines instead of 8).  Everything a wave needs is requested before
+// anything is used (G = k-blocks a wave requests together), what is needed first first.
 //   IN  kInNorm:    X = bf16(x * inv_rms * g): a wave reads whole rows of the residual stream (CI pieces of 256 columns),
 //                   so that it has their sums of squares, and leaves the rows in LDS
-//       kInBf16:    X as it is, straight into operand layout
+//       kInBf16:    X as it is, through the patch like W
 //       kInMerge:   X = the attention's partial results of `splits` key ranges, merged into LDS
 //   EPI kEpiRope:   q/k/v columns: rotation in fp64, queries to `q`, the new key and value to the caches
 //       kEpiSilu:   gate and up columns of the same 16 units: silu(gate) * up
 //       kEpiAdd:    residual addition in place
 // At 64 rows of d = 768, d_ff = 3072 a launch moves 1 to 9 MB: latency, the rate at which a compute unit takes in W and X
 // (64 bytes a cycle: every workgroup reads its rows of X whole) and the instructions fetched once bound it.  Measured
-// there: q/k/v 7.5, o 4.7, gate/up 9.7, down 8.0 us; with the contraction split over workgroups, partial sums in memory and
-// rotation, residual + norm and SwiGLU kernels of their own a layer took 62 us instead of 50.
+// there: q/k/v 7.2, o 4.5, gate/up 9.7, down 6.0 us (down 8.0 with loads straight into operand layout); with the contraction split over workgroups, partial sums in memory and
+// rotation, residual + norm and SwiGLU kernels of their own a layer took 62 us instead of 48.
 enum { kInNorm = 0, kInBf16 = 1, kInMerge = 2 };
 enum { kEpiRope = 0, kEpiSilu = 1, kEpiAdd = 2 };
 
@@ -127,6 +127,8 @@ struct ProjArgs {
     const double2* trig;         // kEpiRope: [M][hd/2] cos, sin of the rows' positions
     uint16_t* act;               // kEpiSilu: [M,N]
 };
+
+constexpr int kBodyPatch = 16 * 144;                  // bytes: 16 rows of one k-block, padded
 
 __host__ __device__ constexpr int staged_row(int K) { return (K + 63) / 64 * 64 + 8; }   // bf16 of one staged row of X, padded
 
@@ -176,13 +178,15 @@ __global__ __launch_bounds__(NW * 64) void k_body_proj(ProjArgs a) {
     constexpr int kElems = (MB * 256 + kThreads - 1) / kThreads;          // result positions (or pairs) per thread
     constexpr int RW = MB * 16 / NW;                                      // kInNorm: rows a wave stages
     static_assert(IN != kInMerge || MB == 1, "the merge stages 16 rows");
-    // staged rows of X, then (after a barrier) the waves' results [NW][NB][MB][16][20]
+    // staged rows of X, the waves' patches, then (after a barrier) their results [NW][NB][MB][16][20]
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     uint16_t* const s_x = reinterpret_cast<uint16_t*>(s_dyn);
     float* const s_acc = reinterpret_cast<float*>(s_dyn);
     const int tile = blockIdx.x, m0 = blockIdx.y * (MB * 16), tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = lane & 15, c = lane >> 4, K = a.K, KB = (K + 63) / 64, xrow = staged_row(K);
+    const int r16 = lane & 15, c = lane >> 4, lrow = lane >> 3, lchunk = lane & 7, K = a.K, KB = (K + 63) / 64, xrow = staged_row(K);
+    constexpr int kPatches = NB + ((IN == kInBf16) ? MB : 0);
+    unsigned char* const patch = s_dyn + ((IN == kInBf16) ? 0 : MB * 16 * xrow * 2) + wave * (kPatches * kBodyPatch);
 
     // which columns: [part][d] for q/k/v; the second tile is the rotation's other half, the up column, or the next 16
     int col0 = tile * 16, col1 = 0, lim0 = a.N, part = 0, j0 = 0;
@@ -206,16 +210,21 @@ __global__ __launch_bounds__(NW * 64) void k_body_proj(ProjArgs a) {
     }
     // uniform bases and 32-bit lane offsets (in bytes): a load is one instruction with no 64-bit address arithmetic
     const char* wb[NB];
-    uint32_t wo[NB], xo[MB];
+    uint32_t wo[NB][2], xo[MB][2];                                        // [rows 8 i + lane / 8 of the tile]
     wb[0] = reinterpret_cast<const char*>(a.W) + (size_t)col0 * K * 2;
-    wo[0] = (uint32_t)min(r16, lim0 - 1 - col0) * (uint32_t)K * 2u;
+    int last0 = lim0 - 1 - col0, last1 = 0;                               // last row of W that a tile may read
     if (NB == 2) {                                                        // (hd < 32: the second 16 columns may start past the part)
         const int lim1 = (EPI == kEpiSilu) ? 2 * a.N : lim0, first = min(col1, lim1 - 1);
         wb[NB - 1] = reinterpret_cast<const char*>(a.W) + (size_t)first * K * 2;
-        wo[NB - 1] = (uint32_t)min(r16, lim1 - 1 - first) * (uint32_t)K * 2u;
+        last1 = lim1 - 1 - first;
     }
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) xo[mb] = (uint32_t)min(mb * 16 + r16, a.M - 1 - m0) * (uint32_t)K * 2u;
+    for (int i = 0; i < 2; ++i) {
+        wo[0][i] = (uint32_t)min(8 * i + lrow, last0) * (uint32_t)K * 2u;
+        if (NB == 2) wo[NB - 1][i] = (uint32_t)min(8 * i + lrow, last1) * (uint32_t)K * 2u;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) xo[mb][i] = (uint32_t)min(mb * 16 + 8 * i + lrow, a.M - 1 - m0) * (uint32_t)K * 2u;
+    }
 
     // ---- requests, in the order of use
     int pos[kElems];
@@ -239,21 +248,20 @@ __global__ __launch_bounds__(NW * 64) void k_body_proj(ProjArgs a) {
             gr[i] = *reinterpret_cast<const f32x4b*>(reinterpret_cast<const char*>(a.g) + (uint32_t)min((i * 64 + lane) * 4, K - 4) * 4u);
         __builtin_amdgcn_sched_barrier(0);
     }
-    bf16x8 wv[G][NB][2], xb[(IN == kInBf16) ? G : 1][MB][2];
+    u32x4b wv[G][NB][2], xb[(IN == kInBf16) ? G : 1][MB][2];
     auto request = [&](int b0) {
 #pragma unroll
         for (int q = 0; q < G; ++q) {
             const int kb = min(b0 + q * NW, KB - 1);                      // past the last block: re-read, not used
+            const uint32_t k = min((uint32_t)(kb * 128 + lchunk * 16), (uint32_t)K * 2u - 16u);   // past the last column: zeroed below
+            const char* const xbase = reinterpret_cast<const char*>(a.X) + (size_t)m0 * K * 2;
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const uint32_t k = min((uint32_t)(kb * 128 + c * 32 + p * 16), (uint32_t)K * 2u - 16u);   // past the last column: masked below
+            for (int i = 0; i < 2; ++i) {
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) wv[q][nb][p] = *reinterpret_cast<const bf16x8*>(wb[nb] + (wo[nb] + k));
+                for (int nb = 0; nb < NB; ++nb) wv[q][nb][i] = *reinterpret_cast<const u32x4b*>(wb[nb] + (wo[nb][i] + k));
                 if (IN == kInBf16) {
-                    const char* xbase = reinterpret_cast<const char*>(a.X) + (size_t)m0 * K * 2;
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
-                        if (m0 + mb * 16 + r16 < a.M) xb[q][mb][p] = *reinterpret_cast<const bf16x8*>(xbase + (xo[mb] + k));
+                    for (int mb = 0; mb < MB; ++mb) xb[q][mb][i] = *reinterpret_cast<const u32x4b*>(xbase + (xo[mb][i] + k));
                 }
             }
         }
@@ -324,38 +332,45 @@ __global__ __launch_bounds__(NW * 64) void k_body_proj(ProjArgs a) {
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x4b{0.f, 0.f, 0.f, 0.f};
-    const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
-    const bool ragged = (K & 63) != 0;
     for (int b0 = wave; b0 < KB; b0 += NW * G) {
         if (b0 != wave) request(b0);
 #pragma unroll
         for (int q = 0; q < G; ++q) {
             const int kb = b0 + q * NW;
-            if (kb < KB) {
+            if (kb < KB) {                                                // LDS operations of one wave execute in order: no barrier
+                const bool out = kb * 64 + lchunk * 8 >= K;               // K is a multiple of 8: a piece is in or out
+                const u32x4b zero = {0u, 0u, 0u, 0u};
+                unsigned char* const to = patch + lrow * 144 + lchunk * 16;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<u32x4b*>(to + nb * kBodyPatch + i * 8 * 144) = out ? zero : wv[q][nb][i];
+                    if (IN == kInBf16) {
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb)
+                            *reinterpret_cast<u32x4b*>(to + (NB + mb) * kBodyPatch + i * 8 * 144) = out ? zero : xb[q][mb][i];
+                    }
+                }
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
-                    const int k = kb * 64 + c * 16 + p * 8;
-                    if (ragged && k >= K) {                               // K is a multiple of 8: a piece is in or out
+                    const unsigned char* const from = patch + r16 * 144 + p * 64 + c * 16;
+                    bf16x8 w[NB];
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) wv[q][nb][p] = zero;
-                        if (IN == kInBf16) {
-#pragma unroll
-                            for (int mb = 0; mb < MB; ++mb) xb[q][mb][p] = zero;
-                        }
-                    }
+                    for (int nb = 0; nb < NB; ++nb) w[nb] = *reinterpret_cast<const bf16x8*>(from + nb * kBodyPatch);
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb) {
-                        const bf16x8 xv = (IN == kInBf16) ? xb[q][mb][p]
-                                        : *reinterpret_cast<const bf16x8*>(s_x + (IN == kInMerge ? min(r16, a.M - 1 - m0) : mb * 16 + r16) * xrow + k);
+                        const bf16x8 xv = (IN == kInBf16) ? *reinterpret_cast<const bf16x8*>(from + (NB + mb) * kBodyPatch)
+                                        : *reinterpret_cast<const bf16x8*>(s_x + (IN == kInMerge ? min(r16, a.M - 1 - m0) : mb * 16 + r16) * xrow +
+                                                                           kb * 64 + p * 32 + c * 8);
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb)
-                            acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[q][nb][p], xv, acc[nb][mb], 0, 0, 0);
+                            acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nb], xv, acc[nb][mb], 0, 0, 0);
                     }
                 }
             }
         }
     }
-    if (IN != kInBf16) __syncthreads();                                   // every wave is done with the staged rows
+    __syncthreads();                                                      // every wave is done with the staged rows and its patch
     // accumulator: lane holds row r16 of the block, columns 4 c .. 4 c + 3 of the tile
     auto slot_of = [&](int w, int nb, int mb, int row, int col) { return (((w * NB + nb) * MB + mb) * 16 + row) * 20 + col; };
 #pragma unroll
@@ -665,19 +680,19 @@ hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStre
 template <int NW, int MB, int G, int CI, int IN, int EPI>
 static hipError_t launch_proj_t(int tiles, hipStream_t s, const ProjArgs& a) {
     constexpr int NB = (EPI == kEpiAdd) ? 1 : 2;
-    const size_t staged = (IN == kInBf16) ? 0 : sizeof(uint16_t) * MB * 16 * (size_t)staged_row(a.K);
-    const size_t results = sizeof(float) * NW * NB * MB * 16 * 20;
+    constexpr size_t patches = (size_t)NW * (NB + (IN == kInBf16 ? MB : 0)) * kBodyPatch, results = sizeof(float) * NW * NB * MB * 16 * 20;
+    auto lds = [&](int K) { return std::max(results, patches + ((IN == kInBf16) ? 0 : sizeof(uint16_t) * MB * 16 * (size_t)staged_row(K))); };
     static std::once_flag once;
     static hipError_t rc = hipSuccess;
-    const size_t most = std::max(results, (IN == kInBf16) ? (size_t)0 : sizeof(uint16_t) * MB * 16 * (size_t)staged_row(IN == kInNorm ? CI * 256 : 1536));
+    const size_t most = lds(IN == kInNorm ? CI * 256 : 1536);
     if (raise_lds_limit(&k_body_proj<NW, MB, G, CI, IN, EPI>, most, once, rc) != hipSuccess) return rc;
     ProfScope prof(TABED_K_BODY, s);
-    launch(&prof, k_body_proj<NW, MB, G, CI, IN, EPI>, dim3(tiles, (a.M + MB * 16 - 1) / (MB * 16)), dim3(NW * 64), std::max(staged, results), s, a);
+    launch(&prof, k_body_proj<NW, MB, G, CI, IN, EPI>, dim3(tiles, (a.M + MB * 16 - 1) / (MB * 16)), dim3(NW * 64), lds(a.K), s, a);
     return hipGetLastError();
 }
 
-// Waves per workgroup and k-blocks a wave requests together: four waves up to 1024 of contraction, eight beyond, and as
-// many requests as cover a wave's share where that is at most eight.  Two row blocks per workgroup where the tiles of
+// Waves per workgroup and k-blocks a wave requests together: four waves up to 1024 of contraction (eight for q/k/v: 7.2
+// against 8.6 us at 64 rows), eight beyond, and as many requests as cover a wave's share where that is at most eight.  Two row blocks per workgroup where the tiles of
 // one already fill the chip twice: W is then read half as often.
 template <int IN, int EPI>
 static hipError_t projection(const ProjArgs& a, int tiles, hipStream_t s) {
@@ -687,8 +702,12 @@ static hipError_t projection(const ProjArgs& a, int tiles, hipStream_t s) {
     if constexpr (IN == kInMerge) {
         return launch_proj_t<8, 1, 3, 1, IN, EPI>(tiles, s, a);
     } else if constexpr (IN == kInNorm) {
-        if (a.K <= 768) return two ? launch_proj_t<8, 2, 2, 3, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 2, 3, IN, EPI>(tiles, s, a);
-        if (a.K <= 1024) return two ? launch_proj_t<8, 2, 2, 4, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 2, 4, IN, EPI>(tiles, s, a);
+        if constexpr (EPI == kEpiRope) {                   // fewer workgroups than compute units: twice the waves in each
+            if (a.K <= 768) return two ? launch_proj_t<8, 2, 2, 3, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 2, 3, IN, EPI>(tiles, s, a);
+            if (a.K <= 1024) return two ? launch_proj_t<8, 2, 2, 4, IN, EPI>(tiles, s, a) : launch_proj_t<8, 1, 2, 4, IN, EPI>(tiles, s, a);
+        }
+        if (a.K <= 768) return two ? launch_proj_t<4, 2, 3, 3, IN, EPI>(tiles, s, a) : launch_proj_t<4, 1, 3, 3, IN, EPI>(tiles, s, a);
+        if (a.K <= 1024) return two ? launch_proj_t<4, 2, 4, 4, IN, EPI>(tiles, s, a) : launch_proj_t<4, 1, 4, 4, IN, EPI>(tiles, s, a);
         return launch_proj_t<8, 1, 4, 8, IN, EPI>(tiles, s, a);
     } else {
         if constexpr (EPI == kEpiAdd) {
