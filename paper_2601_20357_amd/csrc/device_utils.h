@@ -304,20 +304,21 @@ __device__ __forceinline__ float tabed_uniform(uint64_t seed, uint64_t round, ui
 }
 
 // ---------------------------------------------------------------- guarded row loads
-// Four consecutive logits starting at element v (v % 4 == 0) of a row of V floats; elements past the end
-// of the row come back as -inf.  VEC needs V % 4 == 0 and a 16-byte aligned row.
-template <bool VEC>
+// Four consecutive logits starting at element v (v % 4 == 0) of a row of V floats; elements past the end of the row come
+// back as -inf.  A row only needs to be 4-byte aligned (an odd vocabulary's rows are): global loads of 16 bytes take any
+// such address, and reading odd rows element by element made a pass over them two to three times as long.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ float4 load4(const float* __restrict__ row, int v, int V) {
     const float ninf = -INFINITY;
-    if (VEC) {
-        if (v < V) return *reinterpret_cast<const float4*>(row + v);
-        return make_float4(ninf, ninf, ninf, ninf);
+    float4 r = make_float4(ninf, ninf, ninf, ninf);
+    if (v + 4 <= V) {
+        const f32x4_any q = *reinterpret_cast<const f32x4_any*>(row + v);
+        r = make_float4(q[0], q[1], q[2], q[3]);
+    } else if (v < V) {
+        r.x = row[v];
+        if (v + 1 < V) r.y = row[v + 1];
+        if (v + 2 < V) r.z = row[v + 2];
     }
-    float4 r;
-    r.x = (v + 0 < V) ? row[v + 0] : ninf;
-    r.y = (v + 1 < V) ? row[v + 1] : ninf;
-    r.z = (v + 2 < V) ? row[v + 2] : ninf;
-    r.w = (v + 3 < V) ? row[v + 3] : ninf;
     return r;
 }
 

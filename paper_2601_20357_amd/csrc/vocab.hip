@@ -217,7 +217,7 @@ struct SampleArgs {
 // loads before the first use and keeps its tile values in registers.  N = number of drafts when it is known
 // at compile time (0 = run time): then the partials are read ONCE, each thread keeping the n*TI terms
 // ps*exp(pm - m_j) of its own run of tiles in registers for both the log-sum-exp and the tile masses.
-template <bool VEC, int TI, int N>
+template <int TI, int N>
 __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (N > 0) ? N : a.n, NT = a.NT, V = a.V;
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         for (int j = 0; j < n; ++j) {                      // the four loads of a draft row go out together
             float4 x[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = load4<VEC>(rows + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+            for (int u = 0; u < 4; ++u) x[u] = load4(rows + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
             const float cj = s_cf[j], mj = s_m[j];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
@@ -574,26 +574,24 @@ static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char*
     a.cand = reinterpret_cast<Top2Rec*>(ws + L.off_cand);
     a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 0 * c.B;
     const dim3 grid(L.C2, c.B);
-    const bool vec = (c.V % 4 == 0);
     const int ti = (L.NT + kBlock - 1) / kBlock;
     // single-pass instantiations: compile-time draft counts whose n*TI terms (x3 registers) fit a 512-register wave
-    const bool ncomp_ok = vec && ti <= 20 && (c.n == 1 || c.n == 2 || c.n == 4 || (c.n == 8 && ti <= 8));
-    const int nc = ncomp_ok ? c.n : 0;
-#define TABED_LAUNCH_SAMPLE_N(TI_, N_) launch(&prof, k_sample<true, TI_, N_>, grid, dim3(kBlock), 0, s, a)
-#define TABED_LAUNCH_SAMPLE(TI_, ALLOW8_)                                                         \
-    do {                                                                                          \
-        if (!vec) launch(&prof, k_sample<false, TI_, 0>, grid, dim3(kBlock), 0, s, a);            \
-        else if (nc == 1) TABED_LAUNCH_SAMPLE_N(TI_, 1);                                          \
-        else if (nc == 2) TABED_LAUNCH_SAMPLE_N(TI_, 2);                                          \
-        else if (nc == 4) TABED_LAUNCH_SAMPLE_N(TI_, 4);                                          \
-        else if (nc == 8 && ALLOW8_) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 8 : 1));               \
-        else TABED_LAUNCH_SAMPLE_N(TI_, 0);                                                       \
+#define TABED_LAUNCH_SAMPLE_N(TI_, N_) launch(&prof, k_sample<TI_, N_>, grid, dim3(kBlock), 0, s, a)
+#define TABED_LAUNCH_SAMPLE(TI_, ALLOW8_)                                       \
+    do {                                                                        \
+        if (c.n == 1) TABED_LAUNCH_SAMPLE_N(TI_, 1);                            \
+        else if (c.n == 2) TABED_LAUNCH_SAMPLE_N(TI_, 2);                       \
+        else if (c.n == 3) TABED_LAUNCH_SAMPLE_N(TI_, 3);                       \
+        else if (c.n == 4) TABED_LAUNCH_SAMPLE_N(TI_, 4);                       \
+        else if (c.n == 5 && ALLOW8_) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 5 : 1)); \
+        else if (c.n == 8 && ALLOW8_) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 8 : 1)); \
+        else TABED_LAUNCH_SAMPLE_N(TI_, 0);                                     \
     } while (0)
     if (ti <= 1) TABED_LAUNCH_SAMPLE(1, true);
     else if (ti <= 4) TABED_LAUNCH_SAMPLE(4, true);
     else if (ti <= 8) TABED_LAUNCH_SAMPLE(8, true);
     else if (ti <= 20) TABED_LAUNCH_SAMPLE(20, false);
-    else if (ti <= 32) { if (vec) TABED_LAUNCH_SAMPLE_N(32, 0); else launch(&prof, k_sample<false, 32, 0>, grid, dim3(kBlock), 0, s, a); }
+    else if (ti <= 32) TABED_LAUNCH_SAMPLE_N(32, 0);
     else return hipErrorInvalidValue;              // V > 262144: validate_cfg rejects it before this point
 #undef TABED_LAUNCH_SAMPLE_N
 #undef TABED_LAUNCH_SAMPLE
@@ -646,7 +644,7 @@ struct StatsArgs {
     double* stats;
 };
 
-template <bool VEC, int U, int N>
+template <int U, int N>
 __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
     const int c = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma;
@@ -674,12 +672,12 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
     float4 tx[U];
     float4 dx[(N > 0) ? N : 1][U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) tx[u] = load4<VEC>(trow, cb + (u * kBlock + tid) * 4, V);
+    for (int u = 0; u < U; ++u) tx[u] = load4(trow, cb + (u * kBlock + tid) * 4, V);
     if (N > 0 && drafts) {
 #pragma unroll
         for (int j = 0; j < N; ++j)
 #pragma unroll
-            for (int u = 0; u < U; ++u) dx[j][u] = load4<VEC>(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+            for (int u = 0; u < U; ++u) dx[j][u] = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
     }
 
     float st[U * 4], ex[U * 4];
@@ -759,7 +757,7 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int v = cb + (u * kBlock + tid) * 4;
-                    const float4 y = load4<VEC>(qbase + (size_t)j * V, v, V);
+                    const float4 y = load4(qbase + (size_t)j * V, v, V);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float p = ex[u * 4 + e];
@@ -791,12 +789,11 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
 }
 
 // =====================================================================================================
-// Second-pass distances: total variation, and the two-draft grid policy's candidate mixtures.
-// |p - q| (and log of a mixture) cannot be accumulated before the target row's normaliser is known, so
+// Second-pass distances: total variation, also of the two-draft grid policy's candidate mixtures.
+// |p - q| cannot be accumulated before the target row's normaliser is known, so
 // these modes take one more pass over the rows: grid (chunk, position i < gamma, sequence b); every
 // workgroup first combines the row's records from k_stats (lse_p), then sums, over its 4096-wide chunk,
 //   MODE 0: |p - q_j|                         per draft j                (TVD, DW = n)
-//   MODE 1: p (log p - log mix_c)             per candidate c = 0..10    (KL of the mixtures, n = 2)
 //   MODE 2: |p - mix_c|                       per candidate c            (TVD of the mixtures, n = 2)
 //   MODE 3: arg-max_v q_j(v)                  per draft j                (hard labels; needs no target row)
 //   MODE 4: arg-max_v mix_c(v)                per candidate c            (hard labels, n = 2)
@@ -814,10 +811,10 @@ struct DistArgs {
     double* dist;
 };
 
-template <bool VEC, int MODE>
+template <int MODE, int N>
 __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     const int c = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int V = a.V, n = a.n, gamma = a.gamma;
+    const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma;
     constexpr int NC = TABED_GRID_CANDIDATES;
     __shared__ double s_lse;
     __shared__ float s_hi[TABED_MAX_N], s_oml[TABED_MAX_N];
@@ -837,7 +834,7 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
                 ArgMax am{-INFINITY, 0x7fffffff};
                 float4 y[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) y[u] = load4<VEC>(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+                for (int u = 0; u < 4; ++u) y[u] = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -859,8 +856,8 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
             float4 y0[4], y1[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                y0[u] = load4<VEC>(qbase, cb + (u * kBlock + tid) * 4, V);
-                y1[u] = load4<VEC>(qbase + (size_t)V, cb + (u * kBlock + tid) * 4, V);
+                y0[u] = load4(qbase, cb + (u * kBlock + tid) * 4, V);
+                y1[u] = load4(qbase + (size_t)V, cb + (u * kBlock + tid) * 4, V);
             }
             __syncthreads();
             float q0[16], q1[16];
@@ -911,13 +908,14 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     }
     float4 tx[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) tx[u] = load4<VEC>(trow, cb + (u * kBlock + tid) * 4, V);
-    float4 yq[2][4];                                   // grid modes: both draft rows, requested up front
-    if (MODE != 0) {
+    for (int u = 0; u < 4; ++u) tx[u] = load4(trow, cb + (u * kBlock + tid) * 4, V);
+    constexpr int NQ = (MODE != 0) ? 2 : N;
+    float4 yq[NQ > 0 ? NQ : 1][4];                     // the draft rows, requested up front where their number is known
+    if (NQ > 0) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NQ; ++j)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) yq[j][u] = load4<VEC>(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+            for (int u = 0; u < 4; ++u) yq[j][u] = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
     }
     const float T = a.temperature[b];
     const float invT = (T > 0.f) ? 1.f / T : 1.f;
@@ -945,7 +943,7 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     const double lse = s_lse;
     const float lhi = (float)lse, loml = (float)(1.0 - (lse - (double)lhi));
 
-    float pv[16], lp[16];                              // p and log p of this thread's 16 elements
+    float pv[16];                                      // p of this thread's 16 elements
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -954,15 +952,16 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
             const float st = xe * invT;
             const bool ok = xe > -INFINITY;
             pv[u * 4 + e] = ok ? __expf(st - lhi) * loml : 0.f;
-            lp[u * 4 + e] = ok ? (st - lhi) + (loml - 1.f) : 0.f;
         }
 
     if (MODE == 0) {
+        constexpr int kRows = N > 0 ? N : 1;
+#pragma unroll kRows
         for (int j = 0; j < n; ++j) {
             float acc = 0.f;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float4 y = load4<VEC>(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+                const float4 y = (N > 0) ? yq[N > 0 ? j : 0][u] : load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float ye = f4get(y, e);
@@ -990,12 +989,8 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
 #pragma unroll
             for (int x = 0; x < 16; ++x) {
                 const float mix = w0 * q0[x] + w1 * q1[x];
-                // bare v_log_f32 (log2): its ~1e-7 relative error is random per element and averages out under
-                // sum p (..); a mixture below the normal range only occurs where p is negligible too
-                if (MODE == 1) acc += (pv[x] > 0.f) ? pv[x] * (lp[x] * 1.44269504f - __builtin_amdgcn_logf(fmaxf(mix, 1e-37f))) : 0.f;
-                else acc += fabsf(pv[x] - mix);
+                acc += fabsf(pv[x] - mix);
             }
-            if (MODE == 1) acc *= 0.693147181f;            // back from log2 to natural log
             const double t = wave_sum((double)acc);
             if (lane == 0) s_sum[wave][k] = t;
         }
@@ -1017,16 +1012,29 @@ static int pick_stats_unroll(const tabed_cfg& c, int nmax_u) {
     return 1;
 }
 
-template <bool VEC, int N>
+template <int N>
 static void launch_stats_n(const ProfScope* prof, int U, dim3 grid, hipStream_t s, const StatsArgs& a) {
     if (U == 4) {
-        if constexpr (N <= 4) launch(prof, k_stats<VEC, 4, N>, grid, dim3(kBlock), 0, s, a);
+        if constexpr (N <= 4) launch(prof, k_stats<4, N>, grid, dim3(kBlock), 0, s, a);
     } else if (U == 2) {
-        launch(prof, k_stats<VEC, 2, N>, grid, dim3(kBlock), 0, s, a);
+        launch(prof, k_stats<2, N>, grid, dim3(kBlock), 0, s, a);
     } else {
-        launch(prof, k_stats<VEC, 1, N>, grid, dim3(kBlock), 0, s, a);
+        launch(prof, k_stats<1, N>, grid, dim3(kBlock), 0, s, a);
     }
 }
+
+// Draft counts that the passes over the vocabulary know at compile time (all rows of an element requested at once).
+static int compiled_drafts(int n) { return (n <= 5 || n == 8) ? n : 0; }
+#define TABED_FOR_DRAFTS(ncomp, CALL) \
+    switch (ncomp) {                  \
+        case 1: CALL(1); break;       \
+        case 2: CALL(2); break;       \
+        case 3: CALL(3); break;       \
+        case 4: CALL(4); break;       \
+        case 5: CALL(5); break;       \
+        case 8: CALL(8); break;       \
+        default: CALL(0); break;      \
+    }
 
 // =====================================================================================================
 // Accept chain, distances, corrected / bonus token.
@@ -1088,13 +1096,13 @@ struct ResidRow {
 // f and p for S groups of four consecutive elements starting at v[s] (v[s] % 4 == 0; a group at or past V
 // contributes zeros).  Every load is issued before the first use; N is the compile-time number of drafts
 // (0 = run time, one batch of S loads per draft).
-template <bool VEC, int N, int S>
+template <int N, int S>
 __device__ __forceinline__ void resid_eval(const ResidRow& r, int n, int V, const int (&v)[S], const float* s_hi,
                                            const float* s_lo, const float* s_w, float (&f)[S][4], float (&p)[S][4],
                                            float (&q)[S][4]) {
     float4 tx[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) tx[s] = load4<VEC>(r.trow, v[s], V);
+    for (int s = 0; s < S; ++s) tx[s] = load4(r.trow, v[s], V);
 #pragma unroll
     for (int s = 0; s < S; ++s)
 #pragma unroll
@@ -1105,7 +1113,7 @@ __device__ __forceinline__ void resid_eval(const ResidRow& r, int n, int V, cons
 #pragma unroll
             for (int j = 0; j < N; ++j)
 #pragma unroll
-                for (int s = 0; s < S; ++s) dx[j][s] = load4<VEC>(r.qrows + (size_t)j * V, v[s], V);
+                for (int s = 0; s < S; ++s) dx[j][s] = load4(r.qrows + (size_t)j * V, v[s], V);
 #pragma unroll
             for (int j = 0; j < N; ++j) {
                 const float w = s_w[j], hi = s_hi[j], lo = s_lo[j];
@@ -1121,7 +1129,7 @@ __device__ __forceinline__ void resid_eval(const ResidRow& r, int n, int V, cons
             for (int j = 0; j < n; ++j) {
                 float4 y[S];
 #pragma unroll
-                for (int s = 0; s < S; ++s) y[s] = load4<VEC>(r.qrows + (size_t)j * V, v[s], V);
+                for (int s = 0; s < S; ++s) y[s] = load4(r.qrows + (size_t)j * V, v[s], V);
                 const float w = s_w[j], hi = s_hi[j], lo = s_lo[j];
 #pragma unroll
                 for (int s = 0; s < S; ++s)
@@ -1160,7 +1168,7 @@ __device__ __forceinline__ int hard_pred(const double* rec, int Cd, bool* near) 
     return am.i;
 }
 
-template <bool VEC, int N>
+template <int N>
 __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     extern __shared__ __attribute__((aligned(16))) double s_scale[];   // [gamma+1][C3]: exp(m_c - m_row)
     const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1304,7 +1312,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     if (!greedy && !book) {
 #pragma unroll
         for (int s = 0; s < kSegPerWave; ++s) vs[s] = (c * kSegPerChunk + wave + s * kWavesPerBlock) * kSegV + lane * 4;
-        resid_eval<VEC, N, kSegPerWave>(r, n, V, vs, hi_k, lo_k, s_w, f, p, qmix);
+        resid_eval<N, kSegPerWave>(r, n, V, vs, hi_k, lo_k, s_w, f, p, qmix);
     }
 
     if (book) {
@@ -1473,7 +1481,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     if (tid >= kWave) return;
     const int v1[1] = {s_seg * kSegV + lane * 4};
     float f1[1][4], p1[1][4], q1[1][4];
-    resid_eval<VEC, N, 1>(r, n, V, v1, hi_k, lo_k, s_w, f1, p1, q1);
+    resid_eval<N, 1>(r, n, V, v1, hi_k, lo_k, s_w, f1, p1, q1);
     const int v = v1[0];
     const double l1 = (double)f1[0][0], l2 = l1 + (double)f1[0][1], l3 = l2 + (double)f1[0][2], l4 = l3 + (double)f1[0][3];
     const double base = s_prefix + (wave_inclusive_scan(l4) - l4);
@@ -1514,12 +1522,10 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
                          const float* temperature, const float* u_acc, const float* u_res, int32_t* accept_len,
                          int32_t* out_tokens, float* dev, int32_t* n_valid, uint8_t* flags, float* ring,
                          int32_t* ring_head, int32_t* ring_count, float* next_weights, bool tree, hipStream_t s) {
-    const bool vec = (c.V % 4 == 0);
-    // the KL of the two-draft grid's mixtures rides in the statistics pass (vectorised rows only)
-    const bool grid_in_stats = (c.policy == 2 && c.distance == 0 && vec);
-    const bool second_pass = (c.distance != 0 || (c.policy == 2 && !grid_in_stats));   // distances that take a pass of their own
-    const int ncomp = (vec && (c.n == 2 || c.n == 4 || c.n == 8)) ? c.n : 0;   // compile-time draft counts
-    const int U = pick_stats_unroll(c, ncomp == 8 ? 2 : 4);
+    const bool grid_in_stats = (c.policy == 2 && c.distance == 0);   // the KL of the two-draft grid's mixtures rides in the statistics pass
+    const bool second_pass = (c.distance != 0);                      // distances that take a pass of their own
+    const int ncomp = compiled_drafts(c.n);
+    const int U = pick_stats_unroll(c, ncomp > 4 ? 2 : 4);
     const int C3 = (c.V + kBlock * 4 * U - 1) / (kBlock * 4 * U);
     {
         ProfScope prof(TABED_K_STATS, s);
@@ -1530,11 +1536,9 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
         a.target = target_logits; a.dlogits = draft_logits; a.dlse = draft_lse; a.temperature = temperature;
         a.stats = reinterpret_cast<double*>(ws + L.off_stats);
         const dim3 grid(C3, c.gamma + 1, c.B);
-        if (!vec) launch_stats_n<false, 0>(&prof, U, grid, s, a);
-        else if (ncomp == 2) launch_stats_n<true, 2>(&prof, U, grid, s, a);
-        else if (ncomp == 4) launch_stats_n<true, 4>(&prof, U, grid, s, a);
-        else if (ncomp == 8) launch_stats_n<true, 8>(&prof, U, grid, s, a);
-        else launch_stats_n<true, 0>(&prof, U, grid, s, a);
+#define TABED_STATS(N_) launch_stats_n<N_>(&prof, U, grid, s, a)
+        TABED_FOR_DRAFTS(ncomp, TABED_STATS)
+#undef TABED_STATS
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (second_pass) {
@@ -1545,20 +1549,13 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
             d.stats = a.stats;
             d.dist = reinterpret_cast<double*>(ws + L.off_dist);
             const dim3 gd(L.Cd, c.gamma, c.B);
-            const int mode = (c.distance == 2) ? (c.policy != 2 ? 3 : 4) : (c.policy != 2) ? 0 : (c.distance == 0 ? 1 : 2);
-            if (vec) {
-                if (mode == 0) launch(&dprof, k_dist<true, 0>, gd, dim3(kBlock), 0, s, d);
-                else if (mode == 1) launch(&dprof, k_dist<true, 1>, gd, dim3(kBlock), 0, s, d);
-                else if (mode == 2) launch(&dprof, k_dist<true, 2>, gd, dim3(kBlock), 0, s, d);
-                else if (mode == 3) launch(&dprof, k_dist<true, 3>, gd, dim3(kBlock), 0, s, d);
-                else launch(&dprof, k_dist<true, 4>, gd, dim3(kBlock), 0, s, d);
-            } else {
-                if (mode == 0) launch(&dprof, k_dist<false, 0>, gd, dim3(kBlock), 0, s, d);
-                else if (mode == 1) launch(&dprof, k_dist<false, 1>, gd, dim3(kBlock), 0, s, d);
-                else if (mode == 2) launch(&dprof, k_dist<false, 2>, gd, dim3(kBlock), 0, s, d);
-                else if (mode == 3) launch(&dprof, k_dist<false, 3>, gd, dim3(kBlock), 0, s, d);
-                else launch(&dprof, k_dist<false, 4>, gd, dim3(kBlock), 0, s, d);
-            }
+            const int mode = (c.distance == 2) ? (c.policy != 2 ? 3 : 4) : (c.policy != 2 ? 0 : 2);
+#define TABED_DIST(N_) launch(&dprof, k_dist<0, N_>, gd, dim3(kBlock), 0, s, d)
+            if (mode == 0) { TABED_FOR_DRAFTS(ncomp, TABED_DIST) }
+            else if (mode == 2) launch(&dprof, k_dist<2, 0>, gd, dim3(kBlock), 0, s, d);
+            else if (mode == 3) launch(&dprof, k_dist<3, 0>, gd, dim3(kBlock), 0, s, d);
+            else launch(&dprof, k_dist<4, 0>, gd, dim3(kBlock), 0, s, d);
+#undef TABED_DIST
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
@@ -1583,11 +1580,9 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     a.accept_len = accept_len; a.out_tokens = out_tokens; a.dev = dev; a.n_valid = n_valid; a.flags = flags;
     const dim3 grid(L.C5 + 1, c.B);                      // + the book-keeping workgroup of every sequence
     const size_t lds = sizeof(double) * (size_t)(c.gamma + 1) * C3;
-    if (!vec) launch(&prof, k_finish<false, 0>, grid, dim3(kBlock), lds, s, a);
-    else if (ncomp == 2) launch(&prof, k_finish<true, 2>, grid, dim3(kBlock), lds, s, a);
-    else if (ncomp == 4) launch(&prof, k_finish<true, 4>, grid, dim3(kBlock), lds, s, a);
-    else if (ncomp == 8) launch(&prof, k_finish<true, 8>, grid, dim3(kBlock), lds, s, a);
-    else launch(&prof, k_finish<true, 0>, grid, dim3(kBlock), lds, s, a);
+#define TABED_FINISH(N_) launch(&prof, k_finish<N_>, grid, dim3(kBlock), lds, s, a)
+    TABED_FOR_DRAFTS(ncomp, TABED_FINISH)
+#undef TABED_FINISH
     return hipGetLastError();
 }
 
@@ -1740,7 +1735,7 @@ __device__ __forceinline__ int tree_pick_token(const float (&f)[4], int v, int V
     return __builtin_amdgcn_readlane(tok, pick);
 }
 
-template <bool VEC, int N>
+template <int N>
 __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
     const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double* ts = a.tstate + (size_t)b * kTsSlots;
@@ -1782,7 +1777,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
         int vs[kSegPerWave];
 #pragma unroll
         for (int sg = 0; sg < kSegPerWave; ++sg) vs[sg] = (c * kSegPerChunk + wave + sg * kWavesPerBlock) * kSegV + lane * 4;
-        resid_eval<VEC, N, kSegPerWave>(r, n, V, vs, s_hi, s_lo, s_w, f, p, q);
+        resid_eval<N, kSegPerWave>(r, n, V, vs, s_hi, s_lo, s_w, f, p, q);
 #pragma unroll
         for (int sg = 0; sg < kSegPerWave; ++sg) {
             const int seg = c * kSegPerChunk + wave + sg * kWavesPerBlock;
@@ -1853,7 +1848,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
     if (tid >= kWave) return;
     const int v1[1] = {s_seg * kSegV + lane * 4};
     float f1[1][4], p1[1][4], q1[1][4], fl[4];
-    resid_eval<VEC, N, 1>(r, n, V, v1, s_hi, s_lo, s_w, f1, p1, q1);
+    resid_eval<N, 1>(r, n, V, v1, s_hi, s_lo, s_w, f1, p1, q1);
 #pragma unroll
     for (int e = 0; e < 4; ++e) fl[e] = degenerate ? p1[0][e] : level(f1[0][e], q1[0][e]);
     const int tok = tree_pick_token(fl, v1[0], V, s_prefix, target, Z, &flag);
@@ -1868,7 +1863,6 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
 // greedy row).  Every wave leaves, per 256-wide segment, the maximum of the scaled logits and the sum of
 // exp(. - that maximum); the last workgroup combines them (fp64, segment order), finds the segment the uniform
 // falls into and re-evaluates it.  Greedy: per-segment (value, index) arg-max records, merged lowest index first.
-template <bool VEC>
 __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
     const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double* ts = a.tstate + (size_t)b * kTsSlots;
@@ -1893,7 +1887,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
     float4 x[kSegPerWave];
 #pragma unroll
     for (int sg = 0; sg < kSegPerWave; ++sg)
-        x[sg] = load4<VEC>(row, (c * kSegPerChunk + wave + sg * kWavesPerBlock) * kSegV + lane * 4, V);
+        x[sg] = load4(row, (c * kSegPerChunk + wave + sg * kWavesPerBlock) * kSegV + lane * 4, V);
 #pragma unroll
     for (int sg = 0; sg < kSegPerWave; ++sg) {
         const int seg = c * kSegPerChunk + wave + sg * kWavesPerBlock;
@@ -1987,7 +1981,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
     __syncthreads();
     if (tid >= kWave) return;
     const int v = s_seg * kSegV + lane * 4;
-    const float4 xx = load4<VEC>(row, v, V);
+    const float4 xx = load4(row, v, V);
     float f[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -2027,21 +2021,17 @@ hipError_t launch_verify_tree(const tabed_cfg& c, const WsLayout& L, char* ws, u
     launch(&prof, k_tree_begin, dim3(c.B), dim3(64), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || width == 1) return e;
-    const bool vec = (c.V % 4 == 0);
-    const int ncomp = (vec && (c.n == 2 || c.n == 4 || c.n == 8)) ? c.n : 0;
+    const int ncomp = compiled_drafts(c.n);
     const dim3 grid(L.C5, c.B);
     for (int lvl = 2; lvl <= width; ++lvl) {
-        if (!vec) launch(nullptr, k_tree_level<false, 0>, grid, dim3(kBlock), 0, s, a, lvl);
-        else if (ncomp == 2) launch(nullptr, k_tree_level<true, 2>, grid, dim3(kBlock), 0, s, a, lvl);
-        else if (ncomp == 4) launch(nullptr, k_tree_level<true, 4>, grid, dim3(kBlock), 0, s, a, lvl);
-        else if (ncomp == 8) launch(nullptr, k_tree_level<true, 8>, grid, dim3(kBlock), 0, s, a, lvl);
-        else launch(nullptr, k_tree_level<true, 0>, grid, dim3(kBlock), 0, s, a, lvl);
+#define TABED_LEVEL(N_) launch(nullptr, k_tree_level<N_>, grid, dim3(kBlock), 0, s, a, lvl)
+        TABED_FOR_DRAFTS(ncomp, TABED_LEVEL)
+#undef TABED_LEVEL
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 4 * c.B;
-    if (vec) launch(nullptr, k_tree_bonus<true>, grid, dim3(kBlock), 0, s, a);
-    else launch(nullptr, k_tree_bonus<false>, grid, dim3(kBlock), 0, s, a);
+    launch(nullptr, k_tree_bonus, grid, dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
 
