@@ -28,8 +28,9 @@ int validate_cfg(const tabed_cfg* c) {
     return TABED_OK;
 }
 
-WsLayout ws_layout(const tabed_cfg& c) {
+static WsLayout layout_with(const tabed_cfg& c, int ticket_stride) {
     WsLayout L;
+    L.TS = ticket_stride;
     L.M = c.n * c.B;
     L.NT = (c.V + kTileV - 1) / kTileV;
     L.C2 = (c.V + kChunkV - 1) / kChunkV;
@@ -41,7 +42,7 @@ WsLayout ws_layout(const tabed_cfg& c) {
     L.DW = (c.policy == 2) ? TABED_GRID_CANDIDATES : c.n;
     L.Cd = (c.V + kChunkV - 1) / kChunkV;
     size_t off = 0;
-    L.off_tickets = off; off = align_up(off + sizeof(uint32_t) * 5 * (size_t)c.B);
+    L.off_tickets = off; off = align_up(off + sizeof(uint32_t) * 5 * (size_t)c.B * L.TS);
     L.off_pm = off;      off = align_up(off + sizeof(float) * (size_t)L.M * L.NT);
     L.off_ps = off;      off = align_up(off + sizeof(float) * (size_t)L.M * L.NT);
     L.off_cand = off;    off = align_up(off + sizeof(Top2Rec) * (size_t)c.B * L.C2);
@@ -53,6 +54,16 @@ WsLayout ws_layout(const tabed_cfg& c) {
     L.off_tseg = off;    off = align_up(off + sizeof(double) * 2 * (size_t)c.B * L.NSEG);
     L.total = off;
     return L;
+}
+
+// Every sequence's counters have a 128-byte line of their own: atomics on one line are carried out one after the other at
+// the memory side, and 600 workgroups of 8 sequences took 4 us to arrive on one.  Where only that would lift a
+// configuration over what the built-in scratch holds, the counters stay packed.
+WsLayout ws_layout(const tabed_cfg& c) {
+    const WsLayout L = layout_with(c, 32);
+    if (L.total <= (size_t)TABED_STATIC_SCRATCH_BYTES) return L;
+    const WsLayout packed = layout_with(c, 1);
+    return packed.total <= (size_t)TABED_STATIC_SCRATCH_BYTES ? packed : L;
 }
 
 // ---------------------------------------------------------------- event timing

@@ -31,7 +31,8 @@ struct WsLayout {
     int M, NT, C2, C3max, NSEG, C5, RS;
     int DW;              // width of one distance vector: n, or 11 candidate mixtures (policy 2)
     int Cd;              // vocabulary chunks of the second-pass distance kernel
-    size_t off_tickets;  // uint32 [5][B]: arrival counters (0: greedy draft arg-max, 2: corrected/bonus sampler,
+    int TS;              // uint32 between two sequences' arrival counters
+    size_t off_tickets;  // uint32 [5][B][TS]: arrival counters (0: greedy draft arg-max, 1: staged weights, 2: corrected/bonus sampler,
                          // 3: token-tree residual level, 4: token-tree bonus after a leaf)
     size_t off_pm;       // float  [M][NT] tile maxima of scaled logits
     size_t off_ps;       // float  [M][NT] tile sums of exp(scaled logit - tile max)

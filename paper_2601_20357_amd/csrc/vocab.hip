@@ -18,7 +18,7 @@ __global__ void k_fill_u32(uint32_t* p, int count) {
 }
 
 hipError_t launch_ws_init(const tabed_cfg& c, const WsLayout& L, char* ws, hipStream_t s) {
-    const int count = 5 * c.B;
+    const int count = 5 * c.B * L.TS;
     launch(nullptr, k_fill_u32, dim3((count + 255) / 256), dim3(256), 0, s,
                        reinterpret_cast<uint32_t*>(ws + L.off_tickets), count);
     return hipGetLastError();
@@ -195,7 +195,7 @@ hipError_t launch_weights(const tabed_cfg& c, uint64_t round, const float* dev, 
 // to arrive merges the candidates (lowest index wins ties, so arrival order does not matter).
 // =====================================================================================================
 struct SampleArgs {
-    int V, n, B, gamma, pos, NT, C2;
+    int V, n, B, gamma, pos, NT, C2, TS;
     int sib, S;           // token tree: sibling index of this launch (0 = the trunk token) and siblings per position
     const int32_t* trunk; // token tree, sib > 0: trunk tokens [B,gamma] (a greedy row's siblings skip taken tokens)
     uint64_t seed, round;
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         publish_store(&rec->v2, t.v2);
     }
     publish_barrier();                                     // the candidate's stores are acknowledged
-    if (tid == 0) s_last = arrive(&a.tickets[b], (uint32_t)a.C2) ? 1 : 0;
+    if (tid == 0) s_last = arrive(&a.tickets[(size_t)b * a.TS], (uint32_t)a.C2) ? 1 : 0;
     __syncthreads();
     if (!s_last || tid >= kWave) return;
     Top2 t = top2_empty();
@@ -563,7 +563,7 @@ static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char*
                                     uint8_t* flags, int sib, int width, const int32_t* trunk, hipStream_t s) {
     ProfScope prof(TABED_K_SAMPLE, s);
     SampleArgs a;
-    a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.pos = pos; a.NT = L.NT; a.C2 = L.C2;
+    a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.pos = pos; a.NT = L.NT; a.C2 = L.C2; a.TS = L.TS;
     a.sib = sib; a.S = width - 1; a.trunk = trunk;
     a.seed = c.seed; a.round = round;
     a.logits = logits;
@@ -572,7 +572,7 @@ static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char*
     a.weights = weights; a.temperature = temperature; a.u_draft = u_draft;
     a.draft_lse = draft_lse; a.draft_tokens = draft_tokens; a.draft_q = draft_q; a.flags = flags;
     a.cand = reinterpret_cast<Top2Rec*>(ws + L.off_cand);
-    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 0 * c.B;
+    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 0 * (size_t)c.B * L.TS;
     const dim3 grid(L.C2, c.B);
     const int ti = (L.NT + kBlock - 1) / kBlock;
     // single-pass instantiations: compile-time draft counts whose n*TI terms (x3 registers) fit a 512-register wave
@@ -1049,7 +1049,7 @@ static int compiled_drafts(int n) { return (n <= 5 || n == 8) ? n : 0; }
 // target row k and needs no vocabulary pass.
 // =====================================================================================================
 struct FinishArgs {
-    int V, n, B, gamma, C3, RS, NSEG, C5;
+    int V, n, B, gamma, C3, RS, NSEG, C5, TS;
     uint64_t seed, round;
     const float* target;
     const float* dlogits;
@@ -1073,6 +1073,7 @@ struct FinishArgs {
     float* wstage;        // [B][n] next weights, staged until every workgroup of the sequence has arrived
     double* seg;          // [B][2][NSEG]
     uint32_t* tickets;
+    uint32_t* wtickets;   // [B] of the staged weights
     int32_t* accept_len;
     int32_t* out_tokens;
     float* dev;
@@ -1168,6 +1169,36 @@ __device__ __forceinline__ int hard_pred(const double* rec, int Cd, bool* near) 
     return am.i;
 }
 
+// Segment masses of one thread's run [g0, g1) of the CDF, published by other workgroups: all of them requested together.
+// A vocabulary of at most 262144 has 1024 segments, four per thread.
+constexpr int kMaxSegRun = 4;
+__device__ __forceinline__ void load_seg_run(const double* mass, int g0, int g1, double (&m)[kMaxSegRun]) {
+#pragma unroll
+    for (int q = 0; q < kMaxSegRun; ++q) m[q] = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMaxSegRun; ++q)
+        if (g0 + q < g1) m[q] = published_load(&mass[g0 + q]);
+}
+// The owner of the run that contains `target` walks it: first segment whose inclusive prefix exceeds the target, the last
+// non-empty one if rounding lets none exceed it.
+__device__ __forceinline__ void walk_seg_run(const double (&mR)[kMaxSegRun], const double (&mP)[kMaxSegRun], bool from_p, int g0,
+                                             int g1, double excl, double target, int* s_seg, double* s_prefix) {
+    double P = excl, Plast = excl;
+    int gstar = -1, glast = g0;
+#pragma unroll
+    for (int q = 0; q < kMaxSegRun; ++q) {
+        const double mg = from_p ? mP[q] : mR[q];
+        if (g0 + q < g1 && gstar < 0) {
+            if (mg > 0.0) { glast = g0 + q; Plast = P; }
+            if (P + mg > target) gstar = g0 + q;
+            else P += mg;
+        }
+    }
+    if (gstar < 0) { gstar = glast; P = Plast; }
+    *s_seg = gstar;
+    *s_prefix = P;
+}
+
 template <int N>
 __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     extern __shared__ __attribute__((aligned(16))) double s_scale[];   // [gamma+1][C3]: exp(m_c - m_row)
@@ -1185,64 +1216,94 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     __shared__ double s_wpart[64], s_wx[TABED_MAX_N];    // fused window update (one wave)
     __shared__ int s_y[TABED_MAX_GAMMA];                 // drafted tokens (hard labels)
 
-    // ---- everything that does not depend on another load is requested first
+    // ---- everything that does not depend on another load is requested first; the target's logit at a drafted token, which
+    //      does, goes out as soon as the token is here, while the chunk records are on their way
+    const float T = a.temperature[b];
+    const bool greedy = !(T > 0.f);
+    const bool book = (c == a.C5);                        // the book-keeping workgroup of this sequence
+    if (greedy && !book) return;
     int y = -1;
     float rawy = 0.f, uacc = 0.f, qy = 0.f;
     if (tid < gamma) {
         y = a.dtok[(size_t)b * gamma + tid];
-        uacc = a.u_acc ? a.u_acc[(size_t)b * gamma + tid] : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)tid, 1);
+        if (a.u_acc) uacc = a.u_acc[(size_t)b * gamma + tid];
         qy = a.dq[(size_t)b * gamma + tid];
+    }
+    double lse0 = 0.0;
+    if (tid < gamma * n) lse0 = a.dlse[((size_t)(tid / n) * a.B + b) * n + (tid % n)];
+    float w0 = 0.f;
+    if (tid < n) w0 = a.weights[(size_t)b * n + tid];
+
+    // ---- the chunk records of every target row.  A row's C3 chunks sit in an aligned group of
+    //      C3p lanes (C3p = power of two >= C3), so one wave combines 64 / C3p rows per pass, and the records of kPasses
+    //      passes are requested together; rows with more than 64 chunks fall back to one wave per row.
+    const double* sb = a.stats + (size_t)b * (gamma + 1) * C3 * RS;
+    constexpr int kPasses = 2;
+    int C3p = 1;
+    while (C3p < C3) C3p <<= 1;
+    const int rows_per_pass = (C3 <= kWave) ? kWave / C3p : 0, cc = lane & (C3p - 1);
+    double r0v[kPasses], r1v[kPasses];
+    ArgMax ram[kPasses];
+    auto request_records = [&](int row0) {
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const int row = row0 + p * kWavesPerBlock * rows_per_pass + lane / C3p;
+            r0v[p] = -INFINITY; r1v[p] = 0.0;
+            ram[p] = ArgMax{-INFINITY, 0x7fffffff};
+            if (row <= gamma && cc < C3) {
+                const double* r = sb + ((size_t)row * C3 + cc) * RS;
+                r0v[p] = r[0]; r1v[p] = r[1];
+                ram[p] = ArgMax{(float)r[2], (int)r[3]};
+            }
+        }
+    };
+    if (C3 <= kWave) request_records(wave * rows_per_pass);
+    const bool y_ok = (y >= 0 && y < V);
+    if (tid < gamma) {
+        if (y_ok && !greedy) rawy = a.target[((size_t)b * (gamma + 1) + tid) * V + y];
         s_y[tid] = y;
+        if (!a.u_acc) uacc = tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)tid, 1);
     }
     for (int q = tid; q < gamma * n; q += kBlock) {      // draft log-sum-exps of every position, split hi + lo
-        const double l = a.dlse[((size_t)(q / n) * a.B + b) * n + (q % n)];
+        const double l = (q == tid) ? lse0 : a.dlse[((size_t)(q / n) * a.B + b) * n + (q % n)];
         const float hi = (float)l;
         s_hi[q / n][q % n] = hi;
         s_lo[q / n][q % n] = (float)(1.0 - (l - (double)hi));      // 1 - lo, the first-order factor of exp(-lo)
     }
-    if (tid < n) s_w[tid] = a.weights[(size_t)b * n + tid];
-    const float T = a.temperature[b];
+    if (tid < n) s_w[tid] = w0;
 
-    // ---- combine the chunk records of every target row.  A row's C3 chunks sit in an aligned group of
-    //      C3p lanes (C3p = power of two >= C3), so one wave combines 64 / C3p rows per pass with one
-    //      load round trip; rows with more than 64 chunks fall back to one wave per row.
-    const double* sb = a.stats + (size_t)b * (gamma + 1) * C3 * RS;
+    // ---- combine them (fp64, chunk order)
     if (C3 <= kWave) {
-        int C3p = 1;
-        while (C3p < C3) C3p <<= 1;
-        const int rows_per_pass = kWave / C3p;
-        const int cc = lane & (C3p - 1);
-        for (int row0 = wave * rows_per_pass; row0 <= gamma; row0 += kWavesPerBlock * rows_per_pass) {
-            const int row = row0 + lane / C3p;
-            const bool live = (row <= gamma && cc < C3);
-            double r0v = -INFINITY, r1v = 0.0;
-            ArgMax am{-INFINITY, 0x7fffffff};
-            if (live) {
-                const double* r = sb + ((size_t)row * C3 + cc) * RS;
-                r0v = r[0]; r1v = r[1];
-                am = ArgMax{(float)r[2], (int)r[3]};
+        for (int row0 = wave * rows_per_pass; row0 <= gamma; row0 += kPasses * kWavesPerBlock * rows_per_pass) {
+            if (row0 != wave * rows_per_pass) request_records(row0);
+#pragma unroll
+            for (int p = 0; p < kPasses; ++p) {
+                const int row = row0 + p * kWavesPerBlock * rows_per_pass + lane / C3p;
+                const bool live = (row <= gamma && cc < C3);
+                if (row0 + p * kWavesPerBlock * rows_per_pass > gamma) break;          // uniform over the wave
+                ArgMax am = ram[p];
+                // all-reduce inside aligned groups of C3p lanes: DPP for the first four doublings (no LDS traffic),
+                // ds_bpermute only beyond a 16-lane row
+                double m = r0v[p];
+                if (C3p > 1) m = fmax(m, dpp_f64<kDppXor1>(m));
+                if (C3p > 2) m = fmax(m, dpp_f64<kDppXor2>(m));
+                if (C3p > 4) m = fmax(m, dpp_f64<kDppHalfMirror>(m));
+                if (C3p > 8) m = fmax(m, dpp_f64<kDppMirror>(m));
+                for (int o = 16; o < C3p; o <<= 1) m = fmax(m, __shfl_xor(m, o));
+                const double sc = (r0v[p] > -INFINITY) ? exp(r0v[p] - m) : 0.0;
+                if (live) s_scale[row * C3 + cc] = sc;
+                double Z = r1v[p] * sc;
+                if (C3p > 1) { Z += dpp_f64<kDppXor1>(Z); am = argmax_dpp_step<kDppXor1>(am); }
+                if (C3p > 2) { Z += dpp_f64<kDppXor2>(Z); am = argmax_dpp_step<kDppXor2>(am); }
+                if (C3p > 4) { Z += dpp_f64<kDppHalfMirror>(Z); am = argmax_dpp_step<kDppHalfMirror>(am); }
+                if (C3p > 8) { Z += dpp_f64<kDppMirror>(Z); am = argmax_dpp_step<kDppMirror>(am); }
+                for (int o = 16; o < C3p; o <<= 1) {
+                    Z += __shfl_xor(Z, o);
+                    const ArgMax other{__shfl_xor(am.v, o), __shfl_xor(am.i, o)};
+                    am = argmax_merge(am, other);
+                }
+                if (live && cc == 0) { s_rowm[row] = m; s_rowZ[row] = Z; s_rowlse[row] = m + log(Z); s_rowam[row] = am.i; }
             }
-            // all-reduce inside aligned groups of C3p lanes: DPP for the first four doublings (no LDS traffic),
-            // ds_bpermute only beyond a 16-lane row
-            double m = r0v;
-            if (C3p > 1) m = fmax(m, dpp_f64<kDppXor1>(m));
-            if (C3p > 2) m = fmax(m, dpp_f64<kDppXor2>(m));
-            if (C3p > 4) m = fmax(m, dpp_f64<kDppHalfMirror>(m));
-            if (C3p > 8) m = fmax(m, dpp_f64<kDppMirror>(m));
-            for (int o = 16; o < C3p; o <<= 1) m = fmax(m, __shfl_xor(m, o));
-            const double sc = (r0v > -INFINITY) ? exp(r0v - m) : 0.0;
-            if (live) s_scale[row * C3 + cc] = sc;
-            double Z = r1v * sc;
-            if (C3p > 1) { Z += dpp_f64<kDppXor1>(Z); am = argmax_dpp_step<kDppXor1>(am); }
-            if (C3p > 2) { Z += dpp_f64<kDppXor2>(Z); am = argmax_dpp_step<kDppXor2>(am); }
-            if (C3p > 4) { Z += dpp_f64<kDppHalfMirror>(Z); am = argmax_dpp_step<kDppHalfMirror>(am); }
-            if (C3p > 8) { Z += dpp_f64<kDppMirror>(Z); am = argmax_dpp_step<kDppMirror>(am); }
-            for (int o = 16; o < C3p; o <<= 1) {
-                Z += __shfl_xor(Z, o);
-                const ArgMax other{__shfl_xor(am.v, o), __shfl_xor(am.i, o)};
-                am = argmax_merge(am, other);
-            }
-            if (live && cc == 0) { s_rowm[row] = m; s_rowZ[row] = Z; s_rowlse[row] = m + log(Z); s_rowam[row] = am.i; }
         }
     } else {
         for (int row = wave; row <= gamma; row += kWavesPerBlock) {
@@ -1265,12 +1326,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
             if (lane == 0) { s_rowm[row] = m; s_rowZ[row] = Z; s_rowlse[row] = m + log(Z); s_rowam[row] = am.i; }
         }
     }
-    const bool greedy = !(T > 0.f);
-    const bool book = (c == a.C5);                        // the book-keeping workgroup of this sequence
-    if (greedy && !book) return;
     const float invT = greedy ? 1.f : 1.f / T;
-    const bool y_ok = (y >= 0 && y < V);
-    if (tid < gamma && y_ok && !greedy) rawy = a.target[((size_t)b * (gamma + 1) + tid) * V + y];
     __syncthreads();
 
     // ---- gamma accept tests in parallel, k = first failure
@@ -1319,23 +1375,48 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
         if (a.dist == nullptr) {
             // ---- distances: thread per (position, draft or candidate mixture), chunks in order with the scales
             //      computed above.  KL(p || q_j) = A_j / Z - lse_p + lse_j; a mixture's sums already hold its logarithm.
-            const int dw = a.grid_kl ? a.DW : n;
-            for (int q = tid; q < gamma * dw; q += kBlock) {
-                const int ii = q / dw, j = q % dw;
+            //      Eight lanes share an entry's chunks and request up to eight of them each at once (one thread per entry
+            //      made this workgroup, which the window waits for, the last of its sequence: 11 us of a 20 us launch
+            //      with 38 chunks).
+            const int dw = a.grid_kl ? a.DW : n, l8 = tid & 7;
+            for (int q0 = 0; q0 < gamma * dw; q0 += kBlock / 8) {
+                const int q = q0 + (tid >> 3), qc = min(q, gamma * dw - 1), ii = qc / dw, j = qc % dw;
                 const double* r0 = sb + (size_t)ii * C3 * RS + kStatHdr + j;
+                const double lq = a.grid_kl ? 0.0 : a.dlse[((size_t)ii * a.B + b) * n + j];
                 double A = 0.0;
-#pragma unroll 8
-                for (int cc = 0; cc < C3; ++cc) A += r0[(size_t)cc * RS] * s_scale[ii * C3 + cc];
-                const double kl = A / s_rowZ[ii] - s_rowlse[ii] + (a.grid_kl ? 0.0 : a.dlse[((size_t)ii * a.B + b) * n + j]);
-                publish_store(&a.dev[((size_t)b * gamma + ii) * dw + j], (float)kl);
+                for (int c0 = l8; c0 < C3; c0 += 64) {
+                    double v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = r0[(size_t)min(c0 + 8 * u, C3 - 1) * RS];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (c0 + 8 * u < C3) A += v[u] * s_scale[ii * C3 + c0 + 8 * u];
+                }
+                A += dpp_f64<kDppXor1>(A);
+                A += dpp_f64<kDppXor2>(A);
+                A += dpp_f64<kDppHalfMirror>(A);
+                const double kl = A / s_rowZ[ii] - s_rowlse[ii] + lq;
+                if (l8 == 0 && q < gamma * dw) publish_store(&a.dev[(size_t)b * gamma * dw + q], (float)kl);
             }
         } else if (!a.hard) {
             // ---- distances from the second pass: add the chunk sums in chunk order
-            for (int q = tid; q < gamma * a.DW; q += kBlock) {
-                const double* r0 = a.dist + ((size_t)b * gamma * a.DW + q) * a.Cd * 2;
+            const int l8 = tid & 7;                        // eight lanes an entry, as above
+            for (int q0 = 0; q0 < gamma * a.DW; q0 += kBlock / 8) {
+                const int q = q0 + (tid >> 3);
+                const double* r0 = a.dist + ((size_t)b * gamma * a.DW + min(q, gamma * a.DW - 1)) * a.Cd * 2;
                 double D = 0.0;
-                for (int cc = 0; cc < a.Cd; ++cc) D += r0[cc * 2];
-                publish_store(&a.dev[(size_t)b * gamma * a.DW + q], (float)((double)a.dist_scale * D));
+                for (int c0 = l8; c0 < a.Cd; c0 += 64) {
+                    double v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = r0[min(c0 + 8 * u, a.Cd - 1) * 2];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (c0 + 8 * u < a.Cd) D += v[u];
+                }
+                D += dpp_f64<kDppXor1>(D);
+                D += dpp_f64<kDppXor2>(D);
+                D += dpp_f64<kDppHalfMirror>(D);
+                if (l8 == 0 && q < gamma * a.DW) publish_store(&a.dev[(size_t)b * gamma * a.DW + q], (float)((double)a.dist_scale * D));
             }
         } else {
             // ---- hard labels: 1 where a candidate's arg-max differs from the token emitted at the position.
@@ -1386,15 +1467,23 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     double* segR = a.seg + ((size_t)b * 2 + 0) * NSEG;
     double* segP = a.seg + ((size_t)b * 2 + 1) * NSEG;
     if (book) {
-        // window + next weights, off the critical path of the sampler.  The weights are staged: the buffer
-        // they go to may be the one the siblings are still reading this block's weights from.
-        if (a.fuse && !a.hard) {
+        // window + next weights, beside the sampler, which does not wait for them.  The weights are staged: the buffer
+        // they go to may be the one the siblings are still reading this block's weights from.  Whoever comes second of
+        // this workgroup and the sampler's last one, which knows that all siblings have read them, copies them out.
+        // (With hard labels the window waits for the corrected token: there this workgroup is one of the siblings.)
+        if (!a.hard) {
+            if (!a.fuse) return;
             publish_barrier();                             // the distances above are acknowledged
-            if (tid < kWave) {
-                WindowArgs wa = a.win;
-                wa.weights = a.wstage;
-                window_update<true>(wa, b, lane, a.dev, nv_k, s_wpart, s_wx);
-            }
+            if (tid >= kWave) return;
+            WindowArgs wa = a.win;
+            wa.weights = a.wstage;
+            window_update<true>(wa, b, lane, a.dev, nv_k, s_wpart, s_wx);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's staged weights are acknowledged
+            int second = 0;
+            if (lane == 0) second = arrive(&a.wtickets[(size_t)b * a.TS], 2u) ? 1 : 0;
+            if (__builtin_amdgcn_readfirstlane(second) && lane < n)
+                a.win.weights[(size_t)b * n + lane] = published_load(&a.wstage[(size_t)b * n + lane]);
+            return;
         }
     } else {
 #pragma unroll
@@ -1406,10 +1495,16 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
         }
     }
     publish_barrier();                                     // every wave's published stores are acknowledged
-    if (tid == 0) s_last = arrive(&a.tickets[b], (uint32_t)(a.C5 + 1)) ? 1 : 0;
+    if (tid == 0) s_last = arrive(&a.tickets[(size_t)b * a.TS], (uint32_t)(a.C5 + (a.hard ? 1 : 0))) ? 1 : 0;
+    const float u_final = a.u_res ? a.u_res[b] : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)gamma, 0);
     __syncthreads();
     if (!s_last) return;
-    if (a.fuse && !a.hard && tid < n) a.win.weights[(size_t)b * n + tid] = published_load(&a.wstage[(size_t)b * n + tid]);
+    if (a.fuse && !a.hard && wave == kWavesPerBlock - 1) {  // every sibling has read this block's weights
+        int second = 0;
+        if (lane == 0) second = arrive(&a.wtickets[(size_t)b * a.TS], 2u) ? 1 : 0;
+        if (__builtin_amdgcn_readfirstlane(second) && lane < n)
+            a.win.weights[(size_t)b * n + lane] = published_load(&a.wstage[(size_t)b * n + lane]);
+    }
     // hard labels: the rejected position's distances and the window update wait for the corrected token
     // returns the flag bit of a near-tie among the mixtures' arg-maxes at position k
     auto finish_hard = [&](int tok) -> uint32_t {          // wave 0 only
@@ -1430,19 +1525,23 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     };
 
     // ---- last workgroup of sequence b: locate the segment, then the token
-    const int S = (NSEG + kBlock - 1) / kBlock;
+    const int S = (NSEG + kBlock - 1) / kBlock;            // at most kMaxSegRun consecutive segments per thread
     const int g0 = min(NSEG, tid * S), g1 = min(NSEG, g0 + S);
     uint32_t flag = s_aflag[k];
+    double mR[kMaxSegRun], mP[kMaxSegRun];                 // requested together, kept for the walk below
+    load_seg_run(segR, g0, g1, mR);
+    load_seg_run(segP, g0, g1, mP);
     double runR = 0.0, runP = 0.0;
-    for (int g = g0; g < g1; ++g) { runR += published_load(&segR[g]); runP += published_load(&segP[g]); }
-    double run = runP;
-    const double* mass = segP;
-    double Z1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMaxSegRun; ++q) { runR += mR[q]; runP += mP[q]; }
+    double run = runP, Z = 0.0, excl = 0.0, Z1 = 0.0;
+    bool from_p = true;
     if (!r.bonus) {
-        const double Zr = block_sum(runR, s_redd);
-        if (Zr > 0.0) { run = runR; mass = segR; Z1 = Zr; }
+        excl = block_exclusive_scan(runR, s_redd, &Z);
+        if (Z > 0.0) { run = runR; from_p = false; Z1 = Z; }
         else { r.bonus = true; flag |= TABED_FLAG_DEGENERATE; }   // empty residual: draw from p_k
     }
+    if (from_p) excl = block_exclusive_scan(runP, s_redd, &Z);
     if (a.tstate != nullptr && tid == 0) {                 // token tree: the first residual level is known here
         double* ts = a.tstate + (size_t)b * kTsSlots;
         ts[kTsK] = (double)k;
@@ -1451,10 +1550,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
         ts[kTsZ1] = Z1;                                    // 0: all gamma accepted, or an empty residual
         ts[kTsArgmax] = (double)s_rowam[k];
     }
-    double Z;
-    const double excl = block_exclusive_scan(run, s_redd, &Z);
-    const float u = a.u_res ? a.u_res[b] : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)gamma, 0);
-    const double target = (double)u * Z;
+    const double target = (double)u_final * Z;
     const int owner = block_find_owner(excl, run, target, s_first, s_lastw);
     if (owner < 0) {
         if (tid == 0) {
@@ -1464,19 +1560,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
         if (a.hard && tid < kWave) finish_hard(0);
         return;
     }
-    if (tid == owner) {
-        double P = excl, Plast = excl;
-        int gstar = -1, glast = g0;
-        for (int g = g0; g < g1; ++g) {
-            const double mg = published_load(&mass[g]);
-            if (mg > 0.0) { glast = g; Plast = P; }
-            if (P + mg > target) { gstar = g; break; }
-            P += mg;
-        }
-        if (gstar < 0) { gstar = glast; P = Plast; }
-        s_seg = gstar;
-        s_prefix = P;
-    }
+    if (tid == owner) walk_seg_run(mR, mP, from_p, g0, g1, excl, target, &s_seg, &s_prefix);
     __syncthreads();
     if (tid >= kWave) return;
     const int v1[1] = {s_seg * kSegV + lane * 4};
@@ -1562,7 +1646,7 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     }
     ProfScope prof(TABED_K_RESID, s);
     FinishArgs a;
-    a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.C3 = C3; a.RS = L.RS; a.NSEG = L.NSEG; a.C5 = L.C5;
+    a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.C3 = C3; a.RS = L.RS; a.NSEG = L.NSEG; a.C5 = L.C5; a.TS = L.TS;
     a.seed = c.seed; a.round = round;
     a.target = target_logits; a.dlogits = draft_logits; a.dlse = draft_lse; a.dtok = draft_tokens; a.dq = draft_q;
     a.weights = weights; a.temperature = temperature; a.u_acc = u_acc; a.u_res = u_res;
@@ -1576,7 +1660,8 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     a.wstage = reinterpret_cast<float*>(ws + L.off_wstage);
     a.tstate = tree ? reinterpret_cast<double*>(ws + L.off_tstate) : nullptr;
     a.seg = reinterpret_cast<double*>(ws + L.off_seg);
-    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 2 * c.B;
+    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 2 * (size_t)c.B * L.TS;
+    a.wtickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 1 * (size_t)c.B * L.TS;
     a.accept_len = accept_len; a.out_tokens = out_tokens; a.dev = dev; a.n_valid = n_valid; a.flags = flags;
     const dim3 grid(L.C5 + 1, c.B);                      // + the book-keeping workgroup of every sequence
     const size_t lds = sizeof(double) * (size_t)(c.gamma + 1) * C3;
@@ -1600,7 +1685,7 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
 // token, k_tree_bonus draws the token after an accepted leaf.  Sequences whose walk is over skip every pass.
 // =====================================================================================================
 struct TreeArgs {
-    int V, n, B, gamma, S, NSEG, C5;       // S = width - 1 siblings per position
+    int V, n, B, gamma, S, NSEG, C5, TS;   // S = width - 1 siblings per position
     uint64_t seed, round;
     const float* target;                   // [B,gamma+1,V]
     const float* leaf_logits;              // [B,gamma,S,V]
@@ -1789,7 +1874,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
         }
     }
     publish_barrier();
-    if (tid == 0) s_last = arrive(&a.tickets[b], (uint32_t)a.C5) ? 1 : 0;
+    if (tid == 0) s_last = arrive(&a.tickets[(size_t)b * a.TS], (uint32_t)a.C5) ? 1 : 0;
     __syncthreads();
     if (!s_last) return;
 
@@ -1915,7 +2000,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
         }
     }
     publish_barrier();
-    if (tid == 0) s_last = arrive(&a.tickets[b], (uint32_t)a.C5) ? 1 : 0;
+    if (tid == 0) s_last = arrive(&a.tickets[(size_t)b * a.TS], (uint32_t)a.C5) ? 1 : 0;
     __syncthreads();
     if (!s_last) return;
 
@@ -2007,7 +2092,7 @@ hipError_t launch_verify_tree(const tabed_cfg& c, const WsLayout& L, char* ws, u
                               int32_t* n_out, hipStream_t s) {
     ProfScope prof(TABED_K_TREE, s);
     TreeArgs a;
-    a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.S = width - 1; a.NSEG = L.NSEG; a.C5 = L.C5;
+    a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.S = width - 1; a.NSEG = L.NSEG; a.C5 = L.C5; a.TS = L.TS;
     a.seed = c.seed; a.round = round;
     a.target = target_logits; a.leaf_logits = leaf_logits; a.dlogits = draft_logits; a.dlse = draft_lse;
     a.sib_tokens = sib_tokens; a.sib_q = sib_q; a.weights = weights; a.temperature = temperature;
@@ -2016,7 +2101,7 @@ hipError_t launch_verify_tree(const tabed_cfg& c, const WsLayout& L, char* ws, u
     a.segP = reinterpret_cast<const double*>(ws + L.off_seg);
     a.tseg = reinterpret_cast<double*>(ws + L.off_tseg);
     a.out_tokens = out_tokens; a.flags = flags; a.leaf = leaf; a.n_out = n_out;
-    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 3 * c.B;
+    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 3 * (size_t)c.B * L.TS;
     // sibling 1 against the first residual (its mass is known from tabed_verify's pass); width 1: leaf = 0, n_out = k + 1
     launch(&prof, k_tree_begin, dim3(c.B), dim3(64), 0, s, a);
     hipError_t e = hipGetLastError();
@@ -2030,7 +2115,7 @@ hipError_t launch_verify_tree(const tabed_cfg& c, const WsLayout& L, char* ws, u
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 4 * c.B;
+    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 4 * (size_t)c.B * L.TS;
     launch(nullptr, k_tree_bonus, grid, dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
