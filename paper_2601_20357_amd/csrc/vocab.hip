@@ -4,6 +4,8 @@
 // DPP lane exchanges and a few LDS words do the reductions, fp64 carries the cross-wave and cross-workgroup
 // sums, and partial results cross workgroups through device-scope atomic stores that are waited for before an
 // arrival counter moves (no cache-flushing fences).
+#include <type_traits>
+
 #include "device_utils.h"
 #include "internal.h"
 
@@ -236,7 +238,12 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     __shared__ double s_term[TABED_MAX_N][kTileV];
     __shared__ float s_wm[kWavesPerBlock][TABED_MAX_N];
     __shared__ double s_wsum[kWavesPerBlock][TABED_MAX_N];
-    __shared__ double s_wtot[kWavesPerBlock][5];        // wave totals of the tile-mass scan, per chunk row
+    __shared__ double s_wtot[kWavesPerBlock][8];        // wave totals of the tile-mass scan, per chunk row
+    constexpr int kMaxTiles = kBlock * TI, kMaxListed = 64;                // greedy rows: tiles that may hold the arg-max
+    __shared__ uint32_t s_live[(kMaxTiles + 31) / 32];
+    __shared__ int s_list[kMaxListed], s_count;
+    __shared__ ArgMax s_wtop[kWavesPerBlock];
+    __shared__ float s_reach;
 
     const float* pmb = a.pm + (size_t)b * n * NT;      // partials of this sequence: [n][NT]
     const float* psb = a.ps + (size_t)b * n * NT;
@@ -256,41 +263,48 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
             if (t < a.sib) taken[t] = a.draft_tokens[((size_t)b * a.gamma + a.pos) * a.S + (t - 1)];
     }
 
-    // Which tiles a thread owns.  Two-pass kernels and TI = 1: the contiguous run [tid*TI, tid*TI + TI).
-    // Single-pass kernels: TI/4 chunks of 4 consecutive tiles, chunk q*256 + tid for q < TI/4 (for TI = 4 that
-    // is the same run) -- every load is then 16 bytes and a wave's load is one contiguous kilobyte.
-    constexpr bool CHUNKED = (N > 0 && TI >= 4);
+    // Which tiles a thread owns.  TI = 1: tile tid.  Else TI/4 chunks of 4 consecutive tiles, chunk q*256 + tid for
+    // q < TI/4 -- every load is then 16 bytes and a wave's load is one contiguous kilobyte.  (A run of TI = 20 tiles per
+    // thread read element by element looked up 40 lines an instruction: 65 us at V = 128256 with 8 drafts, 64 sequences.)
+    constexpr bool CHUNKED = (TI >= 4);
     constexpr int TPC = CHUNKED ? 4 : TI;              // tiles per chunk
     constexpr int Q = TI / TPC;                        // chunks per thread
     auto tile_of = [&](int i) { return CHUNKED ? ((i / 4) * kBlock + tid) * 4 + (i & 3) : tid * TI + i; };
 
+    // this thread's tiles of one draft's partials: maxima and, with WITH_SUMS, sums
+    auto load_tiles = [&](int j, float (&m)[TI], float (&sum)[TI], auto with_sums) {
+        const float* pr = pmb + (size_t)j * NT;
+        const float* sr = psb + (size_t)j * NT;
+        if (CHUNKED && (NT & 3) == 0) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int t = tile_of(4 * q);
+                float4 m4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY), s4 = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (t < NT) {
+                    m4 = *reinterpret_cast<const float4*>(pr + t);
+                    if (with_sums.value) s4 = *reinterpret_cast<const float4*>(sr + t);
+                }
+                m[4 * q] = m4.x; m[4 * q + 1] = m4.y; m[4 * q + 2] = m4.z; m[4 * q + 3] = m4.w;
+                if (with_sums.value) { sum[4 * q] = s4.x; sum[4 * q + 1] = s4.y; sum[4 * q + 2] = s4.z; sum[4 * q + 3] = s4.w; }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+                const int t = tile_of(i);
+                m[i] = t < NT ? pr[t] : -INFINITY;
+                if (with_sums.value) sum[i] = t < NT ? sr[t] : 0.f;
+            }
+        }
+    };
     float uu[(N > 0) ? N : 1][TI];                     // single pass: terms of this thread's tiles, all drafts
+    float pmv[(N > 0) ? N : 1][TI];                    // and their maxima
     double lse_mine = 0.0;
     if (N > 0) {
         // ---- single pass over the partials of every draft
-        float pmv[(N > 0) ? N : 1][TI], psv[(N > 0) ? N : 1][TI];
+        float psv[(N > 0) ? N : 1][TI];
 #pragma unroll
         for (int j = 0; j < N; ++j) {
-            if (CHUNKED && (NT & 3) == 0) {
-#pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    const int t = tile_of(4 * q);
-                    float4 m4 = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY), s4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (t < NT) {
-                        m4 = *reinterpret_cast<const float4*>(pmb + (size_t)j * NT + t);
-                        s4 = *reinterpret_cast<const float4*>(psb + (size_t)j * NT + t);
-                    }
-                    pmv[j][4 * q] = m4.x; pmv[j][4 * q + 1] = m4.y; pmv[j][4 * q + 2] = m4.z; pmv[j][4 * q + 3] = m4.w;
-                    psv[j][4 * q] = s4.x; psv[j][4 * q + 1] = s4.y; psv[j][4 * q + 2] = s4.z; psv[j][4 * q + 3] = s4.w;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int t = tile_of(i);
-                    pmv[j][i] = t < NT ? pmb[(size_t)j * NT + t] : -INFINITY;
-                    psv[j][i] = t < NT ? psb[(size_t)j * NT + t] : 0.f;
-                }
-            }
+            load_tiles(j, pmv[j], psv[j], std::true_type{});
         }
 #pragma unroll
         for (int j = 0; j < N; ++j) {
@@ -380,15 +394,10 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
                 for (int i = 0; i < TI; ++i) mt[i] += cj * (double)uu[j][i];
             }
         } else {
-#pragma unroll 4
+#pragma unroll 2
             for (int j = 0; j < n; ++j) {
                 float pmv[TI], psv[TI];
-#pragma unroll
-                for (int i = 0; i < TI; ++i) {
-                    const int t = tile_of(i);
-                    pmv[i] = t < NT ? pmb[(size_t)j * NT + t] : -INFINITY;
-                    psv[i] = t < NT ? psb[(size_t)j * NT + t] : 0.f;
-                }
+                load_tiles(j, pmv, psv, std::true_type{});
                 const double cj = s_c[j];
                 const float mj = s_m[j];
                 Z += cj * s_S[j];
@@ -491,42 +500,133 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         return;
     }
 
-    // ---- greedy row: arg-max (with runner-up) of the mixture over this workgroup's chunk
-    // (at most kMaxGreedyChunks workgroups per row: every one of them repeats the log-sum-exp pass over the
-    // row's partials, so a large vocabulary is walked in several 4096-wide strides per workgroup instead)
-    Top2 best = top2_empty();
-    for (int cb = c * kChunkV; cb < V; cb += a.C2 * kChunkV) {
-        float q[4][4];
+    // ---- greedy row: arg-max (with runner-up) of the mixture.  A tile's partials bound the mixture inside it,
+    //      q(v) <= sum_j (w_j / S_j) exp(pm_jt - m_j); the tile with the largest bound is evaluated first, and only tiles whose
+    //      bound reaches its maximum (less a margin far above the rounding of either side and the 1e-6 of the near-tie
+    //      flag) can hold the arg-max or a runner-up that matters.  With language-model logits these are a handful: one
+    //      workgroup evaluates them, its siblings leave.  If there are more (flat distributions) the row's workgroups
+    //      (at most kMaxGreedyChunks: every one of them repeats the pass over the row's partials) share the walk over the
+    //      vocabulary and read the surviving tiles only.
+    float ub[TI];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+    for (int i = 0; i < TI; ++i) ub[i] = 0.f;
+    if (N > 0) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) q[u][e] = 0.f;
-        for (int j = 0; j < n; ++j) {                      // the four loads of a draft row go out together
-            float4 x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = load4(rows + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+        for (int j = 0; j < N; ++j) {
             const float cj = s_cf[j], mj = s_m[j];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) q[u][e] += cj * __expf(f4get(x[u], e) * invT - mj);
+            for (int i = 0; i < TI; ++i) ub[i] += cj * __expf(pmv[j][i] - mj);
         }
+    } else {
+#pragma unroll 2
+        for (int j = 0; j < n; ++j) {
+            const float cj = s_cf[j], mj = s_m[j];
+            float pj[TI];
+            load_tiles(j, pj, pj, std::false_type{});
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int v = cb + (u * kBlock + tid) * 4;
+            for (int i = 0; i < TI; ++i) ub[i] += cj * __expf(pj[i] - mj);
+        }
+    }
+    ArgMax top{-INFINITY, 0x7fffffff};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                bool free_tok = (v + e < V);
+    for (int i = 0; i < TI; ++i)
+        if (tile_of(i) < NT) top = argmax_merge(top, ArgMax{ub[i], tile_of(i)});
+    top = wave_argmax(top);
+    if (lane == 0) s_wtop[wave] = top;
+    for (int i = tid; i < (kMaxTiles + 31) / 32; i += kBlock) s_live[i] = 0u;
+    if (tid == 0) s_count = 0;
+    __syncthreads();
+    const int t0 = argmax_merge(argmax_merge(s_wtop[0], s_wtop[1]), argmax_merge(s_wtop[2], s_wtop[3])).i;
+    // the mixture at one vocabulary entry, drafts in order, and whether it may be drawn
+    auto mixture = [&](int v) {
+        float q = 0.f;
+        if (N > 0) {
+            float x[(N > 0) ? N : 1];
 #pragma unroll
-                for (int t = 0; t < TABED_MAX_TREE_WIDTH - 1; ++t) free_tok = free_tok && (v + e != taken[t]);
-                if (free_tok) best = top2_push(best, q[u][e], v + e);
+            for (int j = 0; j < N; ++j) x[j] = rows[(size_t)j * V + v];
+#pragma unroll
+            for (int j = 0; j < N; ++j) q += s_cf[j] * __expf(x[j] * invT - s_m[j]);
+        } else {
+#pragma unroll 8
+            for (int j = 0; j < n; ++j) q += s_cf[j] * __expf(rows[(size_t)j * V + v] * invT - s_m[j]);
+        }
+        return q;
+    };
+    auto may_draw = [&](int v) {
+        bool ok = (v < V);
+#pragma unroll
+        for (int t = 0; t < TABED_MAX_TREE_WIDTH - 1; ++t) ok = ok && (v != taken[t]);
+        return ok;
+    };
+    if (wave == 0) {
+        const int v = t0 * kTileV + (lane & 31);
+        const float q = (t0 < NT && may_draw(v)) ? mixture(v) : -INFINITY;
+        const float reach = wave_max(q);
+        if (lane == 0) s_reach = (reach > 0.f) ? reach * (1.f - 3e-5f) : -INFINITY;
+    }
+    __syncthreads();
+    const float reach = s_reach;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        const int t = tile_of(i);
+        if (t < NT && !(ub[i] < reach)) {
+            atomicOr(&s_live[t >> 5], 1u << (t & 31));
+            const int at = atomicAdd(&s_count, 1);
+            if (at < kMaxListed) s_list[at] = t;
+        }
+    }
+    __syncthreads();
+    const int listed = s_count;
+    Top2 best = top2_empty();
+    const bool few = (listed <= kMaxListed);              // the same in every workgroup of the row
+    if (few) {
+        if (c != 0) return;
+        for (int at = tid >> 5; at < listed; at += kBlock / kTileV) {
+            const int v = s_list[at] * kTileV + (tid & 31);
+            if (may_draw(v)) best = top2_push(best, mixture(v), v);
+        }
+    } else {
+        for (int cb = c * kChunkV; cb < V; cb += a.C2 * kChunkV) {
+            float q[4][4];
+            bool live[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int t = min(cb + (u * kBlock + tid) * 4, V - 1) / kTileV;
+                live[u] = (s_live[t >> 5] >> (t & 31)) & 1u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) q[u][e] = 0.f;
+            }
+            constexpr int JB = 4;                          // draft rows requested together
+            for (int j0 = 0; j0 < n; j0 += JB) {
+                float4 x[JB][4];
+#pragma unroll
+                for (int jj = 0; jj < JB; ++jj)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (j0 + jj < n && live[u]) x[jj][u] = load4(rows + (size_t)(j0 + jj) * V, cb + (u * kBlock + tid) * 4, V);
+#pragma unroll
+                for (int jj = 0; jj < JB; ++jj)
+                    if (j0 + jj < n) {
+                        const float cj = s_cf[j0 + jj], mj = s_m[j0 + jj];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) q[u][e] += cj * __expf(f4get(x[jj][u], e) * invT - mj);
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int v = cb + (u * kBlock + tid) * 4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (live[u] && may_draw(v + e)) best = top2_push(best, q[u][e], v + e);
             }
         }
     }
     best = wave_top2(best);
     if (lane == 0) s_top[wave] = best;
     __syncthreads();
-    if (tid == 0) {
+    if (!few && tid == 0) {
         Top2 t = s_top[0];
         for (int w = 1; w < kWavesPerBlock; ++w) t = top2_merge(t, s_top[w]);
         Top2Rec* rec = &a.cand[(size_t)b * a.C2 + c];
@@ -534,19 +634,25 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         publish_store(&rec->i1, t.i1);
         publish_store(&rec->v2, t.v2);
     }
-    publish_barrier();                                     // the candidate's stores are acknowledged
-    if (tid == 0) s_last = arrive(&a.tickets[(size_t)b * a.TS], (uint32_t)a.C2) ? 1 : 0;
-    __syncthreads();
-    if (!s_last || tid >= kWave) return;
     Top2 t = top2_empty();
-    for (int cc = lane; cc < a.C2; cc += kWave) {
-        const Top2Rec* r = &a.cand[(size_t)b * a.C2 + cc];
-        t = top2_merge(t, Top2{published_load(&r->v1), published_load(&r->i1), published_load(&r->v2)});
+    if (few) {
+        if (tid >= kWave) return;
+        if (lane < kWavesPerBlock) t = s_top[lane];
+    } else {
+        publish_barrier();                                 // the candidate's stores are acknowledged
+        if (tid == 0) s_last = arrive(&a.tickets[(size_t)b * a.TS], (uint32_t)a.C2) ? 1 : 0;
+        __syncthreads();
+        if (!s_last || tid >= kWave) return;
+        for (int cc = lane; cc < a.C2; cc += kWave) {
+            const Top2Rec* r = &a.cand[(size_t)b * a.C2 + cc];
+            t = top2_merge(t, Top2{published_load(&r->v1), published_load(&r->i1), published_load(&r->v2)});
+        }
     }
     t = wave_top2(t);
     if (lane != 0) return;
     const int y = (t.i1 >= 0 && t.i1 < V) ? t.i1 : 0;
     double f = 0.0;
+#pragma unroll 8
     for (int j = 0; j < n; ++j) f += s_c[j] * (double)__expf(rows[(size_t)j * V + y] * invT - s_m[j]);
     uint32_t flag = 0;
     if (V > 1 + a.sib && (t.v1 - t.v2) < kMargin * fabsf(t.v1)) flag |= TABED_FLAG_SAMPLE_MARGIN;

@@ -15,3 +15,33 @@ def test_rounds_on_unaligned_rows(oracle, V, n, policy, distance):
     wl = synth.scaled(synth.WORKLOADS["serving"], V=V, d=64, n=n, B=5, gamma=3, h=4, cfg_id=160 + V % 9)
     tally = harness.run_rounds(oracle, wl, 4, synth.make_temperature(wl, "mixed07"), policy=policy, distance=distance)
     assert tally.flagged_divergences <= max(2, tally.decisions // 50)
+
+
+@pytest.mark.parametrize("V,n", [(33, 1), (1003, 3), (8200, 8), (33000, 4), (70004, 4), (128256, 8), (200003, 2), (40001, 6)])
+@pytest.mark.parametrize("scale", [8.0, 0.2, 0.0], ids=["peaked", "flat", "ties"])
+def test_greedy_draft_token(V, n, scale):
+    """Arg-max of the mixture whether a few tiles of the vocabulary can hold it (peaked), many (flat) or all (ties)."""
+    import torch
+    from paper_2601_20357_amd import binding
+    print(f"greedy V={V} n={n} scale={scale}", flush=True)
+    B, d = 3, 64
+    g = torch.Generator(device="cuda:0").manual_seed(V + n)
+    cfg = binding.make_cfg(V=V, d=d, n=n, B=B, gamma=1, h=1, w_dtype=1)
+    buf = binding.RoundBuffers(cfg)
+    buf.weights.copy_(torch.softmax(torch.randn((B, n), generator=g, device="cuda:0"), -1))
+    W = (torch.randn((V, d), generator=g, device="cuda:0") * 0.15).bfloat16()
+    H = (torch.randn((B, n, d), generator=g, device="cuda:0") * scale).bfloat16()
+    buf.draft_step(0, 0, W, H, torch.zeros(B, device="cuda:0"))
+    torch.cuda.synchronize()
+    q = (torch.softmax(buf.draft_logits[0].double(), -1) * buf.weights.double()[:, :, None]).sum(1)      # [B,V]
+    top, at = q.topk(2, -1)
+    near = (top[:, 0] - top[:, 1]) < 1e-6 * top[:, 0]
+    y = buf.draft_tokens[:, 0].long()
+    assert bool(((y == at[:, 0]) | near).all())
+    # a probability is off by at most the fp32 exponentials' and sums' few units in the last place
+    assert bool(((buf.draft_q[:, 0].double() - q.gather(1, y[:, None])[:, 0]).abs() <= 1e-5 * top[:, 0]).all())
+    flagged = (buf.draft_flags[:, 0] & binding.FLAG_SAMPLE_MARGIN) != 0
+    assert bool((flagged | ~((top[:, 0] - top[:, 1]) < 5e-7 * top[:, 0])).all())     # a clear near-tie is flagged,
+    assert bool((~flagged | ((top[:, 0] - top[:, 1]) < 2e-6 * top[:, 0])).all())     # a clear winner is not
+    if scale == 0.0:
+        assert bool((y == 0).all())
