@@ -222,38 +222,41 @@ __device__ __forceinline__ bool arrive(uint32_t* counter, uint32_t expected) {
     return true;
 }
 
-// ---------------------------------------------------------------- arg-max with runner-up
-struct Top2 {
+// ---------------------------------------------------------------- the three largest
+struct Top3 {
     float v1;  // maximum
     int i1;    // its lowest index
-    float v2;  // largest value among all other elements
+    float v2;  // second largest
+    int i2;    // its lowest index
+    float v3;  // largest value among all other elements
 };
-__device__ __forceinline__ Top2 top2_empty() { return Top2{-INFINITY, 0x7fffffff, -INFINITY}; }
-__device__ __forceinline__ Top2 top2_merge(const Top2& a, const Top2& b) {
-    const bool b_wins = (b.v1 > a.v1) || (b.v1 == a.v1 && b.i1 < a.i1);
-    Top2 r;
-    if (b_wins) { r.v1 = b.v1; r.i1 = b.i1; r.v2 = fmaxf(a.v1, b.v2); }
-    else        { r.v1 = a.v1; r.i1 = a.i1; r.v2 = fmaxf(a.v2, b.v1); }
-    return r;
+__device__ __forceinline__ Top3 top3_empty() { return Top3{-INFINITY, 0x7fffffff, -INFINITY, 0x7fffffff, -INFINITY}; }
+__device__ __forceinline__ bool ranks_before(float va, int ia, float vb, int ib) { return va > vb || (va == vb && ia < ib); }
+// NB: merging a candidate with a copy of itself must not happen (it would count an element as its own runner-up); the DPP
+// steps below always pair disjoint lane groups.
+__device__ __forceinline__ Top3 top3_merge(const Top3& a, const Top3& b) {
+    const bool swap = ranks_before(b.v1, b.i1, a.v1, a.i1);
+    const Top3 x = swap ? b : a, y = swap ? a : b;        // x holds the maximum
+    const bool y_second = ranks_before(y.v1, y.i1, x.v2, x.i2);
+    return y_second ? Top3{x.v1, x.i1, y.v1, y.i1, fmaxf(x.v2, y.v2)} : Top3{x.v1, x.i1, x.v2, x.i2, fmaxf(x.v3, y.v1)};
 }
-__device__ __forceinline__ Top2 top2_push(const Top2& a, float x, int idx) {
-    return top2_merge(a, Top2{x, idx, -INFINITY});
+__device__ __forceinline__ Top3 top3_push(const Top3& a, float x, int idx) {
+    return top3_merge(a, Top3{x, idx, -INFINITY, 0x7fffffff, -INFINITY});
 }
 template <int CTRL>
-__device__ __forceinline__ Top2 top2_dpp_step(const Top2& t) {
-    return top2_merge(t, Top2{dpp_f32<CTRL>(t.v1), dpp_i32<CTRL>(t.i1), dpp_f32<CTRL>(t.v2)});
+__device__ __forceinline__ Top3 top3_dpp_step(const Top3& t) {
+    return top3_merge(t, Top3{dpp_f32<CTRL>(t.v1), dpp_i32<CTRL>(t.i1), dpp_f32<CTRL>(t.v2), dpp_i32<CTRL>(t.i2), dpp_f32<CTRL>(t.v3)});
 }
-__device__ __forceinline__ Top2 top2_at(const Top2& t, int lane) {
-    return Top2{lane_f32(t.v1, lane), __builtin_amdgcn_readlane(t.i1, lane), lane_f32(t.v2, lane)};
+__device__ __forceinline__ Top3 top3_at(const Top3& t, int lane) {
+    return Top3{lane_f32(t.v1, lane), __builtin_amdgcn_readlane(t.i1, lane), lane_f32(t.v2, lane), __builtin_amdgcn_readlane(t.i2, lane),
+                lane_f32(t.v3, lane)};
 }
-// NB: merging a candidate with a copy of itself must not happen (it would count the maximum as its own
-// runner-up); the DPP steps below always pair disjoint lane groups.
-__device__ __forceinline__ Top2 wave_top2(Top2 t) {
-    t = top2_dpp_step<kDppXor1>(t);
-    t = top2_dpp_step<kDppXor2>(t);
-    t = top2_dpp_step<kDppHalfMirror>(t);
-    t = top2_dpp_step<kDppMirror>(t);
-    return top2_merge(top2_merge(top2_at(t, 0), top2_at(t, 16)), top2_merge(top2_at(t, 32), top2_at(t, 48)));
+__device__ __forceinline__ Top3 wave_top3(Top3 t) {
+    t = top3_dpp_step<kDppXor1>(t);
+    t = top3_dpp_step<kDppXor2>(t);
+    t = top3_dpp_step<kDppHalfMirror>(t);
+    t = top3_dpp_step<kDppMirror>(t);
+    return top3_merge(top3_merge(top3_at(t, 0), top3_at(t, 16)), top3_merge(top3_at(t, 32), top3_at(t, 48)));
 }
 
 // Plain (value, lowest index) arg-max.

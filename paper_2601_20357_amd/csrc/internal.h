@@ -26,6 +26,15 @@ struct Top2Rec {                // chunk candidate of the greedy draft arg-max
     int pad;
 };
 
+struct Top3Rec {                // the same of a token tree's siblings
+    float v1;
+    int i1;
+    float v2;
+    int i2;
+    float v3;
+    int pad;
+};
+
 // Where everything lives inside the caller's workspace (byte offsets, 256-byte aligned).
 struct WsLayout {
     int M, NT, C2, C3max, NSEG, C5, RS;

@@ -198,8 +198,8 @@ hipError_t launch_weights(const tabed_cfg& c, uint64_t round, const float* dev, 
 // =====================================================================================================
 struct SampleArgs {
     int V, n, B, gamma, pos, NT, C2, TS;
-    int sib, S;           // token tree: sibling index of this launch (0 = the trunk token) and siblings per position
-    const int32_t* trunk; // token tree, sib > 0: trunk tokens [B,gamma] (a greedy row's siblings skip taken tokens)
+    int S;                // token tree: siblings per position; 0: this launch draws the trunk token
+    const int32_t* trunk; // token tree: trunk tokens [B,gamma] (a greedy row's siblings skip the trunk's token)
     uint64_t seed, round;
     const float* logits;  // [B,n,V] of this position
     const float* pm;      // [B*n,NT]
@@ -211,8 +211,9 @@ struct SampleArgs {
     int32_t* draft_tokens;
     float* draft_q;
     uint8_t* flags;
-    Top2Rec* cand;
-    uint32_t* tickets;
+    Top2Rec* cand;        // [B][C2] trunk token
+    Top3Rec* cand3;       // [S][B][C2] siblings
+    uint32_t* tickets;    // siblings: S counters of a sequence, B * TS apart
 };
 
 // TI = tiles per thread, a compile-time bound with NT <= kBlock * TI, so that every phase issues all of its
@@ -223,6 +224,7 @@ template <int TI, int N>
 __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (N > 0) ? N : a.n, NT = a.NT, V = a.V;
+    const int sib = a.S > 0 ? (int)blockIdx.z + 1 : 0;     // 0: the trunk token; siblings of a position in one launch
     // Workgroup 0 of a sequence always has work, so its temperature load overlaps the loads below; the
     // other workgroups only exist for greedy rows and leave at once otherwise.
     const float T = a.temperature[b];
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     __shared__ float s_cf[TABED_MAX_N];
     __shared__ int s_first[kWavesPerBlock], s_lastw[kWavesPerBlock], s_tile, s_last;
     __shared__ double s_prefix;
-    __shared__ Top2 s_top[kWavesPerBlock];
+    __shared__ Top3 s_top[kWavesPerBlock];
     __shared__ double s_term[TABED_MAX_N][kTileV];
     __shared__ float s_wm[kWavesPerBlock][TABED_MAX_N];
     __shared__ double s_wsum[kWavesPerBlock][TABED_MAX_N];
@@ -248,20 +250,13 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     const float* pmb = a.pm + (size_t)b * n * NT;      // partials of this sequence: [n][NT]
     const float* psb = a.ps + (size_t)b * n * NT;
     // the trunk token goes to [B,gamma]; sibling s of a token tree to [B,gamma,S] and has a Philox block of its own
-    const size_t out_idx = (a.sib == 0) ? (size_t)b * a.gamma + a.pos
-                                        : ((size_t)b * a.gamma + a.pos) * a.S + (a.sib - 1);
+    const size_t out_idx = (sib == 0) ? (size_t)b * a.gamma + a.pos
+                                      : ((size_t)b * a.gamma + a.pos) * a.S + (sib - 1);
     const float wj = (tid < n) ? a.weights[(size_t)b * n + tid] : 0.f;
     const float u = a.u_draft ? a.u_draft[out_idx]
-                              : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)a.pos + (uint32_t)a.sib * kSiblingStride, 0);
-    int taken[TABED_MAX_TREE_WIDTH - 1];               // greedy siblings: tokens already in the candidate list
-#pragma unroll
-    for (int t = 0; t < TABED_MAX_TREE_WIDTH - 1; ++t) taken[t] = -1;
-    if (a.sib > 0) {
-        taken[0] = a.trunk[(size_t)b * a.gamma + a.pos];
-#pragma unroll
-        for (int t = 1; t < TABED_MAX_TREE_WIDTH - 1; ++t)
-            if (t < a.sib) taken[t] = a.draft_tokens[((size_t)b * a.gamma + a.pos) * a.S + (t - 1)];
-    }
+                              : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)a.pos + (uint32_t)sib * kSiblingStride, 0);
+    // greedy siblings: the largest entries other than the trunk's token; sibling s takes the s-th of them
+    const int taken = (sib > 0) ? a.trunk[(size_t)b * a.gamma + a.pos] : -1, rank = (sib > 0) ? sib - 1 : 0;
 
     // Which tiles a thread owns.  TI = 1: tile tid.  Else TI/4 chunks of 4 consecutive tiles, chunk q*256 + tid for
     // q < TI/4 -- every load is then 16 bytes and a wave's load is one contiguous kilobyte.  (A run of TI = 20 tiles per
@@ -360,7 +355,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
             if (lane == 0) {
                 s_m[j] = M;
                 s_S[j] = S;
-                if (c == 0 && a.sib == 0) a.draft_lse[((size_t)a.pos * a.B + b) * n + j] = (double)M + log(S);
+                if (c == 0 && sib == 0) a.draft_lse[((size_t)a.pos * a.B + b) * n + j] = (double)M + log(S);
             }
         }
     }
@@ -368,7 +363,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     const float invT = greedy ? 1.f : 1.f / T;
     __syncthreads();
     if (N > 0) {
-        if (tid < N && c == 0 && a.sib == 0) a.draft_lse[((size_t)a.pos * a.B + b) * n + tid] = lse_mine;
+        if (tid < N && c == 0 && sib == 0) a.draft_lse[((size_t)a.pos * a.B + b) * n + tid] = lse_mine;
     } else {
         if (tid < n) {
             s_c[tid] = (double)wj / s_S[tid];
@@ -552,16 +547,14 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         }
         return q;
     };
-    auto may_draw = [&](int v) {
-        bool ok = (v < V);
-#pragma unroll
-        for (int t = 0; t < TABED_MAX_TREE_WIDTH - 1; ++t) ok = ok && (v != taken[t]);
-        return ok;
-    };
+    auto may_draw = [&](int v) { return v < V && v != taken; };
     if (wave == 0) {
         const int v = t0 * kTileV + (lane & 31);
-        const float q = (t0 < NT && may_draw(v)) ? mixture(v) : -INFINITY;
-        const float reach = wave_max(q);
+        const float q = (lane < kTileV && t0 < NT && may_draw(v)) ? mixture(v) : -INFINITY;
+        Top3 t = top3_empty();
+        if (q > -INFINITY) t = Top3{q, v, -INFINITY, 0x7fffffff, -INFINITY};
+        t = wave_top3(t);
+        const float reach = (rank == 0) ? t.v1 : t.v2;     // at least rank + 1 entries reach this
         if (lane == 0) s_reach = (reach > 0.f) ? reach * (1.f - 3e-5f) : -INFINITY;
     }
     __syncthreads();
@@ -577,13 +570,13 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     }
     __syncthreads();
     const int listed = s_count;
-    Top2 best = top2_empty();
+    Top3 best = top3_empty();
     const bool few = (listed <= kMaxListed);              // the same in every workgroup of the row
     if (few) {
         if (c != 0) return;
         for (int at = tid >> 5; at < listed; at += kBlock / kTileV) {
             const int v = s_list[at] * kTileV + (tid & 31);
-            if (may_draw(v)) best = top2_push(best, mixture(v), v);
+            if (may_draw(v)) best = top3_push(best, mixture(v), v);
         }
     } else {
         for (int cb = c * kChunkV; cb < V; cb += a.C2 * kChunkV) {
@@ -619,58 +612,75 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
                 const int v = cb + (u * kBlock + tid) * 4;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (live[u] && may_draw(v + e)) best = top2_push(best, q[u][e], v + e);
+                    if (live[u] && may_draw(v + e)) best = top3_push(best, q[u][e], v + e);
             }
         }
     }
-    best = wave_top2(best);
+    best = wave_top3(best);
     if (lane == 0) s_top[wave] = best;
     __syncthreads();
     if (!few && tid == 0) {
-        Top2 t = s_top[0];
-        for (int w = 1; w < kWavesPerBlock; ++w) t = top2_merge(t, s_top[w]);
-        Top2Rec* rec = &a.cand[(size_t)b * a.C2 + c];
-        publish_store(&rec->v1, t.v1);
-        publish_store(&rec->i1, t.i1);
-        publish_store(&rec->v2, t.v2);
+        Top3 t = s_top[0];
+        for (int w = 1; w < kWavesPerBlock; ++w) t = top3_merge(t, s_top[w]);
+        if (sib == 0) {
+            Top2Rec* rec = &a.cand[(size_t)b * a.C2 + c];
+            publish_store(&rec->v1, t.v1);
+            publish_store(&rec->i1, t.i1);
+            publish_store(&rec->v2, t.v2);
+        } else {
+            Top3Rec* rec = &a.cand3[((size_t)rank * a.B + b) * a.C2 + c];
+            publish_store(&rec->v1, t.v1);
+            publish_store(&rec->i1, t.i1);
+            publish_store(&rec->v2, t.v2);
+            publish_store(&rec->i2, t.i2);
+            publish_store(&rec->v3, t.v3);
+        }
     }
-    Top2 t = top2_empty();
+    Top3 t = top3_empty();
     if (few) {
         if (tid >= kWave) return;
         if (lane < kWavesPerBlock) t = s_top[lane];
     } else {
         publish_barrier();                                 // the candidate's stores are acknowledged
-        if (tid == 0) s_last = arrive(&a.tickets[(size_t)b * a.TS], (uint32_t)a.C2) ? 1 : 0;
+        if (tid == 0) s_last = arrive(&a.tickets[((size_t)rank * a.B + b) * a.TS], (uint32_t)a.C2) ? 1 : 0;
         __syncthreads();
         if (!s_last || tid >= kWave) return;
         for (int cc = lane; cc < a.C2; cc += kWave) {
-            const Top2Rec* r = &a.cand[(size_t)b * a.C2 + cc];
-            t = top2_merge(t, Top2{published_load(&r->v1), published_load(&r->i1), published_load(&r->v2)});
+            if (sib == 0) {
+                const Top2Rec* r = &a.cand[(size_t)b * a.C2 + cc];
+                t = top3_merge(t, Top3{published_load(&r->v1), published_load(&r->i1), published_load(&r->v2), 0x7ffffffe, -INFINITY});
+            } else {
+                const Top3Rec* r = &a.cand3[((size_t)rank * a.B + b) * a.C2 + cc];
+                t = top3_merge(t, Top3{published_load(&r->v1), published_load(&r->i1), published_load(&r->v2), published_load(&r->i2),
+                                       published_load(&r->v3)});
+            }
         }
     }
-    t = wave_top2(t);
+    t = wave_top3(t);
     if (lane != 0) return;
-    const int y = (t.i1 >= 0 && t.i1 < V) ? t.i1 : 0;
+    const float won = (rank == 0) ? t.v1 : t.v2, next = (rank == 0) ? t.v2 : t.v3;
+    const int at = (rank == 0) ? t.i1 : t.i2;
+    const int y = (at >= 0 && at < V) ? at : 0;
     double f = 0.0;
 #pragma unroll 8
     for (int j = 0; j < n; ++j) f += s_c[j] * (double)__expf(rows[(size_t)j * V + y] * invT - s_m[j]);
     uint32_t flag = 0;
-    if (V > 1 + a.sib && (t.v1 - t.v2) < kMargin * fabsf(t.v1)) flag |= TABED_FLAG_SAMPLE_MARGIN;
+    if (V > 1 + sib && (won - next) < kMargin * fabsf(won)) flag |= TABED_FLAG_SAMPLE_MARGIN;
     a.draft_tokens[out_idx] = y;
     a.draft_q[out_idx] = (float)f;
     a.flags[out_idx] = (uint8_t)flag;
 }
 
-// sib = 0: the trunk token of Alg. 1 (Sample step).  sib >= 1 (token tree of `width`): sibling `sib` of the position, from
-// the same softmax partials; the output arrays are then the [B,gamma,width-1] sibling arrays.
+// S = 0: the trunk token of Alg. 1 (Sample step).  S >= 1 (token tree): the S siblings of the position in one launch, from
+// the same softmax partials; the output arrays are then the [B,gamma,S] sibling arrays.
 static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char* ws, uint64_t round, int pos,
                                     const float* logits, const float* weights, const float* temperature,
                                     const float* u_draft, double* draft_lse, int32_t* draft_tokens, float* draft_q,
-                                    uint8_t* flags, int sib, int width, const int32_t* trunk, hipStream_t s) {
+                                    uint8_t* flags, int S, const int32_t* trunk, hipStream_t s) {
     ProfScope prof(TABED_K_SAMPLE, s);
     SampleArgs a;
     a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.pos = pos; a.NT = L.NT; a.C2 = L.C2; a.TS = L.TS;
-    a.sib = sib; a.S = width - 1; a.trunk = trunk;
+    a.S = S; a.trunk = trunk;
     a.seed = c.seed; a.round = round;
     a.logits = logits;
     a.pm = reinterpret_cast<const float*>(ws + L.off_pm);
@@ -678,8 +688,10 @@ static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char*
     a.weights = weights; a.temperature = temperature; a.u_draft = u_draft;
     a.draft_lse = draft_lse; a.draft_tokens = draft_tokens; a.draft_q = draft_q; a.flags = flags;
     a.cand = reinterpret_cast<Top2Rec*>(ws + L.off_cand);
-    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 0 * (size_t)c.B * L.TS;
-    const dim3 grid(L.C2, c.B);
+    // siblings: the counters and the room of the tree passes, which run after them (3 C2 <= NSEG wherever a row is shared)
+    a.cand3 = reinterpret_cast<Top3Rec*>(ws + L.off_tseg);
+    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + (S > 0 ? 3 : 0) * (size_t)c.B * L.TS;
+    const dim3 grid(L.C2, c.B, S > 0 ? S : 1);
     const int ti = (L.NT + kBlock - 1) / kBlock;
     // single-pass instantiations: compile-time draft counts whose n*TI terms (x3 registers) fit a 512-register wave
 #define TABED_LAUNCH_SAMPLE_N(TI_, N_) launch(&prof, k_sample<TI_, N_>, grid, dim3(kBlock), 0, s, a)
@@ -709,21 +721,18 @@ hipError_t launch_sample(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
                          const float* u_draft, double* draft_lse, int32_t* draft_tokens, float* draft_q,
                          uint8_t* flags, hipStream_t s) {
     return launch_sample_any(c, L, ws, round, pos, logits, weights, temperature, u_draft, draft_lse, draft_tokens,
-                             draft_q, flags, 0, 1, nullptr, s);
+                             draft_q, flags, 0, nullptr, s);
 }
 
-// Token tree: the width-1 siblings of position pos, one sampler launch each (a greedy row's sibling s needs
-// siblings 1..s-1 to skip them).  Uses the softmax partials the LM head of this position left in the workspace.
+// Token tree: the width-1 siblings of position pos.  Uses the softmax partials the LM head of this position left in the
+// workspace.  One launch for all of them (one each took 5.7 us a sibling).
 hipError_t launch_siblings(const tabed_cfg& c, const WsLayout& L, char* ws, uint64_t round, int pos, int width,
                            const float* logits, const int32_t* draft_tokens, const float* weights,
                            const float* temperature, const float* u_sib, int32_t* sib_tokens, float* sib_q,
                            uint8_t* sib_flags, hipStream_t s) {
-    for (int sib = 1; sib < width; ++sib) {
-        const hipError_t e = launch_sample_any(c, L, ws, round, pos, logits, weights, temperature, u_sib, nullptr,
-                                               sib_tokens, sib_q, sib_flags, sib, width, draft_tokens, s);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    static_assert(TABED_MAX_TREE_WIDTH == 3, "greedy siblings are the two largest entries besides the trunk's");
+    return launch_sample_any(c, L, ws, round, pos, logits, weights, temperature, u_sib, nullptr, sib_tokens, sib_q, sib_flags,
+                             width - 1, draft_tokens, s);
 }
 
 // =====================================================================================================

@@ -45,3 +45,35 @@ def test_greedy_draft_token(V, n, scale):
     assert bool((~flagged | ((top[:, 0] - top[:, 1]) < 2e-6 * top[:, 0])).all())     # a clear winner is not
     if scale == 0.0:
         assert bool((y == 0).all())
+
+
+@pytest.mark.parametrize("V,n", [(3, 2), (40, 1), (2050, 3), (33000, 4), (128256, 8), (200003, 2)])
+@pytest.mark.parametrize("scale", [8.0, 0.2, 0.0], ids=["peaked", "flat", "ties"])
+def test_greedy_siblings(V, n, scale):
+    """Both siblings of a greedy row: the two largest entries besides the trunk's token, lowest index on ties."""
+    import torch
+    from paper_2601_20357_amd import binding
+    print(f"siblings V={V} n={n} scale={scale}", flush=True)
+    B, d = 3, 64
+    g = torch.Generator(device="cuda:0").manual_seed(V + n)
+    cfg = binding.make_cfg(V=V, d=d, n=n, B=B, gamma=1, h=1, w_dtype=1)
+    buf = binding.RoundBuffers(cfg)
+    buf.enable_tree(3)
+    buf.weights.fill_(1.0 / n)
+    W = (torch.randn((V, d), generator=g, device="cuda:0") * 0.15).bfloat16()
+    H = (torch.randn((B, n, d), generator=g, device="cuda:0") * scale).bfloat16()
+    temp = torch.zeros(B, device="cuda:0")
+    sib = buf.prepare_draft_siblings(0, 0, temp)
+    for _ in range(2):                                    # the second pass finds the counters re-armed
+        buf.draft_step(0, 0, W, H, temp)
+        sib()
+        torch.cuda.synchronize()
+        q = (torch.softmax(buf.draft_logits[0].double(), -1) * buf.weights.double()[:, :, None]).sum(1)
+        order = torch.sort(q, stable=True, dim=-1, descending=True)
+        got = torch.cat([buf.draft_tokens, buf.sib_tokens[:, 0]], 1).long()
+        if scale == 0.0:
+            assert bool((got == torch.arange(3, device="cuda:0")).all())
+        gap = (order.values[:, :3] - torch.nn.functional.pad(order.values, (0, 1))[:, 1:4]).abs() < 1e-6 * order.values[:, :3]
+        clear = ~(gap.any(-1))
+        assert bool((got[clear] == order.indices[clear, :3]).all())
+        assert bool(((buf.sib_q[:, 0].double() - q.gather(1, got[:, 1:])).abs() <= 1e-5 * order.values[:, :1]).all())
