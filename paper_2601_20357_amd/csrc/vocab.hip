@@ -986,7 +986,7 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
                 }
             for (int k = 0; k < NC; ++k) {
                 const float w1 = (float)k / (float)(NC - 1), w0 = 1.f - w1;
-                // the mixture is evaluated in fp32 here and in fp64 by a checker: the runner-up travels with the
+                // the mixture is evaluated in fp32 here, a 64-bit evaluation can differ: the runner-up travels with the
                 // arg-max so that a near-tie can be flagged where the label is known
                 ArgMax am{-INFINITY, 0x7fffffff};
                 float sec = -INFINITY;
