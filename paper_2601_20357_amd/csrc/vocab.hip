@@ -895,9 +895,11 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
         rec[3] = (double)t.i;
     }
     if (grid) {
-        if (tid < TABED_GRID_CANDIDATES)
-            rec[kStatHdr + tid] = ((s_A[0][tid] + s_A[1][tid]) + (s_A[2][tid] + s_A[3][tid])) +
-                                  (double)mc * ((s_redd[0] + s_redd[1]) + (s_redd[2] + s_redd[3]));
+        if (tid < TABED_GRID_CANDIDATES) {
+            const double Zc = (s_redd[0] + s_redd[1]) + (s_redd[2] + s_redd[3]);
+            // a chunk whose target logits are all -inf (masked) has no term in the sum: m_c Z_c would be -inf * 0 there
+            rec[kStatHdr + tid] = ((s_A[0][tid] + s_A[1][tid]) + (s_A[2][tid] + s_A[3][tid])) + (Zc != 0.0 ? (double)mc * Zc : 0.0);
+        }
     } else if (drafts && tid < n) {
         rec[kStatHdr + tid] = (s_A[0][tid] + s_A[1][tid]) + (s_A[2][tid] + s_A[3][tid]);
     }

@@ -77,3 +77,49 @@ def test_greedy_siblings(V, n, scale):
         clear = ~(gap.any(-1))
         assert bool((got[clear] == order.indices[clear, :3]).all())
         assert bool(((buf.sib_q[:, 0].double() - q.gather(1, got[:, 1:])).abs() <= 1e-5 * order.values[:, :1]).all())
+
+
+@pytest.mark.parametrize("V", [8200, 8201])
+@pytest.mark.parametrize("policy,distance", [(2, 0), (2, 1), (2, 2), (0, 0), (0, 1), (0, 2)])
+def test_verify_with_masked_target_logits(oracle, V, policy, distance):
+    """Target rows with long runs of -inf (constrained decoding): whole chunks of the passes without a term, at the end, at the
+    start, on both sides of one allowed run; a term with p = 0 counts nothing."""
+    import numpy as np
+    import torch
+    print(f"masked target V={V} policy={policy} distance={distance}", flush=True)
+    n, B, gamma, h = (2 if policy == 2 else 3), 6, 2, 3
+    wl = synth.scaled(synth.WORKLOADS["serving"], V=V, d=64, n=n, B=B, gamma=gamma, h=h, cfg_id=170 + V % 2)
+    side = harness.GpuSide(wl, seed=4, policy=policy, distance=distance)
+    buf = side.buf
+    W = synth.make_lm_head(wl)
+    H, target = synth.make_round(wl, W, 1)
+    target = np.array(target, np.float32)
+    for b, (lo, hi) in enumerate([(0, 1500), (5000, V), (3000, 3600), (V - 2, V), (0, V), (1024, 2048)]):     # allowed entries
+        target[b, :, :lo] = -np.inf
+        target[b, :, hi:] = -np.inf
+    temp = np.array([1.0, 0.7, 1.0, 0.7, 0.0, 0.0], np.float32)
+    buf.update_weights(True, rnd=0)
+    w = buf.weights.cpu().numpy()
+    W_t, temp_t, target_t = harness.to_dev_store(W, 1), torch.from_numpy(temp).cuda(), torch.from_numpy(target).cuda()
+    for pos in range(gamma):
+        buf.draft_step(0, pos, W_t, harness.to_dev_store(H[pos], 1), temp_t)
+    buf.verify(0, target_t, temp_t, fused_update=True)
+    torch.cuda.synchronize()
+    c = lambda t: t.cpu().numpy()  # noqa: E731
+    want = oracle.verify(V=V, n=n, B=B, gamma=gamma, distance=distance, seed=4, rnd=0, target_logits=target, draft_logits=c(buf.draft_logits),
+                         draft_tokens=c(buf.draft_tokens), draft_q=c(buf.draft_q), weights=w, temperature=temp,
+                         n_cand=oracle.GRID_CANDIDATES if policy == 2 else 0)
+    dev, flags = c(buf.dev), c(buf.verify_flags) | want["flags"]
+    assert np.isfinite(dev).all() and np.isfinite(c(buf.ring)).all() and np.isfinite(c(buf.weights)).all()
+    for b in range(B):
+        if flags[b].any():                            # a decision within its margin may differ
+            continue
+        assert c(buf.accept_len)[b] == want["accept_len"][b] and np.array_equal(c(buf.out_tokens)[b], want["out_tokens"][b])
+        valid = slice(0, want["n_valid"][b])          # the parity harness' tolerance of distances; hard labels are exact
+        err, bound = np.abs(dev[b, valid] - want["dev"][b, valid]), 1e-5 * np.abs(want["dev"][b, valid]) + 1e-6
+        assert (err <= (0.0 if distance == 2 else bound)).all(), (b, dev[b], want["dev"][b])
+    assert (flags == 0).all(axis=1).sum() >= 3
+    ring = np.zeros((B, h, oracle.dev_width(n, policy)), np.float32)
+    nxt = oracle.update_weights(n=n, B=B, gamma=gamma, h=h, policy=policy, tau_w=1.0, eps=1e-6, dev=dev, n_valid=c(buf.n_valid), ring=ring,
+                                ring_head=np.zeros(B, np.int32), ring_count=np.zeros(B, np.int32), seed=4, rnd=1)
+    np.testing.assert_allclose(c(buf.weights), nxt, rtol=1e-6, atol=1e-7)
