@@ -67,10 +67,9 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
 #pragma unroll
     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float base = (mx > -INFINITY) ? mx : 0.f;        // a tile of -inf sums to 0
-    float sum = 0.f;
+    float sum = 0.f;                                       // -inf and NaN logits have no mass: neither takes the tile's with it
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sum += __expf(sc[r] - base);
+    for (int r = 0; r < 16; ++r) sum += (sc[r] > -INFINITY) ? __expf(sc[r] - mx) : 0.f;
     sum += __shfl_xor(sum, 32);
     if (live && half == 0) {
         if (pstage != nullptr) {                    // collected per workgroup: [array][row][tile of the group]

@@ -49,3 +49,29 @@ def test_logits_and_log_sum_exp(shape):
     # the log-sum-exp moves by at most the largest error of a scaled logit; 2e-6 for the fp32 exponentials and their sums
     tol = (bound.max(-1).values * inv) + 2e-6
     assert bool(((buf.draft_lse[1].view(M) - lse).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("V,d,n,B", [(8003, 72, 1, 3), (32000, 768, 4, 4), (33000, 768, 4, 16), (5003, 1024, 4, 16), (33000, 640, 2, 32),
+                                     (32000, 768, 4, 32), (70001, 264, 4, 64)])
+def test_entries_without_mass(V, d, n, B):
+    """A logit that is NaN and a whole softmax tile of -inf count nothing: the rest of their tiles keeps its mass."""
+    M = n * B
+    print(f"entries without mass V={V} d={d} M={M}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    cfg = binding.make_cfg(V=V, d=d, n=n, B=B, gamma=1, h=1, w_dtype=1, seed=1)
+    buf = binding.RoundBuffers(cfg, DEV)
+    buf.weights.fill_(1.0 / n)
+    W = (torch.randn((V, d), generator=g, device=DEV) * 0.05).bfloat16()
+    H = torch.randn((B, n, d), generator=g, device=DEV).bfloat16()
+    H[..., 0] = 1.0
+    W[64:96] = 0.0
+    W[64:96, 0] = float("-inf")
+    W[[17, 5000, V - 1], 0] = float("nan")
+    buf.draft_step(0, 0, W, H, torch.ones(B, device=DEV))
+    torch.cuda.synchronize()
+    L = buf.draft_logits[0].view(M, V)
+    assert bool(L[:, [17, 5000, V - 1]].isnan().all()) and bool((L[:, 64:96] == float("-inf")).all())
+    rest = torch.ones(V, dtype=torch.bool, device=DEV)
+    rest[[17, 5000, V - 1]] = False
+    lse = torch.logsumexp(L[:, rest].double(), -1)
+    assert bool(((buf.draft_lse[0].view(M) - lse).abs() <= 2e-6).all())      # fp32 exponentials and their sums, as above
