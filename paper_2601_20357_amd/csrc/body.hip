@@ -9,6 +9,7 @@
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <mutex>
 #include <utility>
@@ -500,7 +501,7 @@ __global__ __launch_bounds__(kBlock) void k_body_attn(int d, int max_ctx, const 
         qr[0] = a.x * scale; qr[1] = a.y * scale; qr[2] = a.z * scale; qr[3] = a.w * scale;
         qr[4] = b.x * scale; qr[5] = b.y * scale; qr[6] = b.z * scale; qr[7] = b.w * scale;
     }
-    float m = -1e30f, l = 0.f, o[8];
+    float m = -FLT_MAX, l = 0.f, o[8];        // not -inf: a range without keys subtracts it from itself; no finite score lies below
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
     if (t0 < t1) {

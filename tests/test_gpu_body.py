@@ -275,3 +275,16 @@ def test_body_step_on_every_route(oracle, name, bc, rows):
     g = np.random.default_rng(6)
     for _ in range(2):
         pair.step(g.integers(0, bc.V, size=rows))
+
+
+@pytest.mark.parametrize("max_ctx", [24, 520], ids=["one_range", "ranges8"])
+def test_body_attention_when_every_score_is_hugely_negative(oracle, max_ctx):
+    """Keys that are minus the query at a scale of 1e17: the only key of an empty cache scores about -1e33, and still has all of
+    the weight, also where the key ranges that hold no key are merged with it."""
+    bc = synth.BodyConfig(layers=1, d=48, heads=3, d_ff=80, V=40, max_ctx=max_ctx)
+    rows = 5
+    pair = BodyPair(oracle, bc, rows, seed=3, fill=lambda g: np.zeros(rows, dtype=np.int32))
+    q = synth.bf16_to_f32(pair.w["wqkv"][0][:bc.d]) * np.float32(1e17)
+    pair.w["wqkv"][0][:bc.d], pair.w["wqkv"][0][bc.d:2 * bc.d] = synth.bf16_bits(q), synth.bf16_bits(-q)
+    pair.dev["wqkv"][0].copy_(_to_dev(pair.torch, pair.w["wqkv"][0]))
+    pair.step(np.arange(rows))
