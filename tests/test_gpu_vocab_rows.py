@@ -123,3 +123,28 @@ def test_verify_with_masked_target_logits(oracle, V, policy, distance):
     nxt = oracle.update_weights(n=n, B=B, gamma=gamma, h=h, policy=policy, tau_w=1.0, eps=1e-6, dev=dev, n_valid=c(buf.n_valid), ring=ring,
                                 ring_head=np.zeros(B, np.int32), ring_count=np.zeros(B, np.int32), seed=4, rnd=1)
     np.testing.assert_allclose(c(buf.weights), nxt, rtol=1e-6, atol=1e-7)
+
+
+@pytest.mark.parametrize("V,n", [(8192, 3), (8192, 5), (8191, 4), (8191, 1), (8192, 4), (8192, 6), (8190, 8)])
+def test_log_sum_exp_adds_the_tiles_in_64_bits(V, n):
+    """One entry of probability ~1 and 252 of 4e-8, each in a tile and a lane that the first one is not in: added in 32 bits, each
+    is less than half a unit in the last place of the sum and the log-sum-exp loses up to 6e-8; the exponentials' own error is
+    1e-6 of 1e-5."""
+    import torch
+    from paper_2601_20357_amd import binding
+    print(f"tile sums V={V} n={n}", flush=True)
+    B = 2
+    cfg = binding.make_cfg(V=V, d=8, n=n, B=B, gamma=1, h=1, w_dtype=1)
+    buf = binding.RoundBuffers(cfg)
+    buf.weights.fill_(1.0 / n)
+    W = torch.zeros((V, 8), dtype=torch.bfloat16, device="cuda:0")
+    W[:, 0] = -1000.0
+    W[5::32, 0] = -17.0
+    W[5::64 * 32, 0] = -1000.0
+    W[0, 0] = 0.0
+    H = torch.zeros((B, n, 8), dtype=torch.bfloat16, device="cuda:0")
+    H[..., 0] = 1.0
+    buf.draft_step(0, 0, W, H, torch.ones(B, device="cuda:0"))
+    torch.cuda.synchronize()
+    lse = torch.logsumexp(buf.draft_logits[0].double(), -1)
+    assert float((buf.draft_lse[0] - lse).abs().max()) <= 1e-10
