@@ -607,10 +607,18 @@ __global__ void k_body_rollback(int rows, int rows_per_seq, int gamma, const int
 // ---------------------------------------------------------------- host side
 static size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 
-// Whether the fused projections run.  They read W once per 16 or 32 rows, a GEMM once per 256: two layers take 512 us
-// against 937 us with GEMMs at 512 rows of d = 768 (702 against 881 at d = 1024), 843 against 982 at 1024 rows, 1555 against
-// 1149 at 2048 (1142 against 937 at 1024 rows of d = 1024; 454 against 523 at 2048 rows of d = 256).
-static bool fused_rows(int d, int rows) { return rows <= 512 || (long)rows * d <= 1024 * 768; }
+// Whether the fused projections run.  They read W once per 16 or 32 rows, a GEMM once per 64 to 256, but a GEMM writes and
+// reads its result in fp32 and is two launches.  Two layers (d_ff = 4 d), fused / GEMM in us: d = 256 111 / 133 at 1024 rows,
+// 183 / 172 at 2048; d = 768 182 / 195 at 384, 219 / 209 at 512; d = 1024 196 / 210 at 192, 232 / 217 at 256; d = 2048 293 / 407 at
+// 128, 409 / 399 at 192, 949 / 514 at 512; one layer of d = 4096 (d_ff = 11264) 323 / 330 at 96, 397 / 348 at 128.
+// Up to 64 rows the fused ones also keep the shorter chains of sums.
+static bool fused_rows(int d, int rows) { return rows <= 64 || (long)rows * d <= 300 * 1024; }
+
+// Whether a projection normalises its rows itself.  Each of its workgroups reads them whole, in fp32: beyond 1024 columns that
+// leaves room for one block of 16 rows only, and W is read once per 16 rows.  Two layers of d = 2048 with the rows normalised
+// in the projection / by a kernel of their own, in us: 100.5 / 103.0 at 1 row, 113.9 / 113.5 at 16, 146 / 119 at 17, 250 / 182 at
+// 64; d = 1152 75.4 / 76.7 at 16, 84.9 / 81.7 at 17, 136 / 115 at 64.
+static bool norm_in_projection(int d, int rows) { return d <= 1024 || (d <= 2048 && rows <= 16); }
 
 // A projection [rows,K] x [N,K]^T as an LM head with vocabulary N, hidden size K, one draft and `rows` sequences.
 static tabed_cfg gemm_cfg(int rows, int K, int N) {
@@ -619,8 +627,6 @@ static tabed_cfg gemm_cfg(int rows, int K, int N) {
     c.tau_w = 1.f; c.eps = 1e-6f; c.seed = 0;
     return c;
 }
-
-constexpr int kMaxStagedD = 2048;   // hidden sizes whose normalised rows a projection stages in LDS itself
 
 // Key ranges a row's attention is cut into: enough for 768 workgroups (three per compute unit), at most 8, none shorter
 // than 64 positions of a full cache; one where the output projection could not stage the merged rows in LDS.  Measured at
@@ -643,7 +649,7 @@ BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     L.off_trig = off; off = al256(off + sizeof(double2) * (size_t)rows * ((c.d / c.heads) / 2));
     L.off_hb = off;   off = al256(off + sizeof(uint16_t) * (size_t)rows * act);
     const bool many = !fused_rows(c.d, rows);
-    L.off_hn = off;   off = al256(off + (c.d > kMaxStagedD || many ? sizeof(uint16_t) * (size_t)rows * c.d : 0));
+    L.off_hn = off;   off = al256(off + (many || !norm_in_projection(c.d, rows) ? sizeof(uint16_t) * (size_t)rows * c.d : 0));
     L.off_po = off;   off = al256(off + (S > 1 ? sizeof(float) * S * rows * c.d : 0));
     L.off_pml = off;  off = al256(off + (S > 1 ? sizeof(float) * 2 * S * rows * c.heads : 0));
     size_t gemm = 0;
@@ -748,11 +754,11 @@ static hipError_t gemm_projection(const ProjArgs& a, const uint16_t* X, char* ws
     return hipGetLastError();
 }
 
-// RMSNorm + projection: in one launch where the rows fit LDS.
+// RMSNorm + projection: in one launch where the projection normalises its rows itself.
 template <int EPI>
 static hipError_t norm_projection(ProjArgs a, uint16_t* hn, int tiles, char* ws, const BodyLayout& L, hipStream_t s) {
     const bool many = !fused_rows(a.K, a.M);
-    if (!many && a.K <= kMaxStagedD) return projection<kInNorm, EPI>(a, tiles, s);
+    if (!many && norm_in_projection(a.K, a.M)) return projection<kInNorm, EPI>(a, tiles, s);
     const hipError_t e = launch_norm(a, hn, nullptr, s);
     if (e != hipSuccess) return e;
     if (many) return gemm_projection<EPI>(a, hn, ws, L, s);
