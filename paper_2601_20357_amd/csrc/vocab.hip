@@ -928,10 +928,10 @@ struct DistArgs {
     double* dist;
 };
 
-template <int MODE, int N>
+template <int MODE>
 __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     const int c = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma;
+    const int V = a.V, n = a.n, gamma = a.gamma;
     constexpr int NC = TABED_GRID_CANDIDATES;
     __shared__ double s_lse;
     __shared__ float s_hi[TABED_MAX_N], s_oml[TABED_MAX_N];
@@ -1026,11 +1026,10 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     float4 tx[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) tx[u] = load4(trow, cb + (u * kBlock + tid) * 4, V);
-    constexpr int NQ = (MODE != 0) ? 2 : N;
-    float4 yq[NQ > 0 ? NQ : 1][4];                     // the draft rows, requested up front where their number is known
-    if (NQ > 0) {
+    float4 yq[2][4];                                   // the mixtures: both draft rows, requested up front
+    if (MODE != 0) {
 #pragma unroll
-        for (int j = 0; j < NQ; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int u = 0; u < 4; ++u) yq[j][u] = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
     }
@@ -1072,13 +1071,13 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
         }
 
     if (MODE == 0) {
-        constexpr int kRows = N > 0 ? N : 1;
-#pragma unroll kRows
+        // a row at a time: all of them up front is 17 more registers a row, and the workgroups that then no longer fit cost more
+        // than the trips saved (48 sequences of V = 32000, us: 4 drafts 27.5, 8 drafts 59)
         for (int j = 0; j < n; ++j) {
             float acc = 0.f;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const float4 y = (N > 0) ? yq[N > 0 ? j : 0][u] : load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+                const float4 y = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float ye = f4get(y, e);
@@ -1751,12 +1750,10 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
             d.dist = reinterpret_cast<double*>(ws + L.off_dist);
             const dim3 gd(L.Cd, c.gamma, c.B);
             const int mode = (c.distance == 2) ? (c.policy != 2 ? 3 : 4) : (c.policy != 2 ? 0 : 2);
-#define TABED_DIST(N_) launch(&dprof, k_dist<0, N_>, gd, dim3(kBlock), 0, s, d)
-            if (mode == 0) { TABED_FOR_DRAFTS(ncomp, TABED_DIST) }
-            else if (mode == 2) launch(&dprof, k_dist<2, 0>, gd, dim3(kBlock), 0, s, d);
-            else if (mode == 3) launch(&dprof, k_dist<3, 0>, gd, dim3(kBlock), 0, s, d);
-            else launch(&dprof, k_dist<4, 0>, gd, dim3(kBlock), 0, s, d);
-#undef TABED_DIST
+            if (mode == 0) launch(&dprof, k_dist<0>, gd, dim3(kBlock), 0, s, d);
+            else if (mode == 2) launch(&dprof, k_dist<2>, gd, dim3(kBlock), 0, s, d);
+            else if (mode == 3) launch(&dprof, k_dist<3>, gd, dim3(kBlock), 0, s, d);
+            else launch(&dprof, k_dist<4>, gd, dim3(kBlock), 0, s, d);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
