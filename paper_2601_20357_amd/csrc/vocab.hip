@@ -1332,94 +1332,64 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     __shared__ double s_wpart[64], s_wx[TABED_MAX_N];    // fused window update (one wave)
     __shared__ int s_y[TABED_MAX_GAMMA];                 // drafted tokens (hard labels)
 
-    // ---- everything that does not depend on another load is requested first; the target's logit at a drafted token, which
-    //      does, goes out as soon as the token is here, while the chunk records are on their way
-    const float T = a.temperature[b];
-    const bool greedy = !(T > 0.f);
-    const bool book = (c == a.C5);                        // the book-keeping workgroup of this sequence
-    if (greedy && !book) return;
+    // ---- everything that does not depend on another load is requested first
     int y = -1;
     float rawy = 0.f, uacc = 0.f, qy = 0.f;
     if (tid < gamma) {
         y = a.dtok[(size_t)b * gamma + tid];
-        if (a.u_acc) uacc = a.u_acc[(size_t)b * gamma + tid];
+        uacc = a.u_acc ? a.u_acc[(size_t)b * gamma + tid] : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)tid, 1);
         qy = a.dq[(size_t)b * gamma + tid];
-    }
-    double lse0 = 0.0;
-    if (tid < gamma * n) lse0 = a.dlse[((size_t)(tid / n) * a.B + b) * n + (tid % n)];
-    float w0 = 0.f;
-    if (tid < n) w0 = a.weights[(size_t)b * n + tid];
-
-    // ---- the chunk records of every target row.  A row's C3 chunks sit in an aligned group of
-    //      C3p lanes (C3p = power of two >= C3), so one wave combines 64 / C3p rows per pass, and the records of kPasses
-    //      passes are requested together; rows with more than 64 chunks fall back to one wave per row.
-    const double* sb = a.stats + (size_t)b * (gamma + 1) * C3 * RS;
-    constexpr int kPasses = 2;
-    int C3p = 1;
-    while (C3p < C3) C3p <<= 1;
-    const int rows_per_pass = (C3 <= kWave) ? kWave / C3p : 0, cc = lane & (C3p - 1);
-    double r0v[kPasses], r1v[kPasses];
-    ArgMax ram[kPasses];
-    auto request_records = [&](int row0) {
-#pragma unroll
-        for (int p = 0; p < kPasses; ++p) {
-            const int row = row0 + p * kWavesPerBlock * rows_per_pass + lane / C3p;
-            r0v[p] = -INFINITY; r1v[p] = 0.0;
-            ram[p] = ArgMax{-INFINITY, 0x7fffffff};
-            if (row <= gamma && cc < C3) {
-                const double* r = sb + ((size_t)row * C3 + cc) * RS;
-                r0v[p] = r[0]; r1v[p] = r[1];
-                ram[p] = ArgMax{(float)r[2], (int)r[3]};
-            }
-        }
-    };
-    if (C3 <= kWave) request_records(wave * rows_per_pass);
-    const bool y_ok = (y >= 0 && y < V);
-    if (tid < gamma) {
-        if (y_ok && !greedy) rawy = a.target[((size_t)b * (gamma + 1) + tid) * V + y];
         s_y[tid] = y;
-        if (!a.u_acc) uacc = tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)tid, 1);
     }
     for (int q = tid; q < gamma * n; q += kBlock) {      // draft log-sum-exps of every position, split hi + lo
-        const double l = (q == tid) ? lse0 : a.dlse[((size_t)(q / n) * a.B + b) * n + (q % n)];
+        const double l = a.dlse[((size_t)(q / n) * a.B + b) * n + (q % n)];
         const float hi = (float)l;
         s_hi[q / n][q % n] = hi;
         s_lo[q / n][q % n] = (float)(1.0 - (l - (double)hi));      // 1 - lo, the first-order factor of exp(-lo)
     }
-    if (tid < n) s_w[tid] = w0;
+    if (tid < n) s_w[tid] = a.weights[(size_t)b * n + tid];
+    const float T = a.temperature[b];
 
-    // ---- combine them (fp64, chunk order)
+    // ---- combine the chunk records of every target row.  A row's C3 chunks sit in an aligned group of
+    //      C3p lanes (C3p = power of two >= C3), so one wave combines 64 / C3p rows per pass with one
+    //      load round trip; rows with more than 64 chunks fall back to one wave per row.
+    const double* sb = a.stats + (size_t)b * (gamma + 1) * C3 * RS;
     if (C3 <= kWave) {
-        for (int row0 = wave * rows_per_pass; row0 <= gamma; row0 += kPasses * kWavesPerBlock * rows_per_pass) {
-            if (row0 != wave * rows_per_pass) request_records(row0);
-#pragma unroll
-            for (int p = 0; p < kPasses; ++p) {
-                const int row = row0 + p * kWavesPerBlock * rows_per_pass + lane / C3p;
-                const bool live = (row <= gamma && cc < C3);
-                if (row0 + p * kWavesPerBlock * rows_per_pass > gamma) break;          // uniform over the wave
-                ArgMax am = ram[p];
-                // all-reduce inside aligned groups of C3p lanes: DPP for the first four doublings (no LDS traffic),
-                // ds_bpermute only beyond a 16-lane row
-                double m = r0v[p];
-                if (C3p > 1) m = fmax(m, dpp_f64<kDppXor1>(m));
-                if (C3p > 2) m = fmax(m, dpp_f64<kDppXor2>(m));
-                if (C3p > 4) m = fmax(m, dpp_f64<kDppHalfMirror>(m));
-                if (C3p > 8) m = fmax(m, dpp_f64<kDppMirror>(m));
-                for (int o = 16; o < C3p; o <<= 1) m = fmax(m, __shfl_xor(m, o));
-                const double sc = (r0v[p] > -INFINITY) ? exp(r0v[p] - m) : 0.0;
-                if (live) s_scale[row * C3 + cc] = sc;
-                double Z = r1v[p] * sc;
-                if (C3p > 1) { Z += dpp_f64<kDppXor1>(Z); am = argmax_dpp_step<kDppXor1>(am); }
-                if (C3p > 2) { Z += dpp_f64<kDppXor2>(Z); am = argmax_dpp_step<kDppXor2>(am); }
-                if (C3p > 4) { Z += dpp_f64<kDppHalfMirror>(Z); am = argmax_dpp_step<kDppHalfMirror>(am); }
-                if (C3p > 8) { Z += dpp_f64<kDppMirror>(Z); am = argmax_dpp_step<kDppMirror>(am); }
-                for (int o = 16; o < C3p; o <<= 1) {
-                    Z += __shfl_xor(Z, o);
-                    const ArgMax other{__shfl_xor(am.v, o), __shfl_xor(am.i, o)};
-                    am = argmax_merge(am, other);
-                }
-                if (live && cc == 0) { s_rowm[row] = m; s_rowZ[row] = Z; s_rowlse[row] = m + log(Z); s_rowam[row] = am.i; }
+        int C3p = 1;
+        while (C3p < C3) C3p <<= 1;
+        const int rows_per_pass = kWave / C3p;
+        const int cc = lane & (C3p - 1);
+        for (int row0 = wave * rows_per_pass; row0 <= gamma; row0 += kWavesPerBlock * rows_per_pass) {
+            const int row = row0 + lane / C3p;
+            const bool live = (row <= gamma && cc < C3);
+            double r0v = -INFINITY, r1v = 0.0;
+            ArgMax am{-INFINITY, 0x7fffffff};
+            if (live) {
+                const double* r = sb + ((size_t)row * C3 + cc) * RS;
+                r0v = r[0]; r1v = r[1];
+                am = ArgMax{(float)r[2], (int)r[3]};
             }
+            // all-reduce inside aligned groups of C3p lanes: DPP for the first four doublings (no LDS traffic),
+            // ds_bpermute only beyond a 16-lane row
+            double m = r0v;
+            if (C3p > 1) m = fmax(m, dpp_f64<kDppXor1>(m));
+            if (C3p > 2) m = fmax(m, dpp_f64<kDppXor2>(m));
+            if (C3p > 4) m = fmax(m, dpp_f64<kDppHalfMirror>(m));
+            if (C3p > 8) m = fmax(m, dpp_f64<kDppMirror>(m));
+            for (int o = 16; o < C3p; o <<= 1) m = fmax(m, __shfl_xor(m, o));
+            const double sc = (r0v > -INFINITY) ? exp(r0v - m) : 0.0;
+            if (live) s_scale[row * C3 + cc] = sc;
+            double Z = r1v * sc;
+            if (C3p > 1) { Z += dpp_f64<kDppXor1>(Z); am = argmax_dpp_step<kDppXor1>(am); }
+            if (C3p > 2) { Z += dpp_f64<kDppXor2>(Z); am = argmax_dpp_step<kDppXor2>(am); }
+            if (C3p > 4) { Z += dpp_f64<kDppHalfMirror>(Z); am = argmax_dpp_step<kDppHalfMirror>(am); }
+            if (C3p > 8) { Z += dpp_f64<kDppMirror>(Z); am = argmax_dpp_step<kDppMirror>(am); }
+            for (int o = 16; o < C3p; o <<= 1) {
+                Z += __shfl_xor(Z, o);
+                const ArgMax other{__shfl_xor(am.v, o), __shfl_xor(am.i, o)};
+                am = argmax_merge(am, other);
+            }
+            if (live && cc == 0) { s_rowm[row] = m; s_rowZ[row] = Z; s_rowlse[row] = m + log(Z); s_rowam[row] = am.i; }
         }
     } else {
         for (int row = wave; row <= gamma; row += kWavesPerBlock) {
@@ -1442,7 +1412,12 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
             if (lane == 0) { s_rowm[row] = m; s_rowZ[row] = Z; s_rowlse[row] = m + log(Z); s_rowam[row] = am.i; }
         }
     }
+    const bool greedy = !(T > 0.f);
+    const bool book = (c == a.C5);                        // the book-keeping workgroup of this sequence
+    if (greedy && !book) return;
     const float invT = greedy ? 1.f : 1.f / T;
+    const bool y_ok = (y >= 0 && y < V);
+    if (tid < gamma && y_ok && !greedy) rawy = a.target[((size_t)b * (gamma + 1) + tid) * V + y];
     __syncthreads();
 
     // ---- gamma accept tests in parallel, k = first failure
