@@ -596,7 +596,8 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
                 for (int jj = 0; jj < JB; ++jj)
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
-                        if (j0 + jj < n && live[u]) x[jj][u] = load4(rows + (size_t)(j0 + jj) * V, cb + (u * kBlock + tid) * 4, V);
+                        if (j0 + jj < n && live[u])        // (more than kMaxListed tiles: not a short row)
+                            x[jj][u] = load_group(rows + (size_t)(j0 + jj) * V, group_at(cb + (u * kBlock + tid) * 4, V));
 #pragma unroll
                 for (int jj = 0; jj < JB; ++jj)
                     if (j0 + jj < n) {
@@ -609,10 +610,10 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int v = cb + (u * kBlock + tid) * 4;
+                const int v = cb + (u * kBlock + tid) * 4, at = group_at(v, V);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (live[u] && may_draw(v + e)) best = top3_push(best, q[u][e], v + e);
+                    if (live[u] && at + e >= v && may_draw(at + e)) best = top3_push(best, q[u][e], at + e);
             }
         }
     }
@@ -775,6 +776,7 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
     const float* trow = a.target + ((size_t)b * (gamma + 1) + i) * V;
     const float* qbase = a.dlogits + (((size_t)i * a.B + b) * n) * V;   // only dereferenced when i < gamma
     const int cb = c * (kBlock * 4 * U);
+    const bool inside = cb + kBlock * 4 * U <= V;
     const bool drafts = (i < gamma) && a.with_drafts;
     const bool grid = (N == 2) && drafts && a.grid;
     if (N == 2 && grid && tid < 2) {                     // published by the barriers of the maximum below
@@ -786,13 +788,21 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
 
     float4 tx[U];
     float4 dx[(N > 0) ? N : 1][U];
+    auto v = [&](int u) { return cb + (u * kBlock + tid) * 4; };
+    auto at = [&](int u) { return group_at(v(u), V); };
+    with_row_loads(V, [&](auto load) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) tx[u] = load4(trow, cb + (u * kBlock + tid) * 4, V);
-    if (N > 0 && drafts) {
+        for (int u = 0; u < U; ++u) tx[u] = load(trow, at(u));
+        if (N > 0 && drafts) {
 #pragma unroll
-        for (int j = 0; j < N; ++j)
+            for (int j = 0; j < N; ++j)
 #pragma unroll
-            for (int u = 0; u < U; ++u) dx[j][u] = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+                for (int u = 0; u < U; ++u) dx[j][u] = load(qbase + (size_t)j * V, at(u));
+        }
+    });
+    if (!inside) {                                       // (a draft's element counts where the target's does: ex > 0)
+#pragma unroll
+        for (int u = 0; u < U; ++u) mask_group(tx[u], at(u), v(u));
     }
 
     float st[U * 4], ex[U * 4];
@@ -800,11 +810,10 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
     float tmax = -INFINITY;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int v = cb + (u * kBlock + tid) * 4;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float xe = f4get(tx[u], e);
-            if (v + e < V) am = argmax_merge(am, ArgMax{xe, v + e});
+            if (at(u) + e >= v(u) && at(u) + e < V) am = argmax_merge(am, ArgMax{xe, at(u) + e});
             st[u * 4 + e] = xe * invT;
             tmax = fmaxf(tmax, st[u * 4 + e]);
         }
@@ -867,21 +876,24 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
                 if (lane == 0) s_A[wave][j] = Aj;
             }
         } else {
-            for (int j = 0; j < n; ++j) {
-                float aj = 0.f;
+            auto sums = [&](auto load) {
+                for (int j = 0; j < n; ++j) {
+                    float aj = 0.f;
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int v = cb + (u * kBlock + tid) * 4;
-                    const float4 y = load4(qbase + (size_t)j * V, v, V);
+                    for (int u = 0; u < U; ++u) {
+                        const float4 y = load(qbase + (size_t)j * V, u);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float p = ex[u * 4 + e];
-                        if (p > 0.f) aj += p * (st[u * 4 + e] - f4get(y, e) * invT);
+                        for (int e = 0; e < 4; ++e) {
+                            const float p = ex[u * 4 + e];
+                            if (p > 0.f) aj += p * (st[u * 4 + e] - f4get(y, e) * invT);
+                        }
                     }
+                    const double Aj = wave_sum((double)aj);
+                    if (lane == 0) s_A[wave][j] = Aj;
                 }
-                const double Aj = wave_sum((double)aj);
-                if (lane == 0) s_A[wave][j] = Aj;
-            }
+            };
+            if (inside) sums([&](const float* row, int u) { return load_group(row, v(u)); });
+            else with_row_loads(V, [&](auto load) { sums([&](const float* row, int u) { return load(row, at(u)); }); });
         }
     }
     __syncthreads();
@@ -942,6 +954,9 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     const float* trow = a.target + ((size_t)b * (gamma + 1) + i) * V;
     const float* qbase = a.dlogits + (((size_t)i * a.B + b) * n) * V;
     const int cb = c * kChunkV;
+    const bool inside = cb + kChunkV <= V;
+    auto v = [&](int u) { return cb + (u * kBlock + tid) * 4; };
+    auto at = [&](int u) { return group_at(v(u), V); };
     if (MODE >= 3) {
         // ---- hard labels: arg-max of every candidate distribution over this chunk
         const float T3 = a.temperature[b];
@@ -950,15 +965,15 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
             for (int j = 0; j < n; ++j) {                  // softmax is monotone: the arg-max of the raw logits
                 ArgMax am{-INFINITY, 0x7fffffff};
                 float4 y[4];
+                with_row_loads(V, [&](auto load) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) y[u] = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+                    for (int u = 0; u < 4; ++u) y[u] = load(qbase + (size_t)j * V, at(u));
+                });
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int v = cb + (u * kBlock + tid) * 4 + e;
-                        if (v < V) am = argmax_merge(am, ArgMax{f4get(y[u], e), v});
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if (at(u) + e >= v(u) && at(u) + e < V) am = argmax_merge(am, ArgMax{f4get(y[u], e), at(u) + e});
                 am = wave_argmax(am);
                 // fp32 logits compare exactly on both sides of any check: no runner-up is needed for these
                 if (lane == 0) { s_amx[wave][j] = am; s_sec[wave][j] = -INFINITY; }
@@ -971,11 +986,13 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
                 s_oml[tid] = (float)(1.0 - (l - (double)hi));
             }
             float4 y0[4], y1[4];
+            with_row_loads(V, [&](auto load) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                y0[u] = load4(qbase, cb + (u * kBlock + tid) * 4, V);
-                y1[u] = load4(qbase + (size_t)V, cb + (u * kBlock + tid) * 4, V);
-            }
+                for (int u = 0; u < 4; ++u) {
+                    y0[u] = load(qbase, at(u));
+                    y1[u] = load(qbase + (size_t)V, at(u));
+                }
+            });
             __syncthreads();
             float q0[16], q1[16];
 #pragma unroll
@@ -994,9 +1011,9 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
                 float sec = -INFINITY;
 #pragma unroll
                 for (int x = 0; x < 16; ++x) {
-                    const int v = cb + ((x >> 2) * kBlock + tid) * 4 + (x & 3);
-                    if (v < V) {
-                        const ArgMax cand{w0 * q0[x] + w1 * q1[x], v};
+                    const int ve = at(x >> 2) + (x & 3);
+                    if (ve >= v(x >> 2) && ve < V) {
+                        const ArgMax cand{w0 * q0[x] + w1 * q1[x], ve};
                         const ArgMax win = argmax_merge(am, cand);
                         sec = fmaxf(sec, win.i == cand.i ? am.v : cand.v);      // the loser's value
                         am = win;
@@ -1024,14 +1041,26 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
         return;
     }
     float4 tx[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) tx[u] = load4(trow, cb + (u * kBlock + tid) * 4, V);
     float4 yq[2][4];                                   // the mixtures: both draft rows, requested up front
-    if (MODE != 0) {
+    with_row_loads(V, [&](auto load) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int u = 0; u < 4; ++u) tx[u] = load(trow, at(u));
+        if (MODE != 0) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) yq[j][u] = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) yq[j][u] = load(qbase + (size_t)j * V, at(u));
+        }
+    });
+    if (!inside) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            mask_group(tx[u], at(u), v(u));
+            if (MODE != 0) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) mask_group(yq[j][u], at(u), v(u));
+            }
+        }
     }
     const float T = a.temperature[b];
     const float invT = (T > 0.f) ? 1.f / T : 1.f;
@@ -1073,21 +1102,31 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     if (MODE == 0) {
         // a row at a time: all of them up front is 17 more registers a row, and the workgroups that then no longer fit cost more
         // than the trips saved (48 sequences of V = 32000, us: 4 drafts 27.5, 8 drafts 59)
-        for (int j = 0; j < n; ++j) {
-            float acc = 0.f;
+        auto rows = [&](auto load) {
+            for (int j = 0; j < n; ++j) {
+                float acc = 0.f;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float4 y = load4(qbase + (size_t)j * V, cb + (u * kBlock + tid) * 4, V);
+                for (int u = 0; u < 4; ++u) {
+                    const float4 y = load(qbase + (size_t)j * V, u);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float ye = f4get(y, e);
-                    const float q = (ye > -INFINITY) ? __expf(ye * invT - s_hi[j]) * s_oml[j] : 0.f;
-                    acc += fabsf(pv[u * 4 + e] - q);
+                    for (int e = 0; e < 4; ++e) {
+                        const float ye = f4get(y, e);
+                        const float q = (ye > -INFINITY) ? __expf(ye * invT - s_hi[j]) * s_oml[j] : 0.f;
+                        acc += fabsf(pv[u * 4 + e] - q);
+                    }
                 }
+                const double t = wave_sum((double)acc);
+                if (lane == 0) s_sum[wave][j] = t;
             }
-            const double t = wave_sum((double)acc);
-            if (lane == 0) s_sum[wave][j] = t;
-        }
+        };
+        if (inside) rows([&](const float* row, int u) { return load_group(row, v(u)); });
+        else with_row_loads(V, [&](auto load) {
+            rows([&](const float* row, int u) {
+                float4 y = load(row, at(u));
+                mask_group(y, at(u), v(u));
+                return y;
+            });
+        });
     } else {
         // both drafts' probabilities of this thread's 16 elements, then one candidate mixture at a time
         float q0[16], q1[16];
@@ -1210,27 +1249,38 @@ struct ResidRow {
     bool bonus;
 };
 
-// f and p for S groups of four consecutive elements starting at v[s] (v[s] % 4 == 0; a group at or past V
-// contributes zeros).  Every load is issued before the first use; N is the compile-time number of drafts
-// (0 = run time, one batch of S loads per draft).
+// f, p and q for S groups of four consecutive elements, the groups that group_at gives for elements v[s] (v[s] % 4 == 0; f and p
+// are 0 for elements before v[s] or past V; inside: no lane's group reaches past V).  Every load is issued before the first use; N is the compile-time number of drafts
+// (0 = run time, the rows of four drafts at a time).
 template <int N, int S>
-__device__ __forceinline__ void resid_eval(const ResidRow& r, int n, int V, const int (&v)[S], const float* s_hi,
+__device__ __forceinline__ void resid_eval(const ResidRow& r, int n, int V, bool inside, const int (&v)[S], const float* s_hi,
                                            const float* s_lo, const float* s_w, float (&f)[S][4], float (&p)[S][4],
                                            float (&q)[S][4]) {
     float4 tx[S];
+    float4 dx[(N > 0) ? N : 1][S];
+    int at[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) tx[s] = load4(r.trow, v[s], V);
+    for (int s = 0; s < S; ++s) at[s] = group_at(v[s], V);
+    with_row_loads(V, [&](auto load) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) tx[s] = load(r.trow, at[s]);
+        if (N > 0 && !r.bonus) {
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+#pragma unroll
+                for (int s = 0; s < S; ++s) dx[j][s] = load(r.qrows + (size_t)j * V, at[s]);
+        }
+    });
+    if (!inside) {                                       // (f = max(0, p - q) is 0 with p, whatever q)
+#pragma unroll
+        for (int s = 0; s < S; ++s) mask_group(tx[s], at[s], v[s]);
+    }
 #pragma unroll
     for (int s = 0; s < S; ++s)
 #pragma unroll
         for (int e = 0; e < 4; ++e) q[s][e] = 0.f;
     if (!r.bonus) {
         if (N > 0) {
-            float4 dx[(N > 0) ? N : 1][S];
-#pragma unroll
-            for (int j = 0; j < N; ++j)
-#pragma unroll
-                for (int s = 0; s < S; ++s) dx[j][s] = load4(r.qrows + (size_t)j * V, v[s], V);
 #pragma unroll
             for (int j = 0; j < N; ++j) {
                 const float w = s_w[j], hi = s_hi[j], lo = s_lo[j];
@@ -1243,17 +1293,26 @@ __device__ __forceinline__ void resid_eval(const ResidRow& r, int n, int V, cons
                     }
             }
         } else {
-            for (int j = 0; j < n; ++j) {
-                float4 y[S];
+            constexpr int JB = 4;                          // draft rows requested together
+            for (int j0 = 0; j0 < n; j0 += JB) {
+                float4 y[JB][S];
+                with_row_loads(V, [&](auto load) {
 #pragma unroll
-                for (int s = 0; s < S; ++s) y[s] = load4(r.qrows + (size_t)j * V, v[s], V);
-                const float w = s_w[j], hi = s_hi[j], lo = s_lo[j];
+                    for (int jj = 0; jj < JB; ++jj)        // past the last draft: re-read, not used
 #pragma unroll
-                for (int s = 0; s < S; ++s)
+                        for (int s = 0; s < S; ++s) y[jj][s] = load(r.qrows + (size_t)min(j0 + jj, n - 1) * V, at[s]);
+                });
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float ye = f4get(y[s], e);
-                        if (ye > -INFINITY) q[s][e] += w * exp_shifted(ye * r.invT, hi, lo);
+                for (int jj = 0; jj < JB; ++jj)
+                    if (j0 + jj < n) {
+                        const float w = s_w[j0 + jj], hi = s_hi[j0 + jj], lo = s_lo[j0 + jj];
+#pragma unroll
+                        for (int s = 0; s < S; ++s)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float ye = f4get(y[jj][s], e);
+                                if (ye > -INFINITY) q[s][e] += w * exp_shifted(ye * r.invT, hi, lo);
+                            }
                     }
             }
         }
@@ -1459,7 +1518,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     if (!greedy && !book) {
 #pragma unroll
         for (int s = 0; s < kSegPerWave; ++s) vs[s] = (c * kSegPerChunk + wave + s * kWavesPerBlock) * kSegV + lane * 4;
-        resid_eval<N, kSegPerWave>(r, n, V, vs, hi_k, lo_k, s_w, f, p, qmix);
+        resid_eval<N, kSegPerWave>(r, n, V, (c + 1) * kResidChunkV <= V, vs, hi_k, lo_k, s_w, f, p, qmix);
     }
 
     if (book) {
@@ -1654,10 +1713,10 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     if (tid == owner) walk_seg_run(mR, mP, from_p, g0, g1, excl, target, &s_seg, &s_prefix);
     __syncthreads();
     if (tid >= kWave) return;
-    const int v1[1] = {s_seg * kSegV + lane * 4};
+    const int seg1 = __builtin_amdgcn_readfirstlane(s_seg), v1[1] = {seg1 * kSegV + lane * 4};
     float f1[1][4], p1[1][4], q1[1][4];
-    resid_eval<N, 1>(r, n, V, v1, hi_k, lo_k, s_w, f1, p1, q1);
-    const int v = v1[0];
+    resid_eval<N, 1>(r, n, V, (seg1 + 1) * kSegV <= V, v1, hi_k, lo_k, s_w, f1, p1, q1);
+    const int v = group_at(v1[0], V);
     const double l1 = (double)f1[0][0], l2 = l1 + (double)f1[0][1], l3 = l2 + (double)f1[0][2], l4 = l3 + (double)f1[0][3];
     const double base = s_prefix + (wave_inclusive_scan(l4) - l4);
     const double cdf[4] = {base + l1, base + l2, base + l3, base + l4};
@@ -1700,7 +1759,11 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     const bool grid_in_stats = (c.policy == 2 && c.distance == 0);   // the KL of the two-draft grid's mixtures rides in the statistics pass
     const bool second_pass = (c.distance != 0);                      // distances that take a pass of their own
     const int ncomp = compiled_drafts(c.n);
-    const int U = pick_stats_unroll(c, ncomp > 4 ? 2 : 4);
+    // the statistics pass: rows one after the other for three and five drafts, where all of them up front took more registers
+    // than the trips saved are worth (12 sequences of V = 128256, us: 3 drafts 17.5 against 18.5, 5 drafts 24.0 against 26.0),
+    // and where it reads no draft row
+    const int scomp = (second_pass || ncomp == 3 || ncomp == 5) ? 0 : ncomp;
+    const int U = pick_stats_unroll(c, scomp > 4 ? 2 : 4);
     const int C3 = (c.V + kBlock * 4 * U - 1) / (kBlock * 4 * U);
     {
         ProfScope prof(TABED_K_STATS, s);
@@ -1712,7 +1775,13 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
         a.stats = reinterpret_cast<double*>(ws + L.off_stats);
         const dim3 grid(C3, c.gamma + 1, c.B);
 #define TABED_STATS(N_) launch_stats_n<N_>(&prof, U, grid, s, a)
-        TABED_FOR_DRAFTS(ncomp, TABED_STATS)
+        switch (scomp) {
+            case 1: TABED_STATS(1); break;
+            case 2: TABED_STATS(2); break;
+            case 4: TABED_STATS(4); break;
+            case 8: TABED_STATS(8); break;
+            default: TABED_STATS(0); break;
+        }
 #undef TABED_STATS
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1951,7 +2020,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
         int vs[kSegPerWave];
 #pragma unroll
         for (int sg = 0; sg < kSegPerWave; ++sg) vs[sg] = (c * kSegPerChunk + wave + sg * kWavesPerBlock) * kSegV + lane * 4;
-        resid_eval<N, kSegPerWave>(r, n, V, vs, s_hi, s_lo, s_w, f, p, q);
+        resid_eval<N, kSegPerWave>(r, n, V, (c + 1) * kResidChunkV <= V, vs, s_hi, s_lo, s_w, f, p, q);
 #pragma unroll
         for (int sg = 0; sg < kSegPerWave; ++sg) {
             const int seg = c * kSegPerChunk + wave + sg * kWavesPerBlock;
@@ -2020,12 +2089,12 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
         return;
     }
     if (tid >= kWave) return;
-    const int v1[1] = {s_seg * kSegV + lane * 4};
+    const int seg1 = __builtin_amdgcn_readfirstlane(s_seg), v1[1] = {seg1 * kSegV + lane * 4};
     float f1[1][4], p1[1][4], q1[1][4], fl[4];
-    resid_eval<N, 1>(r, n, V, v1, s_hi, s_lo, s_w, f1, p1, q1);
+    resid_eval<N, 1>(r, n, V, (seg1 + 1) * kSegV <= V, v1, s_hi, s_lo, s_w, f1, p1, q1);
 #pragma unroll
     for (int e = 0; e < 4; ++e) fl[e] = degenerate ? p1[0][e] : level(f1[0][e], q1[0][e]);
-    const int tok = tree_pick_token(fl, v1[0], V, s_prefix, target, Z, &flag);
+    const int tok = tree_pick_token(fl, group_at(v1[0], V), V, s_prefix, target, Z, &flag);
     if (lane == 0) {
         a.out_tokens[fidx] = tok;
         a.flags[fidx] = (uint8_t)flag;
@@ -2059,18 +2128,26 @@ __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
 
     constexpr int kSegPerChunk = kResidChunkV / kSegV, kSegPerWave = kSegPerChunk / kWavesPerBlock;
     float4 x[kSegPerWave];
+    int v[kSegPerWave], at[kSegPerWave];
 #pragma unroll
-    for (int sg = 0; sg < kSegPerWave; ++sg)
-        x[sg] = load4(row, (c * kSegPerChunk + wave + sg * kWavesPerBlock) * kSegV + lane * 4, V);
+    for (int sg = 0; sg < kSegPerWave; ++sg) {
+        v[sg] = (c * kSegPerChunk + wave + sg * kWavesPerBlock) * kSegV + lane * 4;
+        at[sg] = group_at(v[sg], V);
+    }
+    with_row_loads(V, [&](auto load) {
+#pragma unroll
+        for (int sg = 0; sg < kSegPerWave; ++sg) x[sg] = load(row, at[sg]);
+    });
+#pragma unroll
+    for (int sg = 0; sg < kSegPerWave; ++sg) mask_group(x[sg], at[sg], v[sg]);
 #pragma unroll
     for (int sg = 0; sg < kSegPerWave; ++sg) {
         const int seg = c * kSegPerChunk + wave + sg * kWavesPerBlock;
-        const int v = seg * kSegV + lane * 4;
         if (greedy) {
             ArgMax am{-INFINITY, 0x7fffffff};
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (v + e < V) am = argmax_merge(am, ArgMax{f4get(x[sg], e), v + e});
+                if (at[sg] + e >= v[sg] && at[sg] + e < V) am = argmax_merge(am, ArgMax{f4get(x[sg], e), at[sg] + e});
             am = wave_argmax(am);
             if (lane == 0 && seg < NSEG) { publish_store(&rec0[seg], (double)am.v); publish_store(&rec1[seg], (double)am.i); }
         } else {
@@ -2154,15 +2231,17 @@ __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
     }
     __syncthreads();
     if (tid >= kWave) return;
-    const int v = s_seg * kSegV + lane * 4;
-    const float4 xx = load4(row, v, V);
+    const int v1 = s_seg * kSegV + lane * 4, at1 = group_at(v1, V);
+    float4 xx;
+    with_row_loads(V, [&](auto load) { xx = load(row, at1); });
+    mask_group(xx, at1, v1);
     float f[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float st = f4get(xx, e) * invT;
         f[e] = (st > -INFINITY) ? __expf(st - M) : 0.f;
     }
-    const int tok = tree_pick_token(f, v, V, s_prefix, target, Z, &flag);
+    const int tok = tree_pick_token(f, at1, V, s_prefix, target, Z, &flag);
     if (lane == 0) {
         a.out_tokens[fidx] = leaf_tok;
         a.out_tokens[fidx + 1] = tok;
