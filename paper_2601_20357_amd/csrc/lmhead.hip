@@ -67,9 +67,15 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
 #pragma unroll
     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    float sum = 0.f;                                       // -inf and NaN logits have no mass: neither takes the tile's with it
+    const float base = (mx > -INFINITY) ? mx : 0.f;        // a tile of -inf sums to 0
+    float sum = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sum += (sc[r] > -INFINITY) ? __expf(sc[r] - mx) : 0.f;
+    for (int r = 0; r < 16; ++r) sum += __expf(sc[r] - base);
+    if (__any(sum != sum)) {                               // a NaN logit has no mass and does not take the tile's with it
+        sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum += (sc[r] > -INFINITY) ? __expf(sc[r] - mx) : 0.f;
+    }
     sum += __shfl_xor(sum, 32);
     if (live && half == 0) {
         if (pstage != nullptr) {                    // collected per workgroup: [array][row][tile of the group]
@@ -110,7 +116,7 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
         }
 }
 
-// ---------------------------------------------------------------- bf16, 33 to 64 rows, d = 512, 768 or 896: W-streaming kernel
+// ---------------------------------------------------------------- bf16, up to 64 rows, d = 512, 768 or 896: W-streaming kernel
 // With n*B <= 64 rows the GEMM moves 2*d bytes of W per n*B*2*d flops: it is bound by streaming W from HBM
 // once, not by the matrix cores.  Design:
 //   * 8 waves per workgroup, one workgroup per compute unit.  All of H (<= 64 x d bf16) is staged once into
@@ -126,7 +132,7 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
 //   * The two K-halves meet through the same patches (LDS-only barriers), each wave finishing one 32-row
 //     block of the 64 x 32 result: logits (turned through the patch once more, stored as whole 128-byte lines
 //     past L2) + softmax partials of the tile.
-// KH = k-blocks (of 64) per wave = d / 128; MT = 32-row blocks of M (2).
+// KH = k-blocks (of 64) per wave = d / 128; MT = 32-row blocks of M.
 constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyThreads = kSkinnyWaves * 64;
 constexpr int kPatchBytes = 32 * 144;
@@ -413,7 +419,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny_kc(int M, int 
 }
 
 // ---------------------------------------------------------------- bf16, up to 64 rows, any hidden size: W-streaming kernel
-// The kernel for up to 32 rows, and for 33 to 64 where the two above do not apply.  Bound by streaming W from HBM once:
+// The kernel for up to 64 rows where the two above and the tiles below are not faster (launch_lmhead).  Bound by streaming W from HBM once:
 // V = 152064, d = 896, 32 rows: 54.8 us for 292 MB, 5.3 TB/s (the kernels above took 56.4); V = 32000, d = 768, 4 rows 9.0 us
 // (10.4); V = 50261, d = 1160, 15 rows 28.6 us (39.2 with 64 x 64 tiles through LDS, which these sizes took before).
 //   * Eight waves per workgroup.  KS of them share a 32-entry vocabulary tile, each taking its share of the k-blocks of 64; a
@@ -814,11 +820,11 @@ __global__ __launch_bounds__(kBlock) void k_lmhead_f32(int M, int d, int V, int 
     }
 }
 
-// Chunked variant: d a multiple of 512, 768 or 896 (k per chunk; the 512-wide chunk is the one that keeps the H prefetch in
-// registers without spills), at least two chunks.
+// k-blocks of 128 per chunk of the chunked kernel (hidden sizes that are at least two times 512, 768 or 896), 0 for other sizes.
+// With two row blocks the 512-wide chunk is the one that keeps the H prefetch in registers without spills.
 static int skinny_kc_kh(const tabed_cfg& c, int M) {
-    if (c.w_dtype != 1 || M > 64) return 0;
-    for (int KH : {4, 6, 7})
+    const int two[3] = {4, 6, 7}, one[3] = {6, 4, 7};
+    for (int KH : (M > 32 ? two : one))
         if (c.d % (KH * 128) == 0 && c.d / (KH * 128) >= 2) return KH;
     return 0;
 }
@@ -841,15 +847,34 @@ static hipError_t launch_skinny_kc_t(const ProfScope* prof, const tabed_cfg& c, 
 static hipError_t launch_skinny_kc(const ProfScope* prof, int KH, const tabed_cfg& c, const WsLayout& Lay, int M,
                              const void* W, const void* H, const float* temperature, float* logits, float* pm,
                              float* ps, hipStream_t s) {
-#define TABED_SKINNY_KC(KH_) \
-    if (KH == KH_) return launch_skinny_kc_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+#define TABED_SKINNY_KC(KH_)                                                                                         \
+    if (KH == KH_)                                                                                                   \
+        return M <= 32 ? launch_skinny_kc_t<KH_, 1>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s)           \
+                       : launch_skinny_kc_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     TABED_SKINNY_KC(4) TABED_SKINNY_KC(6) TABED_SKINNY_KC(7)
 #undef TABED_SKINNY_KC
     return hipErrorInvalidValue;
 }
 
+// (d = 1024 up to 32 rows: two blocks of 32 rows and the patches do not fit LDS)
 static bool skinny_applies(const tabed_cfg& c, int M) {
-    return c.w_dtype == 1 && M <= 64 && (c.d == 4 * 128 || c.d == 6 * 128 || c.d == 7 * 128);
+    return c.d == 4 * 128 || c.d == 6 * 128 || c.d == 7 * 128 || (c.d == 8 * 128 && M <= 32);
+}
+
+// Up to 32 rows: whether the kernels with a compile-time hidden size run, or the W-streaming kernel.  In us, those / streaming:
+//   d = 512: always (V = 32000, 32 rows 11.3 / 13.7; V = 65536, 8 rows 18.6 / 19.9), except for vocabularies that the streaming
+//     kernel cuts finer (V = 8000: 0.9 of the time);
+//   17 to 32 rows, d = 768 and 896: with few groups of 128 entries a workgroup (V = 20000, d = 896 12.3 / 13.6, V = 40000 3 % less;
+//     V = 65536 equal);
+//   17 to 32 rows, H in chunks or d = 1024: V = 40000, d = 2560 45.6 / 49.6; V = 20000, d = 3584 6 % less, d = 1024 13.4 / 14.5; but
+//     rows that lie a multiple of 2 KB apart only while W fits the 256 MB of the last-level cache (d = 2048 V = 65536 3 % less,
+//     V = 100000 9 % more; d = 4096 V = 32000 4 % less, V = 40000 7 % more).
+static bool skinny_wins(const tabed_cfg& c, int M) {
+    if (c.V <= 128 * 128) return false;
+    if (c.d == 512) return true;
+    if (M <= 16) return false;
+    if (c.d % 1024 == 0) return (long)c.V * c.d <= 1l << 27;
+    return c.V <= 384 * 128 || !skinny_applies(c, M);
 }
 
 template <int KH, int MT>
@@ -871,10 +896,13 @@ static hipError_t launch_skinny_t(const ProfScope* prof, const tabed_cfg& c, con
 static hipError_t launch_skinny(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
                           const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
     const int KH = c.d / 128;
-#define TABED_SKINNY(KH_) \
-    if (KH == KH_) return launch_skinny_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+#define TABED_SKINNY(KH_)                                                                                         \
+    if (KH == KH_)                                                                                                \
+        return M <= 32 ? launch_skinny_t<KH_, 1>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s)           \
+                       : launch_skinny_t<KH_, 2>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     TABED_SKINNY(4) TABED_SKINNY(6) TABED_SKINNY(7)
 #undef TABED_SKINNY
+    if (KH == 8 && M <= 32) return launch_skinny_t<8, 1>(prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     return hipErrorInvalidValue;
 }
 
@@ -909,14 +937,18 @@ static hipError_t launch_stream_k(const ProfScope* prof, const tabed_cfg& c, con
 #undef TABED_STREAM
 }
 
-// Waves per vocabulary tile, and which k-blocks each of them adds up.  A logit's value depends on this order in its last
-// bit, and with 1e5 bins a sampled token on the last bits of all of them; so the order stays what it was for every size:
-//   * d = 512, 768, 896 and multiples: two waves, runs of d / 128 (of a chunk's half) in turn;
-//   * other hidden sizes: one wave, all k-blocks in order, where groups of 128 entries would not be one round of a group per
-//     compute unit (V = 38000, d = 1280, 4 rows: 18.9 us, 22.1 with two waves).
-// Up to there two waves take turns (V = 32000, d = 1280, 20 rows: 15.0 us, 17.1 with one), and vocabularies of less than 128
-// groups are cut finer, four waves a tile (V = 10000, d = 1160, 20 rows: 9.0 us, 11.0 with two, 17.9 with one): fewer bins
-// have fewer edges for a uniform to land on.
+// Waves per vocabulary tile, and which k-blocks each of them adds up.  A logit's last bit depends on this order, and with 1e5
+// bins a sampled token on the last bits of all of them.  The order is a function of row count (up to 32, 33 to 64, more),
+// hidden size and vocabulary, and nothing else:
+//   * d = 512, 768, 896 and multiples, up to 64 rows: two waves, runs of half a chunk in turn.  The chunk is 768, 512 or 896 wide
+//     up to 32 rows (the first that divides d; d = 1024 is one chunk), 512, 768 or 896 wide from 33 rows on; the streaming
+//     kernel and the two above share an order, so that which of them runs does not matter.
+//   * other hidden sizes, up to 32 rows: one wave, all k-blocks in order, where groups of 128 entries would not be one round of a
+//     group per compute unit (V = 38000, d = 1280, 4 rows: 18.9 us, 22.1 with two waves).  Up to there two waves take turns
+//     (V = 32000, d = 1280, 20 rows: 15.0 us, 17.1 with one).
+//   * vocabularies of at most 128 groups: four waves a tile (V = 10000, d = 1160, 20 rows: 9.0 us, 11.0 with two, 17.9 with one),
+//     k-blocks in turn.
+//   * tiles (more than 64 rows, other hidden sizes from 33): all k-blocks in order.
 template <int MT>
 static hipError_t launch_stream(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, const void* W, const void* H,
                                 const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
@@ -954,25 +986,29 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
                            static_cast<const float*>(W), static_cast<const float*>(H), temperature, logits, pm, ps);
     } else if (c.d > (1 << 22)) {                       // rows of more than 8 MB: 64-bit offsets inside a tile
         e = launch_tile<128, 128, 2, uint64_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+    } else if (M <= 64 && skinny_applies(c, M) && (M > 32 || skinny_wins(c, M))) {
+        e = launch_skinny(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+    } else if (M <= 64 && skinny_kc_kh(c, M) != 0 && (M > 32 || skinny_wins(c, M))) {
+        e = launch_skinny_kc(&prof, skinny_kc_kh(c, M), c, Lay, M, W, H, temperature, logits, pm, ps, s);
     } else if (M <= 16) {
         e = launch_stream<1>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
     } else if (M <= 32) {
         e = launch_stream<2>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
-    } else if (skinny_applies(c, M)) {
-        e = launch_skinny(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
-    } else if (skinny_kc_kh(c, M) != 0) {
-        e = launch_skinny_kc(&prof, skinny_kc_kh(c, M), c, Lay, M, W, H, temperature, logits, pm, ps, s);
-    } else if (M <= 64 && (c.d <= kStreamMaxKC(4) || c.V <= 256 * 128)) {
-        // (H in several chunks and several groups per workgroup: the tiles below are faster, 67.5 against 79.5 us at 64 rows
-        // of V = 100000, d = 1280)
-        e = launch_stream<4>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
+    } else if (M <= 64 && c.V <= 128 * 128 && c.d > 640) {
+        e = launch_stream_k<4, 4>(&prof, c, Lay, 1, W, H, temperature, logits, pm, ps, s);
+    } else if (M <= 64) {
+        // 64 rows in one tile: V = 32000, 64 rows, d = 1000 19.3 us, with W streamed (H in two chunks) 30.1; d = 64 10.4 / 11.4;
+        // V = 8000, d = 1920 the other way round, 4 % less streamed with four waves a tile
+        e = launch_tile<64, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     } else {
         // the largest tile that still gives the chip three workgroups for every four compute units (a tile reads
         // (BM + BN) / (BM BN) operand elements per product): 312 / 340 / 371 us for 256 x 256, 128 x 256, 128 x 128 at 512 rows
         // of V = 128256, d = 2048; 89 / 103 / 102 at 256 rows of V = 100000, d = 1024; but 30 / 18.1 / 14.4 at 128 rows of
-        // V = 32000, d = 768, where they are 125, 125 and 250 workgroups
+        // V = 32000, d = 768, where they are 125, 125 and 250 workgroups; and the largest one too where the next would take
+        // a second round over the compute units: 256 rows of V = 40000, d = 1024 48 us with 157 workgroups of 256 x 256, 54 with 314
         auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((c.V + bn - 1) / bn); };
-        if (M > 128 && tiles(256, 256) >= 192) e = launch_tile<256, 256, 1, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        if (M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
+            e = launch_tile<256, 256, 1, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (tiles(128, 256) >= 192) e = launch_tile<128, 256, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else e = launch_tile<128, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     }

@@ -13,6 +13,15 @@ SHAPES = [
     (8003, 72, 1, 1), (33, 8, 16, 1), (32003, 1160, 3, 5), (5000, 2056, 1, 7), (31001, 2056, 1, 3), (140001, 256, 1, 5),
     # 32 rows
     (6000, 648, 1, 17), (32777, 1032, 4, 8), (31000, 1088, 1, 32), (70001, 1096, 2, 16),
+    # runs of more than one k-block a wave (2 x 128, 512, 768 or 896 columns in turn), K whole and in two, three, four chunks of H
+    (20000, 1024, 1, 4), (33000, 1024, 1, 32), (33000, 2048, 1, 9), (40000, 3072, 1, 5), (33000, 1536, 4, 4), (33000, 2048, 1, 20),
+    (33000, 3072, 1, 24), (70003, 1792, 1, 13), (66000, 2048, 4, 8),
+    # kernels with a compile-time hidden size, one block of up to 32 rows: whole rows of H and chunks
+    (33000, 512, 1, 5), (20001, 512, 4, 8), (20000, 768, 1, 17), (32001, 896, 4, 8), (20000, 1536, 4, 6), (40000, 2560, 1, 18),
+    (20002, 1792, 2, 10), (20000, 2048, 1, 32),
+    # tiles of 64 rows, and W streamed with four waves a tile and H in chunks
+    (20000, 776, 1, 33), (32768, 1000, 1, 64), (40001, 1920, 1, 48), (3001, 64, 1, 40), (33000, 72, 1, 64), (16384, 3200, 1, 64),
+    (129, 648, 1, 35),
     # 64 rows (hidden sizes that the kernels with a compile-time size do not take), K whole and in chunks
     (3001, 640, 1, 33), (32767, 640, 8, 8), (33001, 640, 1, 64), (33001, 1096, 1, 20), (9000, 1160, 1, 50), (32768, 776, 1, 64),
     # tiles of 128 x 128, 128 x 256, 256 x 256 rows x vocabulary; one k-block, a ragged last one, a last row block of one row

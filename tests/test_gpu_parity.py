@@ -68,7 +68,7 @@ SHAPES = [
     (257,    40,  16, 2, 2,    2, 0, "one"),        # maximum number of drafts, fp32 storage
     (5000,   64,  5, 70, 2,    3, 1, "mixed07"),    # more rows than one 64-row MFMA tile
     (1,      8,   2, 2, 2,     2, 0, "one"),        # single-token vocabulary
-    # shapes that take the W-streaming LM-head kernel (bf16, n*B <= 64, d in {512, 768, 896, 1024})
+    # up to 64 rows of hidden size 512, 768, 896 and 1024: W-streaming LM-head kernels
     (1000,   512, 2, 3, 2,     4, 1, "one"),        # one 32-row block of M, ragged last vocabulary tile
     (2084,   896, 4, 8, 2,     3, 1, "mixed07"),    # n*B = 32, tile count not a multiple of 4
     (4099,  1024, 4, 16, 2,    3, 1, "one"),        # n*B = 64, V % 4 != 0
@@ -77,14 +77,14 @@ SHAPES = [
     (70004,  64,  4, 3, 2,     3, 1, "mixed07"),    # more than 2048 softmax tiles: 20 tiles per sampler thread
     (200003, 64,  2, 2, 1,     2, 1, "mixed07"),    # beyond 163840: 32 tiles per sampler thread, two-pass sampler
     (700,    16,  16, 2, 32,   300, 1, "mixed07"),  # maximum block length and draft count, window longer than the run
-    # larger hidden sizes with n*B <= 64: the K-chunked streaming LM head
+    # larger hidden sizes with n*B <= 64: H in chunks where there are more than 16 rows
     (2100,  1024, 4, 16, 2,    3, 1, "one"),        # two chunks of 512, two row blocks
-    (40000, 1536, 2, 5, 1,     3, 1, "mixed07"),    # two chunks of 768, one row block, persistent loop twice
+    (40000, 1536, 2, 5, 1,     3, 1, "mixed07"),    # H whole, runs of six k-blocks, more groups than workgroups
     (1000,  2048, 4, 12, 2,    3, 1, "one"),        # four chunks of 512, ragged last tile
-    (700,   1792, 3, 3, 1,     2, 1, "greedy"),     # two chunks of 896
-    # shapes that take the many-rows LM-head kernel (bf16, n*B > 64, d % 64 == 0)
-    (4099,   256, 8, 40, 2,    3, 1, "one"),        # 320 rows: two row blocks, V % 4 != 0 (element-wise epilogue)
-    (3000,   128, 8, 70, 1,    3, 1, "mixed07"),    # 560 rows: three row blocks, ragged last vocabulary block
+    (700,   1792, 3, 3, 1,     2, 1, "greedy"),     # four waves a vocabulary tile
+    # more than 64 rows: tiled LM head
+    (4099,   256, 8, 40, 2,    3, 1, "one"),        # 320 rows in tiles of 128, V % 4 != 0
+    (3000,   128, 8, 70, 1,    3, 1, "mixed07"),    # 560 rows: five row blocks, ragged last vocabulary block
     (900,    64,  8, 20, 1,    2, 1, "one"),        # 160 rows, one k-block in all
     (262144, 64,  2, 2, 1,     2, 1, "mixed07"),    # the largest vocabulary the library takes
 ]
