@@ -574,18 +574,51 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     const bool few = (listed <= kMaxListed);              // the same in every workgroup of the row
     if (few) {
         if (c != 0) return;
-        for (int at = tid >> 5; at < listed; at += kBlock / kTileV) {
-            const int v = s_list[at] * kTileV + (tid & 31);
-            if (may_draw(v)) best = top3_push(best, mixture(v), v);
-        }
+        // a half-wave takes TB tiles at a time, all drafts of all of them requested together (64 tiles one after the other: 11 us)
+        auto evaluate = [&](auto tb) {
+            constexpr int TB = tb.value, kApart = kBlock / kTileV;
+            for (int a0 = tid >> 5; a0 < listed; a0 += TB * kApart) {
+                int v[TB];
+                float q[TB];
+#pragma unroll
+                for (int b = 0; b < TB; ++b) {
+                    v[b] = s_list[min(a0 + b * kApart, listed - 1)] * kTileV + (tid & 31);
+                    q[b] = 0.f;
+                }
+                if (N > 0) {
+                    float x[TB][(N > 0) ? N : 1];
+#pragma unroll
+                    for (int b = 0; b < TB; ++b)
+#pragma unroll
+                        for (int j = 0; j < N; ++j) x[b][j] = rows[(size_t)j * V + min(v[b], V - 1)];
+#pragma unroll
+                    for (int b = 0; b < TB; ++b)
+#pragma unroll
+                        for (int j = 0; j < N; ++j) q[b] += s_cf[j] * __expf(x[b][j] * invT - s_m[j]);
+                } else {
+#pragma unroll 4
+                    for (int j = 0; j < n; ++j)
+#pragma unroll
+                        for (int b = 0; b < TB; ++b) q[b] += s_cf[j] * __expf(rows[(size_t)j * V + min(v[b], V - 1)] * invT - s_m[j]);
+                }
+#pragma unroll
+                for (int b = 0; b < TB; ++b)
+                    if (a0 + b * kApart < listed && may_draw(v[b])) best = top3_push(best, q[b], v[b]);
+            }
+        };
+        if (listed <= kBlock / kTileV) evaluate(std::integral_constant<int, 1>{});
+        else evaluate(std::integral_constant<int, 4>{});
     } else {
         for (int cb = c * kChunkV; cb < V; cb += a.C2 * kChunkV) {
             float q[4][4];
             bool live[4];
+            int at[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int t = min(cb + (u * kBlock + tid) * 4, V - 1) / kTileV;
+                const int v = cb + (u * kBlock + tid) * 4, t = min(v, V - 1) / kTileV;
                 live[u] = (s_live[t >> 5] >> (t & 31)) & 1u;
+                at[u] = live[u] ? group_at(v, V) : 0;      // (a group that cannot matter costs one shared line: behind a branch,
+                                                           // every load waited for the one before it, 9 us a chunk)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) q[u][e] = 0.f;
             }
@@ -593,11 +626,10 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
             for (int j0 = 0; j0 < n; j0 += JB) {
                 float4 x[JB][4];
 #pragma unroll
-                for (int jj = 0; jj < JB; ++jj)
+                for (int jj = 0; jj < JB; ++jj)            // past the last draft: re-read, not used
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (j0 + jj < n && live[u])        // (more than kMaxListed tiles: not a short row)
-                            x[jj][u] = load_group(rows + (size_t)(j0 + jj) * V, group_at(cb + (u * kBlock + tid) * 4, V));
+                    for (int u = 0; u < 4; ++u)            // (more than kMaxListed tiles: not a short row)
+                        x[jj][u] = load_group(rows + (size_t)min(j0 + jj, n - 1) * V, at[u]);
 #pragma unroll
                 for (int jj = 0; jj < JB; ++jj)
                     if (j0 + jj < n) {
@@ -610,10 +642,10 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int v = cb + (u * kBlock + tid) * 4, at = group_at(v, V);
+                const int v = cb + (u * kBlock + tid) * 4;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (live[u] && at + e >= v && may_draw(at + e)) best = top3_push(best, q[u][e], at + e);
+                    if (live[u] && at[u] + e >= v && may_draw(at[u] + e)) best = top3_push(best, q[u][e], at[u] + e);
             }
         }
     }
