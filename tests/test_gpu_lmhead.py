@@ -63,7 +63,8 @@ def test_logits_and_log_sum_exp(shape):
 @pytest.mark.parametrize("V,d,n,B", [(8003, 72, 1, 3), (32000, 768, 4, 4), (33000, 768, 4, 16), (5003, 1024, 4, 16), (33000, 640, 2, 32),
                                      (32000, 768, 4, 32), (70001, 264, 4, 64)])
 def test_entries_without_mass(V, d, n, B):
-    """A logit that is NaN and a whole softmax tile of -inf count nothing: the rest of their tiles keeps its mass."""
+    """A logit that is NaN and a whole softmax tile of -inf count nothing: the rest of their tiles keeps its mass, and a greedy row
+    takes the largest of the other entries."""
     M = n * B
     print(f"entries without mass V={V} d={d} M={M}", flush=True)
     g = torch.Generator(device=DEV).manual_seed(V)
@@ -84,3 +85,9 @@ def test_entries_without_mass(V, d, n, B):
     rest[[17, 5000, V - 1]] = False
     lse = torch.logsumexp(L[:, rest].double(), -1)
     assert bool(((buf.draft_lse[0].view(M) - lse).abs() <= 2e-6).all())      # fp32 exponentials and their sums, as above
+    buf.draft_step(0, 0, W, H, torch.zeros(B, device=DEV))
+    torch.cuda.synchronize()
+    q = (buf.draft_logits[0].double() - lse.view(B, n, 1)).exp().mean(1).nan_to_num(nan=-1.0)
+    top, at = q.topk(2, -1)
+    y = buf.draft_tokens[:, 0].long()
+    assert bool(((y == at[:, 0]) | ((top[:, 0] - top[:, 1]) < 1e-6 * top[:, 0])).all())

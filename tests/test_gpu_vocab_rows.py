@@ -148,3 +148,48 @@ def test_log_sum_exp_adds_the_tiles_in_64_bits(V, n):
     torch.cuda.synchronize()
     lse = torch.logsumexp(buf.draft_logits[0].double(), -1)
     assert float((buf.draft_lse[0] - lse).abs().max()) <= 1e-10
+
+
+def test_arrival_counters_packed_to_fit_the_built_in_scratch():
+    """Where a line for every sequence's counters would lift a configuration over the built-in scratch, the counters are packed:
+    the same sequences give the same results there as in a smaller batch, whose counters are not (two rounds: re-armed counters)."""
+    import torch
+    from paper_2601_20357_amd import binding
+    V, n, d, gamma, width = 32000, 4, 64, 1, 3
+    cfg_of = lambda B: binding.make_cfg(V=V, d=d, n=n, B=B, gamma=gamma, h=3, w_dtype=1, seed=5)  # noqa: E731
+    size = lambda B: binding.tabed_workspace_bytes(cfg_of(B))  # noqa: E731
+    B = next(B for B in range(20, 2000) if size(B) < size(B - 1))
+    assert size(B) <= binding.STATIC_SCRATCH_BYTES < size(B - 1) + (size(B - 1) - size(B - 2))
+    few = B // 2
+    print(f"packed counters B={B}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(9)
+    W = (torch.randn((V, d), generator=g, device="cuda:0") * 0.15).bfloat16()
+    H = torch.randn((B, n, d), generator=g, device="cuda:0") * 4.0
+    H[::5] = 0.0                                          # rows of equal logits: every workgroup of the row arrives
+    H = H.bfloat16()
+    target = torch.randn((B, gamma + 1, V), generator=g, device="cuda:0") * 2.0
+    leaves = torch.randn((B, gamma, width - 1, V), generator=g, device="cuda:0") * 2.0
+    temp = torch.ones(B, device="cuda:0")
+    temp[::2] = 0.0
+
+    def run(b):
+        buf = binding.RoundBuffers(cfg_of(b))
+        buf.enable_tree(width)
+        out = []
+        sib = buf.prepare_draft_siblings(0, 0, temp[:b])
+        tree = buf.prepare_verify_tree(0, target[:b].contiguous(), leaves[:b].contiguous(), temp[:b])
+        for rnd in range(2):
+            buf.update_weights(rnd == 0, rnd=rnd)
+            buf.draft_step(rnd, 0, W, H[:b].contiguous(), temp[:b])
+            sib()
+            tree()
+            first = [buf.out_tokens, buf.leaf, buf.n_out]
+            out += [t[:few].clone() for t in first]
+            buf.verify(rnd, target[:b].contiguous(), temp[:b], fused_update=True)
+            out += [t[:few].clone() for t in (buf.draft_lse[0], buf.draft_tokens, buf.draft_q, buf.draft_flags, buf.sib_tokens, buf.sib_q, buf.accept_len,
+                                              buf.out_tokens, buf.dev, buf.n_valid, buf.verify_flags, buf.ring, buf.weights)]
+        torch.cuda.synchronize()
+        return out
+
+    for x, y in zip(run(B), run(few)):
+        assert torch.equal(x, y)
