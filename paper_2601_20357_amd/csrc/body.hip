@@ -699,13 +699,17 @@ static hipError_t launch_proj_t(int tiles, hipStream_t s, const ProjArgs& a) {
 }
 
 // Waves per workgroup and k-blocks a wave requests together: four waves up to 1024 of contraction (eight for q/k/v: 7.2
-// against 8.6 us at 64 rows), eight beyond, and as many requests as cover a wave's share where that is at most eight.  Two row blocks per workgroup where the tiles of
-// one already fill the chip twice: W is then read half as often.
+// against 8.6 us at 64 rows), eight beyond, and as many requests as cover a wave's share where that is at most eight.  Two row
+// blocks per workgroup, so that W is read half as often, where the tiles of one already fill the chip twice (once, for rows that
+// are normalised here); with more than 48 k-blocks, whose W takes longest, where 192 workgroups are left (two layers of
+// d = 2048, d_ff = 16384, 33 rows 264 us, 284 with one; d = 1024, d_ff = 4096, 64 rows, where 128 would be left, 84, 88 with two).
 template <int IN, int EPI>
 static hipError_t projection(const ProjArgs& a, int tiles, hipStream_t s) {
     const int mblocks = (a.M + 15) / 16;
-    const bool two = mblocks > 1 && (long)tiles * mblocks >= (IN == kInNorm ? 256 : 512);
     const int KB = (a.K + 63) / 64;
+    const bool two = mblocks > 1 && (IN == kInNorm ? (long)tiles * mblocks >= 256
+                                     : KB > 48     ? (long)tiles * ((mblocks + 1) / 2) >= 192
+                                                   : (long)tiles * mblocks >= 512);
     if constexpr (IN == kInMerge) {
         return launch_proj_t<8, 1, 3, 1, IN, EPI>(tiles, s, a);
     } else if constexpr (IN == kInNorm) {
