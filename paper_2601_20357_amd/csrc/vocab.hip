@@ -972,10 +972,10 @@ struct DistArgs {
     double* dist;
 };
 
-template <int MODE>
+template <int MODE, int N>
 __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     const int c = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int V = a.V, n = a.n, gamma = a.gamma;
+    const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma;
     constexpr int NC = TABED_GRID_CANDIDATES;
     __shared__ double s_lse;
     __shared__ float s_hi[TABED_MAX_N], s_oml[TABED_MAX_N];
@@ -1073,25 +1073,22 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
         return;
     }
     float4 tx[4];
-    float4 yq[2][4];                                   // the mixtures: both draft rows, requested up front
+    constexpr int NQ = (MODE != 0) ? 2 : N;
+    float4 yq[NQ > 0 ? NQ : 1][4];                     // the draft rows, where they are requested up front
     with_row_loads(V, [&](auto load) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) tx[u] = load(trow, at(u));
-        if (MODE != 0) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < NQ; ++j)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) yq[j][u] = load(qbase + (size_t)j * V, at(u));
-        }
+            for (int u = 0; u < 4; ++u) yq[j][u] = load(qbase + (size_t)j * V, at(u));
     });
     if (!inside) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             mask_group(tx[u], at(u), v(u));
-            if (MODE != 0) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j) mask_group(yq[j][u], at(u), v(u));
-            }
+            for (int j = 0; j < NQ; ++j) mask_group(yq[j][u], at(u), v(u));
         }
     }
     const float T = a.temperature[b];
@@ -1132,14 +1129,14 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
         }
 
     if (MODE == 0) {
-        // a row at a time: all of them up front is 17 more registers a row, and the workgroups that then no longer fit cost more
-        // than the trips saved (48 sequences of V = 32000, us: 4 drafts 27.5, 8 drafts 59)
         auto rows = [&](auto load) {
+            constexpr int kRows = N > 0 ? N : 1;
+#pragma unroll kRows
             for (int j = 0; j < n; ++j) {
                 float acc = 0.f;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const float4 y = load(qbase + (size_t)j * V, u);
+                    const float4 y = load(j, u);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float ye = f4get(y, e);
@@ -1151,10 +1148,11 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
                 if (lane == 0) s_sum[wave][j] = t;
             }
         };
-        if (inside) rows([&](const float* row, int u) { return load_group(row, v(u)); });
+        if (N > 0) rows([&](int j, int u) { return yq[N > 0 ? j : 0][u]; });
+        else if (inside) rows([&](int j, int u) { return load_group(qbase + (size_t)j * V, v(u)); });
         else with_row_loads(V, [&](auto load) {
-            rows([&](const float* row, int u) {
-                float4 y = load(row, at(u));
+            rows([&](int j, int u) {
+                float4 y = load(qbase + (size_t)j * V, at(u));
                 mask_group(y, at(u), v(u));
                 return y;
             });
@@ -1834,10 +1832,17 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
             d.dist = reinterpret_cast<double*>(ws + L.off_dist);
             const dim3 gd(L.Cd, c.gamma, c.B);
             const int mode = (c.distance == 2) ? (c.policy != 2 ? 3 : 4) : (c.policy != 2 ? 0 : 2);
-            if (mode == 0) launch(&dprof, k_dist<0>, gd, dim3(kBlock), 0, s, d);
-            else if (mode == 2) launch(&dprof, k_dist<2>, gd, dim3(kBlock), 0, s, d);
-            else if (mode == 3) launch(&dprof, k_dist<3>, gd, dim3(kBlock), 0, s, d);
-            else launch(&dprof, k_dist<4>, gd, dim3(kBlock), 0, s, d);
+            // Total variation: all draft rows of a chunk up front while the grid is at most two workgroups a compute unit, one row
+            // after the other beyond, where the 17 registers a row cost more workgroups than the trips saved are worth (us, up
+            // front / in turn: 32 workgroups, V = 8001, 4 drafts 7.9 / 9.4; 624, V = 50261, 3 drafts 11.9 / 11.8; 1536, V = 32000,
+            // 2, 4 and 8 drafts 17.7 / 11.9, 27.9 / 18.8, 58.6 / 33.9)
+            const int dcomp = ((long)L.Cd * c.gamma * c.B <= 512) ? ncomp : 0;
+#define TABED_DIST(N_) launch(&dprof, k_dist<0, N_>, gd, dim3(kBlock), 0, s, d)
+            if (mode == 0) { TABED_FOR_DRAFTS(dcomp, TABED_DIST) }
+            else if (mode == 2) launch(&dprof, k_dist<2, 0>, gd, dim3(kBlock), 0, s, d);
+            else if (mode == 3) launch(&dprof, k_dist<3, 0>, gd, dim3(kBlock), 0, s, d);
+            else launch(&dprof, k_dist<4, 0>, gd, dim3(kBlock), 0, s, d);
+#undef TABED_DIST
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
