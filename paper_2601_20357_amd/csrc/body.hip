@@ -23,7 +23,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4b;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4b;
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {            // round to nearest even
     return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
@@ -105,8 +104,9 @@ __global__ __launch_bounds__(kBlock) void k_body_norm(int d, float eps, const fl
 //       kEpiAdd:    residual addition in place
 // At 64 rows of d = 768, d_ff = 3072 a launch moves 1 to 9 MB: latency, the rate at which a compute unit takes in W and X
 // (64 bytes a cycle: every workgroup reads its rows of X whole) and the instructions fetched once bound it.  Measured
-// there: q/k/v 7.2, o 4.5, gate/up 9.7, down 6.0 us (down 8.0 with loads straight into operand layout); with the contraction split over workgroups, partial sums in memory and
-// rotation, residual + norm and SwiGLU kernels of their own a layer took 62 us instead of 48.
+// there (kernel trace, average): q/k/v 7.2, o 4.6, gate/up 10.0, down 5.9 us (down 8.0 with loads straight into operand
+// layout); with the contraction split over workgroups, partial sums in memory and rotation, residual + norm and SwiGLU kernels
+// of their own a layer took 62 us instead of 48.
 enum { kInNorm = 0, kInBf16 = 1, kInMerge = 2 };
 enum { kEpiRope = 0, kEpiSilu = 1, kEpiAdd = 2 };
 

@@ -84,14 +84,6 @@ __device__ __forceinline__ float block_max(float v, float* lds4) {
     __syncthreads();
     return r;
 }
-__device__ __forceinline__ double block_sum(double v, double* lds4) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double r = (lds4[0] + lds4[1]) + (lds4[2] + lds4[3]);
-    __syncthreads();
-    return r;
-}
 
 // Inclusive prefix sum across the 64 lanes of a wave, fixed order, no LDS traffic: Hillis-Steele inside each
 // 16-lane row with row_shr (lanes shifted in from outside the row read 0), then the total of row 0 goes to

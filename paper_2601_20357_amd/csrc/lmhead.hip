@@ -2,8 +2,8 @@
 //   L[r, v] = sum_k H[r, k] * W[v, k],   r = b*n + j  (M = n*B rows),
 // with the first half of the per-draft softmax fused into the epilogue: for every row and every 32-wide
 // vocabulary tile the kernel also writes  pm = max_v s(v)  and  ps = sum_v exp(s(v) - pm),  s = L / T_b.
-// gfx950: bf16 operands go through v_mfma_f32_32x32x16_bf16 (fp32 accumulate); fp32 operands (the tiny
-// correctness configuration) use plain FMAs.
+// gfx950: bf16 operands go through v_mfma_f32_32x32x16_bf16, in the W-streaming kernel v_mfma_f32_16x16x32_bf16 (fp32
+// accumulate); fp32 operands (the tiny correctness configuration) use plain FMAs.
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -419,9 +419,10 @@ __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny_kc(int M, int 
 }
 
 // ---------------------------------------------------------------- bf16, up to 64 rows, any hidden size: W-streaming kernel
-// The kernel for up to 64 rows where the two above and the tiles below are not faster (launch_lmhead).  Bound by streaming W from HBM once:
-// V = 152064, d = 896, 32 rows: 54.8 us for 292 MB, 5.3 TB/s (the kernels above took 56.4); V = 32000, d = 768, 4 rows 9.0 us
-// (10.4); V = 50261, d = 1160, 15 rows 28.6 us (39.2 with 64 x 64 tiles through LDS, which these sizes took before).
+// The kernel for up to 64 rows where the two above and the tiles below are not faster (launch_lmhead).  Bound by streaming W
+// from HBM once.  Kernel trace, average (fastest) of 60 launches that take three copies of W in turn, in us: V = 152064,
+// d = 896, 32 rows 55.6 (53.6) for 292 MB, 5.2 TB/s, the kernels above 56.4; V = 32000, d = 768, 4 rows 10.2 (8.1), the kernels
+// above 10.4; V = 50261, d = 1160, 15 rows 28.8 (27.6), with 64 x 64 tiles through LDS 39.2.
 //   * Eight waves per workgroup.  KS of them share a 32-entry vocabulary tile, each taking its share of the k-blocks of 64; a
 //     workgroup owns 8 / KS tiles and walks over the vocabulary.
 //   * A wave reads its k-block of W as whole 128-byte lines, 8 lanes a row, PF k-blocks ahead of the one being multiplied,
@@ -657,7 +658,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_lmhead_stream(int M, int d, 
     }
 }
 
-// ---------------------------------------------------------------- bf16, many rows (M > 64): tiled GEMM
+// ---------------------------------------------------------------- bf16, many rows (more than 64, other hidden sizes from 33): tiled GEMM
 // Workgroup tile BM (rows) x BN (vocabulary) x 64 (k), 8 waves, each a BM/2 x BN/4 block of 32x32 MFMA tiles (W as the row
 // operand, so that the accumulator is [vocabulary][row] and the transposed epilogue applies).  Both operands are staged
 // through LDS in two buffers; the operand fragments of k-step s+1 are read from LDS while the MFMAs of k-step s run, and the
@@ -665,8 +666,9 @@ __global__ __launch_bounds__(kStreamThreads) void k_lmhead_stream(int M, int d, 
 // whole 128-byte line of every row.  Rows padded by 16 bytes against bank conflicts.  Workgroups are numbered so that the row
 // blocks that share a vocabulary block run back to back on the same XCD (workgroup w goes to XCD w % 8): W is then read from
 // HBM once and from L2 afterwards.  Bound by how fast a workgroup takes in its operands and, with few k-blocks, by the logits'
-// stores, which the larger tiles do not overlap with another tile's products: 512 rows of V = 128256, d = 2048 312 us = 0.86
-// PFLOP/s; 128 rows of V = 32000, d = 768 14.4 us (28.5 when every tile was 256 x 256).
+// stores, which the larger tiles do not overlap with another tile's products.  Kernel trace, average (fastest) of 60 launches:
+// 512 rows of V = 128256, d = 2048 339 us (314) = 0.79 PFLOP/s; 128 rows of V = 32000, d = 768 16.2 us (15.4), 30.1 when every tile
+// was 256 x 256.
 constexpr int kLBK = 64, kLRow = (kLBK + 8) * 2;                            // k-block; LDS row stride in bytes (144)
 constexpr int kLCh = kLBK / 8;                                              // 16-byte chunks per row of a k-block
 constexpr int kLargeThreads = 512;
@@ -861,7 +863,8 @@ static bool skinny_applies(const tabed_cfg& c, int M) {
     return c.d == 4 * 128 || c.d == 6 * 128 || c.d == 7 * 128 || (c.d == 8 * 128 && M <= 32);
 }
 
-// Up to 32 rows: whether the kernels with a compile-time hidden size run, or the W-streaming kernel.  In us, those / streaming:
+// Up to 32 rows: whether the kernels with a compile-time hidden size run, or the W-streaming kernel.  Whole draft steps
+// replayed back to back on one copy of W, in us, those / streaming:
 //   d = 512: always (V = 32000, 32 rows 11.3 / 13.7; V = 65536, 8 rows 18.6 / 19.9), except for vocabularies that the streaming
 //     kernel cuts finer (V = 8000: 0.9 of the time);
 //   17 to 32 rows, d = 768 and 896: with few groups of 128 entries a workgroup (V = 20000, d = 896 12.3 / 13.6, V = 40000 3 % less;
@@ -939,7 +942,7 @@ static hipError_t launch_stream_k(const ProfScope* prof, const tabed_cfg& c, con
 
 // Waves per vocabulary tile, and which k-blocks each of them adds up.  A logit's last bit depends on this order, and with 1e5
 // bins a sampled token on the last bits of all of them.  The order is a function of row count (up to 32, 33 to 64, more),
-// hidden size and vocabulary, and nothing else:
+// hidden size and vocabulary, and nothing else.  (Times: back to back on one copy of W; a copy that is not cached adds 1 to 2 us.)
 //   * d = 512, 768, 896 and multiples, up to 64 rows: two waves, runs of half a chunk in turn.  The chunk is 768, 512 or 896 wide
 //     up to 32 rows (the first that divides d; d = 1024 is one chunk), 512, 768 or 896 wide from 33 rows on; the streaming
 //     kernel and the two above share an order, so that which of them runs does not matter.
@@ -997,15 +1000,16 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
     } else if (M <= 64 && c.V <= 128 * 128 && c.d > 640) {
         e = launch_stream_k<4, 4>(&prof, c, Lay, 1, W, H, temperature, logits, pm, ps, s);
     } else if (M <= 64) {
-        // 64 rows in one tile: V = 32000, 64 rows, d = 1000 19.3 us, with W streamed (H in two chunks) 30.1; d = 64 10.4 / 11.4;
-        // V = 8000, d = 1920 the other way round, 4 % less streamed with four waves a tile
+        // 64 rows in one tile.  Whole draft steps in us: V = 32000, 64 rows, d = 1000 19.3, with W streamed (H in two chunks) 30.1;
+        // d = 64 10.4 / 11.4; V = 8000, d = 1920 the other way round, 4 % less streamed with four waves a tile
         e = launch_tile<64, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     } else {
         // the largest tile that still gives the chip three workgroups for every four compute units (a tile reads
-        // (BM + BN) / (BM BN) operand elements per product): 312 / 340 / 371 us for 256 x 256, 128 x 256, 128 x 128 at 512 rows
-        // of V = 128256, d = 2048; 89 / 103 / 102 at 256 rows of V = 100000, d = 1024; but 30 / 18.1 / 14.4 at 128 rows of
-        // V = 32000, d = 768, where they are 125, 125 and 250 workgroups; and the largest one too where the next would take
-        // a second round over the compute units: 256 rows of V = 40000, d = 1024 48 us with 157 workgroups of 256 x 256, 54 with 314
+        // (BM + BN) / (BM BN) operand elements per product): fastest launches of 312 / 340 / 371 us for 256 x 256, 128 x 256,
+        // 128 x 128 at 512 rows of V = 128256, d = 2048; 89 / 103 / 102 at 256 rows of V = 100000, d = 1024; but 30 / 18.1 / 14.4 at
+        // 128 rows of V = 32000, d = 768, where they are 125, 125 and 250 workgroups; and the largest one too where the next would
+        // take a second round over the compute units: a draft step of 256 rows of V = 40000, d = 1024 48 us with 157 workgroups of
+        // 256 x 256, 54 with 314
         auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((c.V + bn - 1) / bn); };
         if (M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
             e = launch_tile<256, 256, 1, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);

@@ -1224,11 +1224,11 @@ static int compiled_drafts(int n) { return (n <= 5 || n == 8) ? n : 0; }
 // =====================================================================================================
 // Accept chain, distances, corrected / bonus token.
 // Grid (chunk + 1, sequence b).  Every workgroup of a sequence first combines the chunk records of all
-// gamma+1 target rows (fp64, chunk order), evaluates the gamma accept tests of Sec. 3 item 3 in parallel
+// gamma+1 target rows (fp64, fixed order), evaluates the gamma accept tests of Sec. 3 item 3 in parallel
 // and takes k = the first failing position.  The last workgroup of the row (the "book-keeping" one) has
 // no vocabulary chunk: it writes KL(p_i || q_i^(j)) and the bookkeeping outputs and, when asked to,
-// advances the window and computes the next weights while its siblings work on the residual row.  For a sampling row the emitted token comes from f = max(0, p_k - q_k) (k < gamma)
-// or f = p_gamma (k = gamma): every wave writes the mass of f over its 256-wide segments; the last
+// advances the window and computes the next weights while its siblings work on the residual row.  For a
+// sampling row the emitted token comes from f = max(0, p_k - q_k) (k < gamma) or f = p_gamma (k = gamma): every wave writes the mass of f over its 256-wide segments; the last
 // workgroup of the sequence to arrive prefixes the segment masses in order, finds the segment the uniform
 // falls into, and one wave re-evaluates that segment element by element.  A greedy row emits the arg-max of
 // target row k and needs no vocabulary pass.
@@ -1561,11 +1561,11 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
 
     if (book) {
         if (a.dist == nullptr) {
-            // ---- distances: thread per (position, draft or candidate mixture), chunks in order with the scales
+            // ---- distances: an entry per (position, draft or candidate mixture): its chunk sums times the scales
             //      computed above.  KL(p || q_j) = A_j / Z - lse_p + lse_j; a mixture's sums already hold its logarithm.
-            //      Eight lanes share an entry's chunks and request up to eight of them each at once (one thread per entry
-            //      made this workgroup, which the window waits for, the last of its sequence: 11 us of a 20 us launch
-            //      with 38 chunks).
+            //      Eight lanes add an entry's chunks, each every eighth one in order, eight requested at once; their sums are
+            //      added in a fixed order (one thread per entry made this workgroup, which the window waits for, the last of
+            //      its sequence: 11 us of a 20 us launch with 38 chunks).
             const int dw = a.grid_kl ? a.DW : n, l8 = tid & 7;
             for (int q0 = 0; q0 < gamma * dw; q0 += kBlock / 8) {
                 const int q = q0 + (tid >> 3), qc = min(q, gamma * dw - 1), ii = qc / dw, j = qc % dw;
@@ -1587,8 +1587,8 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
                 if (l8 == 0 && q < gamma * dw) publish_store(&a.dev[(size_t)b * gamma * dw + q], (float)kl);
             }
         } else if (!a.hard) {
-            // ---- distances from the second pass: add the chunk sums in chunk order
-            const int l8 = tid & 7;                        // eight lanes an entry, as above
+            // ---- distances from the second pass: add the chunk sums
+            const int l8 = tid & 7;                        // eight lanes an entry, in the order above
             for (int q0 = 0; q0 < gamma * a.DW; q0 += kBlock / 8) {
                 const int q = q0 + (tid >> 3);
                 const double* r0 = a.dist + ((size_t)b * gamma * a.DW + min(q, gamma * a.DW - 1)) * a.Cd * 2;
