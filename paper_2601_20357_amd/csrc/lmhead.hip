@@ -674,8 +674,10 @@ constexpr int kLCh = kLBK / 8;                                              // 1
 constexpr int kLargeThreads = 512;
 
 // Off: type of a byte offset inside a tile (32 bits while a tile's rows span less than 4 GiB).
-template <int BM, int BN, int PF, typename Off>
-__global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128) ? 4 : 2) void k_lmhead_tile(int M, int d, int V, int n, int NT,
+// NA: partial sums of a logit, over the k-blocks in turn, added in order at the end: those of the W-streaming kernel, whose
+// waves share a tile in the same way (launch_stream).
+template <int BM, int BN, int PF, typename Off, int NA = 1>
+__global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 4 : 2) void k_lmhead_tile(int M, int d, int V, int n, int NT,
                                                                 int mblocks, const uint16_t* __restrict__ W,
                                                                 const uint16_t* __restrict__ H,
                                                                 const float* __restrict__ temperature,
@@ -725,15 +727,17 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128) ? 4 : 2) void
         for (int t = 0; t < HP; ++t) *reinterpret_cast<u32x4*>(sW + (BN + t * (kLargeThreads / kLCh)) * kLRow) = out ? zero : rh[set][t];
     };
 
-    f32x16 acc[TV][TM];                                   // [vocabulary tile][row tile]
+    f32x16 acc[NA][TV][TM];                               // [partial sum][vocabulary tile][row tile]
 #pragma unroll
-    for (int a = 0; a < TV; ++a)
+    for (int i = 0; i < NA; ++i)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
+        for (int a = 0; a < TV; ++a)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+            for (int b = 0; b < TM; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][a][b][r] = 0.f;
 
-    auto multiply = [&](int kb) {
+    auto multiply = [&](int kb, int i) {                  // i = kb % NA, known at compile time
         const unsigned char* sW = lds + (kb & 1) * kStage + (wn * 32 * TV + nn) * kLRow + half * 16;
         const unsigned char* sH = lds + (kb & 1) * kStage + (BN + wm * (BM / 2) + nn) * kLRow + half * 16;
         // operand fragments of k-step ks+1 are read from LDS while the MFMAs of k-step ks run
@@ -753,7 +757,7 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128) ? 4 : 2) void
             for (int a = 0; a < TV; ++a)
 #pragma unroll
                 for (int b = 0; b < TM; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][a], hf[ks & 1][b], acc[a][b], 0, 0, 0);
+                    acc[i][a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][a], hf[ks & 1][b], acc[i][a][b], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -767,28 +771,50 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128) ? 4 : 2) void
     lds_barrier();
     // register set q holds k-block kb + 1 with (kb + 1) % PF = q: it goes to LDS after k-block kb is multiplied and is
     // refilled with the k-block PF later, except in the last PF k-blocks
-    auto block = [&](int kb0, auto refill) {
+    auto block = [&](int kb0, auto refill, auto first) {
 #pragma unroll
         for (int q = 0; q < PF; ++q) {
             const int kb = kb0 + q;
             if (kb < KB) {
-                multiply(kb);
+                multiply(kb, (first.value + q) % NA);
                 if (kb + 1 < KB) stash((q + 1) % PF, kb + 1);
                 if constexpr (refill.value) fetch((q + 1) % PF, kb + 1 + PF);
                 lds_barrier();
             }
         }
     };
+    static_assert(PF % NA == 0 || NA == 2 * PF, "block() runs PF k-blocks");
+    constexpr std::integral_constant<int, 0> zero{};
+    constexpr std::integral_constant<int, (NA > PF) ? PF : 0> next{};
     int kb0 = 0;
-    for (; kb0 + PF < KB; kb0 += PF) block(kb0, std::true_type{});
-    block(kb0, std::false_type{});
+    if constexpr (NA > PF) {
+        for (; kb0 + 2 * PF < KB; kb0 += 2 * PF) {
+            block(kb0, std::true_type{}, zero);
+            block(kb0 + PF, std::true_type{}, next);
+        }
+        if (kb0 + PF < KB) {
+            block(kb0, std::true_type{}, zero);
+            block(kb0 + PF, std::false_type{}, next);
+        } else {
+            block(kb0, std::false_type{}, zero);
+        }
+    } else {
+        for (; kb0 + PF < KB; kb0 += PF) block(kb0, std::true_type{}, zero);
+        block(kb0, std::false_type{}, zero);
+    }
+#pragma unroll
+    for (int i = 1; i < NA; ++i)
+#pragma unroll
+        for (int a = 0; a < TV; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) acc[0][a][b] += acc[i][a][b];
     // ---- epilogue: every wave turns its 32x32 blocks through a private patch carved from buffer 0
     unsigned char* tpatch = lds + wave * kPatchBytes;
 #pragma unroll
     for (int a = 0; a < TV; ++a)
 #pragma unroll
         for (int b = 0; b < TM; ++b)
-            store_tile_32x32_t(acc[a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
+            store_tile_32x32_t(acc[0][a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
 }
 
 // ---------------------------------------------------------------- fp32 operands: one output per thread
@@ -941,17 +967,20 @@ static hipError_t launch_stream_k(const ProfScope* prof, const tabed_cfg& c, con
 }
 
 // Waves per vocabulary tile, and which k-blocks each of them adds up.  A logit's last bit depends on this order, and with 1e5
-// bins a sampled token on the last bits of all of them.  The order is a function of row count (up to 32, 33 to 64, more),
-// hidden size and vocabulary, and nothing else.  (Times: back to back on one copy of W; a copy that is not cached adds 1 to 2 us.)
+// bins a sampled token on the last bits of all of them.  The order is a function of row count (up to 64, more; for
+// the first line's sizes also up to 32, 33 to 64), hidden size and vocabulary, and nothing else.  (Times: back to back on one
+// copy of W; a copy that is not cached adds 1 to 2 us.)
 //   * d = 512, 768, 896 and multiples, up to 64 rows: two waves, runs of half a chunk in turn.  The chunk is 768, 512 or 896 wide
 //     up to 32 rows (the first that divides d; d = 1024 is one chunk), 512, 768 or 896 wide from 33 rows on; the streaming
 //     kernel and the two above share an order, so that which of them runs does not matter.
-//   * other hidden sizes, up to 32 rows: one wave, all k-blocks in order, where groups of 128 entries would not be one round of a
+//   * other hidden sizes, up to 64 rows: one wave, all k-blocks in order, where groups of 128 entries would not be one round of a
 //     group per compute unit (V = 38000, d = 1280, 4 rows: 18.9 us, 22.1 with two waves).  Up to there two waves take turns
 //     (V = 32000, d = 1280, 20 rows: 15.0 us, 17.1 with one).
 //   * vocabularies of at most 128 groups: four waves a tile (V = 10000, d = 1160, 20 rows: 9.0 us, 11.0 with two, 17.9 with one),
-//     k-blocks in turn.
-//   * tiles (more than 64 rows, other hidden sizes from 33): all k-blocks in order.
+//     k-blocks in turn; from 33 rows on not for the first line's sizes.  (The tiles that take 33 to 64 rows keep as many partial sums, NA.  One sum over all k-blocks there had 1.4
+//     to 1.8 times the error: V = 8000, d = 640, 48 rows 14.2e-8 relative, 8.0e-8 with four; V = 32000, d = 1160 19.8e-8, 13.7e-8
+//     with two.)
+//   * more than 64 rows: all k-blocks in order.
 template <int MT>
 static hipError_t launch_stream(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, const void* W, const void* H,
                                 const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
@@ -962,16 +991,16 @@ static hipError_t launch_stream(const ProfScope* prof, const tabed_cfg& c, const
     return launch_stream_k<MT, 2>(prof, c, Lay, run ? run : 1, W, H, temperature, logits, pm, ps, s);
 }
 
-template <int BM, int BN, int PF, typename Off>
+template <int BM, int BN, int PF, typename Off, int NA = 1>
 static hipError_t launch_tile(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
                               const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
     const size_t lds = 2 * (size_t)(BM + BN) * kLRow;
     static std::once_flag once;
     static hipError_t rc = hipSuccess;
-    if (raise_lds_limit(&k_lmhead_tile<BM, BN, PF, Off>, lds, once, rc) != hipSuccess) return rc;
+    if (raise_lds_limit(&k_lmhead_tile<BM, BN, PF, Off, NA>, lds, once, rc) != hipSuccess) return rc;
     const int mblocks = (M + BM - 1) / BM, nblocks = (c.V + BN - 1) / BN;
     const int nrounds = (nblocks + 7) / 8;             // vocabulary blocks are dealt to the 8 XCDs in rounds
-    launch(prof, k_lmhead_tile<BM, BN, PF, Off>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
+    launch(prof, k_lmhead_tile<BM, BN, PF, Off, NA>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
            static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
     return hipSuccess;
 }
@@ -997,12 +1026,15 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
         e = launch_stream<1>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
     } else if (M <= 32) {
         e = launch_stream<2>(&prof, c, Lay, W, H, temperature, logits, pm, ps, s);
-    } else if (M <= 64 && c.V <= 128 * 128 && c.d > 640) {
+    } else if (M <= 64 && c.V <= 128 * 128 && c.d > 512) {
         e = launch_stream_k<4, 4>(&prof, c, Lay, 1, W, H, temperature, logits, pm, ps, s);
     } else if (M <= 64) {
         // 64 rows in one tile.  Whole draft steps in us: V = 32000, 64 rows, d = 1000 19.3, with W streamed (H in two chunks) 30.1;
-        // d = 64 10.4 / 11.4; V = 8000, d = 1920 the other way round, 4 % less streamed with four waves a tile
-        e = launch_tile<64, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        // d = 64 10.4 / 11.4; V = 16384, 48 rows, d = 320 10.5 / 10.9; d = 640 the other way round, 12.2 / 11.9, and V = 8000, d = 1920
+        // 4 % less streamed with four waves a tile.  The partial sums cost 0.1 to 0.3 us.
+        if (c.V <= 128 * 128) e = launch_tile<64, 128, 2, uint32_t, 4>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else if (c.V <= 256 * 128) e = launch_tile<64, 128, 2, uint32_t, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else e = launch_tile<64, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
     } else {
         // the largest tile that still gives the chip three workgroups for every four compute units (a tile reads
         // (BM + BN) / (BM BN) operand elements per product): fastest launches of 312 / 340 / 371 us for 256 x 256, 128 x 256,

@@ -91,3 +91,22 @@ def test_entries_without_mass(V, d, n, B):
     top, at = q.topk(2, -1)
     y = buf.draft_tokens[:, 0].long()
     assert bool(((y == at[:, 0]) | ((top[:, 0] - top[:, 1]) < 1e-6 * top[:, 0])).all())
+
+
+@pytest.mark.parametrize("V,d", [(8003, 8), (8003, 72), (8003, 136), (8003, 200), (8003, 264), (8003, 328), (16384, 504), (16384, 640), (12001, 1000), (16385, 64),
+                                 (16385, 136), (32768, 200), (20000, 640), (32001, 1160), (32769, 200), (50261, 1160)])
+def test_order_of_a_logits_products_up_to_64_rows(V, d):
+    """Hidden sizes outside the 512 / 768 / 896 families: a row's logits are the same bits with 32 rows and with 33 to 64, where
+    tiles take the place of the kernel that streams W: one, two or four partial sums over the k-blocks, none to all of them filled."""
+    g = torch.Generator(device=DEV).manual_seed(V + d)
+    W = (torch.randn((V, d), generator=g, device=DEV) * 0.05).bfloat16()
+    H = torch.randn((64, 1, d), generator=g, device=DEV).bfloat16()
+    out = {}
+    for B in (32, 33, 64):
+        print(f"lm head order V={V} d={d} rows={B}", flush=True)
+        buf = binding.RoundBuffers(binding.make_cfg(V=V, d=d, n=1, B=B, gamma=1, h=1, w_dtype=1, seed=1), DEV)
+        buf.weights.fill_(1.0)
+        buf.draft_step(0, 0, W, H[:B].contiguous(), torch.ones(B, device=DEV))
+        torch.cuda.synchronize()
+        out[B] = buf.draft_logits[0].view(B, V)
+    assert torch.equal(out[32], out[33][:32]) and torch.equal(out[33], out[64][:33])
