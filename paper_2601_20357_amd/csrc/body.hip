@@ -1,35 +1,23 @@
 // Draft-model body in front of the LM head (Sec. 5.1 "Ensemble learning via Batched Inference", Sec. 4.1 "Target and
 // Draft Models"): one decode step of a LLaMA-style decoder for the n*B rows of the batch of drafting methods, each
-// with its own key / value cache.  At 64 rows every projection streams a few megabytes of weights and is bound by
+// with its own key / value cache.  Up to 16 rows the step is one launch where its sizes allow (body_gang.hip); here are the
+// others.  At 64 rows every projection streams a few megabytes of weights and is bound by
 // launch and latency, not bandwidth, so a layer is five launches and nothing in between: every projection normalises
 // (or merges the attention's partial results) while its weights are on their way and finishes what its result feeds --
 // rotation and cache append, residual addition, SwiGLU -- before it stores.  Storage points: bf16 for weights, caches
 // and everything that feeds a projection; fp32 for the residual stream, the rotated queries and the attention's
 // partial sums.
-#include <hip/hip_bf16.h>
-
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <mutex>
 #include <utility>
 
+#include "body_utils.h"
 #include "device_utils.h"
 #include "internal.h"
 
 namespace tabed {
-
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4b;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4b;
-
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {            // round to nearest even
-    return __builtin_bit_cast(uint16_t, (__bf16)f);
-}
-
-__device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d) {
-    return make_uint2(f32_to_bf16_bits(a) | ((uint32_t)f32_to_bf16_bits(b) << 16), f32_to_bf16_bits(c) | ((uint32_t)f32_to_bf16_bits(d) << 16));
-}
 
 __device__ __forceinline__ float block_sum_f32(float v, float* lds4) {
     v = wave_sum(v);
@@ -46,8 +34,10 @@ __device__ __forceinline__ float block_sum_f32(float v, float* lds4) {
 __global__ __launch_bounds__(kBlock) void k_body_embed(int d, int V, const int32_t* __restrict__ token_src, int token_stride,
                                                        int rows_per_token, const uint16_t* __restrict__ embed,
                                                        float* __restrict__ x, const int32_t* __restrict__ ctx_len, int max_ctx,
-                                                       int hd, double log2_theta, double2* __restrict__ trig /* [rows][hd/2] */) {
+                                                       int hd, double log2_theta, double2* __restrict__ trig /* [rows][hd/2] */,
+                                                       uint64_t* __restrict__ gang_key) {
     const int r = blockIdx.x;
+    if (r == 0 && threadIdx.x == 0) *gang_key = 0;      // a one-launch step on the same workspace finds its buffers used otherwise
     const int pos = min(max(ctx_len[r], 0), max_ctx - 1);
     int tok = token_src[(size_t)(r / rows_per_token) * token_stride];
     tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
@@ -644,6 +634,7 @@ BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     const int act = (c.d > c.d_ff) ? c.d : c.d_ff;
     const size_t S = (size_t)attn_splits(c, rows);
     size_t off = 0;
+    L.off_ctl = off;  off += kGangControlBytes;
     L.off_x = off;    off = al256(off + sizeof(float) * (size_t)rows * c.d);
     L.off_q = off;    off = al256(off + sizeof(float) * (size_t)rows * c.d);
     L.off_trig = off; off = al256(off + sizeof(double2) * (size_t)rows * ((c.d / c.heads) / 2));
@@ -659,6 +650,7 @@ BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     L.off_y = off;    off = al256(off + (many ? sizeof(float) * (size_t)rows * std::max(3 * c.d, 2 * c.d_ff) : 0));
     L.off_gemm = off; off = al256(off + gemm);
     L.off_ones = off; off = al256(off + (many ? sizeof(float) * (size_t)rows : 0));
+    L.off_gang = off; off = al256(off + (gang_applies(c, rows) ? gang_bytes(c, rows) : 0));
     L.total = off;
     return L;
 }
@@ -676,10 +668,12 @@ int validate_body_cfg(const tabed_body_cfg* c, int rows) {
     return TABED_OK;
 }
 
-// Only the GEMM route has something to prepare: the temperatures (all one) that the LM head's kernels divide by.
+// The one-launch step's control block (at the same place for all sizes: a workspace may be used for fewer rows than it was
+// prepared for), and for the GEMM route the temperatures (all one) that the LM head's kernels divide by.
 hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStream_t s) {
-    if (fused_rows(c.d, rows)) return hipSuccess;
     const BodyLayout L = body_layout(c, rows);
+    const hipError_t e = launch_gang_init(ws + L.off_ctl, s);
+    if (e != hipSuccess || fused_rows(c.d, rows)) return e;
     launch(nullptr, k_body_fill_ones, dim3((rows + 255) / 256), dim3(256), 0, s, reinterpret_cast<float*>(ws + L.off_ones), rows);
     return hipGetLastError();
 }
@@ -780,6 +774,8 @@ hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w
                             const int32_t* token_src, int token_stride, int rows_per_token, int32_t* ctx_len,
                             uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s) {
     const BodyLayout L = body_layout(c, rows);
+    if (gang_applies(c, rows))
+        return launch_gang(c, w, ws + L.off_ctl, ws + L.off_gang, rows, token_src, token_stride, rows_per_token, ctx_len, kcache, vcache, H, s);
     uint16_t* hb = reinterpret_cast<uint16_t*>(ws + L.off_hb);
     float* po = reinterpret_cast<float*>(ws + L.off_po);
     float* pml = reinterpret_cast<float*>(ws + L.off_pml);
@@ -799,7 +795,7 @@ hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w
         ProfScope prof(TABED_K_BODY, s);
         launch(&prof, k_body_embed, dim3(rows), dim3(kBlock), 0, s, d, c.V, token_src, token_stride, rows_per_token,
                static_cast<const uint16_t*>(w.embed), base.x, static_cast<const int32_t*>(ctx_len), c.max_ctx, hd,
-               std::log2((double)c.rope_theta), trig);
+               std::log2((double)c.rope_theta), trig, gang_key(ws + L.off_ctl));
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (int l = 0; l < c.layers; ++l) {

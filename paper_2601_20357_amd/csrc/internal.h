@@ -102,7 +102,9 @@ hipError_t launch_null(hipStream_t s);
 hipError_t launch_philox(const tabed_cfg& c, uint64_t round, float* out, hipStream_t s);
 
 // ---------------------------------------------------------------- draft-model body
+constexpr size_t kGangControlBytes = 4096;           // counters of the one-launch step
 struct BodyLayout {
+    size_t off_ctl;    // uint32: the one-launch step's counters, always first
     size_t off_x;      // float [rows,d] residual stream
     size_t off_q;      // float [rows,d] rotated queries of the current layer
     size_t off_trig;   // double2 [rows][head_dim/2] cos and sin of the rows' positions
@@ -113,6 +115,7 @@ struct BodyLayout {
     size_t off_y;      // many rows (GEMM route) only: float [rows, max(3d, 2 d_ff)] result of the current projection,
     size_t off_gemm;   //   scratch of the GEMM launches (softmax partials nobody reads),
     size_t off_ones;   //   float [rows]: the "temperature" they divide by
+    size_t off_gang;   // one-launch step only: its buffers, layer after layer
     size_t total;
 };
 BodyLayout body_layout(const tabed_body_cfg& c, int rows);
@@ -121,6 +124,12 @@ hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStre
 hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w, char* ws, int rows,
                             const int32_t* token_src, int token_stride, int rows_per_token, int32_t* ctx_len,
                             uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s);
+bool gang_applies(const tabed_body_cfg& c, int rows);
+size_t gang_bytes(const tabed_body_cfg& c, int rows);
+uint64_t* gang_key(char* ctl);
+hipError_t launch_gang_init(char* ctl, hipStream_t s);
+hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, char* ctl, char* buf, int rows, const int32_t* token_src,
+                       int token_stride, int rows_per_token, int32_t* ctx_len, uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s);
 hipError_t launch_body_rollback(int rows, int rows_per_seq, int gamma, const int32_t* ctx_base, const int32_t* accept_len,
                                 int32_t* ctx_len, hipStream_t s);
 
