@@ -817,6 +817,126 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 
             store_tile_32x32_t(acc[0][a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
 }
 
+// ---------------------------------------------------------------- bf16, more than 64 rows, hidden size a multiple of 64: operands straight to LDS
+// The tiled GEMM above for the hidden sizes whose rows are whole lines: the same workgroup tiles, waves and order of sums (and so
+// the same bits), but the operands go from memory to LDS without registers in between (global_load_lds, 16 bytes a lane), S
+// stages of one k-block each, S - 1 of them in flight; a wave keeps its registers for operand fragments, and nothing waits to write
+// LDS.  A stage has rows of 128 bytes without padding; row r keeps its 16-byte pieces in the order piece ^ (r & 7), which the
+// lanes bring about by the address they load from, so that the fragment reads of 8 consecutive rows hit all banks.
+// One barrier per k-block: before it a wave has waited for its own share of the stage that comes next, after it all of that
+// stage is there and the stage that was multiplied last is free.  The loads are written in assembly (they have no destination
+// register): with the builtin the compiler waits for all LDS reads in flight at every second step, 256 us instead of 232 for the
+// product alone below.
+// What bounds it, 512 rows of V = 128256, d = 2048: without the loads 200 us, without the products 165 us, both 232 us, with the
+// logits' 263 MB, which all workgroups store at about the same times, 276 us (the loop by itself; products alone 155 to 165 us,
+// 2.4 GHz would give 110: the clock follows the power).
+__device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off)[4], uint32_t lds, uint32_t step) {
+    // (the waits: M0 written before an LDS load, and a scalar that may have come from a vector instruction)
+    asm volatile("s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %6\n\ts_add_u32 m0, m0, %1\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %3, %6\n\ts_add_u32 m0, m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %6\n\t"
+                 "s_add_u32 m0, m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %6"
+                 :: "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "scc");
+}
+__device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off)[2], uint32_t lds, uint32_t step) {
+    asm volatile("s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_add_u32 m0, m0, %1\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %3, %4"
+                 :: "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "scc");
+}
+
+template <int BM, int BN, int S>
+__global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, int V, int n, int NT, int mblocks, const uint16_t* __restrict__ W,
+                                                                 const uint16_t* __restrict__ H, const float* __restrict__ temperature,
+                                                                 float* __restrict__ L, float* __restrict__ pm, float* __restrict__ ps) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    __shared__ float s_invt[BM];
+    constexpr int kRow = kLBK * 2, kStage = (BM + BN) * kRow;               // W's rows, then H's
+    constexpr int TV = BN / 128, TM = BM / 64;                              // 32-wide tiles of a wave
+    constexpr int WI = BN / 64, HI = BM / 64;                               // loads of a wave per stage: 8 rows of 128 bytes each
+    constexpr uint32_t kStep = 8 * 8 * kRow;                                // LDS bytes from one of a wave's loads to its next
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nn = lane & 31, half = lane >> 5;
+    // (numbering as above: row blocks of a vocabulary block back to back on one XCD)
+    const int w = blockIdx.x, xcd = w & 7, slot = w >> 3;
+    const int mb = slot % mblocks, nb = (slot / mblocks) * 8 + xcd;
+    const int m0 = mb * BM, v0 = nb * BN;
+    if (v0 >= V) return;                                                    // uniform: padding workgroups of the last XCD round
+    const int wm = wave >> 2, wn = wave & 3;
+    const float my_temp = temperature[min(m0 + (tid & (BM - 1)), M - 1) / n];       // used after the loop
+    const int KB = d / kLBK;
+    const char* const wbase = reinterpret_cast<const char*>(W) + (size_t)v0 * d * 2;
+    const char* const hbase = reinterpret_cast<const char*>(H) + (size_t)m0 * d * 2;
+    uint32_t wo[WI], ho[HI];                                                // rows past the end re-read the last one (masked in the epilogue)
+    {
+        const int r = lane >> 3;
+        const uint32_t piece = (uint32_t)((lane & 7) ^ r) * 16u;
+#pragma unroll
+        for (int i = 0; i < WI; ++i) wo[i] = (uint32_t)min((i * 8 + wave) * 8 + r, V - 1 - v0) * (uint32_t)d * 2u + piece;
+#pragma unroll
+        for (int i = 0; i < HI; ++i) ho[i] = (uint32_t)min((i * 8 + wave) * 8 + r, M - 1 - m0) * (uint32_t)d * 2u + piece;
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds + (uint32_t)wave * 8u * kRow;
+    auto request = [&](int kb, int stage) {                                 // past the last k-block: the last one again, into a stage nobody reads
+        const int k = min(kb, KB - 1) * kRow;
+        dma_lines(hbase + k, ho, lds0 + (uint32_t)(stage * kStage + BN * kRow), kStep);
+        dma_lines(wbase + k, wo, lds0 + (uint32_t)(stage * kStage), kStep);
+    };
+
+    f32x16 acc[TV][TM];                                                     // [vocabulary tile][row tile]
+#pragma unroll
+    for (int a = 0; a < TV; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+    const uint32_t wrow = (uint32_t)(wn * 32 * TV + nn) * kRow, hrow = (uint32_t)(BN + wm * (BM / 2) + nn) * kRow, turn = (uint32_t)(nn & 7);
+    auto multiply = [&](int stage) {
+        const unsigned char* sW = lds + stage * kStage + wrow;
+        const unsigned char* sH = lds + stage * kStage + hrow;
+        // operand fragments of k-step ks+1 are read from LDS while the MFMAs of k-step ks run
+        bf16x8 wf[2][TV], hf[2][TM];
+        auto read_frags = [&](int ks, int set) {
+            const uint32_t c = ((uint32_t)(2 * ks + half) ^ turn) * 16u;
+#pragma unroll
+            for (int a = 0; a < TV; ++a) wf[set][a] = *reinterpret_cast<const bf16x8*>(sW + a * 32 * kRow + c);
+#pragma unroll
+            for (int b = 0; b < TM; ++b) hf[set][b] = *reinterpret_cast<const bf16x8*>(sH + b * 32 * kRow + c);
+        };
+        read_frags(0, 0);
+#pragma unroll
+        for (int ks = 0; ks < kLBK / 16; ++ks) {
+            if (ks + 1 < kLBK / 16) read_frags(ks + 1, (ks + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int a = 0; a < TV; ++a)
+#pragma unroll
+                for (int b = 0; b < TM; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][a], hf[ks & 1][b], acc[a][b], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+#pragma unroll
+    for (int q = 0; q < S - 1; ++q) request(q, q);
+    int stage = 0;
+    for (int kb = 0; kb < KB; ++kb) {
+        // this wave's share of k-block kb is there once no more than what it asked for after that is outstanding
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((S - 2) * (WI + HI)) : "memory");
+        request(kb + S - 1, stage == 0 ? S - 1 : stage - 1);
+        multiply(stage);
+        stage = (stage + 1 == S) ? 0 : stage + 1;
+    }
+    if (tid < BM) s_invt[tid] = inv_temperature(my_temp);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                        // nothing is on its way to LDS any more
+    __syncthreads();
+    // ---- epilogue: every wave turns its 32x32 blocks through a private patch carved from the stages
+    unsigned char* tpatch = lds + wave * kPatchBytes;
+#pragma unroll
+    for (int a = 0; a < TV; ++a)
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+            store_tile_32x32_t(acc[a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
+}
+
 // ---------------------------------------------------------------- fp32 operands: one output per thread
 // Workgroup = 8 rows x 32 vocabulary entries; a half-wave shares one row, so the tile partials are a
 // half-wave reduction.  Only the tiny correctness configuration stores fp32 weights.
@@ -1005,6 +1125,21 @@ static hipError_t launch_tile(const ProfScope* prof, const tabed_cfg& c, const W
     return hipSuccess;
 }
 
+template <int BM, int BN, int S>
+static hipError_t launch_dma(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
+                             const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
+    const size_t lds = (size_t)S * (BM + BN) * kLBK * 2;
+    static_assert((size_t)S * (BM + BN) * kLBK * 2 >= 8 * kPatchBytes, "the epilogue's patches");
+    static std::once_flag once;
+    static hipError_t rc = hipSuccess;
+    if (raise_lds_limit(&k_lmhead_dma<BM, BN, S>, lds, once, rc) != hipSuccess) return rc;
+    const int mblocks = (M + BM - 1) / BM, nblocks = (c.V + BN - 1) / BN;
+    const int nrounds = (nblocks + 7) / 8;             // vocabulary blocks are dealt to the 8 XCDs in rounds
+    launch(prof, k_lmhead_dma<BM, BN, S>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
+           static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
+    return hipSuccess;
+}
+
 hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, const void* W, const void* H,
                          const float* temperature, float* logits, hipStream_t s, int prof_id) {
     ProfScope prof(prof_id, s);
@@ -1043,7 +1178,20 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
         // take a second round over the compute units: a draft step of 256 rows of V = 40000, d = 1024 48 us with 157 workgroups of
         // 256 x 256, 54 with 314
         auto tiles = [&](int bm, int bn) { return (long)((M + bm - 1) / bm) * ((c.V + bn - 1) / bn); };
-        if (M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
+        // Rows of whole lines: operands go straight to LDS.  Whole draft steps in us, straight / through registers: 337 / 354 at 512
+        // rows of V = 128256, d = 2048; 66.1 / 70.5 at 160 rows of 50261, 1152; 24.9 / 25.4 at 128 of 32000, 768; 87.5 / 94.3 at 96 of
+        // 152064, 896; 76.4 / 76.3 at 96 of 32000, 4096; 19.7 / 19.8 at 256 of 9000, 512.  With one or two k-blocks there is nothing to have in
+        // flight: 16.3 / 15.9 at 400 rows of 8000, 64, 33.6 / 33.1 at 256 of 65536, 128.
+        const bool lines = c.d % kLBK == 0 && c.d >= 512;
+        if (lines && M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
+            e = launch_dma<256, 256, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else if (lines && tiles(128, 256) >= 192)
+            e = launch_dma<128, 256, 3>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else if (lines && tiles(128, 128) > 256)       // two workgroups a compute unit (192 rows of 20000, 896 33.7 us with one, 29.0; 30.2 through registers)
+            e = launch_dma<128, 128, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else if (lines)
+            e = launch_dma<128, 128, 4>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+        else if (M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
             e = launch_tile<256, 256, 1, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (tiles(128, 256) >= 192) e = launch_tile<128, 256, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else e = launch_tile<128, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
