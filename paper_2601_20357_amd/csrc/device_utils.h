@@ -136,13 +136,15 @@ __device__ __forceinline__ int wave_max_i32(int v) {
 }
 // Smallest `first_key` over the workgroup (keys order the candidates along the prefix); if no thread offers
 // one (first_key = INT_MAX everywhere), the largest `last_key`; -1 if there is none either.
-__device__ __forceinline__ int block_pick_key(int first_key, int last_key, int* lds_first4, int* lds_last4) {
+template <int NW = kWavesPerBlock>                       // waves of the workgroup
+__device__ __forceinline__ int block_pick_key(int first_key, int last_key, int* lds_first, int* lds_last) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int f = wave_min_i32(first_key), l = wave_max_i32(last_key);
-    if (lane == 0) { lds_first4[w] = f; lds_last4[w] = l; }
+    if (lane == 0) { lds_first[w] = f; lds_last[w] = l; }
     __syncthreads();
-    const int first = min(min(lds_first4[0], lds_first4[1]), min(lds_first4[2], lds_first4[3]));
-    const int last = max(max(lds_last4[0], lds_last4[1]), max(lds_last4[2], lds_last4[3]));
+    int first = lds_first[0], last = lds_last[0];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) { first = min(first, lds_first[i]); last = max(last, lds_last[i]); }
     __syncthreads();
     return first != 0x7fffffff ? first : last;
 }

@@ -220,9 +220,13 @@ struct SampleArgs {
 // loads before the first use and keeps its tile values in registers.  N = number of drafts when it is known
 // at compile time (0 = run time): then the partials are read ONCE, each thread keeping the n*TI terms
 // ps*exp(pm - m_j) of its own run of tiles in registers for both the log-sum-exp and the tile masses.
-template <int TI, int N>
-__global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
-    const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <int TI, int N, int THR = kBlock>
+__global__ __launch_bounds__(THR) void k_sample(SampleArgs a) {
+    constexpr int NWV = THR / kWave;
+    static_assert(N == 0 || THR == kBlock, "the sums of the single pass are those of four waves");
+    const int c = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int b = (int)blockIdx.x + c;                           // (blockIdx.x + c) % B, c < 8
+    while (b >= a.B) b -= a.B;
     const int n = (N > 0) ? N : a.n, NT = a.NT, V = a.V;
     const int sib = a.S > 0 ? (int)blockIdx.z + 1 : 0;     // 0: the trunk token; siblings of a position in one launch
     // Workgroup 0 of a sequence always has work, so its temperature load overlaps the loads below; the
@@ -234,17 +238,17 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     __shared__ double s_S[TABED_MAX_N];   // sum_v exp(scaled - max)
     __shared__ double s_c[TABED_MAX_N];   // w_j / S_j
     __shared__ float s_cf[TABED_MAX_N];
-    __shared__ int s_first[kWavesPerBlock], s_lastw[kWavesPerBlock], s_tile, s_last;
+    __shared__ int s_first[NWV], s_lastw[NWV], s_tile, s_last;
     __shared__ double s_prefix;
-    __shared__ Top3 s_top[kWavesPerBlock];
+    __shared__ Top3 s_top[NWV];
     __shared__ double s_term[TABED_MAX_N][kTileV];
-    __shared__ float s_wm[kWavesPerBlock][TABED_MAX_N];
-    __shared__ double s_wsum[kWavesPerBlock][TABED_MAX_N];
-    __shared__ double s_wtot[kWavesPerBlock][8];        // wave totals of the tile-mass scan, per chunk row
-    constexpr int kMaxTiles = kBlock * TI, kMaxListed = 64;                // greedy rows: tiles that may hold the arg-max
+    __shared__ float s_wm[NWV][TABED_MAX_N];
+    __shared__ double s_wsum[NWV][TABED_MAX_N];
+    __shared__ double s_wtot[NWV][8];        // wave totals of the tile-mass scan, per chunk row
+    constexpr int kMaxTiles = THR * TI, kMaxListed = 64;                // greedy rows: tiles that may hold the arg-max
     __shared__ uint32_t s_live[(kMaxTiles + 31) / 32];
     __shared__ int s_list[kMaxListed], s_count;
-    __shared__ ArgMax s_wtop[kWavesPerBlock];
+    __shared__ ArgMax s_wtop[NWV];
     __shared__ float s_reach;
 
     const float* pmb = a.pm + (size_t)b * n * NT;      // partials of this sequence: [n][NT]
@@ -264,7 +268,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     constexpr bool CHUNKED = (TI >= 4);
     constexpr int TPC = CHUNKED ? 4 : TI;              // tiles per chunk
     constexpr int Q = TI / TPC;                        // chunks per thread
-    auto tile_of = [&](int i) { return CHUNKED ? ((i / 4) * kBlock + tid) * 4 + (i & 3) : tid * TI + i; };
+    auto tile_of = [&](int i) { return CHUNKED ? ((i / 4) * THR + tid) * 4 + (i & 3) : tid * TI + i; };
 
     // this thread's tiles of one draft's partials: maxima and, with WITH_SUMS, sums
     auto load_tiles = [&](int j, float (&m)[TI], float (&sum)[TI], auto with_sums) {
@@ -335,8 +339,8 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         }
     } else {
         // ---- per-draft log-sum-exp: one wave per draft row, lanes strided over the row's tiles
-        constexpr int TL = TI * kWavesPerBlock;        // tiles per lane when one wave covers a whole row
-        for (int j = wave; j < n; j += kWavesPerBlock) {
+        constexpr int TL = TI * NWV;        // tiles per lane when one wave covers a whole row
+        for (int j = wave; j < n; j += NWV) {
             float pmv[TL], psv[TL];
 #pragma unroll
             for (int i = 0; i < TL; ++i) {
@@ -424,13 +428,15 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
                 for (int w = 0; w < wave; ++w) before += s_wtot[w][q];
                 excl[q] = before + (cinc[q] - cs[q]);
                 if (cs[q] > 0.0) {
-                    if (first_key == 0x7fffffff && excl[q] + cs[q] > target) first_key = q * kBlock + tid;
-                    last_key = q * kBlock + tid;
+                    if (first_key == 0x7fffffff && excl[q] + cs[q] > target) first_key = q * THR + tid;
+                    last_key = q * THR + tid;
                 }
-                rowbase += ((s_wtot[0][q] + s_wtot[1][q]) + s_wtot[2][q]) + s_wtot[3][q];
+                double row = s_wtot[0][q];
+                for (int w = 1; w < NWV; ++w) row += s_wtot[w][q];
+                rowbase += row;
             }
         }
-        const int key = block_pick_key(first_key, last_key, s_first, s_lastw);   // -1 only if every mass is zero
+        const int key = block_pick_key<NWV>(first_key, last_key, s_first, s_lastw);   // -1 only if every mass is zero
         if (key < 0) {
             if (tid == 0) {
                 a.draft_tokens[out_idx] = 0;
@@ -439,8 +445,8 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
             }
             return;
         }
-        if (tid == (key & (kBlock - 1))) {
-            const int qs = key / kBlock;
+        if (tid == (key & (THR - 1))) {
+            const int qs = key / THR;
             double P = 0.0, Plast = 0.0;
             int istar = -1, ilast = 0;
 #pragma unroll
@@ -466,7 +472,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         // ---- the tile's logits: thread (draft j, lane v) -> one round trip for all drafts, summed by wave 0
         {
             const int vl = tid & (kTileV - 1), v = s_tile * kTileV + vl;
-            for (int j = tid / kTileV; j < n; j += kBlock / kTileV)
+            for (int j = tid / kTileV; j < n; j += THR / kTileV)
                 s_term[j][vl] = (v < V) ? s_c[j] * (double)__expf(rows[(size_t)j * V + v] * invT - s_m[j]) : 0.0;
         }
         __syncthreads();
@@ -528,10 +534,12 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         if (tile_of(i) < NT) top = argmax_merge(top, ArgMax{ub[i], tile_of(i)});
     top = wave_argmax(top);
     if (lane == 0) s_wtop[wave] = top;
-    for (int i = tid; i < (kMaxTiles + 31) / 32; i += kBlock) s_live[i] = 0u;
+    for (int i = tid; i < (kMaxTiles + 31) / 32; i += THR) s_live[i] = 0u;
     if (tid == 0) s_count = 0;
     __syncthreads();
-    const int t0 = argmax_merge(argmax_merge(s_wtop[0], s_wtop[1]), argmax_merge(s_wtop[2], s_wtop[3])).i;
+    ArgMax first = s_wtop[0];
+    for (int w = 1; w < NWV; ++w) first = argmax_merge(first, s_wtop[w]);
+    const int t0 = first.i;
     // the mixture at one vocabulary entry, drafts in order, and whether it may be drawn
     auto mixture = [&](int v) {
         float q = 0.f;
@@ -576,7 +584,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
         if (c != 0) return;
         // a half-wave takes TB tiles at a time, all drafts of all of them requested together (64 tiles one after the other: 11 us)
         auto evaluate = [&](auto tb) {
-            constexpr int TB = tb.value, kApart = kBlock / kTileV;
+            constexpr int TB = tb.value, kApart = THR / kTileV;
             for (int a0 = tid >> 5; a0 < listed; a0 += TB * kApart) {
                 int v[TB];
                 float q[TB];
@@ -606,16 +614,17 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
                     if (a0 + b * kApart < listed && may_draw(v[b])) best = top3_push(best, q[b], v[b]);
             }
         };
-        if (listed <= kBlock / kTileV) evaluate(std::integral_constant<int, 1>{});
+        if (listed <= THR / kTileV) evaluate(std::integral_constant<int, 1>{});
         else evaluate(std::integral_constant<int, 4>{});
     } else {
         for (int cb = c * kChunkV; cb < V; cb += a.C2 * kChunkV) {
-            float q[4][4];
-            bool live[4];
-            int at[4];
+            constexpr int UG = kChunkV / (THR * 4);        // groups of four entries a thread
+            float q[UG][4];
+            bool live[UG];
+            int at[UG];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int v = cb + (u * kBlock + tid) * 4, t = min(v, V - 1) / kTileV;
+            for (int u = 0; u < UG; ++u) {
+                const int v = cb + (u * THR + tid) * 4, t = min(v, V - 1) / kTileV;
                 live[u] = (s_live[t >> 5] >> (t & 31)) & 1u;
                 at[u] = live[u] ? group_at(v, V) : 0;      // (a group that cannot matter costs one shared line: behind a branch,
                                                            // every load waited for the one before it, 9 us a chunk)
@@ -624,25 +633,25 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
             }
             constexpr int JB = 4;                          // draft rows requested together
             for (int j0 = 0; j0 < n; j0 += JB) {
-                float4 x[JB][4];
+                float4 x[JB][UG];
 #pragma unroll
                 for (int jj = 0; jj < JB; ++jj)            // past the last draft: re-read, not used
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)            // (more than kMaxListed tiles: not a short row)
+                    for (int u = 0; u < UG; ++u)            // (more than kMaxListed tiles: not a short row)
                         x[jj][u] = load_group(rows + (size_t)min(j0 + jj, n - 1) * V, at[u]);
 #pragma unroll
                 for (int jj = 0; jj < JB; ++jj)
                     if (j0 + jj < n) {
                         const float cj = s_cf[j0 + jj], mj = s_m[j0 + jj];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u)
+                        for (int u = 0; u < UG; ++u)
 #pragma unroll
                             for (int e = 0; e < 4; ++e) q[u][e] += cj * __expf(f4get(x[jj][u], e) * invT - mj);
                     }
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int v = cb + (u * kBlock + tid) * 4;
+            for (int u = 0; u < UG; ++u) {
+                const int v = cb + (u * THR + tid) * 4;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (live[u] && at[u] + e >= v && may_draw(at[u] + e)) best = top3_push(best, q[u][e], at[u] + e);
@@ -654,7 +663,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     __syncthreads();
     if (!few && tid == 0) {
         Top3 t = s_top[0];
-        for (int w = 1; w < kWavesPerBlock; ++w) t = top3_merge(t, s_top[w]);
+        for (int w = 1; w < NWV; ++w) t = top3_merge(t, s_top[w]);
         if (sib == 0) {
             Top2Rec* rec = &a.cand[(size_t)b * a.C2 + c];
             publish_store(&rec->v1, t.v1);
@@ -672,7 +681,7 @@ __global__ __launch_bounds__(kBlock) void k_sample(SampleArgs a) {
     Top3 t = top3_empty();
     if (few) {
         if (tid >= kWave) return;
-        if (lane < kWavesPerBlock) t = s_top[lane];
+        if (lane < NWV) t = s_top[lane];
     } else {
         publish_barrier();                                 // the candidate's stores are acknowledged
         if (tid == 0) s_last = arrive(&a.tickets[((size_t)rank * a.B + b) * a.TS], (uint32_t)a.C2) ? 1 : 0;
@@ -724,25 +733,36 @@ static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char*
     // siblings: the counters and the room of the tree passes, which run after them (3 C2 <= NSEG wherever a row is shared)
     a.cand3 = reinterpret_cast<Top3Rec*>(ws + L.off_tseg);
     a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + (S > 0 ? 3 : 0) * (size_t)c.B * L.TS;
-    const dim3 grid(L.C2, c.B, S > 0 ? S : 1);
     const int ti = (L.NT + kBlock - 1) / kBlock;
+    const bool wide = (ti > 8 && c.n > 4) || ti > 20;
+    // Eight waves of 250 registers: one workgroup a compute unit, so that half as many share a greedy row where all would not fit at once.
+    if (wide && ti <= 24 && (long)c.B * a.C2 > 256) a.C2 = (a.C2 + 1) / 2;
+    // The first workgroups of the rows, which do the work of sampling rows alone, on every XCD in turn (all on one with the row's
+    // workgroups next to each other: V = 128256, 8 drafts, 64 sampling rows, a draft step with d = 256 128 us, 103 so), and a greedy
+    // row's on different ones.
+    const dim3 grid(c.B, a.C2, S > 0 ? S : 1);
     // single-pass instantiations: compile-time draft counts whose n*TI terms (x3 registers) fit a 512-register wave
 #define TABED_LAUNCH_SAMPLE_N(TI_, N_) launch(&prof, k_sample<TI_, N_>, grid, dim3(kBlock), 0, s, a)
+    // Vocabularies of more than 65536 with more than four drafts, or of more than 163840: eight waves, since one workgroup a row
+    // reads all of its partials twice (sampler at V = 128256, 8 drafts, 64 sequences, half of them greedy: 37 us with four waves and
+    // all rows' first workgroups on one XCD, 27; draft steps of small batches: 8 drafts of 70000 34.9 / 30.7 us, 16 of 150001 58.6 / 44.9,
+    // 8 of 190001 68 / 49; rows of equal logits, 4 sequences of 8 drafts 64 / 52).
 #define TABED_LAUNCH_SAMPLE(TI_, ALLOW8_)                                       \
     do {                                                                        \
         if (c.n == 1) TABED_LAUNCH_SAMPLE_N(TI_, 1);                            \
         else if (c.n == 2) TABED_LAUNCH_SAMPLE_N(TI_, 2);                       \
         else if (c.n == 3) TABED_LAUNCH_SAMPLE_N(TI_, 3);                       \
         else if (c.n == 4) TABED_LAUNCH_SAMPLE_N(TI_, 4);                       \
-        else if (c.n == 5 && ALLOW8_) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 5 : 1)); \
-        else if (c.n == 8 && ALLOW8_) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 8 : 1)); \
-        else TABED_LAUNCH_SAMPLE_N(TI_, 0);                                     \
+        else if (c.n == 5) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 5 : 1));       \
+        else if (c.n == 8) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 8 : 1));       \
+        else TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 0 : 1));                     \
     } while (0)
     if (ti <= 1) TABED_LAUNCH_SAMPLE(1, true);
     else if (ti <= 4) TABED_LAUNCH_SAMPLE(4, true);
     else if (ti <= 8) TABED_LAUNCH_SAMPLE(8, true);
-    else if (ti <= 20) TABED_LAUNCH_SAMPLE(20, false);
-    else if (ti <= 32) TABED_LAUNCH_SAMPLE_N(32, 0);
+    else if (!wide) TABED_LAUNCH_SAMPLE(20, false);
+    else if (ti <= 24) launch(&prof, k_sample<12, 0, 512>, grid, dim3(512), 0, s, a);
+    else if (ti <= 32) TABED_LAUNCH_SAMPLE_N(32, 0);   // (eight waves of 16 tiles a thread spill)
     else return hipErrorInvalidValue;              // V > 262144: validate_cfg rejects it before this point
 #undef TABED_LAUNCH_SAMPLE_N
 #undef TABED_LAUNCH_SAMPLE
