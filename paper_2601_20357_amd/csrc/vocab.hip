@@ -421,18 +421,24 @@ __global__ __launch_bounds__(THR) void k_sample(SampleArgs a) {
         double excl[Q];
         int first_key = 0x7fffffff, last_key = -1;
         {
-            double rowbase = 0.0;
+            double rowbase = 0.0, wt[NWV][Q];              // all totals requested together (one after the other 1 us at V = 152064)
+#pragma unroll
+            for (int w = 0; w < NWV; ++w)
+#pragma unroll
+                for (int q = 0; q < Q; ++q) wt[w][q] = s_wtot[w][q];
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
                 double before = rowbase;
-                for (int w = 0; w < wave; ++w) before += s_wtot[w][q];
+#pragma unroll
+                for (int w = 0; w < NWV - 1; ++w) before = (w < wave) ? before + wt[w][q] : before;
                 excl[q] = before + (cinc[q] - cs[q]);
                 if (cs[q] > 0.0) {
                     if (first_key == 0x7fffffff && excl[q] + cs[q] > target) first_key = q * THR + tid;
                     last_key = q * THR + tid;
                 }
-                double row = s_wtot[0][q];
-                for (int w = 1; w < NWV; ++w) row += s_wtot[w][q];
+                double row = wt[0][q];
+#pragma unroll
+                for (int w = 1; w < NWV; ++w) row += wt[w][q];
                 rowbase += row;
             }
         }
