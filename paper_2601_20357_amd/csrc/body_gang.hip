@@ -141,8 +141,8 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
     if (tid == 0)
         before = __hip_atomic_fetch_or(reinterpret_cast<uint64_t*>(ctl + (kLineReg + (blockIdx.x & 7)) * 32), 1ull << (blockIdx.x >> 3),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // ---- positions and tokens.  (A workgroup that reads them after the positions have moved on has no item left that counts:
-    //      they move on when all items are done.)
+    // ---- positions and tokens.  (The positions move on when all workgroups have left: one that read them later would cut the
+    //      attention into other pieces than the rest, and could wait for pieces that nobody computes.)
     if (wave == 1) {
         const int r = min(lane, rows - 1);
         const int pos = min(max(a.ctx_len[r], 0), a.max_ctx - 1);
@@ -804,7 +804,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
             if (l + 1 < a.layers) touch_layer(l + 1);                       // in the shadow of the phases that end the layer
         }
 
-        // ================================================================ final norm, positions move on
+        // ================================================================ final norm
         new_phase();
         const uint32_t xo = (uint32_t)(a.layers - 1) * a.layer_bytes + a.off_xm;
         if (wave == 0) {
@@ -841,15 +841,15 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
                             pack_bf16x4(v[i][0] * inv * g[0], v[i][1] * inv * g[1], v[i][2] * inv * g[2], v[i][3] * inv * g[3]);
                     }
                 }
-                if (lane == 0) a.ctx_len[row] += 1;
             }
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                    // no word is on its way to LDS any more
     }
-    // ---- the last workgroup to leave re-arms the control block for the next launch
+    // ---- the last workgroup to leave moves the positions on and re-arms the control block for the next launch
     if (tid == 0) {
         const uint32_t left = __hip_atomic_fetch_add(ctl + kLineExit * 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (left == kGangGroups - 1) {
+            for (int r = 0; r < a.rows; ++r) __hip_atomic_fetch_add(a.ctx_len + r, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             uint64_t* state = reinterpret_cast<uint64_t*>(ctl + kLineState * 32);
             __hip_atomic_store(state, a.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(state + 1, (uint64_t)(s_set ^ 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

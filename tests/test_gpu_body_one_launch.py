@@ -33,6 +33,16 @@ def test_one_launch_step_matches_the_oracle(oracle, name, bc, ctx):
         pair.step(g.integers(0, bc.V, size=len(ctx)))
 
 
+def test_positions_that_change_how_the_attention_is_cut(oracle):
+    """Most workgroups have no projection to do here, and with every 32 positions a row's keys are cut into one more piece: a
+    workgroup that took the positions of the step after would wait for pieces that nobody computes.  Steps across two such edges."""
+    bc = B(layers=1, d=64, heads=1, d_ff=8, V=30, max_ctx=200)
+    pair = BodyPair(oracle, bc, 3, seed=4, fill=lambda g: [30, 62, 95])
+    g = np.random.default_rng(8)
+    for _ in range(36):
+        pair.step(g.integers(0, bc.V, size=3))
+
+
 class _Device:
     """One body on the GPU: weights, caches, a step from the same start whenever asked."""
 
