@@ -635,6 +635,8 @@ BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     const size_t S = (size_t)attn_splits(c, rows);
     size_t off = 0;
     L.off_ctl = off;  off += kGangControlBytes;
+    // (here, so that where its buffers are follows from the sizes that the control block remembers them by, which leave max_ctx out)
+    L.off_gang = off; off = al256(off + (gang_applies(c, rows) ? gang_bytes(c, rows) : 0));
     L.off_x = off;    off = al256(off + sizeof(float) * (size_t)rows * c.d);
     L.off_q = off;    off = al256(off + sizeof(float) * (size_t)rows * c.d);
     L.off_trig = off; off = al256(off + sizeof(double2) * (size_t)rows * ((c.d / c.heads) / 2));
@@ -650,7 +652,6 @@ BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     L.off_y = off;    off = al256(off + (many ? sizeof(float) * (size_t)rows * std::max(3 * c.d, 2 * c.d_ff) : 0));
     L.off_gemm = off; off = al256(off + gemm);
     L.off_ones = off; off = al256(off + (many ? sizeof(float) * (size_t)rows : 0));
-    L.off_gang = off; off = al256(off + (gang_applies(c, rows) ? gang_bytes(c, rows) : 0));
     L.total = off;
     return L;
 }

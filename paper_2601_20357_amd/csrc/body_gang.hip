@@ -59,7 +59,7 @@ struct GangArgs {
     uint32_t* ctl;
     char* buf;                                       // two sets; layer l of a set at l * layer_bytes
     uint32_t layer_bytes, set_bytes;
-    uint64_t key;                                    // the sizes that the buffers' layout follows from
+    uint64_t key;                                    // the sizes that the buffers' place and layout follow from
     uint32_t off_q, off_kn, off_vn, off_po, off_att, off_xa, off_act, off_xm;
     tabed_body_weights w;
 };
@@ -925,6 +925,7 @@ hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, cha
     a.token_src = token_src; a.token_stride = token_stride; a.rows_per_token = rows_per_token;
     a.ctx_len = ctx_len; a.kcache = kcache; a.vcache = vcache; a.H = H;
     a.ctl = reinterpret_cast<uint32_t*>(ctl); a.buf = buf; a.layer_bytes = L.layer; a.set_bytes = L.layer * (uint32_t)c.layers;
+    static_assert(TABED_BODY_MAX_LAYERS < 256, "the key's fields");
     a.key = 1ull | ((uint64_t)rows << 1) | ((uint64_t)c.layers << 8) | ((uint64_t)c.d << 16) | ((uint64_t)c.heads << 32) | ((uint64_t)c.d_ff << 44);
     a.off_q = L.off_q; a.off_kn = L.off_kn; a.off_vn = L.off_vn; a.off_po = L.off_po; a.off_att = L.off_att; a.off_xa = L.off_xa; a.off_act = L.off_act; a.off_xm = L.off_xm;
     a.w = w;

@@ -105,6 +105,7 @@ hipError_t launch_philox(const tabed_cfg& c, uint64_t round, float* out, hipStre
 constexpr size_t kGangControlBytes = 4096;           // counters of the one-launch step
 struct BodyLayout {
     size_t off_ctl;    // uint32: the one-launch step's counters, always first
+    size_t off_gang;   // one-launch step only: its buffers, layer after layer, always next
     size_t off_x;      // float [rows,d] residual stream
     size_t off_q;      // float [rows,d] rotated queries of the current layer
     size_t off_trig;   // double2 [rows][head_dim/2] cos and sin of the rows' positions
@@ -115,7 +116,6 @@ struct BodyLayout {
     size_t off_y;      // many rows (GEMM route) only: float [rows, max(3d, 2 d_ff)] result of the current projection,
     size_t off_gemm;   //   scratch of the GEMM launches (softmax partials nobody reads),
     size_t off_ones;   //   float [rows]: the "temperature" they divide by
-    size_t off_gang;   // one-launch step only: its buffers, layer after layer
     size_t total;
 };
 BodyLayout body_layout(const tabed_body_cfg& c, int rows);

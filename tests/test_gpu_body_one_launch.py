@@ -103,6 +103,18 @@ def test_a_workspace_shared_with_other_sizes_gives_the_same_results():
         assert _same(torch, devs[i].once(ws), alone[i]), i
 
 
+@pytest.mark.parametrize("ctx_a,ctx_b", [(80, 256), (256, 1024), (1024, 80)])
+def test_a_workspace_shared_by_bodies_that_differ_in_the_cache_length(ctx_a, ctx_b):
+    """The launches per phase would cut such bodies' attention into other numbers of ranges; the one-launch step's buffers are the same."""
+    torch, binding = _gpu()
+    devs = [_Device(torch, binding, B(layers=3, d=768, heads=12, d_ff=520, V=50, max_ctx=m), 4, 5 + i) for i, m in enumerate((ctx_a, ctx_b))]
+    alone = [d.once() for d in devs]
+    ws = torch.full((max(binding.tabed_body_workspace_bytes(d.cfg, d.rows) for d in devs),), 0x5A, dtype=torch.uint8, device="cuda")
+    binding.tabed_body_workspace_init(devs[0].cfg, devs[0].rows, ws)
+    for i in (0, 1, 0, 1, 1, 0, 0, 1):
+        assert _same(torch, devs[i].once(ws), alone[i]), i
+
+
 def test_graph_replays_of_one_launch_steps():
     """Three steps in a graph, replayed with eager steps and synchronisation in between: each replay gives what eager steps give."""
     torch, binding = _gpu()
