@@ -308,6 +308,12 @@ size_t tabed_body_workspace_bytes(const tabed_body_cfg* cfg, int32_t rows) {
     return body_layout(*cfg, rows).total;
 }
 
+// For the tests, not declared in the header: how a body step runs.  0: one launch; s > 0: a launch per phase, keys in s ranges.
+int tabed_testing_body_route(const tabed_body_cfg* cfg, int32_t rows) {
+    const int rc = validate_body_cfg(cfg, rows);
+    return rc == TABED_OK ? body_route(*cfg, rows) : rc;
+}
+
 int tabed_body_workspace_init(const tabed_body_cfg* cfg, int32_t rows, void* ws, void* stream) {
     const int rc = validate_body_cfg(cfg, rows);
     if (rc != TABED_OK) return rc;

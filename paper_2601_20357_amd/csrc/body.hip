@@ -629,6 +629,8 @@ static int attn_splits(const tabed_body_cfg& c, int rows) {
     return S;
 }
 
+int body_route(const tabed_body_cfg& c, int rows) { return gang_applies(c, rows) ? 0 : attn_splits(c, rows); }
+
 BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     BodyLayout L;
     const int act = (c.d > c.d_ff) ? c.d : c.d_ff;

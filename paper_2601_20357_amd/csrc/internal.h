@@ -124,6 +124,7 @@ hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStre
 hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w, char* ws, int rows,
                             const int32_t* token_src, int token_stride, int rows_per_token, int32_t* ctx_len,
                             uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s);
+int body_route(const tabed_body_cfg& c, int rows);
 bool gang_applies(const tabed_body_cfg& c, int rows);
 size_t gang_bytes(const tabed_body_cfg& c, int rows);
 uint64_t* gang_key(char* ctl);

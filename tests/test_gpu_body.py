@@ -12,6 +12,8 @@ format itself (measured: relative RMS difference 2.7e-4 after one layer, 6e-4 af
     (2^-7 relative, with an absolute floor for entries near zero);
 cache entries written by the step obey the same bars, every other cache entry is untouched, positions advance
 exactly.  Each step is judged from a common state."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -252,18 +254,21 @@ def test_rounds_with_the_body_in_the_loop_are_reproducible_bit_for_bit():
     assert all(torch.isfinite(t[2]).all() for t in one[:3])
 
 
-# Where the step's kernels change: key ranges 2, 4, 8 merged by the output projection (few rows, long caches); rows normalised by
+# Where the step's kernels change (each a launch per phase): key ranges 2, 4, 8 merged by the output projection (few rows, long caches); rows normalised by
 # the projection in one and two row blocks of three and of four column pieces, in one of eight (1024 < d <= 2048, up to 16 rows),
 # by a kernel of their own (more rows, or d > 2048); projections of bf16 rows in one and two row blocks with 12, 13..16, up to 48
 # and more k-blocks of 64, the last of them ragged; the GEMM route (many rows).
 ROUTES = [
-    ("ranges8_hd64", synth.BodyConfig(layers=2, d=256, heads=4, d_ff=1024, V=100, max_ctx=1100), 3, 8),
+    ("ranges8_hd64", synth.BodyConfig(layers=2, d=256, heads=4, d_ff=4104, V=100, max_ctx=1100), 3, 8),
+    ("ranges8_hd64_d1024", synth.BodyConfig(layers=1, d=1024, heads=16, d_ff=4096, V=64, max_ctx=1100), 1, 8),
+    ("ranges8_hd128_d1024", synth.BodyConfig(layers=1, d=1024, heads=8, d_ff=4096, V=64, max_ctx=1100), 4, 8),
     ("ranges8_hd16", synth.BodyConfig(layers=1, d=48, heads=3, d_ff=80, V=40, max_ctx=520), 17, 8),
     ("ranges4_hd16", synth.BodyConfig(layers=1, d=48, heads=3, d_ff=80, V=40, max_ctx=400), 17, 4),
     ("ranges4_hd64", synth.BodyConfig(layers=1, d=768, heads=12, d_ff=264, V=40, max_ctx=260), 20, 4),
     ("ranges2_hd128", synth.BodyConfig(layers=1, d=512, heads=4, d_ff=264, V=40, max_ctx=140), 50, 2),
     ("two_row_blocks", synth.BodyConfig(layers=1, d=768, heads=24, d_ff=2056, V=64, max_ctx=33), 49, 1),
-    ("d1024_one_row_block", synth.BodyConfig(layers=1, d=1024, heads=8, d_ff=1000, V=64, max_ctx=20), 9, 1),
+    ("d1024_one_row_block", synth.BodyConfig(layers=1, d=1024, heads=8, d_ff=4104, V=64, max_ctx=20), 9, 1),
+    ("d1024_one_row_block_16", synth.BodyConfig(layers=1, d=1024, heads=16, d_ff=4104, V=64, max_ctx=20), 16, 1),
     ("d960_two_row_blocks", synth.BodyConfig(layers=1, d=960, heads=15, d_ff=2728, V=64, max_ctx=20), 49, 1),
     ("d1024_bf16_two_row_blocks", synth.BodyConfig(layers=1, d=1024, heads=8, d_ff=1024, V=64, max_ctx=12), 120, 1),
     ("bf16_two_row_blocks_12", synth.BodyConfig(layers=1, d=768, heads=12, d_ff=768, V=64, max_ctx=12), 176, 1),
@@ -279,19 +284,15 @@ ROUTES = [
 ]
 
 
-def _key_ranges(binding, bc, rows):
-    """Key ranges of the attention, from the room their partial results take (one range at 64 positions and less)."""
-    size = lambda max_ctx: binding.tabed_body_workspace_bytes(  # noqa: E731
-        binding.make_body_cfg(layers=bc.layers, d=bc.d, heads=bc.heads, d_ff=bc.d_ff, V=bc.V, max_ctx=max_ctx), rows)
-    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
-    room = size(bc.max_ctx) - size(min(bc.max_ctx, 64))
-    fits = [s for s in (2, 4, 8) if room == up(4 * s * rows * bc.d) + up(8 * s * rows * bc.heads)]
-    return fits[0] if fits else (1 if room == 0 else None)
+def _route(binding, bc, rows):
+    """0: the step is one launch; s > 0: a launch per phase, the keys in s ranges."""
+    cfg = binding.make_body_cfg(layers=bc.layers, d=bc.d, heads=bc.heads, d_ff=bc.d_ff, V=bc.V, max_ctx=bc.max_ctx)
+    return binding.load().tabed_testing_body_route(ctypes.byref(cfg), rows)
 
 
 @pytest.mark.parametrize("name,bc,rows,ranges", ROUTES, ids=[c[0] for c in ROUTES])
 def test_body_step_on_every_route(oracle, name, bc, rows, ranges):
-    assert _key_ranges(_gpu()[1], bc, rows) == ranges
+    assert _route(_gpu()[1], bc, rows) == ranges
     pair = BodyPair(oracle, bc, rows, seed=len(name), fill=lambda g: g.integers(0, bc.max_ctx - 2, size=rows))
     pair.ctx[0] = 0                                   # one key: every range but the first is empty
     pair.ctx[-1] = bc.max_ctx - 2

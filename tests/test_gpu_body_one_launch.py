@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2601_20357_amd import synth
-from test_gpu_body import BodyPair, _gpu, _to_dev
+from test_gpu_body import BodyPair, _gpu, _route, _to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -27,6 +27,7 @@ SHAPES = [
 
 @pytest.mark.parametrize("name,bc,ctx", SHAPES, ids=[s[0] for s in SHAPES])
 def test_one_launch_step_matches_the_oracle(oracle, name, bc, ctx):
+    assert _route(_gpu()[1], bc, len(ctx)) == 0
     pair = BodyPair(oracle, bc, len(ctx), seed=len(name), fill=lambda g: ctx)
     g = np.random.default_rng(7)
     for _ in range(2):
