@@ -288,7 +288,8 @@ int tabed_update_weights(const tabed_cfg* cfg, void* ws, uint64_t round, const f
  *                  incremented by the call; must stay below cfg->max_ctx
  *   kcache, vcache [layers,rows,max_ctx,d] bf16 in/out  entry ctx_len[r] of every row and layer is written
  *   H              [rows,d] bf16 out
- * `ws` is scratch of tabed_body_workspace_bytes(cfg, rows) bytes prepared once by tabed_body_workspace_init.
+ * `ws` is scratch of tabed_body_workspace_bytes(cfg, rows) bytes prepared once by tabed_body_workspace_init; it also serves steps of
+ * fewer rows.
  * Every pointer is 16-byte aligned (TABED_EALIGN otherwise); a ctx_len entry outside [0, max_ctx) is clamped into
  * the range, so nothing is written outside a row's cache.
  */

@@ -66,6 +66,8 @@ WsLayout ws_layout(const tabed_cfg& c) {
     return packed.total <= (size_t)TABED_STATIC_SCRATCH_BYTES ? packed : L;
 }
 
+size_t ws_bytes_unpacked(const tabed_cfg& c) { return layout_with(c, 32).total; }
+
 // ---------------------------------------------------------------- event timing
 struct ProfRec {
     int id;
@@ -305,7 +307,7 @@ int tabed_update_weights(const tabed_cfg* cfg, void* ws, uint64_t round, const f
 
 size_t tabed_body_workspace_bytes(const tabed_body_cfg* cfg, int32_t rows) {
     if (validate_body_cfg(cfg, rows) != TABED_OK) return 0;
-    return body_layout(*cfg, rows).total;
+    return body_workspace_bytes(*cfg, rows);
 }
 
 // For the tests, not declared in the header: how a body step runs.  0: one launch; s > 0: a launch per phase, keys in s ranges.

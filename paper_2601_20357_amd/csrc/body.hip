@@ -35,8 +35,9 @@ __global__ __launch_bounds__(kBlock) void k_body_embed(int d, int V, const int32
                                                        int rows_per_token, const uint16_t* __restrict__ embed,
                                                        float* __restrict__ x, const int32_t* __restrict__ ctx_len, int max_ctx,
                                                        int hd, double log2_theta, double2* __restrict__ trig /* [rows][hd/2] */,
-                                                       uint64_t* __restrict__ gang_key) {
+                                                       uint64_t* __restrict__ gang_key, float* __restrict__ ones /* [rows] or null */) {
     const int r = blockIdx.x;
+    if (ones != nullptr && threadIdx.x == 0) ones[r] = 1.f;     // each step: a step of fewer rows may have had the workspace in between
     if (r == 0 && threadIdx.x == 0) *gang_key = 0;      // a one-launch step on the same workspace finds its buffers used otherwise
     const int pos = min(max(ctx_len[r], 0), max_ctx - 1);
     int tok = token_src[(size_t)(r / rows_per_token) * token_stride];
@@ -453,11 +454,6 @@ __global__ __launch_bounds__(kBlock) void k_body_rope(int d, int hd, int max_ctx
     }
 }
 
-__global__ void k_body_fill_ones(float* p, int count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 1.f;
-}
-
 // ---------------------------------------------------------------- attention over the row's cache
 // Grid (head, row, key range), four waves.  A key's (value's) head slice is hd contiguous bf16: LPK = hd / 8 lanes read it
 // as 16-byte pieces, so one wave instruction fetches 64 / LPK whole slices.  Keys and values of a batch are requested
@@ -650,12 +646,21 @@ BodyLayout body_layout(const tabed_body_cfg& c, int rows) {
     size_t gemm = 0;
     if (many)
         for (const auto& kn : {std::pair<int, int>{c.d, 3 * c.d}, {c.d, c.d}, {c.d, 2 * c.d_ff}, {c.d_ff, c.d}})
-            gemm = std::max(gemm, ws_layout(gemm_cfg(rows, kn.first, kn.second)).total);
+            gemm = std::max(gemm, ws_bytes_unpacked(gemm_cfg(rows, kn.first, kn.second)));
     L.off_y = off;    off = al256(off + (many ? sizeof(float) * (size_t)rows * std::max(3 * c.d, 2 * c.d_ff) : 0));
     L.off_gemm = off; off = al256(off + gemm);
     L.off_ones = off; off = al256(off + (many ? sizeof(float) * (size_t)rows : 0));
     L.total = off;
     return L;
+}
+
+// What steps of any number of rows up to `rows` need.  More rows need more, except that the one-launch step (up to 16 rows) has
+// buffers that others have not, and that more rows have their keys in fewer ranges: each of these at the most rows that it occurs with.
+size_t body_workspace_bytes(const tabed_body_cfg& c, int rows) {
+    size_t most = 0;
+    for (int r : {rows, 16, 767 / (4 * c.heads), 767 / (2 * c.heads), 767 / c.heads})
+        if (r >= 1) most = std::max(most, body_layout(c, std::min(r, rows)).total);
+    return most;
 }
 
 int validate_body_cfg(const tabed_body_cfg* c, int rows) {
@@ -671,15 +676,8 @@ int validate_body_cfg(const tabed_body_cfg* c, int rows) {
     return TABED_OK;
 }
 
-// The one-launch step's control block (at the same place for all sizes: a workspace may be used for fewer rows than it was
-// prepared for), and for the GEMM route the temperatures (all one) that the LM head's kernels divide by.
-hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStream_t s) {
-    const BodyLayout L = body_layout(c, rows);
-    const hipError_t e = launch_gang_init(ws + L.off_ctl, s);
-    if (e != hipSuccess || fused_rows(c.d, rows)) return e;
-    launch(nullptr, k_body_fill_ones, dim3((rows + 255) / 256), dim3(256), 0, s, reinterpret_cast<float*>(ws + L.off_ones), rows);
-    return hipGetLastError();
-}
+// All that a step expects to find is the one-launch step's control block, at the same place for all sizes.
+hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStream_t s) { return launch_gang_init(ws + body_layout(c, rows).off_ctl, s); }
 
 template <int NW, int MB, int G, int CI, int IN, int EPI>
 static hipError_t launch_proj_t(int tiles, hipStream_t s, const ProjArgs& a) {
@@ -798,7 +796,7 @@ hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w
         ProfScope prof(TABED_K_BODY, s);
         launch(&prof, k_body_embed, dim3(rows), dim3(kBlock), 0, s, d, c.V, token_src, token_stride, rows_per_token,
                static_cast<const uint16_t*>(w.embed), base.x, static_cast<const int32_t*>(ctx_len), c.max_ctx, hd,
-               std::log2((double)c.rope_theta), trig, gang_key(ws + L.off_ctl));
+               std::log2((double)c.rope_theta), trig, gang_key(ws + L.off_ctl), many ? reinterpret_cast<float*>(ws + L.off_ones) : nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (int l = 0; l < c.layers; ++l) {

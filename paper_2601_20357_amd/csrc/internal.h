@@ -55,6 +55,7 @@ struct WsLayout {
     size_t total;
 };
 WsLayout ws_layout(const tabed_cfg& c);
+size_t ws_bytes_unpacked(const tabed_cfg& c);     // at least ws_layout(c).total, and never less for a larger B
 int validate_cfg(const tabed_cfg* c);
 
 // ---------------------------------------------------------------- launchers (each enqueues on `s`)
@@ -119,6 +120,7 @@ struct BodyLayout {
     size_t total;
 };
 BodyLayout body_layout(const tabed_body_cfg& c, int rows);
+size_t body_workspace_bytes(const tabed_body_cfg& c, int rows);
 int validate_body_cfg(const tabed_body_cfg* c, int rows);
 hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStream_t s);
 hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w, char* ws, int rows,

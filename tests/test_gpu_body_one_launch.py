@@ -116,6 +116,20 @@ def test_a_workspace_shared_by_bodies_that_differ_in_the_cache_length(ctx_a, ctx
         assert _same(torch, devs[i].once(ws), alone[i]), i
 
 
+def test_a_workspace_of_many_rows_serves_few_and_many_in_turn():
+    """Prepared for rows that take whole matrix products for the projections, then one-launch steps of 16 and 3 rows, whose buffers
+    need more room than those, and the many rows again."""
+    torch, binding = _gpu()
+    bc = B(layers=10, d=1024, heads=8, d_ff=8, V=50, max_ctx=6)
+    devs = [_Device(torch, binding, bc, rows, 5) for rows in (301, 16, 3)]
+    alone = [d.once() for d in devs]
+    ws = torch.full((binding.tabed_body_workspace_bytes(devs[0].cfg, 301) + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    binding.tabed_body_workspace_init(devs[0].cfg, 301, ws)
+    for i in (0, 1, 0, 2, 1, 2, 0):
+        assert _same(torch, devs[i].once(ws), alone[i]), i
+    assert bool((ws[-4096:] == 0x5A).all())
+
+
 def test_graph_replays_of_one_launch_steps():
     """Three steps in a graph, replayed with eager steps and synchronisation in between: each replay gives what eager steps give."""
     torch, binding = _gpu()
