@@ -23,7 +23,9 @@
 // buffers, used in turn: a launch fills the other set with the pattern for the next one (the end of a launch orders that).
 // The control block says which set is next and for which sizes they were filled; where the workspace was used for
 // something else in between, all fill both sets and wait for one another first.  A pattern is recognised per stored piece
-// of 4 or 8 bytes.
+// of 4 or 8 bytes.  A control block that was never prepared, or was written over, is known by a mark that only the preparation
+// writes: nothing in it can be relied on, so the first workgroup does all of the step by itself, which takes milliseconds and
+// is right.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,9 +44,11 @@ constexpr int kGangGroups = 256, kGangThreads = 512, kGangWaves = 8;
 constexpr int kGangChunk = 32;                       // keys: granule in which attention is cut into pieces
 constexpr uint32_t kClosedHi = 0x80000000u;          // upper half of a registration word
 // control block, in 128-byte lines: registration (8), what it was when closed (8), exit count, arrivals at the one common wait
-// (8), and, kept from launch to launch, the state of the buffers: their key and which of the two sets comes next
+// (8), and, kept from launch to launch, the state of the buffers (their key and which of the two sets comes next) and the mark
+// of a block that has been prepared
 constexpr int kLineReg = 0, kLineFinal = 8, kLineExit = 16, kLineArrive = 17, kLineState = 25, kLines = 26;
 static_assert(kLines * 128 <= (int)kGangControlBytes, "control block");
+constexpr uint64_t kPrepared = 0x9e3779b97f4a7c15ull;
 
 struct GangArgs {
     int rows, layers, d, heads, d_ff, V, max_ctx;
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
     constexpr int kPatchRow = 80, kPatch = 16 * kPatchRow;
     constexpr int kRec = hd * 4 + 16;                                       // a piece of attention: sums, maximum, sum of p
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // (its size keeps a second workgroup off the compute unit)
-    __shared__ int s_pos[16], s_tok[16], s_np[16], s_pre[17], s_id, s_P, s_set, s_known;
+    __shared__ int s_pos[16], s_tok[16], s_np[16], s_pre[17], s_id, s_P, s_set, s_known, s_solo;
     __shared__ float s_ml[2][kGangWaves][2];
     __shared__ __attribute__((aligned(16))) float s_ss[16][12], s_o[2][kGangWaves][hd];
     __shared__ __attribute__((aligned(16))) float s_part[kGangWaves][2][64][4];
@@ -179,6 +183,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         const uint64_t* state = reinterpret_cast<const uint64_t*>(ctl + kLineState * 32);
         s_known = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.key;
         s_set = (int)(__hip_atomic_load(state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1);
+        s_solo = __hip_atomic_load(state + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kPrepared;      // (no launch changes that)
     }
     __syncthreads();
     // (in the shadow of the others' arrival) rotation angles of all rows, in fp64: a position times a tiny frequency loses digits in fp32
@@ -187,7 +192,9 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         sincos((double)s_pos[i / half_hd] * exp2(-2.0 * (double)(i % half_hd) / (double)hd * a.log2_theta), &sn, &cs);
         s_trig[i] = make_double2(cs, sn);
     }
-    if (wave == 0) {
+    const bool solo = s_solo != 0;
+    if (solo && tid == 0) { s_id = 0; s_P = (blockIdx.x == 0) ? 1 : 0; }
+    if (wave == 0 && !solo) {
         constexpr int per = kGangGroups / 8;                                // bits of a word
         constexpr uint64_t full = (1ull << per) - 1;
         uint64_t* const words = reinterpret_cast<uint64_t*>(ctl + (kLineReg + (lane & 7)) * 32);
@@ -230,7 +237,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
     const int P = s_P, id = s_id;
     if (P > 0) {
         const int set = __builtin_amdgcn_readfirstlane(s_set);
-        const bool known = s_known != 0;
+        const bool known = s_known != 0 && !solo;
         for (int which = known ? 1 : 0; which < 2; ++which) {
             char* const to = a.buf + (size_t)(set ^ which) * a.set_bytes;
             for (uint32_t o = ((uint32_t)id * kGangThreads + tid) * 16u; o < a.set_bytes; o += (uint32_t)P * kGangThreads * 16u) {
@@ -244,7 +251,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         }
         if (!known) {
             publish_barrier();
-            if (wave == 0) {
+            if (wave == 0 && !solo) {
                 if (lane == 0) __hip_atomic_fetch_add(ctl + (kLineArrive + (id & 7)) * 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const int want = (P - (lane & 7) + 7) >> 3;
                 for (int spin = 0; spin < kMaxSpins; ++spin) {
@@ -847,9 +854,16 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
     }
     // ---- the last workgroup to leave moves the positions on and re-arms the control block for the next launch
     if (tid == 0) {
+        auto move_on = [&]() {
+            for (int r = 0; r < a.rows; ++r) __hip_atomic_fetch_add(a.ctx_len + r, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        if (solo) {
+            if (P > 0) move_on();
+            return;
+        }
         const uint32_t left = __hip_atomic_fetch_add(ctl + kLineExit * 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (left == kGangGroups - 1) {
-            for (int r = 0; r < a.rows; ++r) __hip_atomic_fetch_add(a.ctx_len + r, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            move_on();
             uint64_t* state = reinterpret_cast<uint64_t*>(ctl + kLineState * 32);
             __hip_atomic_store(state, a.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(state + 1, (uint64_t)(s_set ^ 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -897,7 +911,8 @@ uint64_t* gang_key(char* ctl) { return reinterpret_cast<uint64_t*>(ctl + kLineSt
 
 __global__ void k_gang_init(uint32_t* ctl, int words) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < words) ctl[i] = 0u;
+    constexpr int mark = kLineState * 32 + 4;                               // the state's third word
+    if (i < words) ctl[i] = (i == mark) ? (uint32_t)kPrepared : (i == mark + 1) ? (uint32_t)(kPrepared >> 32) : 0u;
 }
 hipError_t launch_gang_init(char* ctl, hipStream_t s) {
     const int words = (int)(kGangControlBytes / 4);

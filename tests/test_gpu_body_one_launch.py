@@ -130,6 +130,23 @@ def test_a_workspace_of_many_rows_serves_few_and_many_in_turn():
     assert bool((ws[-4096:] == 0x5A).all())
 
 
+@pytest.mark.parametrize("fill", [0x00, 0x5A, 0xFF], ids=hex)
+def test_a_workspace_that_nobody_prepared(fill):
+    """Not asked for by the interface, but no reason for a step that does nothing and says nothing: the results are the same bits, and a
+    workspace written over after the preparation is as good as new once it is prepared again."""
+    torch, binding = _gpu()
+    d = _Device(torch, binding, B(layers=2, d=256, heads=4, d_ff=520, V=50, max_ctx=80), 5, 1)
+    alone = d.once()
+    ws = torch.full((binding.tabed_body_workspace_bytes(d.cfg, d.rows),), fill, dtype=torch.uint8, device="cuda")
+    for _ in range(3):
+        assert _same(torch, d.once(ws), alone)
+    binding.tabed_body_workspace_init(d.cfg, d.rows, ws)
+    for _ in range(3):
+        assert _same(torch, d.once(ws), alone)
+    ws.fill_(fill)
+    assert _same(torch, d.once(ws), alone)
+
+
 def test_graph_replays_of_one_launch_steps():
     """Three steps in a graph, replayed with eager steps and synchronisation in between: each replay gives what eager steps give."""
     torch, binding = _gpu()
