@@ -63,6 +63,7 @@ struct GangArgs {
     uint32_t* ctl;
     char* buf;                                       // two sets; layer l of a set at l * layer_bytes
     uint32_t layer_bytes, set_bytes;
+    int late_from;                                   // for tests: workgroups from late_from on come late
     uint64_t key;                                    // the sizes that the buffers' place and layout follow from
     uint32_t off_q, off_kn, off_vn, off_po, off_att, off_xa, off_act, off_xm;
     tabed_body_weights w;
@@ -137,6 +138,10 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         rowc = min(r16, rows - 1);                                          // rows that are not there: one that is
     };
     uint32_t* const ctl = a.ctl;
+    if ((int)blockIdx.x >= a.late_from) {                                   // (tests: when the registration is closed, 3 ms)
+        const uint64_t began = __builtin_amdgcn_s_memrealtime();
+        while (__builtin_amdgcn_s_memrealtime() - began < 300000) __builtin_amdgcn_s_sleep(8);
+    }
 
     // ---- registration: a bit of the workgroup's own in one of eight words.  Normally all come at once and their numbers are
     //      their ids.  Whoever has waited too long closes the words, which settles who is in: the first to close a word
@@ -262,6 +267,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
             }
             __syncthreads();
         }
+        if (id == 0 && tid == 0) __hip_atomic_store(ctl + kLineState * 32 + 6, (uint32_t)P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);     // (for tests)
         char* const buf = a.buf + (size_t)set * a.set_bytes;
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(buf, 0, (int)a.set_bytes, 0x00020000);
         auto coherent16 = [&](uint32_t off) { return __builtin_bit_cast(u32x4b, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 16)); };   // sc1
@@ -932,7 +938,8 @@ static hipError_t launch_gang_t(const GangArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, char* ctl, char* buf, int rows, const int32_t* token_src,
-                       int token_stride, int rows_per_token, int32_t* ctx_len, uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s) {
+                       int token_stride, int rows_per_token, int32_t* ctx_len, uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s,
+                       int late_from) {
     const GangLayout L = gang_layout(c, rows);
     GangArgs a{};
     a.rows = rows; a.layers = c.layers; a.d = c.d; a.heads = c.heads; a.d_ff = c.d_ff; a.V = c.V; a.max_ctx = c.max_ctx;
@@ -943,6 +950,7 @@ hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, cha
     static_assert(TABED_BODY_MAX_LAYERS < 256, "the key's fields");
     a.key = 1ull | ((uint64_t)rows << 1) | ((uint64_t)c.layers << 8) | ((uint64_t)c.d << 16) | ((uint64_t)c.heads << 32) | ((uint64_t)c.d_ff << 44);
     a.off_q = L.off_q; a.off_kn = L.off_kn; a.off_vn = L.off_vn; a.off_po = L.off_po; a.off_att = L.off_att; a.off_xa = L.off_xa; a.off_act = L.off_act; a.off_xm = L.off_xm;
+    a.late_from = late_from < 1 ? kGangGroups : late_from;                  // (the first always comes in time)
     a.w = w;
     const bool wide = c.d > 768 || c.d_ff > 3072;
     if (c.d / c.heads == 64) return wide ? launch_gang_t<8, 4, 16>(a, s) : launch_gang_t<8, 3, 12>(a, s);

@@ -1,6 +1,8 @@
 """The draft body's step as one launch (up to 16 rows, heads of 64 or 128): the sizes where its items, pieces and buffers have
 edges, against the oracle to the bars of test_gpu_body.py; and that what it keeps between launches (counters, two sets of buffers
 in the workspace) survives other uses of the workspace, graph replays, and streams that compete for the compute units."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -54,7 +56,7 @@ class _Device:
             dev[key] = [_to_dev(torch, a) for a in w[key]]
         for key in ("g_attn", "g_mlp"):
             dev[key] = [torch.from_numpy(a).cuda() for a in w[key]]
-        self.binding, self.rows = binding, rows
+        self.torch, self.binding, self.rows = torch, binding, rows
         self.cfg = binding.make_body_cfg(layers=bc.layers, d=bc.d, heads=bc.heads, d_ff=bc.d_ff, V=bc.V, max_ctx=bc.max_ctx)
         self.body = binding.BodyBuffers(self.cfg, rows, dev)
         g = torch.Generator().manual_seed(seed)
@@ -72,6 +74,16 @@ class _Device:
         b = self.body
         self.binding.tabed_draft_body_step(self.cfg, b.table, b.ws if ws is None else ws, self.rows, self.tokens, 1, 1, b.ctx_len, b.kcache,
                                            b.vcache, b.H)
+
+    def step_with(self, ws, late_from=0):
+        """A step whose workgroups from `late_from` on come late; how many took part."""
+        torch, b, c = self.torch, self.body, ctypes
+        ptr = lambda t: c.c_void_p(t.data_ptr())  # noqa: E731
+        rc = self.binding.load().tabed_testing_body_step(
+            c.byref(self.cfg), c.byref(b.table), ptr(ws), c.c_int32(self.rows), ptr(self.tokens), c.c_int32(1), c.c_int32(1), ptr(b.ctx_len),
+            ptr(b.kcache), ptr(b.vcache), ptr(b.H), c.c_void_p(torch.cuda.current_stream().cuda_stream), c.c_int32(late_from))
+        assert rc == 0
+        return int(ws[25 * 128 + 24:25 * 128 + 28].view(torch.int32))
 
     def result(self):
         b = self.body
@@ -196,3 +208,23 @@ def test_one_launch_steps_on_streams_that_compete():
         torch.cuda.synchronize()
         assert _same(torch, a.result(), want_a) and _same(torch, b.result(), want_b)
     assert y.shape == x.shape
+
+
+@pytest.mark.parametrize("late_from", [255, 200, 64, 63, 9, 1])
+@pytest.mark.parametrize("rows,bc", [(5, B(layers=2, d=768, heads=12, d_ff=3072, V=50, max_ctx=600)), (16, B(layers=2, d=256, heads=2, d_ff=1000, V=50, max_ctx=300))],
+                         ids=["rows5_hd64", "rows16_hd128"])
+def test_workgroups_that_come_late_take_no_part(rows, bc, late_from):
+    """The others close the registration (after 20 us, or 1 ms where fewer than 64 are in) and deal all items to themselves: same bits,
+    on a workspace that has to be filled first, on one that is filled, and with all workgroups again afterwards."""
+    torch, binding = _gpu()
+    d = _Device(torch, binding, bc, rows, 9)
+    want = d.once()
+    ws = torch.full((binding.tabed_body_workspace_bytes(d.cfg, rows),), 0x5A, dtype=torch.uint8, device="cuda")
+    binding.tabed_body_workspace_init(d.cfg, rows, ws)
+    for _ in range(3):
+        d.reset()
+        assert d.step_with(ws, late_from=late_from) == late_from
+        assert _same(torch, d.result(), want)
+    d.reset()
+    assert d.step_with(ws) == 256
+    assert _same(torch, d.result(), want)
