@@ -291,7 +291,7 @@ int tabed_update_weights(const tabed_cfg* cfg, void* ws, uint64_t round, const f
  * `ws` has tabed_body_workspace_bytes(cfg, rows) bytes, is prepared once by tabed_body_workspace_init and also serves steps of
  * fewer rows and of other configurations that fit.  A step leaves state in it for the next one: from the preparation on the memory
  * belongs to the library (prepare it again after other use), and steps that share it must not overlap (one stream, or ordered by
- * events).
+ * events).  A step that could not be completed (none is known that cannot) leaves NaN in H and ctx_len as it was.
  * Every pointer is 16-byte aligned (TABED_EALIGN otherwise); a ctx_len entry outside [0, max_ctx) is clamped into
  * the range, so nothing is written outside a row's cache.
  */

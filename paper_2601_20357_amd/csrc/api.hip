@@ -326,10 +326,11 @@ int tabed_body_workspace_init(const tabed_body_cfg* cfg, int32_t rows, void* ws,
 }
 
 // tabed_draft_body_step, for the tests with workgroups of the one-launch step from number late_from on that come after the others
-// have stopped waiting for them (0: as in earnest).
+// have stopped waiting for them, and with one that takes part and does nothing, so that waits for it end unanswered, after
+// milliseconds (0: as in earnest).
 int tabed_testing_body_step(const tabed_body_cfg* cfg, const tabed_body_weights* weights, void* ws, int32_t rows,
                             const int32_t* token_src, int32_t token_stride, int32_t rows_per_token, int32_t* ctx_len,
-                            void* kcache, void* vcache, void* H, void* stream, int32_t late_from) {
+                            void* kcache, void* vcache, void* H, void* stream, int32_t late_from, int32_t absent) {
     const int rc = validate_body_cfg(cfg, rows);
     if (rc != TABED_OK) return rc;
     if (!weights || !ws || !token_src || !ctx_len || !kcache || !vcache || !H) return TABED_ENULL;
@@ -348,14 +349,14 @@ int tabed_testing_body_step(const tabed_body_cfg* cfg, const tabed_body_weights*
         return TABED_EALIGN;
     const hipError_t e = launch_body_step(*cfg, *weights, static_cast<char*>(ws), rows, token_src, token_stride, rows_per_token,
                                           ctx_len, static_cast<uint16_t*>(kcache), static_cast<uint16_t*>(vcache),
-                                          static_cast<uint16_t*>(H), static_cast<hipStream_t>(stream), late_from);
+                                          static_cast<uint16_t*>(H), static_cast<hipStream_t>(stream), late_from, absent);
     return e == hipSuccess ? TABED_OK : fail_hip(e);
 }
 
 int tabed_draft_body_step(const tabed_body_cfg* cfg, const tabed_body_weights* weights, void* ws, int32_t rows,
                           const int32_t* token_src, int32_t token_stride, int32_t rows_per_token, int32_t* ctx_len,
                           void* kcache, void* vcache, void* H, void* stream) {
-    return tabed_testing_body_step(cfg, weights, ws, rows, token_src, token_stride, rows_per_token, ctx_len, kcache, vcache, H, stream, 0);
+    return tabed_testing_body_step(cfg, weights, ws, rows, token_src, token_stride, rows_per_token, ctx_len, kcache, vcache, H, stream, 0, 0);
 }
 
 int tabed_draft_body_rollback(int32_t rows, int32_t rows_per_seq, int32_t gamma, const int32_t* ctx_base,

@@ -773,11 +773,11 @@ static void launch_attn(const ProfScope* prof, const tabed_body_cfg& c, int rows
 
 hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w, char* ws, int rows,
                             const int32_t* token_src, int token_stride, int rows_per_token, int32_t* ctx_len,
-                            uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s, int late_from) {
+                            uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s, int late_from, int absent) {
     const BodyLayout L = body_layout(c, rows);
     if (gang_applies(c, rows))
         return launch_gang(c, w, ws + L.off_ctl, ws + L.off_gang, rows, token_src, token_stride, rows_per_token, ctx_len, kcache, vcache, H, s,
-                           late_from);
+                           late_from, absent);
     uint16_t* hb = reinterpret_cast<uint16_t*>(ws + L.off_hb);
     float* po = reinterpret_cast<float*>(ws + L.off_po);
     float* pml = reinterpret_cast<float*>(ws + L.off_pml);

@@ -17,7 +17,9 @@
 // registration is closed when all have come or after a bounded time, whoever comes later leaves at once, and the items are
 // dealt to those that are in (P of them).  So neither another kernel that holds compute units nor a second step on another
 // stream can stop it; with fewer workgroups it is slower.  Results do not depend on P: items are fixed, and only who
-// computes them varies.
+// computes them varies.  Should a wait go unanswered all the same, it ends after some time, and what it waited for is taken as it
+// is, a NaN, so that those who wait for what follows from it are answered.  The step says so: H has the NaN, the positions stay, and
+// the next launch fills the buffers anew.
 //
 // Why a result is whole.  Every buffer has its own place in every layer and is written once a launch.  There are two sets of
 // buffers, used in turn: a launch fills the other set with the pattern for the next one (the end of a launch orders that).
@@ -63,7 +65,7 @@ struct GangArgs {
     uint32_t* ctl;
     char* buf;                                       // two sets; layer l of a set at l * layer_bytes
     uint32_t layer_bytes, set_bytes;
-    int late_from;                                   // for tests: workgroups from late_from on come late
+    int late_from, absent;                           // for tests: workgroups from late_from on come late, and one that does nothing
     uint64_t key;                                    // the sizes that the buffers' place and layout follow from
     uint32_t off_q, off_kn, off_vn, off_po, off_att, off_xa, off_act, off_xm;
     tabed_body_weights w;
@@ -110,7 +112,10 @@ constexpr int kDppRor8 = 0x128;                      // row_ror:8 = lane ^ 8 wit
 
 __device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 
-constexpr int kMaxSpins = 1 << 22;                   // (every wait is answered; a bound all the same, of seconds)
+// Every wait is answered; a bound all the same, of some tenths of a second.  (What is then taken as it is counts as announced
+// where it is used, so that only those who wait for a workgroup that is lost itself come to it, once a phase.)
+constexpr int kMaxSpins = 1 << 18;
+constexpr uint32_t kGaveUp = 0x10000u;               // in the exit count, for each workgroup in which one has
 
 // LPK: lanes per key (head_dim / 8).  UD, UF: units of 32 of the contraction over d and over d_ff that a wave takes, at most.
 template <int LPK, int UD, int UF>
@@ -119,7 +124,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
     constexpr int kPatchRow = 80, kPatch = 16 * kPatchRow;
     constexpr int kRec = hd * 4 + 16;                                       // a piece of attention: sums, maximum, sum of p
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // (its size keeps a second workgroup off the compute unit)
-    __shared__ int s_pos[16], s_tok[16], s_np[16], s_pre[17], s_id, s_P, s_set, s_known, s_solo;
+    __shared__ int s_pos[16], s_tok[16], s_np[16], s_pre[17], s_id, s_P, s_set, s_known, s_solo, s_gave_up;
     __shared__ float s_ml[2][kGangWaves][2];
     __shared__ __attribute__((aligned(16))) float s_ss[16][12], s_o[2][kGangWaves][hd];
     __shared__ __attribute__((aligned(16))) float s_part[kGangWaves][2][64][4];
@@ -147,6 +152,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
     //      their ids.  Whoever has waited too long closes the words, which settles who is in: the first to close a word
     //      writes down what it held, and the ids are the ranks in that.
     uint64_t before = 0;
+    if (tid == 0) s_gave_up = 0;
     if (tid == 0)
         before = __hip_atomic_fetch_or(reinterpret_cast<uint64_t*>(ctl + (kLineReg + (blockIdx.x & 7)) * 32), 1ull << (blockIdx.x >> 3),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         sincos((double)s_pos[i / half_hd] * exp2(-2.0 * (double)(i % half_hd) / (double)hd * a.log2_theta), &sn, &cs);
         s_trig[i] = make_double2(cs, sn);
     }
-    const bool solo = s_solo != 0;
+    const bool solo = __builtin_amdgcn_readfirstlane(s_solo) != 0;
     if (solo && tid == 0) { s_id = 0; s_P = (blockIdx.x == 0) ? 1 : 0; }
     if (wave == 0 && !solo) {
         constexpr int per = kGangGroups / 8;                                // bits of a word
@@ -222,9 +228,14 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
                     if ((old >> 32) == 0) __hip_atomic_store(finals, old | ((uint64_t)kClosedHi << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 uint64_t f = 0;
-                for (int spin = 0; spin < kMaxSpins; ++spin) {              // (the first to close a word writes it down right away)
+                bool all = false;
+                for (int spin = 0; spin < kMaxSpins && !all; ++spin) {      // (the first to close a word writes it down right away)
                     f = __hip_atomic_load(finals, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (__all((f >> 32) != 0)) break;
+                    all = __all((f >> 32) != 0);
+                }
+                if (!all) {                                                 // takes no part
+                    if (lane == 0) s_gave_up = 1;
+                    break;
                 }
                 const uint32_t bit = blockIdx.x >> 3;
                 for (int q = 0; q < 8; ++q) {                               // rank among those who are in, in the order of their numbers
@@ -236,6 +247,7 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
             }
             __builtin_amdgcn_s_sleep(1);
         }
+        if (id == a.absent) P = 0;
         if (lane == 0) { s_id = id; s_P = P; }
     }
     __syncthreads();
@@ -259,25 +271,39 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
             if (wave == 0 && !solo) {
                 if (lane == 0) __hip_atomic_fetch_add(ctl + (kLineArrive + (id & 7)) * 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const int want = (P - (lane & 7) + 7) >> 3;
-                for (int spin = 0; spin < kMaxSpins; ++spin) {
+                bool all = false;
+                for (int spin = 0; spin < kMaxSpins && !all; ++spin) {
                     const int v = (int)__hip_atomic_load(ctl + (kLineArrive + (lane & 7)) * 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (__all(v >= want)) break;
-                    __builtin_amdgcn_s_sleep(1);
+                    all = __all(v >= want);
+                    if (!all) __builtin_amdgcn_s_sleep(1);
+                }
+                if (!all) {                                                 // takes no part: what stands in the buffers may be anything
+                    if (lane == 0) { s_gave_up = 1; s_P = 0; }
                 }
             }
             __syncthreads();
+            if (s_P == 0 && id == 0)
+                for (uint32_t i = tid; i < (uint32_t)(rows * d) / 2; i += kGangThreads) reinterpret_cast<uint32_t*>(a.H)[i] = 0x7fff7fffu;
         }
+    }
+    if (s_P > 0) {
+        const int set = __builtin_amdgcn_readfirstlane(s_set);
         if (id == 0 && tid == 0) __hip_atomic_store(ctl + kLineState * 32 + 6, (uint32_t)P, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);     // (for tests)
         char* const buf = a.buf + (size_t)set * a.set_bytes;
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(buf, 0, (int)a.set_bytes, 0x00020000);
         auto coherent16 = [&](uint32_t off) { return __builtin_bit_cast(u32x4b, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 16)); };   // sc1
         auto as_f4 = [](const u32x4b& v) { return __builtin_bit_cast(f32x4b, v); };
+        int waited = 0;                                                     // kMaxSpins is in it if a wait of this wave went unanswered
         // load() requests, and says whether anything is missing still
         auto until_set = [&](auto load) {
-            for (int spin = 0; spin < kMaxSpins; ++spin) {
+            int spin = 0;
+            bool missing;
+#pragma nounroll
+            do {
                 keep_order();
-                if (!__any(load())) break;
-            }
+                missing = __any(load());
+            } while (missing && ++spin < kMaxSpins);
+            waited = __builtin_amdgcn_readfirstlane(waited | spin);         // (a branch here, or an LDS store, cost 3 % of a step)
         };
         // Where many wait for the same data, each wave watches one piece of it, of row 0, before it asks for all of its share: 192
         // workgroups that asked for everything time and again kept the stores of what they waited for from getting through (a
@@ -856,22 +882,26 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
                 }
             }
         }
+        if (waited >= kMaxSpins) s_gave_up = 1;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                    // no word is on its way to LDS any more
     }
+    lds_barrier();
     // ---- the last workgroup to leave moves the positions on and re-arms the control block for the next launch
     if (tid == 0) {
         auto move_on = [&]() {
             for (int r = 0; r < a.rows; ++r) __hip_atomic_fetch_add(a.ctx_len + r, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
-        if (solo) {
-            if (P > 0) move_on();
+        if (s_solo) {
+            if (P > 0 && !s_gave_up) move_on();
             return;
         }
-        const uint32_t left = __hip_atomic_fetch_add(ctl + kLineExit * 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (left == kGangGroups - 1) {
-            move_on();
+        const uint32_t mine = s_gave_up ? kGaveUp : 0u;
+        const uint32_t left = __hip_atomic_fetch_add(ctl + kLineExit * 32, 1u + mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((left & (kGaveUp - 1)) == kGangGroups - 1) {
+            const bool whole = left < kGaveUp && mine == 0;
+            if (whole) move_on();
             uint64_t* state = reinterpret_cast<uint64_t*>(ctl + kLineState * 32);
-            __hip_atomic_store(state, a.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(state, whole ? a.key : 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(state + 1, (uint64_t)(s_set ^ 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             for (int i = 0; i < kLineState; ++i)
                 __hip_atomic_store(reinterpret_cast<uint64_t*>(ctl + i * 32), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -939,7 +969,7 @@ static hipError_t launch_gang_t(const GangArgs& a, hipStream_t s) {
 
 hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, char* ctl, char* buf, int rows, const int32_t* token_src,
                        int token_stride, int rows_per_token, int32_t* ctx_len, uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s,
-                       int late_from) {
+                       int late_from, int absent) {
     const GangLayout L = gang_layout(c, rows);
     GangArgs a{};
     a.rows = rows; a.layers = c.layers; a.d = c.d; a.heads = c.heads; a.d_ff = c.d_ff; a.V = c.V; a.max_ctx = c.max_ctx;
@@ -951,6 +981,7 @@ hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, cha
     a.key = 1ull | ((uint64_t)rows << 1) | ((uint64_t)c.layers << 8) | ((uint64_t)c.d << 16) | ((uint64_t)c.heads << 32) | ((uint64_t)c.d_ff << 44);
     a.off_q = L.off_q; a.off_kn = L.off_kn; a.off_vn = L.off_vn; a.off_po = L.off_po; a.off_att = L.off_att; a.off_xa = L.off_xa; a.off_act = L.off_act; a.off_xm = L.off_xm;
     a.late_from = late_from < 1 ? kGangGroups : late_from;                  // (the first always comes in time)
+    a.absent = absent < 1 ? kGangGroups : absent;
     a.w = w;
     const bool wide = c.d > 768 || c.d_ff > 3072;
     if (c.d / c.heads == 64) return wide ? launch_gang_t<8, 4, 16>(a, s) : launch_gang_t<8, 3, 12>(a, s);

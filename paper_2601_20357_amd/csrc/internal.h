@@ -125,7 +125,7 @@ int validate_body_cfg(const tabed_body_cfg* c, int rows);
 hipError_t launch_body_init(const tabed_body_cfg& c, int rows, char* ws, hipStream_t s);
 hipError_t launch_body_step(const tabed_body_cfg& c, const tabed_body_weights& w, char* ws, int rows,
                             const int32_t* token_src, int token_stride, int rows_per_token, int32_t* ctx_len,
-                            uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s, int late_from = 0);
+                            uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s, int late_from = 0, int absent = 0);
 int body_route(const tabed_body_cfg& c, int rows);
 bool gang_applies(const tabed_body_cfg& c, int rows);
 size_t gang_bytes(const tabed_body_cfg& c, int rows);
@@ -133,7 +133,7 @@ uint64_t* gang_key(char* ctl);
 hipError_t launch_gang_init(char* ctl, hipStream_t s);
 hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, char* ctl, char* buf, int rows, const int32_t* token_src,
                        int token_stride, int rows_per_token, int32_t* ctx_len, uint16_t* kcache, uint16_t* vcache, uint16_t* H, hipStream_t s,
-                       int late_from = 0);     // (0: as in earnest; others for tests)
+                       int late_from = 0, int absent = 0);     // (0: as in earnest; others for tests)
 hipError_t launch_body_rollback(int rows, int rows_per_seq, int gamma, const int32_t* ctx_base, const int32_t* accept_len,
                                 int32_t* ctx_len, hipStream_t s);
 

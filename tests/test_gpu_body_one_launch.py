@@ -75,13 +75,13 @@ class _Device:
         self.binding.tabed_draft_body_step(self.cfg, b.table, b.ws if ws is None else ws, self.rows, self.tokens, 1, 1, b.ctx_len, b.kcache,
                                            b.vcache, b.H)
 
-    def step_with(self, ws, late_from=0):
-        """A step whose workgroups from `late_from` on come late; how many took part."""
+    def step_with(self, ws, late_from=0, absent=0):
+        """A step whose workgroups from `late_from` on come late, or whose workgroup `absent` does nothing; how many took part."""
         torch, b, c = self.torch, self.body, ctypes
         ptr = lambda t: c.c_void_p(t.data_ptr())  # noqa: E731
         rc = self.binding.load().tabed_testing_body_step(
             c.byref(self.cfg), c.byref(b.table), ptr(ws), c.c_int32(self.rows), ptr(self.tokens), c.c_int32(1), c.c_int32(1), ptr(b.ctx_len),
-            ptr(b.kcache), ptr(b.vcache), ptr(b.H), c.c_void_p(torch.cuda.current_stream().cuda_stream), c.c_int32(late_from))
+            ptr(b.kcache), ptr(b.vcache), ptr(b.H), c.c_void_p(torch.cuda.current_stream().cuda_stream), c.c_int32(late_from), c.c_int32(absent))
         assert rc == 0
         return int(ws[25 * 128 + 24:25 * 128 + 28].view(torch.int32))
 
@@ -228,3 +228,23 @@ def test_workgroups_that_come_late_take_no_part(rows, bc, late_from):
     d.reset()
     assert d.step_with(ws) == 256
     assert _same(torch, d.result(), want)
+
+
+@pytest.mark.parametrize("absent", [7, 40, 192])
+def test_a_wait_that_ends_unanswered_is_seen(absent):
+    """A workgroup that registers and computes nothing (q/k/v and gate / up, gate / up alone, output and down projections): no result
+    that looks like one, positions where they were, and the next step as ever."""
+    torch, binding = _gpu()
+    d = _Device(torch, binding, B(layers=2, d=256, heads=4, d_ff=1024, V=50, max_ctx=120), 6, 10)
+    want = d.once()
+    ws = torch.full((binding.tabed_body_workspace_bytes(d.cfg, d.rows),), 0x5A, dtype=torch.uint8, device="cuda")
+    binding.tabed_body_workspace_init(d.cfg, d.rows, ws)
+    for filled in (False, True, True):
+        if filled:
+            assert _same(torch, d.once(ws), want)
+        d.reset()
+        d.body.H.zero_()
+        d.step_with(ws, absent=absent)
+        assert torch.equal(d.body.ctx_len, d.base)
+        assert bool(torch.isnan(d.body.H.float()).all())
+    assert _same(torch, d.once(ws), want)
