@@ -778,7 +778,9 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
                 u32x4b xv[UW];
 #pragma unroll
                 for (int u = 0; u < UW; ++u) xv[u] = u32x4b{0u, 0u, 0u, 0u};
-                glance(xo + (uint32_t)((min(wave + (UW - 1) * kGangWaves, K / 32 - 1) * 4 + c) * rows) * 16u);
+                // (the last whole unit of 32, or, with fewer columns than that, pieces that exist)
+                const int watched = min(wave + (UW - 1) * kGangWaves, max(K / 32 - 1, 0)) * 4 + c;
+                glance(xo + (uint32_t)(min(watched, K / 8 - 1) * rows) * 16u);
                 until_set([&]() {
                     if (r16 >= rows) return false;
                     bool missing = false;

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 
 B = synth.BodyConfig
 # rows 1, 2, 3, 5, 8, 9, 16 (lanes, halves and sums of a block of 16 rows); positions around a chunk of 32 keys and a step of 256 (128);
-# d_ff that ends inside a tile of 16, inside a unit of 32, and in neither; d of one and of several units a wave, above 768 too
+# d_ff below a unit of 32, or that ends inside a tile of 16, inside a unit of 32, and in neither; d of one and of several units a wave, above 768 too
 SHAPES = [
     ("rows1_hd64", B(layers=2, d=64, heads=1, d_ff=8, V=30, max_ctx=300), [257]),
     ("rows2_hd128", B(layers=2, d=128, heads=1, d_ff=264, V=30, max_ctx=200), [128, 129]),
+    ("rows2_d_ff_16", B(layers=2, d=64, heads=1, d_ff=16, V=30, max_ctx=40), [20, 31]),
+    ("rows7_d_ff_24", B(layers=1, d=128, heads=2, d_ff=24, V=30, max_ctx=40), list(range(7))),
     ("rows3_hd64", B(layers=1, d=192, heads=3, d_ff=520, V=30, max_ctx=700), [0, 31, 600]),
     ("rows5_hd64", B(layers=2, d=768, heads=12, d_ff=3072, V=30, max_ctx=90), [32, 33, 63, 64, 65]),
     ("rows8_hd128", B(layers=1, d=1024, heads=8, d_ff=4096, V=30, max_ctx=70), [0, 1, 2, 30, 31, 32, 33, 60]),
