@@ -830,17 +830,20 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 
 // What bounds it, 512 rows of V = 128256, d = 2048: without the loads 200 us, without the products 165 us, both 232 us, with the
 // logits' 263 MB, which all workgroups store at about the same times, 276 us (the loop by itself; products alone 155 to 165 us,
 // 2.4 GHz would give 110: the clock follows the power).
+// (M0 is put back: the compiler does not let it be named as clobbered, and keeps what it has in it.)
 __device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off)[4], uint32_t lds, uint32_t step) {
+    uint32_t m0;
     // (the waits: M0 written before an LDS load, and a scalar that may have come from a vector instruction)
-    asm volatile("s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %6\n\ts_add_u32 m0, m0, %1\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %3, %6\n\ts_add_u32 m0, m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %6\n\t"
-                 "s_add_u32 m0, m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %6"
-                 :: "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "scc");
+    asm volatile("s_mov_b32 %0, m0\n\ts_nop 4\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %7\n\ts_add_u32 m0, m0, %2\n\t"
+                 "s_nop 0\n\tglobal_load_lds_dwordx4 %4, %7\n\ts_add_u32 m0, m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %7\n\t"
+                 "s_add_u32 m0, m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %7\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "scc");
 }
 __device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off)[2], uint32_t lds, uint32_t step) {
-    asm volatile("s_nop 4\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_add_u32 m0, m0, %1\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %3, %4"
-                 :: "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "scc");
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_nop 4\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\ts_add_u32 m0, m0, %2\n\t"
+                 "s_nop 0\n\tglobal_load_lds_dwordx4 %4, %5\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "scc");
 }
 
 template <int BM, int BN, int S>
