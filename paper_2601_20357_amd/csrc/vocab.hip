@@ -759,6 +759,7 @@ static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char*
         else if (c.n == 2) TABED_LAUNCH_SAMPLE_N(TI_, 2);                       \
         else if (c.n == 3) TABED_LAUNCH_SAMPLE_N(TI_, 3);                       \
         else if (c.n == 4) TABED_LAUNCH_SAMPLE_N(TI_, 4);                       \
+        else if (!ALLOW8_) return hipErrorInvalidValue;                         \
         else if (c.n == 5) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 5 : 1));       \
         else if (c.n == 8) TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 8 : 1));       \
         else TABED_LAUNCH_SAMPLE_N(TI_, (ALLOW8_ ? 0 : 1));                     \
