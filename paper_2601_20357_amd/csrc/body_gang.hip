@@ -163,7 +163,9 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         const int pos = min(max(a.ctx_len[r], 0), a.max_ctx - 1);
         const int tok = a.token_src[(size_t)(r / a.rows_per_token) * a.token_stride];
         // Attention is cut into pieces: a row's and head's keys into np parts of about equal length, none longer than z chunks; z
-        // is the smallest that gives no more pieces than workgroups (rows * heads <= 256).
+        // is the smallest that gives no more pieces than workgroups (rows * heads <= 256), and at most 8 of a row and head, or 16
+        // where they have 256 keys and more: one wave merges them eight at a time (without that limit one layer of one head of
+        // 64, one row of 7000 positions 41.5 us, 23.7 with 16; of 600 to 1900 25.5, 21.6 with 8; as launches 22.6 and 19.6).
         const int nch = (lane < rows) ? pos / kGangChunk + 1 : 0;
         auto row_sum = [](int x) {
             x += dpp_i32<kDppXor1>(x); x += dpp_i32<kDppXor2>(x); x += dpp_i32<kDppHalfMirror>(x); x += dpp_i32<kDppMirror>(x);
@@ -172,7 +174,8 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         int z0 = 1, z1 = 8192 / kGangChunk;
         while (z0 < z1) {
             const int z = (z0 + z1) >> 1;
-            if (row_sum((nch + z - 1) / z) * heads <= kGangGroups) z1 = z;
+            const int n = (nch + z - 1) / z;
+            if (row_sum(n) * heads <= kGangGroups && __all(n <= (z >= 8 ? 16 : 8))) z1 = z;
             else z0 = z + 1;
         }
         const int np = (nch + z0 - 1) / z0;
