@@ -11,12 +11,14 @@
 // workgroups (measured as a ping-pong), where stores that are waited for, arrival counters, a poll and then the first load
 // took 2.2 us with 256 workgroups, and a kernel boundary more.  With 48 to 192 writers and as many readers a hand-over is 1.3 to
 // 1.9 us from the store to the last reader, and a layer has five: that bounds it now.  One step of 12 layers, d = 768, d_ff = 3072,
-// 4 rows of 600 to 1900 positions: 235 us, 336 as 62 launches; one layer 19 us, 28.
+// 4 rows of 600 to 1900 positions: 228 us, 336 as 62 launches; one layer 19 us, 28.
 //
 // Why nothing can wait for ever.  A workgroup only waits for workgroups that are running: at the start each registers, the
 // registration is closed when all have come or after a bounded time, whoever comes later leaves at once, and the items are
 // dealt to those that are in (P of them).  So neither another kernel that holds compute units nor a second step on another
-// stream can stop it; with fewer workgroups it is slower.  Results do not depend on P: items are fixed, and only who
+// stream can stop it; with fewer workgroups it is slower.  Beside a stream of matrix products, step / product in us, one launch and
+// launches: 12 layers as above and products of 25 us that fill part of the chip 295 / 43 and 367 / 30, of 790 us that fill it
+// 785 / 956 and 1223 / 825; two layers 71 / 33 and 66 / 29, 242 / 845 and 253 / 842.  Results do not depend on P: items are fixed, and only who
 // computes them varies.  Should a wait go unanswered all the same, it ends after some time, and what it waited for is taken as it
 // is, a NaN, so that those who wait for what follows from it are answered.  The step says so: H has the NaN, the positions stay, and
 // the next launch fills the buffers anew.
@@ -310,8 +312,8 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
         };
         // Where many wait for the same data, each wave watches one piece of it, of row 0, before it asks for all of its share: 192
         // workgroups that asked for everything time and again kept the stores of what they waited for from getting through (a
-        // step of 12 layers 241 us, 235 with this).  Measured and not kept: a word per item, behind its result, that one wave of a
-        // workgroup watches, and the results then through the caches (293 us).
+        // step of 12 layers 6 us longer).  Measured and not kept: a word per item, behind its result, that one wave of a
+        // workgroup watches, and the results then through the caches (58 us longer).
         auto glance = [&](uint32_t off) { until_set([&]() { return r16 == 0 && unset(coherent16(off)); }); };
         const int pieces = s_pre[16] * heads;                               // of attention
         const int off3 = P * 3 / 4;                                         // output and down projections start where gate / up leaves room
@@ -915,11 +917,13 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
 }
 
 // ---------------------------------------------------------------- host side
-// Whether a step is one launch.  One launch / a launch per phase, a step in us: 12 layers of d = 768, d_ff = 3072 216 / 277 at 1 row,
-// 220 / 295 at 4, 249 / 367 at 8 rows of 400 to 1200 positions; two such layers 42 / 47, 45 / 50, 51 / 60, and 55 / 68 at 16 rows; one
-// layer of d = 256, d_ff = 1024 22.5 / 25.7 at 1 row, 24 / 26 at 16.  With so many columns that the tiles of gate / up and of the
-// output projections do not fit side by side it needs more than four rows: two layers of d = 1024, d_ff = 4096 61 / 55 at 1 row, 62 / 60
-// at 4, 66 / 71 at 8, 75 / 91 at 16.  (16 rows are one block of the matrix instruction.  From 17 rows on, with counters
+// Whether a step is one launch.  One launch / a launch per phase, a step in us, replayed in a graph, rows of 600 to 1900 positions: 12
+// layers of d = 768, d_ff = 3072 at 4 rows 228 / 336; two such layers 41 / 49 at 1 row, 48 / 56 at 4, 52 / 63 at 8, 63 / 73 at 16; two of d = 256,
+// d_ff = 1024 36.7 / 35.1 at 1 row, 42.9 / 50.1 at 16; one of those 22.1 / 20.0 and 25.6 / 24.1.  Called from the host, which takes 3.7 us a launch,
+// that one layer is 22.8 / 25.7 and 25.9 / 25.7, and it is left as one launch, like all the small ones that a graph would replay faster as
+// launches (one layer below d = 768, two of d <= 128: by up to a fifth).  With so many columns that the tiles of gate / up and of the
+// output projections do not fit side by side one launch needs more than four rows: two layers of d = 1024, d_ff = 4096 61 / 55 at 1 row, 62 / 60
+// at 4, 69 / 73 at 8, 80 / 90 at 16.  (16 rows are one block of the matrix instruction.  From 17 rows on, with counters
 // instead of data that announces itself, which so many rows make too much to watch, one launch was slower: 64 rows
 // 580 us a block of five steps, 495 as launches.)
 bool gang_applies(const tabed_body_cfg& c, int rows) {

@@ -744,7 +744,9 @@ static hipError_t launch_sample_any(const tabed_cfg& c, const WsLayout& L, char*
     a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + (S > 0 ? 3 : 0) * (size_t)c.B * L.TS;
     const int ti = (L.NT + kBlock - 1) / kBlock;
     const bool wide = (ti > 8 && c.n > 4) || ti > 20;
-    // Eight waves of 250 registers: one workgroup a compute unit, so that half as many share a greedy row where all would not fit at once.
+    // Eight waves of 250 registers: one workgroup a compute unit, so that half as many share a greedy row where all would not fit at once
+    // (draft steps, d = 64, with eight / with four a greedy row: V = 128256, 8 drafts, 33 greedy sequences 72.3 / 60.4 us, 64 103.5 / 85.6, 64 of which
+    // half are greedy 97.1 / 82.3; 70001, 5 drafts, 33 70.2 / 59.3; 190001, 3 drafts, 33 93.2 / 80.2).
     if (wide && ti <= 24 && (long)c.B * a.C2 > 256) a.C2 = (a.C2 + 1) / 2;
     // The first workgroups of the rows, which do the work of sampling rows alone, on every XCD in turn (all on one with the row's
     // workgroups next to each other: V = 128256, 8 drafts, 64 sampling rows, a draft step with d = 256 128 us, 103 so), and a greedy
