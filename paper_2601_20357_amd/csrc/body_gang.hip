@@ -919,9 +919,9 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
 // ---------------------------------------------------------------- host side
 // Whether a step is one launch.  One launch / a launch per phase, a step in us, replayed in a graph, rows of 600 to 1900 positions: 12
 // layers of d = 768, d_ff = 3072 at 4 rows 228 / 336; two such layers 41 / 49 at 1 row, 48 / 56 at 4, 52 / 63 at 8, 63 / 73 at 16; two of d = 256,
-// d_ff = 1024 36.7 / 35.1 at 1 row, 42.9 / 50.1 at 16; one of those 22.1 / 20.0 and 25.6 / 24.1.  Called from the host, which takes 3.7 us a launch,
-// that one layer is 22.8 / 25.7 and 25.9 / 25.7, and it is left as one launch, like all the small ones that a graph would replay faster as
-// launches (one layer below d = 768, two of d <= 128: by up to a fifth).  With so many columns that the tiles of gate / up and of the
+// d_ff = 1024 33.0 / 35.2 at 1 row, 39.0 / 50.2 at 16; one of those 20.7 / 20.2 and 23.6 / 24.2.  Called from the host, which takes about 4 us
+// a launch, that one layer is 20.9 / 30 and 23.6 / 30, and it is left as one launch, like all the bodies of one layer that a graph would
+// replay faster as launches (up to d = 384, by up to 7 %, 1.4 us).  With so many columns that the tiles of gate / up and of the
 // output projections do not fit side by side one launch needs more than four rows: two layers of d = 1024, d_ff = 4096 61 / 55 at 1 row, 62 / 60
 // at 4, 69 / 73 at 8, 80 / 90 at 16.  (16 rows are one block of the matrix instruction.  From 17 rows on, with counters
 // instead of data that announces itself, which so many rows make too much to watch, one launch was slower: 64 rows
@@ -992,9 +992,13 @@ hipError_t launch_gang(const tabed_body_cfg& c, const tabed_body_weights& w, cha
     a.late_from = late_from < 1 ? kGangGroups : late_from;                  // (the first always comes in time)
     a.absent = absent < 1 ? kGangGroups : absent;
     a.w = w;
-    const bool wide = c.d > 768 || c.d_ff > 3072;
-    if (c.d / c.heads == 64) return wide ? launch_gang_t<8, 4, 16>(a, s) : launch_gang_t<8, 3, 12>(a, s);
-    return wide ? launch_gang_t<16, 4, 16>(a, s) : launch_gang_t<16, 3, 12>(a, s);
+    // The smallest instance that has the units: one that has more asks for the last ones again, W and activations, which the chain
+    // of a phase waits for (replayed in a graph, with instances for d = 768, d_ff = 3072 and wider only / now: one layer of d = 64
+    // 22.5 / 20.0 us, of d = 256 22.7 / 20.7, two 36.7 / 33.0; two of d = 512, d_ff = 2048 37.6 / 35.9, all at one row).
+    auto fits = [&](int units) { return c.d <= units * 256 && c.d_ff <= units * 1024; };
+    if (c.d / c.heads == 64)
+        return fits(1) ? launch_gang_t<8, 1, 4>(a, s) : fits(2) ? launch_gang_t<8, 2, 8>(a, s) : fits(3) ? launch_gang_t<8, 3, 12>(a, s) : launch_gang_t<8, 4, 16>(a, s);
+    return fits(1) ? launch_gang_t<16, 1, 4>(a, s) : fits(2) ? launch_gang_t<16, 2, 8>(a, s) : fits(3) ? launch_gang_t<16, 3, 12>(a, s) : launch_gang_t<16, 4, 16>(a, s);
 }
 
 }  // namespace tabed

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 B = synth.BodyConfig
 # rows 1, 2, 3, 5, 8, 9, 16 (lanes, halves and sums of a block of 16 rows); positions around a chunk of 32 keys and a step of 256 (128);
-# pieces of 256 keys, up to 8 of shorter ones and 16 of others;
+# pieces of 256 keys, up to 8 of shorter ones and 16 of others; the widest of each number of units a wave, and one past it;
 # d_ff below a unit of 32, or that ends inside a tile of 16, inside a unit of 32, and in neither; d of one and of several units a wave, above 768 too
 SHAPES = [
     ("rows1_hd64", B(layers=2, d=64, heads=1, d_ff=8, V=30, max_ctx=300), [257]),
@@ -26,6 +26,11 @@ SHAPES = [
     ("rows9_hd64", B(layers=1, d=832, heads=13, d_ff=2216, V=30, max_ctx=130), [0, 0, 5, 31, 32, 95, 96, 97, 120]),
     ("rows16_hd64", B(layers=1, d=1024, heads=16, d_ff=2728, V=30, max_ctx=70), list(range(0, 64, 4))),
     ("rows16_hd128", B(layers=1, d=256, heads=2, d_ff=1000, V=30, max_ctx=600), [17 * i for i in range(16)]),
+    ("rows4_quarter", B(layers=2, d=256, heads=4, d_ff=1024, V=30, max_ctx=90), [32, 33, 63, 64]),
+    ("rows2_past_the_quarter", B(layers=1, d=256, heads=2, d_ff=1032, V=30, max_ctx=90), [0, 64]),
+    ("rows3_half", B(layers=1, d=512, heads=8, d_ff=2048, V=30, max_ctx=90), [1, 40, 85]),
+    ("rows6_half_hd128", B(layers=2, d=384, heads=3, d_ff=1360, V=30, max_ctx=300), [5, 64, 100, 127, 128, 297]),
+    ("rows2_past_the_half_hd128", B(layers=1, d=768, heads=6, d_ff=2056, V=30, max_ctx=90), [31, 60]),
     ("rows1_eight_pieces", B(layers=1, d=64, heads=1, d_ff=64, V=30, max_ctx=2100), [2046]),
     ("rows2_nine_to_sixteen_pieces", B(layers=1, d=128, heads=1, d_ff=64, V=30, max_ctx=4200), [2048, 4094]),
     ("rows1_eight_thousand", B(layers=1, d=64, heads=1, d_ff=64, V=30, max_ctx=8192), [8189]),
