@@ -543,11 +543,13 @@ __global__ __launch_bounds__(THR) void k_sample(SampleArgs a) {
     for (int i = tid; i < (kMaxTiles + 31) / 32; i += THR) s_live[i] = 0u;
     if (tid == 0) s_count = 0;
     __syncthreads();
-    // (in pairs: one after the other cost a greedy row 0.3 us, of 10 to 18 a draft step)
-    ArgMax first = argmax_merge(argmax_merge(s_wtop[0], s_wtop[1]), argmax_merge(s_wtop[2], s_wtop[3]));
-#pragma unroll
-    for (int w = 4; w < NWV; w += 4)
-        first = argmax_merge(first, argmax_merge(argmax_merge(s_wtop[w], s_wtop[w + 1]), argmax_merge(s_wtop[w + 2], s_wtop[w + 3])));
+    // (one record after the other cost a greedy row 0.3 us, of 10 to 18 a draft step; in pairs, the sampling rows 0.1 us: the compiler
+    // then allots their part of the kernel other registers)
+    ArgMax first = s_wtop[lane & (NWV - 1)];
+    first = argmax_dpp_step<kDppXor1>(first);
+    first = argmax_dpp_step<kDppXor2>(first);
+    if (NWV > 4) first = argmax_dpp_step<kDppHalfMirror>(first);           // (lane ^ 7: the other four)
+    first = argmax_at(first, 0);
     const int t0 = first.i;
     // the mixture at one vocabulary entry, drafts in order, and whether it may be drawn
     auto mixture = [&](int v) {
