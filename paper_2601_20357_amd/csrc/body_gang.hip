@@ -917,8 +917,8 @@ __global__ __launch_bounds__(kGangThreads, 2) void k_body_gang(GangArgs a) {
 }
 
 // ---------------------------------------------------------------- host side
-// Whether a step is one launch.  One launch / a launch per phase, a step in us, replayed in a graph, rows of 600 to 1900 positions: 12
-// layers of d = 768, d_ff = 3072 at 4 rows 228 / 336; two such layers 41 / 49 at 1 row, 48 / 56 at 4, 52 / 63 at 8, 63 / 73 at 16; two of d = 256,
+// Whether a step is one launch.  One launch / a launch per phase, a step in us, rows of 600 to 1900 positions: 12 layers of d = 768,
+// d_ff = 3072 at 4 rows 228 / 336, called from the host; replayed in a graph, two such layers 41 / 49 at 1 row, 48 / 56 at 4, 52 / 63 at 8, 63 / 73 at 16; two of d = 256,
 // d_ff = 1024 33.0 / 35.2 at 1 row, 39.0 / 50.2 at 16; one of those 20.7 / 20.2 and 23.6 / 24.2.  Called from the host, which takes about 4 us
 // a launch, that one layer is 20.9 / 30 and 23.6 / 30, and it is left as one launch, like all the bodies of one layer that a graph would
 // replay faster as launches (up to d = 384, by up to 7 %, 1.4 us).  With so many columns that the tiles of gate / up and of the
