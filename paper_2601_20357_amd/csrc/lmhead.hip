@@ -39,6 +39,8 @@ __device__ __forceinline__ float half_sum(float v) {
     return v;
 }
 
+constexpr int kPatchBytes = 32 * 144;                  // LDS in which a wave turns 32 rows of 32 floats
+
 // Epilogue of one 32x32 accumulator tile held TRANSPOSED: lane holds result row m_base + lane % 32 and the 16
 // vocabulary entries v_base + 8*(r/4) + 4*(lane/32) + r%4.  The softmax partials of a row are then a
 // 16-value in-register reduction plus one exchange between the two half-waves, and every lane stores four
@@ -55,26 +57,27 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
     const bool live = (m < M);
     const float it = live ? inv_t[m] : 1.f;
     const bool full = v_base + 32 <= V;            // uniform: only the last tile of a row is ragged
-    float sc[16];
+    float x[16];
     float mx = -INFINITY;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sc[r] = acc[r] * it;      // (rows past the end: computed, not stored)
+    for (int r = 0; r < 16; ++r) x[r] = acc[r];            // (rows past the end: computed, not stored)
     if (!full) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (v_base + 8 * (r / 4) + 4 * half + (r % 4) >= V) sc[r] = -INFINITY;
+            if (v_base + 8 * (r / 4) + 4 * half + (r % 4) >= V) x[r] = -INFINITY;
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[r]);
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, x[r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = (mx > -INFINITY) ? mx * it : mx;                  // (the largest product: 1 / T is positive and rounding keeps the order)
     const float base = (mx > -INFINITY) ? mx : 0.f;        // a tile of -inf sums to 0
     float sum = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sum += __expf(sc[r] - base);
+    for (int r = 0; r < 16; ++r) sum += __expf(fmaf(x[r], it, -base));
     if (__any(sum != sum)) {                               // a NaN logit has no mass and does not take the tile's with it
         sum = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum += (sc[r] > -INFINITY) ? __expf(sc[r] - mx) : 0.f;
+        for (int r = 0; r < 16; ++r) sum += (x[r] * it > -INFINITY) ? __expf(fmaf(x[r], it, -mx)) : 0.f;
     }
     sum += __shfl_xor(sum, 32);
     if (live && half == 0) {
@@ -116,6 +119,96 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
         }
 }
 
+// The other half-wave's value beside this one's: {lanes 0-31, lanes 0-31} and {lanes 32-63, lanes 32-63}.
+__device__ __forceinline__ float2 both_halves(float v) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    return make_float2(__builtin_bit_cast(float, (unsigned)p[0]), __builtin_bit_cast(float, (unsigned)p[1]));
+}
+
+// Epilogue of a wave's TV x TM accumulator tiles, none of which reaches past the vocabulary: the values, the operations and their
+// order are those of store_tile_32x32_t.  The row tiles of a vocabulary tile go through each phase side by side, so that none waits for
+// its own chain (maximum, exchange, exponentials, exchange), and the partials of the workgroup's rows are collected in LDS
+// (part: [row][kPT tiles] maxima, kPS floats on the sums), from where a row's are stored 16 bytes at a time: a store of their own for
+// every tile and row was two of three memory requests of the epilogue.
+// rows: how many rows of the wave's block exist; patch: two of kPatchBytes.
+template <int TV, int TM, int kPT, int kPS>
+__device__ __forceinline__ void store_full_tiles(const f32x16 (&acc)[TV][TM], int rows, const float* s_it, float* part, float* L /* row, entry 0 of the block */,
+                                                 int V, unsigned char* patch) {
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    float it[TM];
+#pragma unroll
+    for (int b = 0; b < TM; ++b) it[b] = s_it[b * 32 + col];
+#pragma unroll
+    for (int a = 0; a < TV; ++a) {
+        float mx[TM], base[TM], sum[TM];
+#pragma unroll
+        for (int b = 0; b < TM; ++b) {
+            mx[b] = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx[b] = fmaxf(mx[b], acc[a][b][r]);
+        }
+#pragma unroll
+        for (int b = 0; b < TM; ++b) {
+            const float2 h = both_halves(mx[b]);
+            mx[b] = fmaxf(h.x, h.y);
+            mx[b] = (mx[b] > -INFINITY) ? mx[b] * it[b] : mx[b];
+            base[b] = (mx[b] > -INFINITY) ? mx[b] : 0.f;
+            sum[b] = 0.f;
+        }
+#pragma unroll
+        for (int b = 0; b < TM; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[b] += __expf(fmaf(acc[a][b][r], it[b], -base[b]));
+        bool nan = false;
+#pragma unroll
+        for (int b = 0; b < TM; ++b) nan = nan || sum[b] != sum[b];
+        if (__any(nan)) {                                  // a NaN logit has no mass and does not take the tile's with it
+#pragma unroll
+            for (int b = 0; b < TM; ++b) {
+                if (!__any(sum[b] != sum[b])) continue;    // (tile by tile, as store_tile_32x32_t decides)
+                sum[b] = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    sum[b] += (acc[a][b][r] * it[b] > -INFINITY) ? __expf(fmaf(acc[a][b][r], it[b], -mx[b])) : 0.f;
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < TM; ++b) {
+            const float2 h = both_halves(sum[b]);
+            if (half == 0) {
+                part[(b * 32 + col) * kPT + a] = mx[b];
+                part[(b * 32 + col) * kPT + a + kPS] = h.x + h.y;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < TM; ++b) {
+            if (b * 32 >= rows) continue;                  // uniform
+            unsigned char* const tp = patch + (b & 1) * kPatchBytes;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<float4*>(tp + col * 144 + (8 * g + 4 * half) * 4) =
+                    make_float4(acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]);
+            const int q = lane & 7;
+            float* const out = L + (size_t)(b * 32 + (lane >> 3)) * V + a * 32 + 4 * q;
+            float4 val[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) val[i] = *reinterpret_cast<const float4*>(tp + (8 * i + (lane >> 3)) * 144 + q * 16);
+            auto store = [&](int i) {
+                __builtin_nontemporal_store(f32x4u{val[i].x, val[i].y, val[i].z, val[i].w}, reinterpret_cast<f32x4u*>(out + (size_t)(8 * i) * V));
+            };
+            if ((b + 1) * 32 <= rows) {                    // uniform
+#pragma unroll
+                for (int i = 0; i < 4; ++i) store(i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (b * 32 + 8 * i + (lane >> 3) < rows) store(i);
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------- bf16, up to 64 rows, d = 512, 768 or 896: W-streaming kernel
 // With n*B <= 64 rows the GEMM moves 2*d bytes of W per n*B*2*d flops: it is bound by streaming W from HBM
 // once, not by the matrix cores.  Design:
@@ -135,7 +228,6 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
 // KH = k-blocks (of 64) per wave = d / 128; MT = 32-row blocks of M.
 constexpr int kSkinnyWaves = 8;
 constexpr int kSkinnyThreads = kSkinnyWaves * 64;
-constexpr int kPatchBytes = 32 * 144;
 
 template <int KH, int MT>
 __global__ __launch_bounds__(kSkinnyThreads) void k_lmhead_skinny(int M, int V, int n, int NT, int num_tiles,
@@ -631,7 +723,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_lmhead_stream(int M, int d, 
                         mx = fmaxf(mx, dpp_f32<kDppHalfMirror>(mx));
                         float sum = 0.f;
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) sum += (sc[u] > -INFINITY) ? __expf(sc[u] - mx) : 0.f;
+                        for (int u = 0; u < 4; ++u) sum += (sc[u] > -INFINITY) ? __expf(fmaf(x[u], it, -mx)) : 0.f;
                         sum += dpp_f32<kDppXor1>(sum);
                         sum += dpp_f32<kDppXor2>(sum);
                         sum += dpp_f32<kDppHalfMirror>(sum);
@@ -819,17 +911,21 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 
 
 // ---------------------------------------------------------------- bf16, more than 64 rows, hidden size a multiple of 64: operands straight to LDS
 // The tiled GEMM above for the hidden sizes whose rows are whole lines: the same workgroup tiles, waves and order of sums (and so
-// the same bits), but the operands go from memory to LDS without registers in between (global_load_lds, 16 bytes a lane), S
-// stages of one k-block each, S - 1 of them in flight; a wave keeps its registers for operand fragments, and nothing waits to write
-// LDS.  A stage has rows of 128 bytes without padding; row r keeps its 16-byte pieces in the order piece ^ (r & 7), which the
-// lanes bring about by the address they load from, so that the fragment reads of 8 consecutive rows hit all banks.
-// One barrier per k-block: before it a wave has waited for its own share of the stage that comes next, after it all of that
-// stage is there and the stage that was multiplied last is free.  The loads are written in assembly (they have no destination
+// the same bits), but the operands go from memory to LDS without registers in between (global_load_lds, 16 bytes a lane), in SW
+// stages of a k-block of W and SH of H; a wave keeps its registers for operand fragments, and nothing waits to write LDS.
+// 256 x 256 tiles have room for three stages of W, which comes from memory, and two of H, which comes from L2 (0.8 % less than two
+// of each).  A stage has rows of 128 bytes without padding; row r keeps its 16-byte pieces in the order piece ^ (r / 2 % 8), which
+// the lanes bring about by the address they load from, so that the fragment reads of 16 consecutive rows hit all 64 banks (with
+// piece ^ (r % 8), 8 rows on 32 banks, half of the 212 k LDS cycles a compute unit were conflicts; 0.3 % of the time).
+// One barrier per k-block, before the products of its last k-step: by then its last fragments are in registers and the stage is
+// free, and the next k-block's first fragments are read while those products run.  (With the barrier at the k-block's end its first
+// fragments were waited for: 333 us a draft step, 323.)  The loads are written in assembly (they have no destination
 // register): with the builtin the compiler waits for all LDS reads in flight at every second step, 256 us instead of 232 for the
 // product alone below.
-// What bounds it, 512 rows of V = 128256, d = 2048: without the loads 200 us, without the products 165 us, both 232 us, with the
-// logits' 263 MB, which all workgroups store at about the same times, 276 us (the loop by itself; products alone 155 to 165 us,
-// 2.4 GHz would give 110: the clock follows the power).
+// What bounds it, 512 rows of V = 128256, d = 2048 (269 GFLOP, a draft step 307 us, 333 before): the loop without loads 181 us, with
+// them 231, with the epilogue and its 263 MB of logits, which all workgroups store at about the same times, 280.  The matrix
+// cores are busy for 81, 66 and 48 % of the cycles, at 1.65 GHz in the loop: the clock follows the power.  Measured and not kept:
+// k-blocks walked from a different one in every vocabulary block, so that workgroups read different channels (no change).
 // (M0 is put back: the compiler does not let it be named as clobbered, and keeps what it has in it.)
 __device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off)[4], uint32_t lds, uint32_t step) {
     uint32_t m0;
@@ -846,13 +942,12 @@ __device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off
                  : "=&s"(m0) : "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "scc");
 }
 
-template <int BM, int BN, int S>
+template <int BM, int BN, int SW, int SH>
 __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, int V, int n, int NT, int mblocks, const uint16_t* __restrict__ W,
                                                                  const uint16_t* __restrict__ H, const float* __restrict__ temperature,
                                                                  float* __restrict__ L, float* __restrict__ pm, float* __restrict__ ps) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    __shared__ float s_invt[BM];
-    constexpr int kRow = kLBK * 2, kStage = (BM + BN) * kRow;               // W's rows, then H's
+    constexpr int kRow = kLBK * 2, kStW = BN * kRow, kStH = BM * kRow;       // SW stages of W, then SH of H
     constexpr int TV = BN / 128, TM = BM / 64;                              // 32-wide tiles of a wave
     constexpr int WI = BN / 64, HI = BM / 64;                               // loads of a wave per stage: 8 rows of 128 bytes each
     constexpr uint32_t kStep = 8 * 8 * kRow;                                // LDS bytes from one of a wave's loads to its next
@@ -871,18 +966,15 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
     uint32_t wo[WI], ho[HI];                                                // rows past the end re-read the last one (masked in the epilogue)
     {
         const int r = lane >> 3;
-        const uint32_t piece = (uint32_t)((lane & 7) ^ r) * 16u;
+        const uint32_t piece = (uint32_t)((lane & 7) ^ ((wave & 1) * 4 + (r >> 1))) * 16u;     // row (8 i + wave) * 8 + r
 #pragma unroll
         for (int i = 0; i < WI; ++i) wo[i] = (uint32_t)min((i * 8 + wave) * 8 + r, V - 1 - v0) * (uint32_t)d * 2u + piece;
 #pragma unroll
         for (int i = 0; i < HI; ++i) ho[i] = (uint32_t)min((i * 8 + wave) * 8 + r, M - 1 - m0) * (uint32_t)d * 2u + piece;
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds + (uint32_t)wave * 8u * kRow;
-    auto request = [&](int kb, int stage) {                                 // past the last k-block: the last one again, into a stage nobody reads
-        const int k = min(kb, KB - 1) * kRow;
-        dma_lines(hbase + k, ho, lds0 + (uint32_t)(stage * kStage + BN * kRow), kStep);
-        dma_lines(wbase + k, wo, lds0 + (uint32_t)(stage * kStage), kStep);
-    };
+    auto request_w = [&](int kb, int stage) { dma_lines(wbase + kb * kRow, wo, lds0 + (uint32_t)(stage * kStW), kStep); };       // kb < KB
+    auto request_h = [&](int kb, int stage) { dma_lines(hbase + kb * kRow, ho, lds0 + (uint32_t)(SW * kStW + stage * kStH), kStep); };
 
     f32x16 acc[TV][TM];                                                     // [vocabulary tile][row tile]
 #pragma unroll
@@ -891,53 +983,86 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
         for (int b = 0; b < TM; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-    const uint32_t wrow = (uint32_t)(wn * 32 * TV + nn) * kRow, hrow = (uint32_t)(BN + wm * (BM / 2) + nn) * kRow, turn = (uint32_t)(nn & 7);
-    auto multiply = [&](int stage) {
-        const unsigned char* sW = lds + stage * kStage + wrow;
-        const unsigned char* sH = lds + stage * kStage + hrow;
-        // operand fragments of k-step ks+1 are read from LDS while the MFMAs of k-step ks run
-        bf16x8 wf[2][TV], hf[2][TM];
-        auto read_frags = [&](int ks, int set) {
-            const uint32_t c = ((uint32_t)(2 * ks + half) ^ turn) * 16u;
+    const uint32_t wrow = (uint32_t)(wn * 32 * TV + nn) * kRow, hrow = (uint32_t)(SW * kStW) + (uint32_t)(wm * (BM / 2) + nn) * kRow, turn = (uint32_t)(nn >> 1 & 7);
+    bf16x8 wf[2][TV], hf[2][TM];                                            // fragments of two k-steps of 16
+    int stw = 0, sth = 0;                                                   // stages of the present k-block
+    auto read_frags = [&](int ks, int set) {
+        const unsigned char* sW = lds + stw * kStW + wrow;
+        const unsigned char* sH = lds + sth * kStH + hrow;
+        const uint32_t c = ((uint32_t)(2 * ks + half) ^ turn) * 16u;
 #pragma unroll
-            for (int a = 0; a < TV; ++a) wf[set][a] = *reinterpret_cast<const bf16x8*>(sW + a * 32 * kRow + c);
+        for (int a = 0; a < TV; ++a) wf[set][a] = *reinterpret_cast<const bf16x8*>(sW + a * 32 * kRow + c);
 #pragma unroll
-            for (int b = 0; b < TM; ++b) hf[set][b] = *reinterpret_cast<const bf16x8*>(sH + b * 32 * kRow + c);
-        };
-        read_frags(0, 0);
+        for (int b = 0; b < TM; ++b) hf[set][b] = *reinterpret_cast<const bf16x8*>(sH + b * 32 * kRow + c);
+    };
+    auto products = [&](int set) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ks = 0; ks < kLBK / 16; ++ks) {
-            if (ks + 1 < kLBK / 16) read_frags(ks + 1, (ks + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int a = 0; a < TV; ++a)
 #pragma unroll
-            for (int a = 0; a < TV; ++a)
-#pragma unroll
-                for (int b = 0; b < TM; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][a], hf[ks & 1][b], acc[a][b], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+            for (int b = 0; b < TM; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][a], hf[set][b], acc[a][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
     };
 
+    static_assert(SW == SH || SW == SH + 1, "the order of requests below");
 #pragma unroll
-    for (int q = 0; q < S - 1; ++q) request(q, q);
-    int stage = 0;
-    for (int kb = 0; kb < KB; ++kb) {
-        // this wave's share of k-block kb is there once no more than what it asked for after that is outstanding
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((S - 2) * (WI + HI)) : "memory");
-        request(kb + S - 1, stage == 0 ? S - 1 : stage - 1);
-        multiply(stage);
-        stage = (stage + 1 == S) ? 0 : stage + 1;
+    for (int q = 0; q < SW; ++q) {
+        request_w(q, q);
+        if (q < SH) request_h(q, q);
     }
-    if (tid < BM) s_invt[tid] = inv_temperature(my_temp);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                        // nothing is on its way to LDS any more
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((SW - 1) * WI + (SH - 1) * HI) : "memory");
+    read_frags(0, 0);
+    auto step = [&](int kb, auto refill) {
+#pragma unroll
+        for (int ks = 0; ks < kLBK / 16 - 1; ++ks) {                        // fragments of k-step ks + 1 are read while ks is multiplied
+            read_frags(ks + 1, (ks + 1) & 1);
+            products(ks & 1);
+        }
+        // The stage's last fragments are in registers: it is free once all waves are here.  k-block kb + 1 is there once no more than what
+        // a wave asked for after that is outstanding.  Its first fragments are read while the last products run.
+        if constexpr (refill.value) {
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((SW - 2) * WI + (SH - 2) * HI) : "memory");
+            request_h(kb + SH, sth);
+            request_w(min(kb + SW, KB - 1), stw);
+        } else {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        }
+        stw = (stw + 1 == SW) ? 0 : stw + 1;
+        sth = (sth + 1 == SH) ? 0 : sth + 1;
+        read_frags(0, 0);
+        products(1);
+    };
+    static_assert(kLBK == 64, "the last of a stage's k-steps uses the second set");
+    int kb = 0;
+    for (; kb + SH < KB; ++kb) step(kb, std::true_type{});
+    for (; kb < KB; ++kb) step(kb, std::false_type{});
+    constexpr int kPT = BN / kTileV, kPS = BM * kPT;                        // partials of a row; of all rows
+    float* const s_invt = reinterpret_cast<float*>(lds + 16 * kPatchBytes);
+    float* const s_part = s_invt + BM;                                      // [2][BM][kPT]
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");             // nothing is on its way to LDS any more, nothing is read from it
     __syncthreads();
-    // ---- epilogue: every wave turns its 32x32 blocks through a private patch carved from the stages
-    unsigned char* tpatch = lds + wave * kPatchBytes;
+    if (tid < BM) s_invt[tid] = inv_temperature(my_temp);
+    __syncthreads();
+    // ---- epilogue: every wave turns its 32x32 blocks through private patches carved from the stages
+    unsigned char* const tpatch = lds + wave * 2 * kPatchBytes;
+    if (v0 + BN > V) {                                                      // uniform: the last vocabulary block
 #pragma unroll
-    for (int a = 0; a < TV; ++a)
+        for (int a = 0; a < TV; ++a)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
-            store_tile_32x32_t(acc[a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
+            for (int b = 0; b < TM; ++b)
+                store_tile_32x32_t(acc[a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
+        return;
+    }
+    const int lr = wm * (BM / 2);
+    store_full_tiles<TV, TM, kPT, kPS>(acc, M - m0 - lr, s_invt + lr, s_part + lr * kPT + wn * TV, L + (size_t)(m0 + lr) * V + v0 + wn * 32 * TV, V, tpatch);
+    lds_barrier();
+#pragma unroll
+    for (int t = tid; t < 2 * BM * (kPT / 4); t += kLargeThreads) {
+        const int q = t % (kPT / 4), row = t / (kPT / 4) % BM, arr = t / (kPT / 4) / BM;
+        const f32x4 x = *reinterpret_cast<const f32x4*>(s_part + arr * kPS + row * kPT + 4 * q);
+        if (m0 + row < M) *reinterpret_cast<f32x4u*>((arr == 0 ? pm : ps) + (size_t)(m0 + row) * NT + v0 / kTileV + 4 * q) = f32x4u(x);
+    }
 }
 
 // ---------------------------------------------------------------- fp32 operands: one output per thread
@@ -1128,17 +1253,16 @@ static hipError_t launch_tile(const ProfScope* prof, const tabed_cfg& c, const W
     return hipSuccess;
 }
 
-template <int BM, int BN, int S>
+template <int BM, int BN, int SW, int SH>
 static hipError_t launch_dma(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
                              const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
-    const size_t lds = (size_t)S * (BM + BN) * kLBK * 2;
-    static_assert((size_t)S * (BM + BN) * kLBK * 2 >= 8 * kPatchBytes, "the epilogue's patches");
+    constexpr size_t lds = std::max((size_t)(SW * BN + SH * BM) * kLBK * 2, (size_t)16 * kPatchBytes + BM * 4 + 2 * BM * (BN / kTileV) * 4);
     static std::once_flag once;
     static hipError_t rc = hipSuccess;
-    if (raise_lds_limit(&k_lmhead_dma<BM, BN, S>, lds, once, rc) != hipSuccess) return rc;
+    if (raise_lds_limit(&k_lmhead_dma<BM, BN, SW, SH>, lds, once, rc) != hipSuccess) return rc;
     const int mblocks = (M + BM - 1) / BM, nblocks = (c.V + BN - 1) / BN;
     const int nrounds = (nblocks + 7) / 8;             // vocabulary blocks are dealt to the 8 XCDs in rounds
-    launch(prof, k_lmhead_dma<BM, BN, S>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
+    launch(prof, k_lmhead_dma<BM, BN, SW, SH>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
            static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
     return hipSuccess;
 }
@@ -1187,13 +1311,13 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
         // flight: 16.3 / 15.9 at 400 rows of 8000, 64, 33.6 / 33.1 at 256 of 65536, 128.
         const bool lines = c.d % kLBK == 0 && c.d >= 512;
         if (lines && M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
-            e = launch_dma<256, 256, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = launch_dma<256, 256, 3, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (lines && tiles(128, 256) >= 192)
-            e = launch_dma<128, 256, 3>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = launch_dma<128, 256, 3, 3>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (lines && tiles(128, 128) > 256)       // two workgroups a compute unit (192 rows of 20000, 896 33.7 us with one, 29.0; 30.2 through registers)
-            e = launch_dma<128, 128, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = launch_dma<128, 128, 2, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (lines)
-            e = launch_dma<128, 128, 4>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = launch_dma<128, 128, 4, 4>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
             e = launch_tile<256, 256, 1, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (tiles(128, 256) >= 192) e = launch_tile<128, 256, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
