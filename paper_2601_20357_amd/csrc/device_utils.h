@@ -52,6 +52,13 @@ __device__ __forceinline__ float wave_max(float v) {
     v = fmaxf(v, dpp_f32<kDppMirror>(v));
     return fmaxf(fmaxf(lane_f32(v, 0), lane_f32(v, 16)), fmaxf(lane_f32(v, 32), lane_f32(v, 48)));
 }
+__device__ __forceinline__ double wave_max(double v) {
+    v = fmax(v, dpp_f64<kDppXor1>(v));
+    v = fmax(v, dpp_f64<kDppXor2>(v));
+    v = fmax(v, dpp_f64<kDppHalfMirror>(v));
+    v = fmax(v, dpp_f64<kDppMirror>(v));
+    return fmax(fmax(lane_f64(v, 0), lane_f64(v, 16)), fmax(lane_f64(v, 32), lane_f64(v, 48)));
+}
 __device__ __forceinline__ float wave_sum(float v) {
     v += dpp_f32<kDppXor1>(v);
     v += dpp_f32<kDppXor2>(v);
@@ -260,8 +267,10 @@ struct ArgMax {
     float v;
     int i;
 };
-__device__ __forceinline__ ArgMax argmax_merge(const ArgMax& a, const ArgMax& b) {
-    return ((b.v > a.v) || (b.v == a.v && b.i < a.i)) ? b : a;
+// (By value: a choice between two records in LDS by reference is one between addresses, and goes through scratch memory.)
+__device__ __forceinline__ ArgMax argmax_merge(const ArgMax a, const ArgMax b) {
+    const bool second = (b.v > a.v) | ((b.v == a.v) & (b.i < a.i));
+    return ArgMax{second ? b.v : a.v, second ? b.i : a.i};
 }
 template <int CTRL>
 __device__ __forceinline__ ArgMax argmax_dpp_step(const ArgMax& t) {
