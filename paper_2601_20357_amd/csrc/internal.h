@@ -39,17 +39,17 @@ struct Top3Rec {                // the same of a token tree's siblings
 struct WsLayout {
     int M, NT, C2, C3max, NSEG, C5, RS;
     int DW;              // width of one distance vector: n, or 11 candidate mixtures (policy 2)
-    int Cd;              // vocabulary chunks of the second-pass distance kernel
+    int Cd;              // vocabulary chunks of the total-variation and label distances
     int TS;              // uint32 between two sequences' arrival counters
     size_t off_tickets;  // uint32 [5][B][TS]: arrival counters (0: greedy draft arg-max, 1: staged weights, 2: corrected/bonus sampler,
-                         // 3: token-tree residual level, 4: token-tree bonus after a leaf)
+                         // 3: token-tree residual level; before it, in the chain's launch, total-variation distances, 4: token-tree bonus after a leaf)
     size_t off_pm;       // float  [M][NT] tile maxima of scaled logits
     size_t off_ps;       // float  [M][NT] tile sums of exp(scaled logit - tile max)
     size_t off_cand;     // Top2Rec [B][C2]
     size_t off_stats;    // double [B][gamma+1][C3max][RS]: header + one KL sum per draft (or per grid candidate)
     size_t off_seg;      // double [B][2][NSEG] segment masses: residual, target
     size_t off_wstage;   // float [B][n] next weights staged by the fused window update
-    size_t off_dist;     // double [B][gamma][DW][Cd][2] chunk sums, or chunk arg-maxes (value, index), of the second pass
+    size_t off_dist;     // double [B][gamma][DW][Cd][2] chunk sums, or chunk arg-maxes (value, index), of those distances
     size_t off_tstate;   // double [B][8] token-tree walk of every sequence (see TreeState)
     size_t off_tseg;     // double [B][2][NSEG] token-tree passes: segment masses, segment maxima
     size_t total;

@@ -68,22 +68,19 @@ struct WindowArgs {
     float* weights;
 };
 
-template <bool PUB>
-__device__ __forceinline__ float dev_load(const float* p) { return PUB ? published_load(p) : *p; }
-
-template <bool PUB>
-__device__ __forceinline__ void window_update(const WindowArgs& a, int b, int lane, const float* dev, int nv,
+// dev(q): distance q of the sequence's [gamma, dw].  PUB: the weights are published.
+template <bool PUB, typename Dev>
+__device__ __forceinline__ void window_update(const WindowArgs& a, int b, int lane, Dev dev, int nv,
                                               double* s_part /* [64] */, double* s_x /* [TABED_MAX_N] */) {
     const int n = a.n, dw = a.dw, gamma = a.gamma, h = a.h, policy = a.policy;
-    nv = (dev == nullptr) ? 0 : (nv < 0 ? 0 : (nv > gamma ? gamma : nv));
-    const float* db = dev ? dev + (size_t)b * gamma * dw : nullptr;
+    nv = nv < 0 ? 0 : (nv > gamma ? gamma : nv);
     bool empty;
     if (h == 0) {
         int count = a.ring_count[b];
         count = count < 0 ? 0 : count;
         if (lane < dw) {
             float sum = a.ring[(size_t)b * dw + lane];
-            for (int i = 0; i < nv; ++i) sum = sum + dev_load<PUB>(db + (size_t)i * dw + lane);   // fp32, in order
+            for (int i = 0; i < nv; ++i) sum = sum + dev(i * dw + lane);   // fp32, in order
             if (nv > 0) a.ring[(size_t)b * dw + lane] = sum;
             s_x[lane] = (policy == 2) ? (double)sum : (1.0 / fmax((double)sum, a.eps)) / a.tau_w;
         }
@@ -102,7 +99,7 @@ __device__ __forceinline__ void window_update(const WindowArgs& a, int b, int la
         if (lane < per * dw) {
             for (int r = t0; r < new_count; r += per) {   // r-th newest entry of the new window
                 float v;
-                if (r < nv) v = dev_load<PUB>(db + (size_t)(nv - 1 - r) * dw + j);
+                if (r < nv) v = dev((nv - 1 - r) * dw + j);
                 else        v = rb[(size_t)((((head - 1 - (r - nv)) % h) + h) % h) * dw + j];
                 acc += (double)v;
             }
@@ -117,7 +114,7 @@ __device__ __forceinline__ void window_update(const WindowArgs& a, int b, int la
         if (nv > 0) {                                 // all window loads above are complete: store the new entries
             for (int idx = lane; idx < nv * dw; idx += 64) {
                 const int i = idx / dw, jj = idx % dw;
-                if (i >= nv - h) rb[(size_t)((head + i) % h) * dw + jj] = dev_load<PUB>(db + (size_t)i * dw + jj);
+                if (i >= nv - h) rb[(size_t)((head + i) % h) * dw + jj] = dev(i * dw + jj);
             }
             if (lane == 0) {
                 a.ring_head[b] = (head + nv) % h;
@@ -164,7 +161,8 @@ __global__ __launch_bounds__(64) void k_weights(WindowArgs a, const float* __res
     __shared__ double s_x[TABED_MAX_N];
     const int b = blockIdx.x;
     const int nv = (dev != nullptr && n_valid != nullptr) ? n_valid[b] : 0;
-    window_update<false>(a, b, threadIdx.x, (dev != nullptr && n_valid != nullptr) ? dev : nullptr, nv, s_part, s_x);
+    const float* const db = dev + (size_t)b * a.gamma * a.dw;               // (nv = 0: not read)
+    window_update<false>(a, b, threadIdx.x, [&](int q) { return db[q]; }, nv, s_part, s_x);
 }
 
 static WindowArgs window_args(const tabed_cfg& c, uint64_t round, float* ring, int32_t* ring_head, int32_t* ring_count,
@@ -817,7 +815,7 @@ hipError_t launch_siblings(const tabed_cfg& c, const WsLayout& L, char* ws, uint
 // =====================================================================================================
 struct StatsArgs {
     int V, n, B, gamma, C3, RS;
-    int with_drafts;      // 0: only the target-row part of the records (distances come from k_dist)
+    int with_drafts;      // 0: only the target-row part of the records (distances come from dist_chunk)
     int grid;             // 1 (two drafts): the A sums are those of the 11 candidate mixtures, not of the drafts
     const float* target;
     const float* dlogits;
@@ -827,8 +825,8 @@ struct StatsArgs {
 };
 
 template <int U, int N>
-__global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
-    const int c = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void stats_chunk(const StatsArgs& a, int c, int i, int b) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma;
     const float T = a.temperature[b];
     const float invT = (T > 0.f) ? 1.f / T : 1.f;
@@ -983,18 +981,26 @@ __global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
     }
 }
 
+template <int U, int N>
+__global__ __launch_bounds__(kBlock) void k_stats(StatsArgs a) {
+    stats_chunk<U, N>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
 // =====================================================================================================
-// Second-pass distances: total variation, also of the two-draft grid policy's candidate mixtures.
-// |p - q| cannot be accumulated before the target row's normaliser is known, so
-// these modes take one more pass over the rows: grid (chunk, position i < gamma, sequence b); every
-// workgroup first combines the row's records from k_stats (lse_p), then sums, over its 4096-wide chunk,
+// Distances that do not ride in the records of k_stats: total variation and hard labels, also of the two-draft grid policy's
+// candidate mixtures.  A workgroup sums, over its 4096-wide chunk of position i < gamma of sequence b,
 //   MODE 0: |p - q_j|                         per draft j                (TVD, DW = n)
 //   MODE 2: |p - mix_c|                       per candidate c            (TVD of the mixtures, n = 2)
 //   MODE 3: arg-max_v q_j(v)                  per draft j                (hard labels; needs no target row)
 //   MODE 4: arg-max_v mix_c(v)                per candidate c            (hard labels, n = 2)
-// with mix_c = (1 - c/10) q_1 + (c/10) q_2.  Chunk sums go to dist[b][i][c][chunk][0] (k_finish adds them);
-// chunk arg-maxes go to dist[b][i][c][chunk][0..1] as ((value, runner-up value) as two floats, index), lowest
-// index on ties.
+// with mix_c = (1 - c/10) q_1 + (c/10) q_2.  Chunk sums go to dist[b][i][c][chunk][0]; chunk arg-maxes go to
+// dist[b][i][c][chunk][0..1] as ((value, runner-up value) as two floats, index), lowest index on ties.
+// |p - q| cannot be accumulated before the target row's normaliser is known: every workgroup of modes 0 and 2 first combines the
+// row's records from k_stats (lse_p).  None of them needs anything of the accept chain, nor that anything of theirs, so that modes 0
+// and 2 share k_finish's launch and modes 3 and 4 that of k_stats, and no launch of their own stands between the two.
+// Whole verifications in us, with such a launch / now: total variation, V = 32000, 4 drafts, one sequence 21.1 / 17.1, V = 152064, 8
+// sequences 66.9 / 52.2, V = 20000, 6 drafts, 9 sequences 34.5 / 22.8, V = 128256, 8 drafts, 32 sequences 149 / 141; mixtures of
+// V = 100003, 24 sequences 64.1 / 56.4; hard labels, V = 32000, one sequence 24.1 / 20.8, V = 152064, 8 sequences 68.8 / 63.3.
 // =====================================================================================================
 struct DistArgs {
     int V, n, B, gamma, C3, RS, DW, Cd;
@@ -1007,8 +1013,8 @@ struct DistArgs {
 };
 
 template <int MODE, int N>
-__global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
-    const int c = blockIdx.x, i = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void dist_chunk(const DistArgs& a, int c, int i, int b) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma;
     constexpr int NC = TABED_GRID_CANDIDATES;
     __shared__ double s_lse;
@@ -1135,12 +1141,13 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
     }
     if (wave == 0) {                                   // lse of target row (b, i) from its records
         const double* r0 = a.stats + ((size_t)b * (gamma + 1) + i) * a.C3 * a.RS;
-        double m = -INFINITY;
-        for (int cc = lane; cc < a.C3; cc += kWave) m = fmax(m, r0[(size_t)cc * a.RS]);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-        double Z = 0.0;
-        for (int cc = lane; cc < a.C3; cc += kWave) {
+        double m = -INFINITY, m0 = -INFINITY, z0 = 0.0;
+        if (lane < a.C3) { m0 = r0[(size_t)lane * a.RS]; z0 = r0[(size_t)lane * a.RS + 1]; }      // (one trip for up to 64 chunks)
+        m = m0;
+        for (int cc = lane + kWave; cc < a.C3; cc += kWave) m = fmax(m, r0[(size_t)cc * a.RS]);
+        m = wave_max(m);
+        double Z = (m0 > -INFINITY) ? z0 * exp(m0 - m) : 0.0;
+        for (int cc = lane + kWave; cc < a.C3; cc += kWave) {
             const double* r = r0 + (size_t)cc * a.RS;
             if (r[0] > -INFINITY) Z += r[1] * exp(r[0] - m);
         }
@@ -1163,34 +1170,46 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
         }
 
     if (MODE == 0) {
-        auto rows = [&](auto load) {
-            constexpr int kRows = N > 0 ? N : 1;
-#pragma unroll kRows
-            for (int j = 0; j < n; ++j) {
-                float acc = 0.f;
+        auto row = [&](int j, const float4 (&y)[4]) {
+            float acc = 0.f;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float4 y = load(j, u);
+            for (int u = 0; u < 4; ++u)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float ye = f4get(y, e);
-                        const float q = (ye > -INFINITY) ? __expf(ye * invT - s_hi[j]) * s_oml[j] : 0.f;
-                        acc += fabsf(pv[u * 4 + e] - q);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const float ye = f4get(y[u], e);
+                    const float q = (ye > -INFINITY) ? __expf(ye * invT - s_hi[j]) * s_oml[j] : 0.f;
+                    acc += fabsf(pv[u * 4 + e] - q);
                 }
-                const double t = wave_sum((double)acc);
-                if (lane == 0) s_sum[wave][j] = t;
-            }
+            const double t = wave_sum((double)acc);
+            if (lane == 0) s_sum[wave][j] = t;
         };
-        if (N > 0) rows([&](int j, int u) { return yq[N > 0 ? j : 0][u]; });
-        else if (inside) rows([&](int j, int u) { return load_group(qbase + (size_t)j * V, v(u)); });
-        else with_row_loads(V, [&](auto load) {
-            rows([&](int j, int u) {
-                float4 y = load(qbase + (size_t)j * V, at(u));
-                mask_group(y, at(u), v(u));
-                return y;
+        if (N > 0) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) row(j, yq[j]);
+        } else {
+            // two rows at a time: the next one is on its way while one is summed (past the last draft it is re-read)
+            with_row_loads(V, [&](auto load) {
+                float4 y[2][4];
+                auto request = [&](int j, int set) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) y[set][u] = load(qbase + (size_t)min(j, n - 1) * V, at(u));
+                };
+                auto use = [&](int j, int set) {
+                    if (!inside) {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) mask_group(y[set][u], at(u), v(u));
+                    }
+                    row(j, y[set]);
+                };
+                request(0, 0);
+                for (int j = 0; j < n; j += 2) {
+                    request(j + 1, 1);
+                    use(j, 0);
+                    request(j + 2, 0);
+                    if (j + 1 < n) use(j + 1, 1);
+                }
             });
-        });
+        }
     } else {
         // both drafts' probabilities of this thread's 16 elements, then one candidate mixture at a time
         float q0[16], q1[16];
@@ -1215,9 +1234,23 @@ __global__ __launch_bounds__(kBlock) void k_dist(DistArgs a) {
         }
     }
     __syncthreads();
-    if (tid < a.DW)
-        a.dist[((((size_t)b * gamma + i) * a.DW + tid) * a.Cd + c) * 2] =
-            (s_sum[0][tid] + s_sum[1][tid]) + (s_sum[2][tid] + s_sum[3][tid]);
+    if (tid < a.DW)                                        // another workgroup of this launch adds the chunks
+        publish_store(&a.dist[((((size_t)b * gamma + i) * a.DW + tid) * a.Cd + c) * 2],
+                      (s_sum[0][tid] + s_sum[1][tid]) + (s_sum[2][tid] + s_sum[3][tid]));
+}
+
+// Target statistics and hard labels in one launch: the labels' workgroups first (nd of them), then k_stats'.
+template <int U, int MODE>
+__global__ __launch_bounds__(kBlock) void k_stats_labels(StatsArgs a, DistArgs d, int nd) {
+    int g = blockIdx.x;
+    if (g < nd) {
+        const int c = g % d.Cd, bi = g / d.Cd;
+        dist_chunk<MODE, 0>(d, c, bi % d.gamma, bi / d.gamma);
+    } else {
+        g -= nd;
+        const int c = g % a.C3, bi = g / a.C3;
+        stats_chunk<U, 0>(a, c, bi % (a.gamma + 1), bi / (a.gamma + 1));
+    }
 }
 
 static int pick_stats_unroll(const tabed_cfg& c, int nmax_u) {
@@ -1280,12 +1313,12 @@ struct FinishArgs {
     const float* u_acc;
     const float* u_res;
     const double* stats;
-    const double* dist;   // [B][gamma][DW][Cd] second-pass chunk sums, or nullptr (KL from the records)
+    const double* dist;   // [B][gamma][DW][Cd] chunk sums of dist_chunk, or nullptr (KL from the records)
     int DW, Cd;
     float dist_scale;     // 0.5 for total variation, 1 for KL
     int hard;             // 1: dist holds chunk arg-maxes and the distance is the token-mismatch indicator
     int hard_margin;      // 1: those arg-maxes are of fp32 mixtures: a near-tie flags the position
-    int grid_kl;          // 1: the records of k_stats hold the KL sums of the DW candidate mixtures (no second pass)
+    int grid_kl;          // 1: the records of k_stats hold the KL sums of the DW candidate mixtures
     int fuse;             // 1: the call also advances every sequence's window and writes the next weights
     WindowArgs win;
     double* tstate;       // token tree: [B][kTsSlots] record of every sequence's walk, or nullptr (chain)
@@ -1293,6 +1326,8 @@ struct FinishArgs {
     double* seg;          // [B][2][NSEG]
     uint32_t* tickets;
     uint32_t* wtickets;   // [B] of the staged weights
+    uint32_t* dtickets;   // [B] of the distances, where their workgroups are in this launch
+    int early;            // 1: greedy rows' workgroups without book-keeping leave at once
     int32_t* accept_len;
     int32_t* out_tokens;
     float* dev;
@@ -1438,10 +1473,75 @@ __device__ __forceinline__ void walk_seg_run(const double (&mR)[kMaxSegRun], con
     *s_prefix = P;
 }
 
-template <int N>
-__global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
+// DK: whether the workgroups of the distances are in this launch.  0: no (KL, hard labels); 1, 2: total variation of the drafts, all
+// rows of a chunk up front or one after the other; 3: of the two-draft grid's mixtures.  They come after all others in the
+// grid, and the last to arrive of them and of the book-keeping workgroup, which knows how many positions count, adds a sequence's
+// chunk sums and does what the book-keeping workgroup does otherwise: distances, window, next weights.
+enum DistKind { kDistNone = 0, kDistUpFront = 1, kDistInTurn = 2, kDistMixtures = 3 };
+
+template <int N, int DK>
+__global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a, DistArgs d) {
     extern __shared__ __attribute__((aligned(16))) double s_scale[];   // [gamma+1][C3]: exp(m_c - m_row)
-    const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int c = blockIdx.x, b = blockIdx.y;
+    __shared__ double s_wpart[64], s_wx[TABED_MAX_N];    // window update (one wave)
+    __shared__ int s_last;
+    __shared__ float s_dev[DK != kDistNone ? TABED_MAX_GAMMA * TABED_MAX_N : 1];
+    // the sum of a sequence's distances over their chunks, then window and next weights (all workgroups that it waits for are done)
+    auto sum_distances = [&](bool greedy) {
+        const int l8 = tid & 7, entries = a.gamma * a.DW;  // eight lanes an entry, each every eighth chunk in order
+        for (int q0 = 0; q0 < entries; q0 += kBlock / 8) {
+            const int q = q0 + (tid >> 3);
+            const double* r0 = a.dist + ((size_t)b * entries + min(q, entries - 1)) * a.Cd * 2;
+            double D = 0.0;
+            for (int c0 = l8; c0 < a.Cd; c0 += 64) {
+                double v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = published_load(&r0[min(c0 + 8 * u, a.Cd - 1) * 2]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (c0 + 8 * u < a.Cd) D += v[u];
+            }
+            D += dpp_f64<kDppXor1>(D);
+            D += dpp_f64<kDppXor2>(D);
+            D += dpp_f64<kDppHalfMirror>(D);
+            const float e = (float)((double)a.dist_scale * D);
+            if (l8 == 0 && q < entries) { a.dev[(size_t)b * entries + q] = e; s_dev[q] = e; }
+        }
+        if (!a.fuse) return;
+        __syncthreads();
+        if (tid >= kWave) return;
+        const int nv = published_load(&a.n_valid[b]);
+        WindowArgs wa = a.win;
+        if (!greedy) wa.weights = a.wstage;                // (see the book-keeping workgroup below)
+        window_update<true>(wa, b, lane, [&](int q) { return s_dev[q]; }, nv, s_wpart, s_wx);
+        if (greedy) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        int second = 0;
+        if (lane == 0) second = arrive(&a.wtickets[(size_t)b * a.TS], 2u) ? 1 : 0;
+        if (__builtin_amdgcn_readfirstlane(second) && lane < a.n)
+            a.win.weights[(size_t)b * a.n + lane] = published_load(&a.wstage[(size_t)b * a.n + lane]);
+    };
+    auto arrive_distances = [&]() -> bool {                // by all of a workgroup, its results published
+        publish_barrier();
+        if (tid == 0) s_last = arrive(&a.dtickets[(size_t)b * a.TS], (uint32_t)(a.Cd * a.gamma + 1)) ? 1 : 0;
+        __syncthreads();
+        return s_last != 0;
+    };
+    if constexpr (DK != kDistNone) {
+        const int nf = (a.C5 + 1) * a.B;
+        int g = blockIdx.x;
+        if (g >= nf) {
+            g -= nf;
+            const int bi = g / a.Cd;
+            b = bi / a.gamma;
+            dist_chunk<DK == kDistMixtures ? 2 : 0, DK == kDistInTurn ? 0 : N>(d, g % a.Cd, bi % a.gamma, b);
+            if (arrive_distances()) sum_distances(!(a.temperature[b] > 0.f));
+            return;
+        }
+        b = g / (a.C5 + 1);
+        c = g % (a.C5 + 1);
+    }
     const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma, NSEG = a.NSEG, C3 = a.C3, RS = a.RS;
 
     __shared__ double s_rowm[TABED_MAX_GAMMA + 1], s_rowZ[TABED_MAX_GAMMA + 1], s_rowlse[TABED_MAX_GAMMA + 1];
@@ -1450,16 +1550,15 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     __shared__ uint32_t s_aflag[TABED_MAX_GAMMA + 1];
     __shared__ float s_hi[TABED_MAX_GAMMA][TABED_MAX_N], s_lo[TABED_MAX_GAMMA][TABED_MAX_N], s_w[TABED_MAX_N];
     __shared__ double s_redd[kWavesPerBlock];
-    __shared__ int s_last, s_first[kWavesPerBlock], s_lastw[kWavesPerBlock], s_seg;
+    __shared__ int s_first[kWavesPerBlock], s_lastw[kWavesPerBlock], s_seg;
     __shared__ double s_prefix;
-    __shared__ double s_wpart[64], s_wx[TABED_MAX_N];    // fused window update (one wave)
     __shared__ int s_y[TABED_MAX_GAMMA];                 // drafted tokens (hard labels)
 
     // ---- a greedy row has work for its book-keeping workgroup only.  Where workgroups queue for the chip the others leave at
     //      once (48 sequences of V = 152063, half of them greedy: 22.5 us, 27.5 if they read the records first); elsewhere waiting
     //      for the temperature before anything else is requested would be one more trip for everybody.
     const bool book = (c == a.C5);                        // the book-keeping workgroup of this sequence
-    if (gridDim.x * gridDim.y > 1024 && !book) {
+    if (a.early && !book) {
         if (!(a.temperature[b] > 0.f)) return;
     }
     asm volatile("" ::: "memory");                         // (keeps that load in its branch)
@@ -1594,7 +1693,9 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
     }
 
     if (book) {
-        if (a.dist == nullptr) {
+        if (DK != kDistNone) {
+            // (distances: sum_distances)
+        } else if (a.dist == nullptr) {
             // ---- distances: an entry per (position, draft or candidate mixture): its chunk sums times the scales
             //      computed above.  KL(p || q_j) = A_j / Z - lse_p + lse_j; a mixture's sums already hold its logarithm.
             //      Eight lanes add an entry's chunks, each every eighth one in order, eight requested at once; their sums are
@@ -1619,26 +1720,6 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
                 A += dpp_f64<kDppHalfMirror>(A);
                 const double kl = A / s_rowZ[ii] - s_rowlse[ii] + lq;
                 if (l8 == 0 && q < gamma * dw) publish_store(&a.dev[(size_t)b * gamma * dw + q], (float)kl);
-            }
-        } else if (!a.hard) {
-            // ---- distances from the second pass: add the chunk sums
-            const int l8 = tid & 7;                        // eight lanes an entry, in the order above
-            for (int q0 = 0; q0 < gamma * a.DW; q0 += kBlock / 8) {
-                const int q = q0 + (tid >> 3);
-                const double* r0 = a.dist + ((size_t)b * gamma * a.DW + min(q, gamma * a.DW - 1)) * a.Cd * 2;
-                double D = 0.0;
-                for (int c0 = l8; c0 < a.Cd; c0 += 64) {
-                    double v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = r0[min(c0 + 8 * u, a.Cd - 1) * 2];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (c0 + 8 * u < a.Cd) D += v[u];
-                }
-                D += dpp_f64<kDppXor1>(D);
-                D += dpp_f64<kDppXor2>(D);
-                D += dpp_f64<kDppHalfMirror>(D);
-                if (l8 == 0 && q < gamma * a.DW) publish_store(&a.dev[(size_t)b * gamma * a.DW + q], (float)((double)a.dist_scale * D));
             }
         } else {
             // ---- hard labels: 1 where a candidate's arg-max differs from the token emitted at the position.
@@ -1667,7 +1748,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
         }
         if (tid == 0) {
             a.accept_len[b] = k;
-            a.n_valid[b] = k + 1 < gamma ? k + 1 : gamma;
+            publish_store(&a.n_valid[b], k + 1 < gamma ? k + 1 : gamma);
             if (a.tstate != nullptr && greedy) {           // token tree: where the trunk stopped and what the target wants there
                 double* ts = a.tstate + (size_t)b * kTsSlots;
                 ts[kTsK] = (double)k;
@@ -1676,12 +1757,19 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
             }
         }
     }
+    if constexpr (DK != kDistNone) {
+        if (book) {
+            if (arrive_distances()) sum_distances(greedy);
+            return;
+        }
+    }
     const int nv_k = k + 1 < gamma ? k + 1 : gamma;
+    auto dev_at = [&](int q) { return published_load(&a.dev[(size_t)b * gamma * a.win.dw + q]); };
     if (greedy) {
         // a greedy row is complete here: its single workgroup also advances the window when asked to
         if (a.fuse) {
             publish_barrier();                             // the distances above are acknowledged
-            if (tid < kWave) window_update<true>(a.win, b, lane, a.dev, nv_k, s_wpart, s_wx);
+            if (tid < kWave) window_update<true>(a.win, b, lane, dev_at, nv_k, s_wpart, s_wx);
         }
         return;
     }
@@ -1699,7 +1787,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
             if (tid >= kWave) return;
             WindowArgs wa = a.win;
             wa.weights = a.wstage;
-            window_update<true>(wa, b, lane, a.dev, nv_k, s_wpart, s_wx);
+            window_update<true>(wa, b, lane, dev_at, nv_k, s_wpart, s_wx);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's staged weights are acknowledged
             int second = 0;
             if (lane == 0) second = arrive(&a.wtickets[(size_t)b * a.TS], 2u) ? 1 : 0;
@@ -1741,7 +1829,7 @@ __global__ __launch_bounds__(kBlock) void k_finish(FinishArgs a) {
         const uint32_t extra = (a.hard_margin && __ballot(any)) ? (uint32_t)TABED_FLAG_SAMPLE_MARGIN : 0u;
         if (a.fuse) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's published distances are acknowledged
-            window_update<true>(a.win, b, lane, a.dev, nv_k, s_wpart, s_wx);
+            window_update<true>(a.win, b, lane, dev_at, nv_k, s_wpart, s_wx);
         }
         return extra;
     };
@@ -1829,7 +1917,8 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
                          int32_t* out_tokens, float* dev, int32_t* n_valid, uint8_t* flags, float* ring,
                          int32_t* ring_head, int32_t* ring_count, float* next_weights, bool tree, hipStream_t s) {
     const bool grid_in_stats = (c.policy == 2 && c.distance == 0);   // the KL of the two-draft grid's mixtures rides in the statistics pass
-    const bool second_pass = (c.distance != 0);                      // distances that take a pass of their own
+    const bool second_pass = (c.distance != 0);                      // distances that the records of k_stats do not hold
+    const bool labels = (c.distance == 2);
     const int ncomp = compiled_drafts(c.n);
     // the statistics pass: rows one after the other for three and five drafts, where all of them up front took more registers
     // than the trips saved are worth (12 sequences of V = 128256, us: 3 drafts 17.5 against 18.5, 5 drafts 24.0 against 26.0),
@@ -1837,6 +1926,10 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     const int scomp = (second_pass || ncomp == 3 || ncomp == 5) ? 0 : ncomp;
     const int U = pick_stats_unroll(c, scomp > 4 ? 2 : 4);
     const int C3 = (c.V + kBlock * 4 * U - 1) / (kBlock * 4 * U);
+    DistArgs d{};
+    d.V = c.V; d.n = c.n; d.B = c.B; d.gamma = c.gamma; d.C3 = C3; d.RS = L.RS; d.DW = L.DW; d.Cd = L.Cd;
+    d.target = target_logits; d.dlogits = draft_logits; d.dlse = draft_lse; d.temperature = temperature;
+    d.dist = reinterpret_cast<double*>(ws + L.off_dist);
     {
         ProfScope prof(TABED_K_STATS, s);
         StatsArgs a;
@@ -1846,6 +1939,17 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
         a.target = target_logits; a.dlogits = draft_logits; a.dlse = draft_lse; a.temperature = temperature;
         a.stats = reinterpret_cast<double*>(ws + L.off_stats);
         const dim3 grid(C3, c.gamma + 1, c.B);
+        d.stats = a.stats;
+        if (labels) {
+            const int nd = L.Cd * c.gamma * c.B;
+            const dim3 both(nd + C3 * (c.gamma + 1) * c.B);
+#define TABED_LABELS(U_) (c.policy != 2 ? launch(&prof, k_stats_labels<U_, 3>, both, dim3(kBlock), 0, s, a, d, nd) \
+                                        : launch(&prof, k_stats_labels<U_, 4>, both, dim3(kBlock), 0, s, a, d, nd))
+            if (U == 1) TABED_LABELS(1);
+            else if (U == 2) TABED_LABELS(2);
+            else TABED_LABELS(4);
+#undef TABED_LABELS
+        } else
 #define TABED_STATS(N_) launch_stats_n<N_>(&prof, U, grid, s, a)
         switch (scomp) {
             case 1: TABED_STATS(1); break;
@@ -1857,29 +1961,6 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
 #undef TABED_STATS
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (second_pass) {
-            ProfScope dprof(TABED_K_DIST, s);              // a dispatch of its own: its own event pair
-            DistArgs d;
-            d.V = c.V; d.n = c.n; d.B = c.B; d.gamma = c.gamma; d.C3 = C3; d.RS = L.RS; d.DW = L.DW; d.Cd = L.Cd;
-            d.target = target_logits; d.dlogits = draft_logits; d.dlse = draft_lse; d.temperature = temperature;
-            d.stats = a.stats;
-            d.dist = reinterpret_cast<double*>(ws + L.off_dist);
-            const dim3 gd(L.Cd, c.gamma, c.B);
-            const int mode = (c.distance == 2) ? (c.policy != 2 ? 3 : 4) : (c.policy != 2 ? 0 : 2);
-            // Total variation: all draft rows of a chunk up front while the grid is at most two workgroups a compute unit, one row
-            // after the other beyond, where the 17 registers a row cost more workgroups than the trips saved are worth (us, up
-            // front / in turn: 32 workgroups, V = 8001, 4 drafts 7.9 / 9.4; 624, V = 50261, 3 drafts 11.9 / 11.8; 1536, V = 32000,
-            // 2, 4 and 8 drafts 17.7 / 11.9, 27.9 / 18.8, 58.6 / 33.9)
-            const int dcomp = ((long)L.Cd * c.gamma * c.B <= 512) ? ncomp : 0;
-#define TABED_DIST(N_) launch(&dprof, k_dist<0, N_>, gd, dim3(kBlock), 0, s, d)
-            if (mode == 0) { TABED_FOR_DRAFTS(dcomp, TABED_DIST) }
-            else if (mode == 2) launch(&dprof, k_dist<2, 0>, gd, dim3(kBlock), 0, s, d);
-            else if (mode == 3) launch(&dprof, k_dist<3, 0>, gd, dim3(kBlock), 0, s, d);
-            else launch(&dprof, k_dist<4, 0>, gd, dim3(kBlock), 0, s, d);
-#undef TABED_DIST
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
     }
     ProfScope prof(TABED_K_RESID, s);
     FinishArgs a;
@@ -1900,9 +1981,29 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 2 * (size_t)c.B * L.TS;
     a.wtickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 1 * (size_t)c.B * L.TS;
     a.accept_len = accept_len; a.out_tokens = out_tokens; a.dev = dev; a.n_valid = n_valid; a.flags = flags;
-    const dim3 grid(L.C5 + 1, c.B);                      // + the book-keeping workgroup of every sequence
+    a.dtickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 3 * (size_t)c.B * L.TS;
+    const int finishers = (L.C5 + 1) * c.B;              // with the book-keeping workgroup of every sequence
+    a.early = finishers > 1024 ? 1 : 0;
     const size_t lds = sizeof(double) * (size_t)(c.gamma + 1) * C3;
-#define TABED_FINISH(N_) launch(&prof, k_finish<N_>, grid, dim3(kBlock), lds, s, a)
+    if (second_pass && !labels) {
+        // All draft rows of a chunk up front while the registers of that (16 a row) leave the whole grid resident at once, one row after
+        // the other beyond, where they cost more workgroups than the trips saved are worth (V = 50261, 3 drafts, 12 sequences, 936 workgroups: 25.3 / 26.0 us;
+        // as a launch of their own, 1536 workgroups of V = 32000 with 2, 4 and 8 drafts 17.7 / 11.9, 27.9 / 18.8, 58.6 / 33.9).  Eight drafts
+        // beyond: k_finish without a compile-time draft count has 81 registers instead of 117 (V = 128256, 32 sequences 165 us, 182;
+        // 141 with two rows at a time)
+        const long nd = (long)L.Cd * c.gamma * c.B;
+        const dim3 grid((unsigned)(finishers + nd));
+#define TABED_FINISH(N_)                                                                                          \
+    finishers + nd <= 256 * (N_ <= 4 ? 4 : N_ == 5 ? 3 : 2) ? launch(&prof, k_finish<N_, N_ != 0 ? kDistUpFront : kDistInTurn>, grid, dim3(kBlock), lds, s, a, d) \
+              : launch(&prof, k_finish<N_, kDistInTurn>, grid, dim3(kBlock), lds, s, a, d)
+        if (c.policy == 2) launch(&prof, k_finish<2, kDistMixtures>, grid, dim3(kBlock), lds, s, a, d);
+        else if (c.n == 8 && finishers + nd > 512) TABED_FINISH(0);
+        else { TABED_FOR_DRAFTS(ncomp, TABED_FINISH) }
+#undef TABED_FINISH
+        return hipGetLastError();
+    }
+    const dim3 grid(L.C5 + 1, c.B);
+#define TABED_FINISH(N_) launch(&prof, k_finish<N_, kDistNone>, grid, dim3(kBlock), lds, s, a, d)
     TABED_FOR_DRAFTS(ncomp, TABED_FINISH)
 #undef TABED_FINISH
     return hipGetLastError();
