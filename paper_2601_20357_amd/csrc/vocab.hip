@@ -2018,9 +2018,13 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
 //     f_c(v) = max(0, f_{c-1}(v) / Z_{c-1} - q_k(v)),   Z_c = sum_v f_c(v),
 // sibling c is accepted iff u_c q_k(y_c) Z_c < f_c(y_c); an accepted sibling is emitted and followed by a
 // bonus token from the target's distribution after it (its leaf row); if all are rejected the corrected
-// token comes from f_width.  k_tree_begin decides sibling 1 (Z_1 is known), k_tree_level<L> computes level
-// L >= 2 for the sequences still undecided and either decides sibling L or (L = width) draws the corrected
-// token, k_tree_bonus draws the token after an accepted leaf.  Sequences whose walk is over skip every pass.
+// token comes from f_width.  Sibling 1 needs no pass (Z_1 is known), level L >= 2 is one pass over the row, which either decides
+// sibling L or (L = width) draws the corrected token, and the token after an accepted leaf is one pass over that leaf's row.
+// A sequence needs at most width - 1 passes, one after the other, and is in one of them at a time: a launch does the next pass of every
+// sequence, whichever it is, and the first one tests sibling 1 as well (every workgroup for itself).  Width 2 takes one launch, width 3
+// two; sequences whose walk is over leave at once.  (With launches of their own for the test, each level and the bonus token, two more
+// each: a round of V = 32000, 4 drafts, 4 sequences, width 3
+// 152.8 us, now 142.9; width 2 with 16 sequences 165.0, 155.9.)
 // =====================================================================================================
 struct TreeArgs {
     int V, n, B, gamma, S, NSEG, C5, TS;   // S = width - 1 siblings per position
@@ -2062,42 +2066,41 @@ __device__ __forceinline__ bool tree_test(int L, double py, double qy, double Z1
     return lhs < fy;
 }
 
-__global__ __launch_bounds__(64) void k_tree_begin(TreeArgs a) {
-    const int b = blockIdx.x;
-    if (threadIdx.x != 0) return;
-    double* ts = a.tstate + (size_t)b * kTsSlots;
-    const int gamma = a.gamma, S = a.S, V = a.V;
-    const int k = (int)ts[kTsK];
+struct TreeWalk {
+    int status, index, k;                                   // kTree*; next level or accepted sibling; the rejected position
+    uint32_t flag;                                          // flags of position k so far
+};
+
+// Where the walk of sequence b starts: sibling 1's test, or the greedy row's match.  All threads alike.
+__device__ __forceinline__ TreeWalk tree_begin(const TreeArgs& a, int b) {
+    const double* ts = a.tstate + (size_t)b * kTsSlots;
+    const int gamma = a.gamma, S = a.S, V = a.V, k = __builtin_amdgcn_readfirstlane((int)ts[kTsK]);
     const float T = a.temperature[b];
-    const bool greedy = !(T > 0.f);
-    int status = kTreeDone, index = 0;
-    a.leaf[b] = 0;
-    a.n_out[b] = k + 1;
-    if (k < gamma && S > 0) {
-        const size_t so = ((size_t)b * gamma + k) * S;
-        if (greedy) {
-            const int top = (int)ts[kTsArgmax];
-            for (int sidx = 1; sidx <= S && status == kTreeDone; ++sidx)
-                if (a.sib_tokens[so + sidx - 1] == top) { status = kTreeLeaf; index = sidx; }
-        } else if (ts[kTsZ1] > 0.0) {
-            // the chain's corrected token (drawn from level 1) is replaced: by a leaf, or by a draw from level width
-            uint32_t flag = a.flags[(size_t)b * (gamma + 1) + k] & ~(uint32_t)(TABED_FLAG_SAMPLE_MARGIN | TABED_FLAG_DEGENERATE);
-            const int y = a.sib_tokens[so];
-            status = kTreePending; index = 2;
-            if (y >= 0 && y < V) {
-                const double lse = ts[kTsRowMax] + log(ts[kTsRowZ]);
-                const double py = exp((double)(a.target[((size_t)b * (gamma + 1) + k) * V + y] * (1.f / T)) - lse);
-                const float u = a.u_acc_sib ? a.u_acc_sib[so]
-                                            : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)k + kSiblingStride, 1);
-                if (tree_test(1, py, (double)a.sib_q[so], 0.0, 0.0, ts[kTsZ1], u, &flag)) { status = kTreeLeaf; index = 1; }
-            } else {
-                flag |= TABED_FLAG_DEGENERATE;
-            }
-            a.flags[(size_t)b * (gamma + 1) + k] = (uint8_t)flag;
+    TreeWalk t{kTreeDone, 0, k, 0};
+    if (k >= gamma || S == 0) return t;
+    const size_t so = ((size_t)b * gamma + k) * S;
+    if (!(T > 0.f)) {
+        const int top = (int)ts[kTsArgmax];
+        for (int sidx = 1; sidx <= S && t.status == kTreeDone; ++sidx)
+            if (a.sib_tokens[so + sidx - 1] == top) { t.status = kTreeLeaf; t.index = sidx; }
+    } else if (ts[kTsZ1] > 0.0) {
+        // the chain's corrected token (drawn from level 1) is replaced: by a leaf, or by a draw from level width
+        t.flag = a.flags[(size_t)b * (gamma + 1) + k] & ~(uint32_t)(TABED_FLAG_SAMPLE_MARGIN | TABED_FLAG_DEGENERATE);
+        const int y = a.sib_tokens[so];
+        t.status = kTreePending; t.index = 2;
+        if (y >= 0 && y < V) {
+            const double lse = ts[kTsRowMax] + log(ts[kTsRowZ]);
+            const double py = exp((double)(a.target[((size_t)b * (gamma + 1) + k) * V + y] * (1.f / T)) - lse);
+            const float u = a.u_acc_sib ? a.u_acc_sib[so]
+                                        : tabed_uniform(a.seed, a.round, (uint32_t)b, (uint32_t)k + kSiblingStride, 1);
+            if (tree_test(1, py, (double)a.sib_q[so], 0.0, 0.0, ts[kTsZ1], u, &t.flag)) { t.status = kTreeLeaf; t.index = 1; }
+        } else {
+            t.flag |= TABED_FLAG_DEGENERATE;
         }
     }
-    ts[kTsStatus] = (double)status;
-    ts[kTsIndex] = (double)index;
+    t.status = __builtin_amdgcn_readfirstlane(t.status);
+    t.index = __builtin_amdgcn_readfirstlane(t.index);
+    return t;
 }
 
 // Locates, in the workgroup that finishes a sequence, the 256-wide segment whose prefix of masses crosses
@@ -2148,8 +2151,10 @@ __device__ __forceinline__ int tree_pick_token(const float (&f)[4], int v, int V
     uint32_t mine = 0;
     if (lane == pick) {
         const double tol = (double)kMargin * Z;
-        const double fe = (double)(e == 0 ? f[0] : e == 1 ? f[1] : e == 2 ? f[2] : f[3]);
-        const double hi_edge = e == 0 ? cdf[0] : e == 1 ? cdf[1] : e == 2 ? cdf[2] : cdf[3];
+        double fe = 0.0, hi_edge = 0.0;
+#pragma unroll
+        for (int x = 0; x < 4; ++x)                        // (not f[e]: the arrays stay in registers)
+            if (x == e) { fe = (double)f[x]; hi_edge = cdf[x]; }
         if (fabs(hi_edge - target) < tol && tok + 1 < V) mine |= TABED_FLAG_SAMPLE_MARGIN;
         if (tok > 0 && fabs((hi_edge - fe) - target) < tol) mine |= TABED_FLAG_SAMPLE_MARGIN;
     }
@@ -2158,13 +2163,12 @@ __device__ __forceinline__ int tree_pick_token(const float (&f)[4], int v, int V
     return __builtin_amdgcn_readlane(tok, pick);
 }
 
+// Level L = w.index of a pending sequence (one of its C5 workgroups).
 template <int N>
-__global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
-    const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void tree_level(const TreeArgs& a, int c, int b, const TreeWalk& w) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, L = w.index, k = w.k;
     double* ts = a.tstate + (size_t)b * kTsSlots;
-    if ((int)ts[kTsStatus] != kTreePending || (int)ts[kTsIndex] != L) return;      // uniform over the grid row
     const int V = a.V, n = (N > 0) ? N : a.n, gamma = a.gamma, S = a.S, NSEG = a.NSEG;
-    const int k = (int)ts[kTsK];
     const float T = a.temperature[b];
     const double Z1 = ts[kTsZ1], Z2 = ts[kTsZ2];
     const float invZ1 = (float)(1.0 / Z1), invZ2 = (L >= 3) ? (float)(1.0 / Z2) : 0.f;
@@ -2221,12 +2225,13 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
     const double* massP = a.segP + ((size_t)b * 2 + 1) * NSEG;
     const int SPT = (NSEG + kBlock - 1) / kBlock;
     const int g0 = min(NSEG, tid * SPT), g1 = min(NSEG, g0 + SPT);
+    if (tid == 0) { a.leaf[b] = 0; a.n_out[b] = k + 1; }    // (unless a leaf is accepted after all)
     double run = 0.0;
     for (int g = g0; g < g1; ++g) run += published_load(&massL[g]);
     double Z;
     double excl = block_exclusive_scan(run, s_redd, &Z);
     const size_t fidx = (size_t)b * (gamma + 1) + k;
-    uint32_t flag = a.flags[fidx];
+    uint32_t flag = w.flag;
     const bool degenerate = !(Z > 0.0);
     const double* mass = massL;
     if (degenerate) {
@@ -2254,7 +2259,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
             }
             a.flags[fidx] = (uint8_t)flag;
             if (decided) { ts[kTsStatus] = (double)kTreeLeaf; ts[kTsIndex] = (double)L; }
-            else { ts[kTsIndex] = (double)(L + 1); ts[kTsZ2] = Z; }   // L = 2: widths above 3 would need a Z_3
+            else { ts[kTsStatus] = (double)kTreePending; ts[kTsIndex] = (double)(L + 1); ts[kTsZ2] = Z; }   // L = 2: widths above 3 would need a Z_3
         }
         return;                                            // the next pass continues (or the leaf's bonus pass)
     }
@@ -2286,12 +2291,11 @@ __global__ __launch_bounds__(kBlock) void k_tree_level(TreeArgs a, int L) {
 // greedy row).  Every wave leaves, per 256-wide segment, the maximum of the scaled logits and the sum of
 // exp(. - that maximum); the last workgroup combines them (fp64, segment order), finds the segment the uniform
 // falls into and re-evaluates it.  Greedy: per-segment (value, index) arg-max records, merged lowest index first.
-__global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
-    const int c = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+__device__ __forceinline__ void tree_bonus(const TreeArgs& a, int c, int b, const TreeWalk& w) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double* ts = a.tstate + (size_t)b * kTsSlots;
-    if ((int)ts[kTsStatus] != kTreeLeaf) return;
     const int V = a.V, gamma = a.gamma, S = a.S, NSEG = a.NSEG;
-    const int k = (int)ts[kTsK], sidx = (int)ts[kTsIndex];
+    const int k = w.k, sidx = w.index;
     const float T = a.temperature[b];
     const bool greedy = !(T > 0.f);
     const float invT = greedy ? 1.f : 1.f / T;
@@ -2372,6 +2376,7 @@ __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
         }
         return;
     }
+    if (tid == 0) a.flags[fidx] = (uint8_t)w.flag;
     float ml = -INFINITY;
     for (int g = g0; g < g1; ++g) ml = fmaxf(ml, (float)published_load(&rec1[g]));
     const float M = block_max(ml, s_redf);
@@ -2432,6 +2437,30 @@ __global__ __launch_bounds__(kBlock) void k_tree_bonus(TreeArgs a) {
     }
 }
 
+// The next pass of every sequence.  first: of the walk, which starts here.
+template <int N>
+__global__ __launch_bounds__(kBlock) void k_tree_pass(TreeArgs a, int first) {
+    const int c = blockIdx.x, b = blockIdx.y;
+    double* ts = a.tstate + (size_t)b * kTsSlots;
+    TreeWalk w;
+    if (first) {
+        w = tree_begin(a, b);
+        if (w.status == kTreeDone && c == 0 && threadIdx.x == 0) {
+            a.leaf[b] = 0;
+            a.n_out[b] = w.k + 1;
+            ts[kTsStatus] = (double)kTreeDone;              // (nobody reads it in this launch)
+        }
+    } else {
+        w.status = __builtin_amdgcn_readfirstlane((int)ts[kTsStatus]);
+        if (w.status == kTreeDone) return;
+        w.index = __builtin_amdgcn_readfirstlane((int)ts[kTsIndex]);
+        w.k = __builtin_amdgcn_readfirstlane((int)ts[kTsK]);
+        w.flag = a.flags[(size_t)b * (a.gamma + 1) + w.k];
+    }
+    if (w.status == kTreePending) tree_level<N>(a, c, b, w);
+    else if (w.status == kTreeLeaf) tree_bonus(a, c, b, w);
+}
+
 hipError_t launch_verify_tree(const tabed_cfg& c, const WsLayout& L, char* ws, uint64_t round, int width,
                               const float* target_logits, const float* leaf_logits, const float* draft_logits,
                               const double* draft_lse, const int32_t* sib_tokens, const float* sib_q,
@@ -2450,22 +2479,16 @@ hipError_t launch_verify_tree(const tabed_cfg& c, const WsLayout& L, char* ws, u
     a.tseg = reinterpret_cast<double*>(ws + L.off_tseg);
     a.out_tokens = out_tokens; a.flags = flags; a.leaf = leaf; a.n_out = n_out;
     a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 3 * (size_t)c.B * L.TS;
-    // sibling 1 against the first residual (its mass is known from tabed_verify's pass); width 1: leaf = 0, n_out = k + 1
-    launch(&prof, k_tree_begin, dim3(c.B), dim3(64), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || width == 1) return e;
     const int ncomp = compiled_drafts(c.n);
-    const dim3 grid(L.C5, c.B);
-    for (int lvl = 2; lvl <= width; ++lvl) {
-#define TABED_LEVEL(N_) launch(nullptr, k_tree_level<N_>, grid, dim3(kBlock), 0, s, a, lvl)
-        TABED_FOR_DRAFTS(ncomp, TABED_LEVEL)
-#undef TABED_LEVEL
-        e = hipGetLastError();
+    for (int pass = 0; pass < std::max(1, width - 1); ++pass) {      // (width 1: no sibling, leaf = 0 and n_out = k + 1)
+        const dim3 grid(width == 1 ? 1 : L.C5, c.B);
+#define TABED_PASS(N_) launch(pass == 0 ? &prof : nullptr, k_tree_pass<N_>, grid, dim3(kBlock), 0, s, a, pass == 0 ? 1 : 0)
+        TABED_FOR_DRAFTS(ncomp, TABED_PASS)
+#undef TABED_PASS
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    a.tickets = reinterpret_cast<uint32_t*>(ws + L.off_tickets) + 4 * (size_t)c.B * L.TS;
-    launch(nullptr, k_tree_bonus, grid, dim3(kBlock), 0, s, a);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace tabed
