@@ -39,6 +39,20 @@ __device__ __forceinline__ float half_sum(float v) {
     return v;
 }
 
+// Four logits of a row, past L2 or through it.  Rows whose 64-byte sectors are shared by neighbouring tiles go through L2, which puts
+// the sectors together, where there are so many logits that storing parts of sectors is what takes the time.  Draft steps in us,
+// through / past L2: V = 100003, 255 rows, d = 1024 133 / 155, 128 rows, d = 640 68.8 / 78.4, V = 50004, 96 rows, d = 768 35.4 / 36.2,
+// V = 32001, 480 rows, d = 72 49.3 / 59.9; but below 16 MB of logits, most of which would be left to the write-back at the end, V = 20001,
+// 80 rows, d = 2048 36.1 / 31.3, V = 30001, 120 rows, d = 1160 36.8 / 35.9; up to 64 rows, whose stores go out beside the stream of W,
+// V = 100003 60.3 / 57.8 at 64 rows, 52.4 / 50.6 at 32; and with whole sectors, V = 100000, 128 rows 61.9 / 54.9.
+static bool past_l2(int V, int M) { return M <= 64 || (V & 15) == 0 || (long)M * V < (4l << 20); }
+// (An instance each: a choice at run time between the two stores becomes one that goes through L2.)
+template <bool PAST>
+__device__ __forceinline__ void store_logits(float* p, f32x4u x) {
+    if constexpr (PAST) __builtin_nontemporal_store(x, reinterpret_cast<f32x4u*>(p));
+    else *reinterpret_cast<f32x4u*>(p) = x;
+}
+
 constexpr int kPatchBytes = 32 * 144;                  // LDS in which a wave turns 32 rows of 32 floats
 
 // Epilogue of one 32x32 accumulator tile held TRANSPOSED: lane holds result row m_base + lane % 32 and the 16
@@ -46,6 +60,7 @@ constexpr int kPatchBytes = 32 * 144;                  // LDS in which a wave tu
 // 16-value in-register reduction plus one exchange between the two half-waves, and every lane stores four
 // runs of four consecutive logits.  inv_t[m] = 1/T of row m (LDS table).  With `pstage` the partials go to an
 // LDS table instead, from which the caller writes a workgroup's four tiles of a row as one 16-byte store.
+template <bool PAST = true>
 __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base, int v_base, int M, int V, int NT,
                                                    const float* inv_t, float* __restrict__ L,
                                                    float* __restrict__ pm, float* __restrict__ ps,
@@ -103,8 +118,7 @@ __device__ __forceinline__ void store_tile_32x32_t(const f32x16& acc, int m_base
             const int mr = 8 * i + (lane >> 3), q = lane & 7;
             const float4 val = *reinterpret_cast<const float4*>(tpatch + mr * 144 + q * 16);
             if (m_base + mr < M)                   // (rows of an odd vocabulary are only 4-byte aligned)
-                __builtin_nontemporal_store(f32x4u{val.x, val.y, val.z, val.w},
-                                            reinterpret_cast<f32x4u*>(L + (size_t)(m_base + mr) * V + v_base + 4 * q));
+                store_logits<PAST>(L + (size_t)(m_base + mr) * V + v_base + 4 * q, f32x4u{val.x, val.y, val.z, val.w});
         }
         return;
     }
@@ -131,7 +145,7 @@ __device__ __forceinline__ float2 both_halves(float v) {
 // (part: [row][kPT tiles] maxima, kPS floats on the sums), from where a row's are stored 16 bytes at a time: a store of their own for
 // every tile and row was two of three memory requests of the epilogue.
 // rows: how many rows of the wave's block exist; patch: two of kPatchBytes.
-template <int TV, int TM, int kPT, int kPS>
+template <bool PAST, int TV, int TM, int kPT, int kPS>
 __device__ __forceinline__ void store_full_tiles(const f32x16 (&acc)[TV][TM], int rows, const float* s_it, float* part, float* L /* row, entry 0 of the block */,
                                                  int V, unsigned char* patch) {
     const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
@@ -195,7 +209,7 @@ __device__ __forceinline__ void store_full_tiles(const f32x16 (&acc)[TV][TM], in
 #pragma unroll
             for (int i = 0; i < 4; ++i) val[i] = *reinterpret_cast<const float4*>(tp + (8 * i + (lane >> 3)) * 144 + q * 16);
             auto store = [&](int i) {
-                __builtin_nontemporal_store(f32x4u{val[i].x, val[i].y, val[i].z, val[i].w}, reinterpret_cast<f32x4u*>(out + (size_t)(8 * i) * V));
+                store_logits<PAST>(out + (size_t)(8 * i) * V, f32x4u{val[i].x, val[i].y, val[i].z, val[i].w});
             };
             if ((b + 1) * 32 <= rows) {                    // uniform
 #pragma unroll
@@ -768,7 +782,7 @@ constexpr int kLargeThreads = 512;
 // Off: type of a byte offset inside a tile (32 bits while a tile's rows span less than 4 GiB).
 // NA: partial sums of a logit, over the k-blocks in turn, added in order at the end: those of the W-streaming kernel, whose
 // waves share a tile in the same way (launch_stream).
-template <int BM, int BN, int PF, typename Off, int NA = 1>
+template <int BM, int BN, int PF, typename Off, int NA = 1, bool PAST = true>
 __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 4 : 2) void k_lmhead_tile(int M, int d, int V, int n, int NT,
                                                                 int mblocks, const uint16_t* __restrict__ W,
                                                                 const uint16_t* __restrict__ H,
@@ -906,7 +920,7 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 
     for (int a = 0; a < TV; ++a)
 #pragma unroll
         for (int b = 0; b < TM; ++b)
-            store_tile_32x32_t(acc[0][a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
+            store_tile_32x32_t<PAST>(acc[0][a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
 }
 
 // ---------------------------------------------------------------- bf16, more than 64 rows, hidden size a multiple of 64: operands straight to LDS
@@ -942,7 +956,7 @@ __device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off
                  : "=&s"(m0) : "s"(lds), "s"(step), "v"(off[0]), "v"(off[1]), "s"(base) : "memory", "scc");
 }
 
-template <int BM, int BN, int SW, int SH>
+template <int BM, int BN, int SW, int SH, bool PAST>
 __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, int V, int n, int NT, int mblocks, const uint16_t* __restrict__ W,
                                                                  const uint16_t* __restrict__ H, const float* __restrict__ temperature,
                                                                  float* __restrict__ L, float* __restrict__ pm, float* __restrict__ ps) {
@@ -1055,7 +1069,7 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
         return;
     }
     const int lr = wm * (BM / 2);
-    store_full_tiles<TV, TM, kPT, kPS>(acc, M - m0 - lr, s_invt + lr, s_part + lr * kPT + wn * TV, L + (size_t)(m0 + lr) * V + v0 + wn * 32 * TV, V, tpatch);
+    store_full_tiles<PAST, TV, TM, kPT, kPS>(acc, M - m0 - lr, s_invt + lr, s_part + lr * kPT + wn * TV, L + (size_t)(m0 + lr) * V + v0 + wn * 32 * TV, V, tpatch);
     lds_barrier();
 #pragma unroll
     for (int t = tid; t < 2 * BM * (kPT / 4); t += kLargeThreads) {
@@ -1239,30 +1253,30 @@ static hipError_t launch_stream(const ProfScope* prof, const tabed_cfg& c, const
     return launch_stream_k<MT, 2>(prof, c, Lay, run ? run : 1, W, H, temperature, logits, pm, ps, s);
 }
 
-template <int BM, int BN, int PF, typename Off, int NA = 1>
+template <int BM, int BN, int PF, typename Off, int NA = 1, bool PAST = true>
 static hipError_t launch_tile(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
                               const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
     const size_t lds = 2 * (size_t)(BM + BN) * kLRow;
     static std::once_flag once;
     static hipError_t rc = hipSuccess;
-    if (raise_lds_limit(&k_lmhead_tile<BM, BN, PF, Off, NA>, lds, once, rc) != hipSuccess) return rc;
+    if (raise_lds_limit(&k_lmhead_tile<BM, BN, PF, Off, NA, PAST>, lds, once, rc) != hipSuccess) return rc;
     const int mblocks = (M + BM - 1) / BM, nblocks = (c.V + BN - 1) / BN;
     const int nrounds = (nblocks + 7) / 8;             // vocabulary blocks are dealt to the 8 XCDs in rounds
-    launch(prof, k_lmhead_tile<BM, BN, PF, Off, NA>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
+    launch(prof, k_lmhead_tile<BM, BN, PF, Off, NA, PAST>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
            static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
     return hipSuccess;
 }
 
-template <int BM, int BN, int SW, int SH>
+template <int BM, int BN, int SW, int SH, bool PAST>
 static hipError_t launch_dma(const ProfScope* prof, const tabed_cfg& c, const WsLayout& Lay, int M, const void* W, const void* H,
                              const float* temperature, float* logits, float* pm, float* ps, hipStream_t s) {
     constexpr size_t lds = std::max((size_t)(SW * BN + SH * BM) * kLBK * 2, (size_t)16 * kPatchBytes + BM * 4 + 2 * BM * (BN / kTileV) * 4);
     static std::once_flag once;
     static hipError_t rc = hipSuccess;
-    if (raise_lds_limit(&k_lmhead_dma<BM, BN, SW, SH>, lds, once, rc) != hipSuccess) return rc;
+    if (raise_lds_limit(&k_lmhead_dma<BM, BN, SW, SH, PAST>, lds, once, rc) != hipSuccess) return rc;
     const int mblocks = (M + BM - 1) / BM, nblocks = (c.V + BN - 1) / BN;
     const int nrounds = (nblocks + 7) / 8;             // vocabulary blocks are dealt to the 8 XCDs in rounds
-    launch(prof, k_lmhead_dma<BM, BN, SW, SH>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
+    launch(prof, k_lmhead_dma<BM, BN, SW, SH, PAST>, dim3(nrounds * mblocks * 8), dim3(kLargeThreads), lds, s, M, c.d, c.V, c.n, Lay.NT, mblocks,
            static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), temperature, logits, pm, ps);
     return hipSuccess;
 }
@@ -1309,19 +1323,24 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
         // rows of V = 128256, d = 2048; 66.1 / 70.5 at 160 rows of 50261, 1152; 24.9 / 25.4 at 128 of 32000, 768; 87.5 / 94.3 at 96 of
         // 152064, 896; 76.4 / 76.3 at 96 of 32000, 4096; 19.7 / 19.8 at 256 of 9000, 512.  With one or two k-blocks there is nothing to have in
         // flight: 16.3 / 15.9 at 400 rows of 8000, 64, 33.6 / 33.1 at 256 of 65536, 128.
+        const bool past = past_l2(c.V, M);
+#define TABED_ROWS(FN_, ...)                                                               \
+    past ? FN_<__VA_ARGS__, true>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s)    \
+         : FN_<__VA_ARGS__, false>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s)
         const bool lines = c.d % kLBK == 0 && c.d >= 512;
         if (lines && M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
-            e = launch_dma<256, 256, 3, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = TABED_ROWS(launch_dma, 256, 256, 3, 2);
         else if (lines && tiles(128, 256) >= 192)
-            e = launch_dma<128, 256, 3, 3>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = TABED_ROWS(launch_dma, 128, 256, 3, 3);
         else if (lines && tiles(128, 128) > 256)       // two workgroups a compute unit (192 rows of 20000, 896 33.7 us with one, 29.0; 30.2 through registers)
-            e = launch_dma<128, 128, 2, 2>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = TABED_ROWS(launch_dma, 128, 128, 2, 2);
         else if (lines)
-            e = launch_dma<128, 128, 4, 4>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = TABED_ROWS(launch_dma, 128, 128, 4, 4);
         else if (M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
-            e = launch_tile<256, 256, 1, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
-        else if (tiles(128, 256) >= 192) e = launch_tile<128, 256, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
-        else e = launch_tile<128, 128, 2, uint32_t>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
+            e = TABED_ROWS(launch_tile, 256, 256, 1, uint32_t, 1);
+        else if (tiles(128, 256) >= 192) e = TABED_ROWS(launch_tile, 128, 256, 2, uint32_t, 1);
+        else e = TABED_ROWS(launch_tile, 128, 128, 2, uint32_t, 1);
+#undef TABED_ROWS
     }
     if (e != hipSuccess) return e;
     return hipGetLastError();
