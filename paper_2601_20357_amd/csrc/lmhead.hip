@@ -1027,20 +1027,18 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
     }
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((SW - 1) * WI + (SH - 1) * HI) : "memory");
     read_frags(0, 0);
-    auto step = [&](int kb, auto refill) {
+    auto step = [&](int kb, auto refill, auto left) {
 #pragma unroll
         for (int ks = 0; ks < kLBK / 16 - 1; ++ks) {                        // fragments of k-step ks + 1 are read while ks is multiplied
             read_frags(ks + 1, (ks + 1) & 1);
             products(ks & 1);
         }
         // The stage's last fragments are in registers: it is free once all waves are here.  k-block kb + 1 is there once no more than what
-        // a wave asked for after that is outstanding.  Its first fragments are read while the last products run.
+        // a wave asked for after that (left) is outstanding.  Its first fragments are read while the last products run.
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(left.value) : "memory");
         if constexpr (refill.value) {
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((SW - 2) * WI + (SH - 2) * HI) : "memory");
             request_h(kb + SH, sth);
             request_w(min(kb + SW, KB - 1), stw);
-        } else {
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         }
         stw = (stw + 1 == SW) ? 0 : stw + 1;
         sth = (sth + 1 == SH) ? 0 : sth + 1;
@@ -1049,8 +1047,16 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
     };
     static_assert(kLBK == 64, "the last of a stage's k-steps uses the second set");
     int kb = 0;
-    for (; kb + SH < KB; ++kb) step(kb, std::true_type{});
-    for (; kb < KB; ++kb) step(kb, std::false_type{});
+    for (; kb + SH < KB; ++kb) step(kb, std::true_type{}, std::integral_constant<int, (SW - 2) * WI + (SH - 2) * HI>{});
+    auto tail = [&](auto t) {                                               // the last SH k-blocks (a third stage of W: what it was asked for again)
+        constexpr int pairs = SH - 2 - t.value > 0 ? SH - 2 - t.value : 0;
+        if constexpr (t.value < SH) step(kb + t.value, std::false_type{}, std::integral_constant<int, pairs * (WI + HI) + (SW - SH) * WI>{});
+    };
+    static_assert(SH <= 4, "tail");
+    tail(std::integral_constant<int, 0>{});
+    tail(std::integral_constant<int, 1>{});
+    tail(std::integral_constant<int, 2>{});
+    tail(std::integral_constant<int, 3>{});
     constexpr int kPT = BN / kTileV, kPS = BM * kPT;                        // partials of a row; of all rows
     float* const s_invt = reinterpret_cast<float*>(lds + 16 * kPatchBytes);
     float* const s_part = s_invt + BM;                                      // [2][BM][kPT]
