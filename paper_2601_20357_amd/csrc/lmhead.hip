@@ -933,10 +933,11 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 
 // piece ^ (r % 8), 8 rows on 32 banks, half of the 212 k LDS cycles a compute unit were conflicts; 0.3 % of the time).
 // One barrier per k-block, before the products of its last k-step: by then its last fragments are in registers and the stage is
 // free, and the next k-block's first fragments are read while those products run.  (With the barrier at the k-block's end its first
-// fragments were waited for: 333 us a draft step, 323.)  The loads are written in assembly (they have no destination
+// fragments were waited for: 333 us a draft step, 323.  The last k-blocks are waited for one by one too: with everything on its way
+// waited for at once, 128 rows of V = 32000, d = 768, four stages, took 26.0 us instead of 24.9; 26.3 with the barrier at the end.)  The loads are written in assembly (they have no destination
 // register): with the builtin the compiler waits for all LDS reads in flight at every second step, 256 us instead of 232 for the
 // product alone below.
-// What bounds it, 512 rows of V = 128256, d = 2048 (269 GFLOP, a draft step 307 us, 333 before): the loop without loads 181 us, with
+// What bounds it, 512 rows of V = 128256, d = 2048 (269 GFLOP, a draft step 304 us, 333 before): the loop without loads 181 us, with
 // them 231, with the epilogue and its 263 MB of logits, which all workgroups store at about the same times, 280.  The matrix
 // cores are busy for 81, 66 and 48 % of the cycles, at 1.65 GHz in the loop: the clock follows the power.  Measured and not kept:
 // k-blocks walked from a different one in every vocabulary block, so that workgroups read different channels (no change).
