@@ -928,9 +928,10 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 
 // the same bits), but the operands go from memory to LDS without registers in between (global_load_lds, 16 bytes a lane), in SW
 // stages of a k-block of W and SH of H; a wave keeps its registers for operand fragments, and nothing waits to write LDS.
 // 256 x 256 tiles have room for three stages of W, which comes from memory, and two of H, which comes from L2 (0.8 % less than two
-// of each).  A stage has rows of 128 bytes without padding; row r keeps its 16-byte pieces in the order piece ^ (r / 2 % 8), which
-// the lanes bring about by the address they load from, so that the fragment reads of 16 consecutive rows hit all 64 banks (with
-// piece ^ (r % 8), 8 rows on 32 banks, half of the 212 k LDS cycles a compute unit were conflicts; 0.3 % of the time).
+// of each).  A stage has rows of 128 bytes without padding; row r keeps its 16-byte pieces in the order piece ^ (r % 8), which the lanes
+// bring about by the address they load from.  (Reads of 16 rows then meet on 32 of 64 banks, half of the 212 k LDS cycles a compute
+// unit; the order piece ^ (r / 2 % 8) has no conflicts and gains 0.3 % with 256 x 256 tiles, but 128 rows of V = 32000, d = 768 took 26.5 us
+// with it instead of 24.7 back to back on W in the last-level cache, for a reason not found.)
 // One barrier per k-block, before the products of its last k-step: by then its last fragments are in registers and the stage is
 // free, and the next k-block's first fragments are read while those products run.  (With the barrier at the k-block's end its first
 // fragments were waited for: 333 us a draft step, 323.  The last k-blocks are waited for one by one too: with everything on its way
@@ -981,7 +982,7 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
     uint32_t wo[WI], ho[HI];                                                // rows past the end re-read the last one (masked in the epilogue)
     {
         const int r = lane >> 3;
-        const uint32_t piece = (uint32_t)((lane & 7) ^ ((wave & 1) * 4 + (r >> 1))) * 16u;     // row (8 i + wave) * 8 + r
+        const uint32_t piece = (uint32_t)((lane & 7) ^ r) * 16u;
 #pragma unroll
         for (int i = 0; i < WI; ++i) wo[i] = (uint32_t)min((i * 8 + wave) * 8 + r, V - 1 - v0) * (uint32_t)d * 2u + piece;
 #pragma unroll
@@ -998,7 +999,7 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
         for (int b = 0; b < TM; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-    const uint32_t wrow = (uint32_t)(wn * 32 * TV + nn) * kRow, hrow = (uint32_t)(SW * kStW) + (uint32_t)(wm * (BM / 2) + nn) * kRow, turn = (uint32_t)(nn >> 1 & 7);
+    const uint32_t wrow = (uint32_t)(wn * 32 * TV + nn) * kRow, hrow = (uint32_t)(SW * kStW) + (uint32_t)(wm * (BM / 2) + nn) * kRow, turn = (uint32_t)(nn & 7);
     bf16x8 wf[2][TV], hf[2][TM];                                            // fragments of two k-steps of 16
     int stw = 0, sth = 0;                                                   // stages of the present k-block
     auto read_frags = [&](int ks, int set) {
