@@ -293,6 +293,15 @@ int tabed_verify_tree(const tabed_cfg* cfg, void* ws, uint64_t round, int32_t tr
     return e == hipSuccess ? TABED_OK : fail_hip(e);
 }
 
+// For the tests, not declared in the header: the grid in which tabed_verify launches the statistics together with hard labels.
+int tabed_testing_labels_grid(const tabed_cfg* cfg, uint32_t* grid /* [3] */) {
+    const int rc = validate_cfg(cfg);
+    if (rc != TABED_OK) return rc;
+    const dim3 g = stats_labels_grid(*cfg, ws_layout(*cfg));
+    grid[0] = g.x; grid[1] = g.y; grid[2] = g.z;
+    return TABED_OK;
+}
+
 int tabed_update_weights(const tabed_cfg* cfg, void* ws, uint64_t round, const float* dev, const int32_t* n_valid, float* ring,
                          int32_t* ring_head, int32_t* ring_count, float* weights, void* stream) {
     (void)ws;

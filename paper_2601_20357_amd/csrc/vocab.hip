@@ -1242,13 +1242,14 @@ __device__ __forceinline__ void dist_chunk(const DistArgs& a, int c, int i, int 
 // Target statistics and hard labels in one launch: the labels' workgroups first (nd of them), then k_stats'.
 template <int U, int MODE>
 __global__ __launch_bounds__(kBlock) void k_stats_labels(StatsArgs a, DistArgs d, int nd) {
-    int g = blockIdx.x;
+    int g = blockIdx.y * gridDim.x + blockIdx.x;
     if (g < nd) {
         const int c = g % d.Cd, bi = g / d.Cd;
         dist_chunk<MODE, 0>(d, c, bi % d.gamma, bi / d.gamma);
     } else {
         g -= nd;
         const int c = g % a.C3, bi = g / a.C3;
+        if (bi >= (a.gamma + 1) * a.B) return;             // (the last row of a grid of several)
         stats_chunk<U, 0>(a, c, bi % (a.gamma + 1), bi / (a.gamma + 1));
     }
 }
@@ -1263,6 +1264,18 @@ static int pick_stats_unroll(const tabed_cfg& c, int nmax_u) {
     }
     return 1;
 }
+
+static int stats_chunks(const tabed_cfg& c, int U) { return (c.V + kBlock * 4 * U - 1) / (kBlock * 4 * U); }
+
+// Grid of k_stats_labels.  A launch takes fewer than 2^32 threads a dimension, and four chunks a row of 65535 sequences with 32 positions
+// are more: beyond 2^20 workgroups there is more than one row of them.  (k_finish with distances stays below: its workgroups reach
+// 2^24 with eight chunks of 65535 x 32 positions, whose logits are 480 GB.)
+static dim3 stats_labels_grid(const tabed_cfg& c, const WsLayout& L, int C3) {
+    constexpr uint32_t kRow = 1u << 20;
+    const uint32_t total = (uint32_t)(L.Cd * c.gamma + C3 * (c.gamma + 1)) * (uint32_t)c.B;
+    return total <= kRow ? dim3(total) : dim3(kRow, (total + kRow - 1) / kRow);
+}
+dim3 stats_labels_grid(const tabed_cfg& c, const WsLayout& L) { return stats_labels_grid(c, L, stats_chunks(c, pick_stats_unroll(c, 4))); }
 
 template <int N>
 static void launch_stats_n(const ProfScope* prof, int U, dim3 grid, hipStream_t s, const StatsArgs& a) {
@@ -1924,8 +1937,7 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     // than the trips saved are worth (12 sequences of V = 128256, us: 3 drafts 17.5 against 18.5, 5 drafts 24.0 against 26.0),
     // and where it reads no draft row
     const int scomp = (second_pass || ncomp == 3 || ncomp == 5) ? 0 : ncomp;
-    const int U = pick_stats_unroll(c, scomp > 4 ? 2 : 4);
-    const int C3 = (c.V + kBlock * 4 * U - 1) / (kBlock * 4 * U);
+    const int U = pick_stats_unroll(c, scomp > 4 ? 2 : 4), C3 = stats_chunks(c, U);
     DistArgs d{};
     d.V = c.V; d.n = c.n; d.B = c.B; d.gamma = c.gamma; d.C3 = C3; d.RS = L.RS; d.DW = L.DW; d.Cd = L.Cd;
     d.target = target_logits; d.dlogits = draft_logits; d.dlse = draft_lse; d.temperature = temperature;
@@ -1942,7 +1954,7 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
         d.stats = a.stats;
         if (labels) {
             const int nd = L.Cd * c.gamma * c.B;
-            const dim3 both(nd + C3 * (c.gamma + 1) * c.B);
+            const dim3 both = stats_labels_grid(c, L, C3);
 #define TABED_LABELS(U_) (c.policy != 2 ? launch(&prof, k_stats_labels<U_, 3>, both, dim3(kBlock), 0, s, a, d, nd) \
                                         : launch(&prof, k_stats_labels<U_, 4>, both, dim3(kBlock), 0, s, a, d, nd))
             if (U == 1) TABED_LABELS(1);

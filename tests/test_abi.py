@@ -172,3 +172,15 @@ def test_body_entry_points_validate_before_any_launch(lib):
     assert lib.tabed_draft_body_rollback(64, 4, 5, None, vp(fake), vp(fake), None) == -1
     assert lib.tabed_draft_body_rollback(64, 0, 5, vp(fake), vp(fake), vp(fake), None) == -3
     assert lib.tabed_body_workspace_init(C.byref(bc), 64, None, None) == -1
+
+
+@pytest.mark.parametrize("V,n,B,gamma", [(12289, 1, 65535, 32), (16384, 1, 65535, 32), (8193, 2, 65535, 32), (32000, 4, 16, 5), (3, 1, 1, 1)])
+def test_launch_of_statistics_and_labels_is_one_the_runtime_takes(lib, V, n, B, gamma):
+    """A launch has fewer than 2^32 threads in each dimension (and 65536 workgroups in the second and third): also with every sequence
+    and position that a call may have, at a vocabulary whose logits (209 GB at 12289 entries) still fit the card's memory."""
+    grid = (C.c_uint32 * 3)()
+    assert lib.tabed_testing_labels_grid(C.byref(good_cfg(V=V, n=n, B=B, gamma=gamma, distance=2)), grid) == 0
+    assert grid[0] * 256 < 1 << 32 and grid[1] < 1 << 16 and grid[2] == 1
+    if B * V > 1 << 20:                                              # chunks of 4096 entries: labels of gamma positions, statistics of gamma + 1
+        chunks = (V + 4095) // 4096
+        assert grid[0] * (grid[1] - 1) < chunks * B * (2 * gamma + 1) <= grid[0] * grid[1]

@@ -34,6 +34,7 @@ def _inputs(V, n, B, gamma, distance, policy, h):
     (50261, 4, 12, 5, 0, 4),                                         # 1092 (in turn)
     (30001, 5, 16, 4, 0, 4), (30001, 5, 19, 4, 0, 4),                # five drafts: 768 (up front), 912
     (20001, 8, 16, 4, 0, 4), (20001, 8, 18, 4, 0, 4), (20001, 6, 9, 3, 0, 4),   # eight: 496, 558; six: rows in turn
+    (5, 2, 60001, 10, 0, 4), (5, 2, 60001, 10, 2, 4),                # labels: 1260021 workgroups, in two rows of the grid
     (70001, 2, 15, 6, 2, 4), (33, 2, 3, 2, 2, 0)])
 @pytest.mark.parametrize("distance", [1, 2], ids=["tv", "labels"])
 def test_distances_and_window(V, n, B, gamma, policy, h, distance):
