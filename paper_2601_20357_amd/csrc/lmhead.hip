@@ -45,7 +45,18 @@ __device__ __forceinline__ float half_sum(float v) {
 // V = 32001, 480 rows, d = 72 49.3 / 59.9; but below 16 MB of logits, most of which would be left to the write-back at the end, V = 20001,
 // 80 rows, d = 2048 36.1 / 31.3, V = 30001, 120 rows, d = 1160 36.8 / 35.9; up to 64 rows, whose stores go out beside the stream of W,
 // V = 100003 60.3 / 57.8 at 64 rows, 52.4 / 50.6 at 32; and with whole sectors, V = 100000, 128 rows 61.9 / 54.9.
-static bool past_l2(int V, int M) { return M <= 64 || (V & 15) == 0 || (long)M * V < (4l << 20); }
+// The exception: W of about the last-level cache's size (256 MB) stays there from one draft step to the next, unless logits stored
+// through L2 take its place, which costs more than the sectors where the logits are few beside W (the ratio of their bytes is 2 M / d).
+// Steps back to back on the same buffers, through / past L2, us.  128 rows, d = 3000, W of 240 MB, V = 40001 98.6 / 75.2, 40008 96.8 / 74.3; of 205 MB,
+// 34168 73.6 / 73.1, of 320 MB, 53329 104.7 / 107.5.  d = 1328, 225 MB, V = 84708 85.8 / 80.6, with 256 rows 130.6 / 135.8, V = 84705 86.5 / 83.9,
+// 132.2 / 142.2; 205 MB 67.8 / 76.9.  66 rows, d = 520, 255 MB, V = 245192 112.8 / 100.5, 128 rows 142.5 / 138.9.  Whole lines lose less, later:
+// 128 rows, d = 2048, 240 MB 54.5 / 56.8, 270 MB, V = 65908 98.8 / 91.7, 320 MB 119.4 / 126.7; 96 rows, d = 896, 255 MB 82.7 / 83.9.
+static bool past_l2(int V, int d, int M) {
+    if (M <= 64 || (V & 15) == 0 || (long)M * V < (4l << 20)) return true;
+    const bool lines = d % 64 == 0;
+    const long w = 2l * V * d;
+    return w > (lines ? 250000000l : 222000000l) && w < (lines ? 300000000l : 278000000l) && 2l * d >= (lines ? 28l : (V & 3) ? 22l : 15l) * M;
+}
 // (An instance each: a choice at run time between the two stores becomes one that goes through L2.)
 template <bool PAST>
 __device__ __forceinline__ void store_logits(float* p, f32x4u x) {
@@ -1331,7 +1342,7 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
         // rows of V = 128256, d = 2048; 66.1 / 70.5 at 160 rows of 50261, 1152; 24.9 / 25.4 at 128 of 32000, 768; 87.5 / 94.3 at 96 of
         // 152064, 896; 76.4 / 76.3 at 96 of 32000, 4096; 19.7 / 19.8 at 256 of 9000, 512.  With one or two k-blocks there is nothing to have in
         // flight: 16.3 / 15.9 at 400 rows of 8000, 64, 33.6 / 33.1 at 256 of 65536, 128.
-        const bool past = past_l2(c.V, M);
+        const bool past = past_l2(c.V, c.d, M);
 #define TABED_ROWS(FN_, ...)                                                               \
     past ? FN_<__VA_ARGS__, true>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s)    \
          : FN_<__VA_ARGS__, false>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s)

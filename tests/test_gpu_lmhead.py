@@ -27,6 +27,7 @@ SHAPES = [
     # tiles of 128 x 128, 128 x 256, 256 x 256 rows x vocabulary; one k-block, a ragged last one, a last row block of one row
     (4099, 72, 1, 65), (33000, 1160, 1, 50), (8200, 2048, 1, 128), (2000, 8, 1, 129),
     (49153, 264, 1, 66), (24600, 136, 1, 257), (49161, 264, 1, 129), (25000, 64, 1, 511),
+    (84712, 1328, 1, 120),                                           # W of the last-level cache's size: logits past L2
 ]
 
 
