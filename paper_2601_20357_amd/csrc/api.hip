@@ -70,7 +70,7 @@ size_t ws_bytes_unpacked(const tabed_cfg& c) { return layout_with(c, 32).total; 
 
 // ---------------------------------------------------------------- event timing
 struct ProfRec {
-    int id;
+    int id, also;
     hipEvent_t start, stop;
 };
 static std::mutex g_prof_mu;
@@ -80,16 +80,19 @@ static double g_prof_ms[TABED_K_COUNT];
 static int64_t g_prof_n[TABED_K_COUNT];
 
 bool prof_on() { return g_prof_on.load(std::memory_order_relaxed); }
-void prof_push(int id, hipEvent_t start, hipEvent_t stop) {
+void prof_push(int id, int also, hipEvent_t start, hipEvent_t stop) {
     std::lock_guard<std::mutex> lk(g_prof_mu);
-    g_prof_pending.push_back(ProfRec{id, start, stop});
+    g_prof_pending.push_back(ProfRec{id, also, start, stop});
 }
 static void prof_drain() {
     for (ProfRec& r : g_prof_pending) {
         float ms = 0.f;
         if (hipEventSynchronize(r.stop) == hipSuccess && hipEventElapsedTime(&ms, r.start, r.stop) == hipSuccess) {
-            g_prof_ms[r.id] += (double)ms;
-            g_prof_n[r.id] += 1;
+            for (int id : {r.id, r.also})
+                if (id >= 0) {
+                    g_prof_ms[id] += (double)ms;
+                    g_prof_n[id] += 1;
+                }
         }
         (void)hipEventDestroy(r.start);
         (void)hipEventDestroy(r.stop);

@@ -144,15 +144,15 @@ hipError_t launch_body_rollback(int rows, int rows_per_seq, int gamma, const int
 // event to the dispatch itself: the pair measures the kernel's own begin-to-end time (what a kernel trace
 // reports), not the dispatch gaps around it.
 bool prof_on();
-void prof_push(int id, hipEvent_t start, hipEvent_t stop);
+void prof_push(int id, int also, hipEvent_t start, hipEvent_t stop);
 struct ProfScope {
-    int id;
+    int id, also;      // also: a second id that the launch counts under, or -1
     bool on;
     hipEvent_t start = nullptr, stop = nullptr;
-    ProfScope(int id_, hipStream_t) : id(id_), on(prof_on()) {
+    ProfScope(int id_, hipStream_t, int also_ = -1) : id(id_), also(also_), on(prof_on()) {
         if (on && (hipEventCreate(&start) != hipSuccess || hipEventCreate(&stop) != hipSuccess)) on = false;
     }
-    ~ProfScope() { if (on) prof_push(id, start, stop); }
+    ~ProfScope() { if (on) prof_push(id, also, start, stop); }
     ProfScope(const ProfScope&) = delete;
     ProfScope& operator=(const ProfScope&) = delete;
 };

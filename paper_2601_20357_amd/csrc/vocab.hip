@@ -1943,7 +1943,7 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
     d.target = target_logits; d.dlogits = draft_logits; d.dlse = draft_lse; d.temperature = temperature;
     d.dist = reinterpret_cast<double*>(ws + L.off_dist);
     {
-        ProfScope prof(TABED_K_STATS, s);
+        ProfScope prof(TABED_K_STATS, s, labels ? TABED_K_DIST : -1);
         StatsArgs a;
         a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.RS = L.RS; a.C3 = C3;
         a.with_drafts = second_pass ? 0 : 1;
@@ -1974,7 +1974,7 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    ProfScope prof(TABED_K_RESID, s);
+    ProfScope prof(TABED_K_RESID, s, second_pass && !labels ? TABED_K_DIST : -1);
     FinishArgs a;
     a.V = c.V; a.n = c.n; a.B = c.B; a.gamma = c.gamma; a.C3 = C3; a.RS = L.RS; a.NSEG = L.NSEG; a.C5 = L.C5; a.TS = L.TS;
     a.seed = c.seed; a.round = round;

@@ -81,3 +81,29 @@ def test_distances_and_window(V, n, B, gamma, policy, h, distance):
             want = (at[..., 0] != label[:, None]).float()
             assert bool(((dev[:, i] == want) | ~clear)[emitted].all())
             assert bool((dev[:, i][~emitted] == 1).all())
+
+
+def _timed(calls, ids):
+    binding.tabed_prof_reset()
+    binding.tabed_prof_enable(True)
+    for call in calls:
+        call()
+    binding.tabed_prof_enable(False)
+    return [binding.tabed_prof_read(i) for i in ids]
+
+
+@pytest.mark.parametrize("distance", [0, 1, 2], ids=["kl", "tv", "labels"])
+def test_distances_are_timed_under_their_own_id(distance):
+    """K_DIST reports the launch that holds the distances, which counts under the id of what it shares it with as well; the
+    divergence, which rides in the statistics' records, has none."""
+    cfg, temp, _, logits, target, weights, lse, tokens, _ = _inputs(8003, 4, 3, 3, distance, 0, 4)
+    buf = binding.RoundBuffers(cfg, DEV)
+    buf.draft_logits.view(logits.shape).copy_(logits)
+    buf.draft_lse.view(lse.shape).copy_(lse)
+    buf.draft_tokens.copy_(tokens)
+    buf.draft_q.fill_(0.1)
+    buf.weights.copy_(weights)
+    stats, resid, dist = _timed([lambda: buf.verify(4, target, temp)] * 3, (binding.K_STATS, binding.K_RESID, binding.K_DIST))
+    assert stats[1] == 3 and resid[1] == 3
+    assert dist == {0: (0.0, 0), 1: resid, 2: stats}[distance]
+    binding.tabed_prof_reset()
