@@ -84,7 +84,7 @@ def parse():
                     help="run the draft model's body (random weights) in front of every LM-head call instead of "
                          "feeding pre-generated hidden states; reports rounds/s of body + head + verify")
     ap.add_argument("--policy", type=int, default=0, help="weight policy (0 softmax of 1/e, 1 static, 2 two-draft grid, 3 random)")
-    ap.add_argument("--distance", type=int, default=0, help="0 KL, 1 total variation")
+    ap.add_argument("--distance", type=int, default=0, help="0 KL, 1 total variation, 2 hard labels")
     ap.add_argument("--drafts", type=int, default=0, help="override the workload's number of drafts n (2 for --policy 2)")
     ap.add_argument("--hidden", type=int, default=0, help="override the workload's draft hidden size d")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MB",
@@ -386,8 +386,14 @@ def main():
                   + (wl.B - n_sampling) * wl.n * wl.V * 4,                        # greedy rows: the whole row
         "stats": wl.B * (wl.gamma + 1) * wl.V * 4 + wl.gamma * M * wl.V * 4,     # target rows + draft rows
         "resid": n_sampling * (1 + wl.n) * wl.V * 4,                              # one target row + n draft rows
-        "dist": wl.B * wl.gamma * (1 + wl.n) * wl.V * 4,
     }
+    # distances that the statistics' records do not hold: in the launch of the corrected token or of the (then draft-less) statistics
+    if args.distance == 1:
+        alg_bytes["stats"] -= wl.gamma * M * wl.V * 4
+        alg_bytes["resid"] += wl.gamma * (wl.B + M) * wl.V * 4                    # target and draft rows
+        alg_bytes["dist"] = alg_bytes["resid"]                                    # (the same launch under its second id)
+    elif args.distance == 2:
+        alg_bytes["dist"] = alg_bytes["stats"]                                    # (the same; the labels read the draft rows)
     body_weight_bytes = 0
     if body is not None:                       # what a body step must stream: every layer's matrices once
         body_weight_bytes = bc.layers * 2 * (3 * bc.d * bc.d + bc.d * bc.d + 3 * bc.d * bc.d_ff)
@@ -449,8 +455,7 @@ def main():
                         mfma_tflops=tflops, mfma_frac_of_bf16_peak=tflops / MFMA_BF16_PEAK_TFLOPS,
                         instrumented_ms_per_step=dt_inst / args.steps * 1e3)
 
-    round_bytes = wl.gamma * (lm_bytes + alg_bytes["sample"]) + alg_bytes["stats"] + alg_bytes["resid"] \
-        + (alg_bytes["dist"] if (args.distance != 0 or args.policy == 2) else 0)
+    round_bytes = wl.gamma * (lm_bytes + alg_bytes["sample"]) + alg_bytes["stats"] + alg_bytes["resid"]
     out = {
         "metric": ("ensemble-draft+verify steps/sec at V=32k,n=4,B=16; HBM GB/s & MFMA % of peak"
                    if wl.name == "serving" and not tree and body is None else "ensemble-draft+verify steps/sec"),
