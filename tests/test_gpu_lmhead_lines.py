@@ -10,9 +10,14 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+# (through L2: the logits of rows that share 64-byte sectors, from 2^22 logits on; of the staged tiles as well)
 @pytest.mark.parametrize("V,d,M", [(4099, 512, 65), (8200, 576, 128), (20000, 896, 192), (13001, 640, 129),      # 128 x 128, one and two a compute unit
-                                   (49153, 512, 66), (33000, 768, 128), (24577, 1152, 129),                      # 128 x 256
-                                   (24600, 512, 257), (49161, 704, 129), (100003, 2048, 512)])                   # 256 x 256
+                                   (33000, 768, 128),                                                            # through L2
+                                   (49153, 512, 66), (24577, 1152, 129),                                         # 128 x 256
+                                   (50001, 512, 100), (60004, 640, 128),                                         # through L2
+                                   (58600, 2176, 72),                                                            # W of 255 MB: past L2 all the same
+                                   (49168, 704, 129), (128256, 512, 500),                                        # 256 x 256
+                                   (24600, 512, 257), (49161, 704, 129), (100003, 2048, 512)])                   # through L2
 def test_logits_are_those_of_the_staged_tiles(V, d, M):
     print(f"lm head lines V={V} d={d} rows={M}", flush=True)
     g = torch.Generator(device=DEV).manual_seed(V + d)
