@@ -39,7 +39,7 @@ __device__ __forceinline__ float half_sum(float v) {
     return v;
 }
 
-// Four logits of a row, past L2 or through it.  Rows whose 64-byte sectors are shared by neighbouring tiles go through L2, which puts
+// Four logits of a row, past L2 or, of more than 64 rows, through it.  Rows whose 64-byte sectors are shared by neighbouring tiles go through L2, which puts
 // the sectors together, where there are so many logits that storing parts of sectors is what takes the time.  Draft steps in us,
 // through / past L2: V = 100003, 255 rows, d = 1024 133 / 155, 128 rows, d = 640 68.8 / 78.4, V = 50004, 96 rows, d = 768 35.4 / 36.2,
 // V = 32001, 480 rows, d = 72 49.3 / 59.9; but below 16 MB of logits, most of which would be left to the write-back at the end, V = 20001,
@@ -52,7 +52,7 @@ __device__ __forceinline__ float half_sum(float v) {
 // 132.2 / 142.2; 205 MB 67.8 / 76.9.  66 rows, d = 520, 255 MB, V = 245192 112.8 / 100.5, 128 rows 142.5 / 138.9.  Whole lines lose less, later:
 // 128 rows, d = 2048, 240 MB 54.5 / 56.8, 270 MB, V = 65908 98.8 / 91.7, 320 MB 119.4 / 126.7; 96 rows, d = 896, 255 MB 82.7 / 83.9.
 static bool past_l2(int V, int d, int M) {
-    if (M <= 64 || (V & 15) == 0 || (long)M * V < (4l << 20)) return true;
+    if ((V & 15) == 0 || (long)M * V < (4l << 20)) return true;
     const bool lines = d % 64 == 0;
     const long w = 2l * V * d;
     return w > (lines ? 250000000l : 222000000l) && w < (lines ? 300000000l : 278000000l) && 2l * d >= (lines ? 28l : (V & 3) ? 22l : 15l) * M;
@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(kLargeThreads, 2) void k_lmhead_dma(int M, int d, i
         for (int a = 0; a < TV; ++a)
 #pragma unroll
             for (int b = 0; b < TM; ++b)
-                store_tile_32x32_t(acc[a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
+                store_tile_32x32_t<PAST>(acc[a][b], m0 + wm * (BM / 2) + b * 32, v0 + wn * 32 * TV + a * 32, M, V, NT, s_invt - m0, L, pm, ps, tpatch);
         return;
     }
     const int lr = wm * (BM / 2);
@@ -1353,8 +1353,8 @@ hipError_t launch_lmhead(const tabed_cfg& c, const WsLayout& Lay, char* ws, cons
             e = TABED_ROWS(launch_dma, 128, 256, 3, 3);
         else if (lines && tiles(128, 128) > 256)       // two workgroups a compute unit (192 rows of 20000, 896 33.7 us with one, 29.0; 30.2 through registers)
             e = TABED_ROWS(launch_dma, 128, 128, 2, 2);
-        else if (lines)
-            e = TABED_ROWS(launch_dma, 128, 128, 4, 4);
+        else if (lines)                                // (at most 256 tiles: M V reaches 2^22 with whole ones only, and such a V goes past L2)
+            e = launch_dma<128, 128, 4, 4, true>(&prof, c, Lay, M, W, H, temperature, logits, pm, ps, s);
         else if (M > 128 && (tiles(256, 256) >= 192 || tiles(128, 256) > 256))
             e = TABED_ROWS(launch_tile, 256, 256, 1, uint32_t, 1);
         else if (tiles(128, 256) >= 192) e = TABED_ROWS(launch_tile, 128, 256, 2, uint32_t, 1);
