@@ -2002,14 +2002,15 @@ hipError_t launch_verify(const tabed_cfg& c, const WsLayout& L, char* ws, uint64
         // the other beyond, where they cost more workgroups than the trips saved are worth (V = 50261, 3 drafts, 12 sequences, 936 workgroups: 25.3 / 26.0 us;
         // as a launch of their own, 1536 workgroups of V = 32000 with 2, 4 and 8 drafts 17.7 / 11.9, 27.9 / 18.8, 58.6 / 33.9).  Eight drafts
         // beyond: k_finish without a compile-time draft count has 81 registers instead of 117 (V = 128256, 32 sequences 165 us, 182;
-        // 141 with two rows at a time)
+        // 141 with two rows at a time).  (The registers decide: with the records' scales, at most 17 KB, a workgroup has 26 KB of LDS, six
+        // of which fit a compute unit.)
         const long nd = (long)L.Cd * c.gamma * c.B;
         const dim3 grid((unsigned)(finishers + nd));
+        const bool up_front = finishers + nd <= 256 * (ncomp <= 4 ? 4 : ncomp == 5 ? 3 : 2);
 #define TABED_FINISH(N_)                                                                                          \
-    finishers + nd <= 256 * (N_ <= 4 ? 4 : N_ == 5 ? 3 : 2) ? launch(&prof, k_finish<N_, N_ != 0 ? kDistUpFront : kDistInTurn>, grid, dim3(kBlock), lds, s, a, d) \
-              : launch(&prof, k_finish<N_, kDistInTurn>, grid, dim3(kBlock), lds, s, a, d)
+    up_front ? launch(&prof, k_finish<N_, N_ != 0 ? kDistUpFront : kDistInTurn>, grid, dim3(kBlock), lds, s, a, d) \
+             : launch(&prof, k_finish<N_ != 8 ? N_ : 0, kDistInTurn>, grid, dim3(kBlock), lds, s, a, d)
         if (c.policy == 2) launch(&prof, k_finish<2, kDistMixtures>, grid, dim3(kBlock), lds, s, a, d);
-        else if (c.n == 8 && finishers + nd > 512) TABED_FINISH(0);
         else { TABED_FOR_DRAFTS(ncomp, TABED_FINISH) }
 #undef TABED_FINISH
         return hipGetLastError();
