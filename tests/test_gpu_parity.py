@@ -479,6 +479,26 @@ def test_token_tree_matches_oracle(oracle, case):
     assert tally.leaves > 0 or mode == "greedy" or B * 5 < 20      # sibling acceptances are exercised
 
 
+# Total variation: the siblings' arg-max, the distances and the tree's passes count their workgroups' arrivals on the same counter, one after
+# the other, each up to a number of its own; five rounds of them.
+@pytest.mark.parametrize("case", [
+    (1000,   64,  2, 3, 3, 4,  0, "one",     2, False),
+    (4099,   72,  3, 5, 4, 5,  1, "mixed07", 3, True),
+    (5000,   64,  6, 9, 2, 3,  1, "mixed07", 2, True),
+    (20001,  64,  8, 5, 3, 4,  1, "mixed07", 3, False),
+    (8200,   128, 4, 6, 2, 3,  1, "greedy",  3, False),
+    (152064, 896, 4, 4, 2, 16, 1, "mixed07", 3, True),               # greedy siblings shared by several workgroups
+    (152064, 896, 4, 2, 2, 16, 1, "greedy",  2, False),
+], ids=lambda c: f"V{c[0]}n{c[2]}B{c[3]}w{c[8]}{c[7]}")
+def test_token_tree_with_total_variation(oracle, case):
+    V, d, n, B, gamma, h, w_dtype, mode, width, fused = case
+    _say(f"token tree, total variation {case}")
+    wl = synth.scaled(SERVING, V=V, d=d, n=n, B=B, gamma=gamma, h=h, w_dtype=w_dtype, cfg_id=150 + V % 11)
+    tally = harness.run_rounds_tree(oracle, wl, 5, synth.make_temperature(wl, mode), width, distance=1, fused=fused)
+    _say(f"{tally} leaves={tally.leaves} emitted={tally.emitted}")
+    assert tally.flagged_divergences <= max(2, tally.decisions // 50)
+
+
 def test_token_tree_of_width_one_is_the_chain(oracle):
     """tabed_verify_tree with tree_width = 1 leaves exactly what tabed_verify leaves, plus leaf = 0 and n_out = k + 1."""
     wl = synth.scaled(SERVING, V=8200, d=128, B=6, gamma=3, cfg_id=141)
