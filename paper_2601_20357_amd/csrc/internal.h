@@ -42,7 +42,7 @@ struct WsLayout {
     int Cd;              // vocabulary chunks of the total-variation and label distances
     int TS;              // uint32 between two sequences' arrival counters
     size_t off_tickets;  // uint32 [5][B][TS]: arrival counters (0: greedy draft arg-max, 1: staged weights, 2: corrected/bonus sampler,
-                         // 3: token-tree pass; before it, in the chain's launch, total-variation distances, 4: unused)
+                         // 3, 4: arg-max of a greedy row's first and second sibling; 3 then total-variation distances, then the tree's passes)
     size_t off_pm;       // float  [M][NT] tile maxima of scaled logits
     size_t off_ps;       // float  [M][NT] tile sums of exp(scaled logit - tile max)
     size_t off_cand;     // Top2Rec [B][C2]

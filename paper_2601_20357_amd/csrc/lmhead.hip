@@ -949,9 +949,9 @@ __global__ __launch_bounds__(kLargeThreads, (BM * BN <= 128 * 128 && NA <= 2) ? 
 // waited for at once, 128 rows of V = 32000, d = 768, four stages, took 26.0 us instead of 24.9; 26.3 with the barrier at the end.)  The loads are written in assembly (they have no destination
 // register): with the builtin the compiler waits for all LDS reads in flight at every second step, 256 us instead of 232 for the
 // product alone below.
-// What bounds it, 512 rows of V = 128256, d = 2048 (269 GFLOP, a draft step 304 us, 333 before): the loop without loads 181 us, with
-// them 231, with the epilogue and its 263 MB of logits, which all workgroups store at about the same times, 280.  The matrix
-// cores are busy for 81, 66 and 48 % of the cycles, at 1.65 GHz in the loop: the clock follows the power.  Measured and not kept:
+// What bounds it, 512 rows of V = 128256, d = 2048 (269 GFLOP, a draft step 304 us, 327 before): the loop without loads 178 us, with
+// them 230, with the epilogue and its 263 MB of logits, which all workgroups store at about the same times, 283, launches apart; 188, 265
+// and 315 on average back to back.  The matrix cores are busy for 76, 60 and 47 % of the cycles, at 1.9 GHz: the clock follows the power.  Measured and not kept:
 // k-blocks walked from a different one in every vocabulary block, so that workgroups read different channels (no change).
 // (M0 is put back: the compiler does not let it be named as clobbered, and keeps what it has in it.)
 __device__ __forceinline__ void dma_lines(const char* base, const uint32_t (&off)[4], uint32_t lds, uint32_t step) {
