@@ -350,7 +350,7 @@ int tabed_philox_uniforms(const tabed_cfg* cfg, uint64_t round, float* out, void
 #define TABED_K_STATS 2   /* target statistics + distances + accept chain */
 #define TABED_K_RESID 3   /* corrected / bonus token            */
 #define TABED_K_WEIGHTS 4 /* window + weights                   */
-#define TABED_K_DIST 5    /* the launch that such distances share: total variation RESID's, hard labels STATS' (counted there too) */
+#define TABED_K_DIST 5    /* the launch that holds total variation (RESID's) or hard labels (STATS'), counted there too */
 #define TABED_K_TREE 6    /* token tree: the first pass of the walk (the second, of width 3, is not timed) */
 #define TABED_K_BODY 7    /* draft-model body: every kernel of tabed_draft_body_step */
 #define TABED_K_NULL 8    /* empty kernel, see tabed_prof_null  */
